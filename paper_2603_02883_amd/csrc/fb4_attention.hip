@@ -6,6 +6,32 @@
 
 using namespace fb4;
 
+namespace {
+
+// Blocks of 32 queries per wavefront of the long-group kernel.  A workgroup's time goes with b + 0.7 (0.7: what a step
+// costs whatever the number of blocks; 24 groups x 16384 tokens x 128 channels take 1157 / 1255 / 1337 / 1657 us with
+// 4 / 3 / 2 / 1), m workgroups on a compute unit take about 0.2 + 0.8 m times as long as one, and the last workgroup
+// of a group has only the blocks that are left.  So long launches take 4 and short ones fewer, to reach more
+// compute units: 16 x 400 x 72 channels 4.0 us with 1 and 7.1 with 4, 8 x 3000 x 72 16 and 27, 24 x 4000 x 64 45
+// with 3 and 50 with 4; 272 x 1350 x 64 62 with 4 and 65 with 3.
+uint32_t dma_blocks_per_wave(int64_t groups, uint32_t n_blk)
+{
+    constexpr double kCus = 256.0, kStep = 0.7;
+    uint32_t best = kDmaQB;
+    double best_cost = 0.0;
+    for (uint32_t b = kDmaQB; b >= 1; --b) {
+        const uint32_t full = n_blk / (2 * b), rest = n_blk - full * 2 * b;
+        const double units = full * (b + kStep) + (rest ? (rest + 1) / 2 + kStep : 0.0);
+        const double load = (double)groups * units / ((b + kStep) * kCus);
+        const double m = load > 1.0 ? (double)(int64_t)(load + 0.999) : 1.0;
+        const double cost = (b + kStep) * (0.2 + 0.8 * m);
+        if (b == (uint32_t)kDmaQB || cost < best_cost) { best_cost = cost; best = b; }
+    }
+    return best;
+}
+
+}  // namespace
+
 extern "C" {
 
 int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t tokens, int64_t dim, int mode,
@@ -21,25 +47,38 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
     if (tokens * dim > 0x7FFFFFFFll || groups * bpg > 0x7FFFFFFFll) return FB4_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)(groups * bpg));
-    if (dim == kDmaDim && !small && tokens % 128 == 0) {
-        // rows of exactly 128 channels, key halves made of whole 64-key blocks: the kernel that loads straight to LDS
-        if (mode) hipLaunchKernelGGL(attention_scores_dma_kernel<true>, grid, dim3(kScoreThreads), 0, s, static_cast<const uint16_t*>(q),
-                                     static_cast<const uint16_t*>(k), (uint32_t)tokens, (uint32_t)bpg, scores);
-        else hipLaunchKernelGGL(attention_scores_dma_kernel<false>, grid, dim3(kScoreThreads), 0, s, static_cast<const uint16_t*>(q),
-                                static_cast<const uint16_t*>(k), (uint32_t)tokens, (uint32_t)bpg, scores);
+    if (!small && dim <= 8 * kDmaMaxPieces) {   // (longer rows: too many registers for four blocks of queries)
+        const uint32_t n_blk = (uint32_t)((tokens + 31) / 32);
+        uint32_t bpw = dma_blocks_per_wave(groups, n_blk);
+        const uint32_t n_full = n_blk / (2 * bpw), n_wg = n_full + (n_blk % (2 * bpw) ? 1 : 0);
+        const dim3 dgrid((unsigned)(groups * n_wg));
+#define FB4_DMA_ARGS static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), (uint32_t)groups, (uint32_t)tokens, n_full, bpw, scores
+#define FB4_DMA_CASE(p)                                                                                                               \
+    case p:                                                                                                                           \
+        if (mode) hipLaunchKernelGGL((attention_scores_dma_kernel<p, true>), dgrid, dim3(kScoreThreads), 0, s, FB4_DMA_ARGS);         \
+        else hipLaunchKernelGGL((attention_scores_dma_kernel<p, false>), dgrid, dim3(kScoreThreads), 0, s, FB4_DMA_ARGS);             \
+        break;
+        switch ((int)(dim / 8)) {
+            FB4_DMA_CASE(1) FB4_DMA_CASE(2) FB4_DMA_CASE(3) FB4_DMA_CASE(4) FB4_DMA_CASE(5) FB4_DMA_CASE(6) FB4_DMA_CASE(7)
+            FB4_DMA_CASE(8) FB4_DMA_CASE(9) FB4_DMA_CASE(10) FB4_DMA_CASE(11) FB4_DMA_CASE(12) FB4_DMA_CASE(13)
+            FB4_DMA_CASE(14) FB4_DMA_CASE(15) FB4_DMA_CASE(16)
+            default: return FB4_ERR_UNSUPPORTED;
+        }
+#undef FB4_DMA_CASE
+#undef FB4_DMA_ARGS
         return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
     }
 #define FB4_SCORE_ARGS static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), (uint32_t)tokens, (uint32_t)dim, (uint32_t)bpg, scores
 #define FB4_SCORE_LAUNCH(d, relu, qb, keys) hipLaunchKernelGGL((attention_scores_kernel<d, relu, qb, keys>), grid, dim3(kScoreThreads), 0, s, FB4_SCORE_ARGS)
-#define FB4_SCORE_CASE(d)                                   \
-    case d:                                                 \
-        if (small) {                                        \
-            if (mode) FB4_SCORE_LAUNCH(d, true, 1, 32);     \
-            else FB4_SCORE_LAUNCH(d, false, 1, 32);         \
-        } else {                                            \
-            if (mode) FB4_SCORE_LAUNCH(d, true, 2, 64);     \
-            else FB4_SCORE_LAUNCH(d, false, 2, 64);         \
-        }                                                   \
+#define FB4_SCORE_CASE(d)                                                    \
+    case d:                                                                  \
+        if (small) {                                                         \
+            if (mode) FB4_SCORE_LAUNCH(d, true, 1, 32);                      \
+            else FB4_SCORE_LAUNCH(d, false, 1, 32);                          \
+        } else if constexpr (d * 4 > kDmaMaxPieces) {                        \
+            if (mode) FB4_SCORE_LAUNCH(d, true, 2, 64);                      \
+            else FB4_SCORE_LAUNCH(d, false, 2, 64);                          \
+        }                                                                    \
         break;
     switch ((int)((dim + 31) / 32)) {
         FB4_SCORE_CASE(1) FB4_SCORE_CASE(2) FB4_SCORE_CASE(3) FB4_SCORE_CASE(4)

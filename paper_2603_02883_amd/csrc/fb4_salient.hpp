@@ -4,8 +4,8 @@
 // its attention group of |Q.K^T| (spatial / 3D attention) or max(Q.K^T, 0)
 // (temporal attention), pre-softmax.
 //
-// attention_scores_kernel: the one dense contraction of this library, on the
-// matrix cores.  A workgroup of four wavefronts takes 256 queries of one group;
+// attention_scores_kernel and the kernels behind it: the one dense contraction of
+// this library, on the matrix cores.  A workgroup of four wavefronts takes 256 queries of one group;
 // every wavefront keeps its 64 queries as B operands in registers for the whole
 // pass and walks over the group's keys 64 at a time: the key block goes through
 // LDS once for the four wavefronts (rows padded by 16 bytes so that the 16-byte
@@ -22,6 +22,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 namespace fb4 {
 
@@ -144,126 +146,197 @@ __global__ __launch_bounds__(kScoreThreads) void attention_scores_kernel(const u
     }
 }
 
-// The same scores for groups whose rows are exactly 128 channels and whose tokens are a multiple of 128: four blocks
-// of 32 queries per wavefront, so that one 16-byte operand read from LDS feeds four MFMAs (the kernel above feeds
-// two and is bound by that LDS traffic).  128 queries x 128 channels of B operands and four accumulator blocks
-// need about 220 registers; to keep two wavefronts per SIMD beside them, key blocks are not staged through
-// registers: `global_load_lds_dwordx4` writes a wavefront's 64 x 16 bytes straight into LDS.  Those 1 KiB land
-// contiguously, so rows cannot be padded; instead piece p (16 bytes) of key row r sits at position p ^ (r % 16) of
-// the row (the load fetches the matching piece of global memory), which spreads the 16 rows that the lanes of one
-// LDS pass read over all 64 banks.
-// A workgroup of four wavefronts takes 256 queries: wavefront w holds queries 128 (w % 2) .. and walks the keys of
-// half w / 2 of the group, 64 per barrier, from that half's own double-buffered LDS region; the two halves' sums
-// meet in LDS at the end (always half 0 + half 1).
-constexpr int kDmaQB = 4;                  // blocks of 32 queries per wavefront
-constexpr int kDmaQueries = 2 * 32 * kDmaQB;   // per workgroup
+// Long groups of up to 128 channels: four blocks of 32 queries per wavefront, so that one 16-byte operand read from
+// LDS feeds four MFMAs.  Channels are taken in steps of 16, not padded to 32: 72 channels are 5 steps.
+// kP: 16-byte pieces per row (dim / 8).  Queries as B operands (16 registers per step) and four accumulator blocks
+// leave no room to stage key blocks through registers: `global_load_lds_dwordx4` writes a wavefront's 64 x 16 bytes
+// straight into LDS.  Those 1 KiB land contiguously, so rows cannot be padded; instead piece p of key row r sits at
+// position p ^ ((r / (16 / G)) % G) of its row, G = gcd(kP, 16) (the load fetches the matching piece of global
+// memory), which spreads the 16 rows that the lanes of one LDS pass read over all 64 banks.  With an odd kP the upper
+// half of the last step lies past the row: its lanes read a zeroed piece behind the buffer.
+// A workgroup of four wavefronts takes up to 2 * blocks_per_wave blocks of queries: wavefront w holds those of set
+// w % 2 and walks the keys of half w / 2 of the group, 64 per barrier, from that half's own double-buffered LDS
+// region; the two halves' sums meet in LDS at the end (always half 0 + half 1).  Queries that do not fill a workgroup
+// are taken by one short workgroup per group; those are the last of the launch, so that they fill up its end.
+// Measured (us; before: every row through registers into padded LDS rows, channels padded to 32, two MFMAs per
+// operand read): 272 groups x 1350 tokens x 72 channels 132 -> 70.5 (71.4 GFLOP: 1.0 PFLOP/s), 64 channels 91 -> 62,
+// 300 x 1000 x 96 81 -> 60, 300 x 1000 x 40 41 -> 28.6; 384 x 1024 x 128, which had a kernel of this kind, 95 -> 93.
+constexpr int kDmaQB = 4;                  // blocks of 32 queries per wavefront at most
 constexpr int kDmaKeys = 64;               // per barrier and half
-constexpr int kDmaDim = 128;
-constexpr uint32_t kDmaBlockBytes = kDmaKeys * kDmaDim * 2;   // 16 KiB
+constexpr int kDmaMaxPieces = 16;
+// Wavefronts per SIMD: three where 168 registers hold the kernel (up to 72 channels), else two.  With three the sums
+// of 32 keys are kept from being moved among the next 32 keys' MFMAs, which would need a second set of accumulators
+// (272 groups x 1350 tokens x 72 channels: 76.6 us with two, 70.5 with three; 64 channels 67 and 62).
+constexpr int dma_waves(int pieces) { return pieces <= 9 ? 3 : 2; }
 
-template <bool kRelu>
-__global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t tokens, uint32_t blocks_per_group,
-                                 float* scores)
+template <int kP, bool kRelu>
+__global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(dma_waves(kP), dma_waves(kP))))
+void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t groups, uint32_t tokens, uint32_t n_full,
+                                 uint32_t blocks_per_wave, float* scores)
 {
-    constexpr int kSteps = kDmaDim / 16;
+    constexpr int kSteps = (kP + 1) / 2;
+    constexpr uint32_t kRowBytes = kP * 16;
+    constexpr uint32_t kHalfBytes = kDmaKeys * kRowBytes;
+    constexpr uint32_t kG = kP % 16 == 0 ? 16 : kP % 8 == 0 ? 8 : kP % 4 == 0 ? 4 : kP % 2 == 0 ? 2 : 1;
     // Two buffers per key half, as two arrays: the compiler then sees that the loads into one do not touch the
     // operand reads from the other and does not wait for them.
-    __shared__ __align__(1024) uint8_t lds_a[2 * kDmaBlockBytes];   // [half], even key blocks
-    __shared__ __align__(1024) uint8_t lds_b[2 * kDmaBlockBytes];   // [half], odd key blocks
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ __align__(1024) uint8_t lds_a[2 * kHalfBytes + 16];   // [half], even steps; zeros
+    __shared__ __align__(1024) uint8_t lds_b[2 * kHalfBytes + 16];   // [half], odd steps; zeros
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t qset = wave & 1u, kh = wave >> 1;
-    const uint32_t pos = xcd_local_position(blockIdx.x, gridDim.x);
-    const uint32_t g = pos / blocks_per_group;
-    const uint32_t q0 = (pos - g * blocks_per_group) * kDmaQueries + qset * (32u * kDmaQB);
-    const uint16_t* qg = q + (size_t)g * tokens * kDmaDim;
-    const uint32_t half_keys = tokens / 2;                       // a multiple of 64
-    const uint8_t* kbase = reinterpret_cast<const uint8_t*>(k + ((size_t)g * tokens + (size_t)kh * half_keys) * kDmaDim);
+    const uint32_t n_blk = (tokens + 31u) / 32u;
+    // ---- this workgroup's blocks of queries
+    uint32_t g, first, cnt;
+    if (blockIdx.x < groups * n_full) {
+        const uint32_t pos = xcd_local_position(blockIdx.x, groups * n_full);
+        g = pos / n_full;
+        first = (pos - g * n_full) * 2u * blocks_per_wave;
+        cnt = 2u * blocks_per_wave;
+    } else {
+        g = blockIdx.x - groups * n_full;
+        first = n_full * 2u * blocks_per_wave;
+        cnt = n_blk - first;
+    }
+    const uint32_t cnt0 = (cnt + 1u) / 2u;
+    first += qset ? cnt0 : 0u;
+    cnt = qset ? cnt - cnt0 : cnt0;
+    // ---- this wavefront's keys: half 0 takes whole steps, half 1 the rest (at most as many steps)
+    const uint32_t n_steps = (n_blk + 3u) / 4u;
+    const uint32_t key_first = kh ? n_steps * kDmaKeys : 0u, my_steps = kh ? (n_blk - 2u * n_steps + 1u) / 2u : n_steps;
+    const uint16_t* qg = q + (size_t)g * tokens * (kP * 8);
+    const uint8_t* kg = reinterpret_cast<const uint8_t*>(k + (size_t)g * tokens * (kP * 8));
     const uint32_t half = lane >> 5, col = lane & 31u;
 
-    // ---- key blocks: this wavefront loads rows 32 (w % 2) .. + 31 of its half's block, eight loads of four rows
-    const uint32_t lrow = lane >> 4, lpos = lane & 15u;          // row within a load, position within the row
-    auto fetch = [&](uint32_t kb, uint8_t* buffer) {
+    // Position j (16 bytes) of a half's 64 rows: row j / kP.  kP loads of 64 positions, shared by the half's two
+    // wavefronts.  Rows past the group's last key are zeros: their products add nothing.
+    auto fetch = [&](uint32_t step, uint8_t* buffer) {
+        if (step >= my_steps) return;
+        // (opaque to the optimizer, which would otherwise keep every load's offset in a register of its own: with
+        // 72 channels these registers spill, 81 us instead of 70)
+        uint32_t l = lane;
+        asm volatile("" : "+v"(l));
+        const uint32_t key0 = key_first + step * kDmaKeys;
+        const uint8_t* base = kg + (size_t)key0 * kRowBytes;   // wave-uniform
+        auto piece_of = [&](uint32_t i, uint32_t& row) {   // the row and the piece that belong to load i's position of this lane
+            const uint32_t j = 64u * i + l;
+            row = j / kP;
+            return (j - row * kP) ^ ((row / (16u / kG)) & (kG - 1u));
+        };
+        if (key0 + kDmaKeys <= tokens) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t row = qset * 32u + 4u * i + lrow;      // key row of the block
-            const uint8_t* src = kbase + ((size_t)kb * kDmaKeys + row) * (kDmaDim * 2) + ((lpos ^ (row & 15u)) << 4);
-            const uint32_t dst = __builtin_amdgcn_readfirstlane(kh * kDmaBlockBytes + (qset * 32u + 4u * i) * 256u);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(buffer + dst), 16, 0, 0);
+            for (int i2 = 0; i2 < (kP + 1) / 2; ++i2) {
+                const uint32_t i = 2u * i2 + qset;
+                if (2 * i2 + 1 >= kP && i >= (uint32_t)kP) break;
+                uint32_t row;
+                const uint32_t piece = piece_of(i, row);
+                const uint8_t* src = base + (row * kP + piece) * 16u;
+                const uint32_t dst = __builtin_amdgcn_readfirstlane(kh * kHalfBytes + i * 1024u);
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                                 (__attribute__((address_space(3))) void*)(buffer + dst), 16, 0, 0);
+            }
+        } else {
+#pragma unroll 1
+            for (uint32_t i = qset; i < (uint32_t)kP; i += 2) {   // the group's last step: through registers
+                uint32_t row;
+                const uint32_t piece = piece_of(i, row);
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (key0 + row < tokens) v = *reinterpret_cast<const uint4*>(base + (row * kP + piece) * 16u);
+                *reinterpret_cast<uint4*>(buffer + kh * kHalfBytes + i * 1024u + l * 16u) = v;
+            }
         }
     };
-    const uint32_t n_kb = half_keys / kDmaKeys;
-    fetch(0, lds_a);
+    // LDS offset of this lane's A operand of step s: key row lane % 32 of the first 32, piece 2 s + lane / 32
+    const uint32_t row_at = kh * kHalfBytes + col * kRowBytes, swz = (col / (16u / kG)) & (kG - 1u);
+    auto operand = [&](int s, int kk) -> uint32_t {
+        const uint32_t at = row_at + ((((uint32_t)(2 * s) + half) ^ swz) << 4) + kk * 32u * kRowBytes;
+        return (kP % 2 && s == kSteps - 1 && half) ? 2u * kHalfBytes : at;
+    };
+    float* meet = reinterpret_cast<float*>(lds_a);               // [query set][32 * kDmaQB]
 
-    // ---- this wavefront's queries as B operands (a query past the end reads the last one)
-    mfma_bf16x8 qf[kDmaQB][kSteps];
+    auto run = [&](auto blocks) {
+        constexpr int NB = decltype(blocks)::value;
+        // ---- this wavefront's queries as B operands (a query past the end reads the last one)
+        mfma_bf16x8 qf[NB > 0 ? NB : 1][kSteps];
 #pragma unroll
-    for (int b = 0; b < kDmaQB; ++b) {
-        const uint16_t* row = qg + (size_t)min(q0 + 32u * b + col, tokens - 1u) * kDmaDim;
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s)
-            qf[b][s] = __builtin_bit_cast(mfma_bf16x8, *reinterpret_cast<const uint4*>(row + 16u * s + 8u * half));
-    }
-    float sum[kDmaQB];
-#pragma unroll
-    for (int b = 0; b < kDmaQB; ++b) sum[b] = 0.0f;
-    // A operand of step s: key row 32 kk + lane % 32, piece 2 s + lane / 32, swizzled
-    const uint32_t a0 = kh * kDmaBlockBytes + col * 256u + (((col & 15u) ^ half) << 4);
-    auto compute = [&](const uint8_t* buffer) {
-        // the operand of the next step is read while this step's MFMAs run
-        uint4 a_next = *reinterpret_cast<const uint4*>(buffer + a0);
-#pragma unroll
-        for (int kk = 0; kk < kDmaKeys / 32; ++kk) {
-            mfma_f32x16 acc[kDmaQB];
-#pragma unroll
-            for (int b = 0; b < kDmaQB; ++b) acc[b] = mfma_f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        for (int b = 0; b < NB; ++b) {
+            const uint16_t* row = qg + (size_t)min((first + b) * 32u + col, tokens - 1u) * (kP * 8);
 #pragma unroll
             for (int s = 0; s < kSteps; ++s) {
-                const uint4 a = a_next;
-                const int ns = (s + 1) % kSteps, nk = kk + (s + 1) / kSteps;
-                if (nk < kDmaKeys / 32)
-                    a_next = *reinterpret_cast<const uint4*>(buffer + ((a0 ^ ((uint32_t)ns << 5)) + nk * 32 * 256));
-#pragma unroll
-                for (int b = 0; b < kDmaQB; ++b)
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mfma_bf16x8, a), qf[b][s], acc[b], 0, 0, 0);
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (!(kP % 2 && s == kSteps - 1) || half == 0) v = *reinterpret_cast<const uint4*>(row + 16u * s + 8u * half);
+                qf[b][s] = __builtin_bit_cast(mfma_bf16x8, v);
             }
+        }
+        float sum[NB > 0 ? NB : 1];
 #pragma unroll
-            for (int b = 0; b < kDmaQB; ++b) {
+        for (int b = 0; b < NB; ++b) sum[b] = 0.0f;
+        auto compute = [&](const uint8_t* buffer, uint32_t step) {
+            if (NB == 0 || step >= my_steps) return;
+            // the operand of the next step is read while this step's MFMAs run
+            uint4 a_next = *reinterpret_cast<const uint4*>(buffer + operand(0, 0));
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sum[b] += kRelu ? fmaxf(acc[b][r], 0.0f) : fabsf(acc[b][r]);
+            for (int kk = 0; kk < kDmaKeys / 32; ++kk) {
+                mfma_f32x16 acc[NB > 0 ? NB : 1];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b] = mfma_f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) {
+                    const uint4 a = a_next;
+                    const int ns = (s + 1) % kSteps, nk = kk + (s + 1) / kSteps;
+                    if (nk < kDmaKeys / 32) a_next = *reinterpret_cast<const uint4*>(buffer + operand(ns, nk));
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mfma_bf16x8, a), qf[b][s], acc[b], 0, 0, 0);
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum[b] += kRelu ? fmaxf(acc[b][r], 0.0f) : fabsf(acc[b][r]);
+                }
+                if (dma_waves(kP) > 2) __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the first step's keys are in LDS
+        __syncthreads();
+        for (uint32_t step = 0; step < n_steps; step += 2) {
+            if (step + 1 < n_steps) fetch(step + 1, lds_b);
+            compute(lds_a, step);
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // the next step's keys have landed before anyone reads them
+            __syncthreads();
+            if (step + 1 < n_steps) {
+                if (step + 2 < n_steps) fetch(step + 2, lds_a);
+                compute(lds_b, step + 1);
+                __builtin_amdgcn_s_waitcnt(0x0F70);
+                __syncthreads();
+            }
+        }
+        // ---- the two key halves meet: half 1 through LDS, then half 0 + half 1
+#pragma unroll
+        for (int b = 0; b < NB; ++b) sum[b] += __shfl_xor(sum[b], 32);   // the two half-wavefronts hold different keys
+        if (kh == 1 && half == 0) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) meet[qset * (32u * kDmaQB) + 32u * b + col] = sum[b];
+        }
+        __syncthreads();
+        if (kh == 0 && half == 0) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const uint32_t qi = (first + b) * 32u + col;
+                if (qi < tokens) scores[(size_t)g * tokens + qi] = (sum[b] + meet[qset * (32u * kDmaQB) + 32u * b + col]) / (float)tokens;
             }
         }
     };
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the first block is in LDS
-    __syncthreads();
-    for (uint32_t kb = 0; kb < n_kb; kb += 2) {
-        if (kb + 1 < n_kb) fetch(kb + 1, lds_b);
-        compute(lds_a);
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // the next block has landed before anyone reads it
-        __syncthreads();
-        if (kb + 1 < n_kb) {
-            if (kb + 2 < n_kb) fetch(kb + 2, lds_a);
-            compute(lds_b);
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            __syncthreads();
-        }
+    fetch(0, lds_a);
+    if (kP % 2 && threadIdx.x < 8) {   // the zeroed pieces
+        reinterpret_cast<uint32_t*>((threadIdx.x & 4u ? lds_b : lds_a) + 2 * kHalfBytes)[threadIdx.x & 3u] = 0;
     }
-    // ---- the two key halves meet: half 1 through LDS, then half 0 + half 1
-    float* meet = reinterpret_cast<float*>(lds_a);               // [query set][128]
-#pragma unroll
-    for (int b = 0; b < kDmaQB; ++b) sum[b] += __shfl_xor(sum[b], 32);   // the two half-wavefronts hold different keys
-    if (kh == 1 && half == 0) {
-#pragma unroll
-        for (int b = 0; b < kDmaQB; ++b) meet[qset * 128u + 32u * b + col] = sum[b];
-    }
-    __syncthreads();
-    if (kh == 0 && half == 0) {
-#pragma unroll
-        for (int b = 0; b < kDmaQB; ++b) {
-            const uint32_t qi = q0 + 32u * b + col;
-            if (qi < tokens) scores[(size_t)g * tokens + qi] = (sum[b] + meet[qset * 128u + 32u * b + col]) / (float)tokens;
-        }
+    // (wave-uniform; every path meets the same barriers)
+    switch (cnt) {
+    case 0: run(std::integral_constant<int, 0>{}); break;
+    case 1: run(std::integral_constant<int, 1>{}); break;
+    case 2: run(std::integral_constant<int, 2>{}); break;
+    case 3: run(std::integral_constant<int, 3>{}); break;
+    default: run(std::integral_constant<int, 4>{}); break;
     }
 }
 

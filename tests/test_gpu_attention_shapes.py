@@ -1,0 +1,77 @@
+"""Attention scores at the edges of the kernels' tiles: token counts around the blocks of 32 queries and 64 keys, rows of
+every kind of length (odd and even numbers of 16-byte pieces), values that must not leave their row."""
+
+import numpy as np
+import pytest
+import torch
+
+from fb4_inputs import synth
+
+pytestmark = pytest.mark.gpu
+
+LONG_TOKENS = [65, 95, 96, 97, 127, 128, 129, 161, 192, 255, 257, 289, 513]
+DIMS = [8, 16, 24, 32, 40, 56, 64, 72, 80, 96, 104, 112, 120, 128]
+
+
+@pytest.fixture(scope="module")
+def F():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_02883_amd as F
+    return F
+
+
+def reference(q, k, mode):
+    """(scores, error bound) in float64.  The products of two bf16 are exact in fp32; at most dim + tokens + 8 additions
+    and one division follow, each rounding by at most 2^-24 (chopping included: 2^-23) of the sum of absolute values."""
+    s = torch.matmul(q.double().cpu(), k.double().cpu().transpose(1, 2))
+    ref = (s.clamp_min(0) if mode else s.abs()).mean(dim=2)
+    mass = torch.matmul(q.double().cpu().abs(), k.double().cpu().abs().transpose(1, 2)).mean(dim=2)
+    return ref, mass * (q.shape[2] + q.shape[1] + 8) * 2.0 ** -23 + 1e-30
+
+
+def check(F, q, k, mode):
+    groups, tokens, dim = q.shape
+    out = torch.full((groups * tokens + 64,), -7.0, device="cuda")       # what lies behind the scores stays
+    F.fb4_attention_scores(q, k, mode, scores=out[:groups * tokens].view(groups, tokens))
+    torch.cuda.synchronize()
+    assert (out[groups * tokens:] == -7.0).all()
+    got = out[:groups * tokens].view(groups, tokens).double().cpu()
+    ref, bound = reference(q, k, mode)
+    assert ((got - ref).abs() <= bound).all(), (groups, tokens, dim, mode)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("tokens", LONG_TOKENS)
+def test_long_groups(F, tokens, mode):
+    for i, dim in enumerate(DIMS):
+        groups = (1, 3, 10)[i % 3]
+        q, k = synth.attention_qk(groups, tokens, dim, seed=100 * tokens + dim, device="cuda")
+        check(F, q, k, mode)
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 3, 4])
+def test_long_groups_with_every_number_of_query_blocks(F, blocks):
+    # launches whose size makes the launcher take 1, 2, 3 and 4 blocks of queries per wavefront
+    groups, tokens = {1: (16, 390), 2: (8, 1500), 3: (24, 999), 4: (130, 480)}[blocks]
+    q, k = synth.attention_qk(groups, tokens, 72, seed=blocks, device="cuda")
+    check(F, q, k, 0)
+
+
+@pytest.mark.parametrize("dim", [24, 64, 72, 128])
+@pytest.mark.parametrize("tokens", [67, 130])
+def test_infinities_and_nans_stay_in_their_rows(F, tokens, dim):
+    q, k = synth.attention_qk(3, tokens, dim, seed=dim + tokens, device="cuda")
+    clean = F.fb4_attention_scores(q, k, 0).clone()
+    q2, k2 = q.clone(), k.clone()
+    q2[0, 5, dim - 1] = float("nan")         # one query of group 0
+    k2[2, tokens - 1, 0] = float("inf")      # the last key of group 2: every score of that group is infinite
+    k2[2, tokens - 1, 1:] = 0.0
+    q2[2, :, 0] = 1.0
+    got = F.fb4_attention_scores(q2, k2, 0)
+    torch.cuda.synchronize()
+    assert torch.isnan(got[0, 5])
+    keep = torch.ones(tokens, dtype=torch.bool, device="cuda")
+    keep[5] = False
+    assert torch.equal(got[0][keep], clean[0][keep]) and torch.equal(got[1], clean[1])
+    assert torch.isinf(got[2]).all()
