@@ -1,6 +1,8 @@
 // C ABI of the FB4 quantizer library, the attention-guided entry points (Sec. 3.3, 3.4, App. F): scores on the
 // matrix cores, the per-tile choice, SeDA's main anchors and correlated tokens.  Declarations and contracts are in
 // include/fb4.h.
+#include <algorithm>
+
 #include "fb4_common.hpp"
 #include "fb4_salient.hpp"
 
@@ -42,12 +44,50 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
     if (!q || !k || !scores || dim == 0) return FB4_ERR_INVALID_ARG;
     if ((dim % 8) || dim > 256 || !aligned(q, 16) || !aligned(k, 16) || !aligned(scores, 4)) return FB4_ERR_UNSUPPORTED;
     const bool small = tokens <= (int64_t)kScoreShortGroup;
-    const int64_t per_wg = small ? 128 : 256;   // queries per workgroup of the two kernel shapes
+    const int64_t per_wg = small ? 128 : 256;
     const int64_t bpg = (tokens + per_wg - 1) / per_wg;
     if (tokens * dim > 0x7FFFFFFFll || groups * bpg > 0x7FFFFFFFll) return FB4_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const dim3 grid((unsigned)(groups * bpg));
-    if (!small && dim <= 8 * kDmaMaxPieces) {   // (longer rows: too many registers for four blocks of queries)
+    if (small) {
+        const uint32_t pieces = (uint32_t)(dim / 8);
+        const uint32_t rows_per_task = tokens > 32 ? (uint32_t)tokens : (32u / (uint32_t)tokens) * (uint32_t)tokens;
+        // One to four wavefronts per workgroup, at most 64 KiB of LDS: what puts most of them on a compute unit, up to
+        // eight (24576 groups x 16 tokens x 128 channels: 37.7 us with four, 35.4 with eight, 38.0 with ten).
+        const uint32_t per_wave = short_wave_bytes(rows_per_task, pieces);
+        uint32_t waves = 1, most = 0;
+        for (uint32_t w = 4; w >= 1; --w) {
+            if (w * per_wave > 65536u) continue;
+            const uint32_t n = std::min(163840u / (w * per_wave), 8u / w);
+            if (n * w > most) { most = n * w; waves = w; }
+        }
+        // (row numbers are 32 bits in the kernel: longer inputs take several launches)
+        const int64_t at_once = ((1ll << 30) / rows_per_task) * rows_per_task / tokens;
+        for (int64_t g0 = 0; g0 < groups; g0 += at_once) {
+            const uint32_t n_rows = (uint32_t)(std::min(at_once, groups - g0) * tokens);
+            const uint32_t n_tasks = (n_rows + rows_per_task - 1) / rows_per_task;
+            // every wavefront with the same number of tasks (6000 x 48 x 72: 16.3 us; with the last round ragged 17.5)
+            const uint32_t rounds = (n_tasks + 256u * most - 1) / (256u * most);
+            const dim3 sgrid((n_tasks + rounds * waves - 1) / (rounds * waves));
+            const uint16_t* qs = static_cast<const uint16_t*>(q) + (size_t)(g0 * tokens * dim);
+            const uint16_t* ks = static_cast<const uint16_t*>(k) + (size_t)(g0 * tokens * dim);
+            float* out = scores + g0 * tokens;
+#define FB4_SHORT_LAUNCH(p, n) hipLaunchKernelGGL((attention_scores_short_kernel<p, n>), sgrid, dim3(64 * waves), waves * per_wave, s, qs, ks, n_rows, (uint32_t)tokens, rows_per_task, n_tasks, pieces, (uint32_t)mode, out)
+#define FB4_SHORT_CASE(n)                               \
+            switch (pieces) {                           \
+            case 8: FB4_SHORT_LAUNCH(8, n); break;      \
+            case 9: FB4_SHORT_LAUNCH(9, n); break;      \
+            case 12: FB4_SHORT_LAUNCH(12, n); break;    \
+            case 16: FB4_SHORT_LAUNCH(16, n); break;    \
+            default: FB4_SHORT_LAUNCH(0, n); break;     \
+            }
+            if (tokens <= 32) { FB4_SHORT_CASE(1) } else { FB4_SHORT_CASE(2) }
+#undef FB4_SHORT_CASE
+#undef FB4_SHORT_LAUNCH
+            if (hipGetLastError() != hipSuccess) return FB4_ERR_HIP;
+        }
+        return FB4_OK;
+    }
+    if (dim <= 8 * kDmaMaxPieces) {   // (longer rows: too many registers for four blocks of queries)
         const uint32_t n_blk = (uint32_t)((tokens + 31) / 32);
         uint32_t bpw = dma_blocks_per_wave(groups, n_blk);
         const uint32_t n_full = n_blk / (2 * bpw), n_wg = n_full + (n_blk % (2 * bpw) ? 1 : 0);
@@ -68,25 +108,18 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
 #undef FB4_DMA_ARGS
         return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
     }
+    const dim3 grid((unsigned)(groups * bpg));
 #define FB4_SCORE_ARGS static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), (uint32_t)tokens, (uint32_t)dim, (uint32_t)bpg, scores
-#define FB4_SCORE_LAUNCH(d, relu, qb, keys) hipLaunchKernelGGL((attention_scores_kernel<d, relu, qb, keys>), grid, dim3(kScoreThreads), 0, s, FB4_SCORE_ARGS)
-#define FB4_SCORE_CASE(d)                                                    \
-    case d:                                                                  \
-        if (small) {                                                         \
-            if (mode) FB4_SCORE_LAUNCH(d, true, 1, 32);                      \
-            else FB4_SCORE_LAUNCH(d, false, 1, 32);                          \
-        } else if constexpr (d * 4 > kDmaMaxPieces) {                        \
-            if (mode) FB4_SCORE_LAUNCH(d, true, 2, 64);                      \
-            else FB4_SCORE_LAUNCH(d, false, 2, 64);                          \
-        }                                                                    \
+#define FB4_SCORE_CASE(d)                                                                                                          \
+    case d:                                                                                                                        \
+        if (mode) hipLaunchKernelGGL((attention_scores_kernel<d, true>), grid, dim3(kScoreThreads), 0, s, FB4_SCORE_ARGS);         \
+        else hipLaunchKernelGGL((attention_scores_kernel<d, false>), grid, dim3(kScoreThreads), 0, s, FB4_SCORE_ARGS);             \
         break;
     switch ((int)((dim + 31) / 32)) {
-        FB4_SCORE_CASE(1) FB4_SCORE_CASE(2) FB4_SCORE_CASE(3) FB4_SCORE_CASE(4)
         FB4_SCORE_CASE(5) FB4_SCORE_CASE(6) FB4_SCORE_CASE(7) FB4_SCORE_CASE(8)
         default: return FB4_ERR_UNSUPPORTED;
     }
 #undef FB4_SCORE_CASE
-#undef FB4_SCORE_LAUNCH
 #undef FB4_SCORE_ARGS
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }

@@ -4,16 +4,13 @@
 // its attention group of |Q.K^T| (spatial / 3D attention) or max(Q.K^T, 0)
 // (temporal attention), pre-softmax.
 //
-// attention_scores_kernel and the kernels behind it: the one dense contraction of
-// this library, on the matrix cores.  A workgroup of four wavefronts takes 256 queries of one group;
-// every wavefront keeps its 64 queries as B operands in registers for the whole
-// pass and walks over the group's keys 64 at a time: the key block goes through
-// LDS once for the four wavefronts (rows padded by 16 bytes so that the 16-byte
-// operand reads of the 16 lanes of a pass fall into 16 different bank groups),
-// each step is a 32x32x16 bf16 MFMA with fp32 accumulation computing S^T = K Q^T -- transposed
+// The scores are the one dense contraction of this library and run on the matrix
+// cores: 32x32x16 bf16 MFMAs with fp32 accumulation computing S^T = K Q^T -- transposed
 // so that a lane's 16 accumulators are 16 keys of ONE query: |.| or max(., 0)
 // and the sum over keys then stay inside the lane, and the two half-wavefronts
-// are only added up once at the very end.
+// are only added up once at the very end.  Three kernels: groups of up to 64 tokens
+// (attention_scores_short_kernel), longer ones with rows of up to 128 channels
+// (attention_scores_dma_kernel) and of more (attention_scores_kernel).
 //
 // select_salient_kernel: per frame the head mean (in double, head by head), the
 // best token of every tile (lowest index on ties, a NaN never wins), and the
@@ -41,13 +38,16 @@ __device__ __forceinline__ uint32_t xcd_local_position(uint32_t b, uint32_t n)
     const uint32_t chunk = n / 8u;
     return b < chunk * 8u ? (b % 8u) * chunk + b / 8u : b;
 }
-// Two shapes of the kernel: 64 queries per wavefront and 64 keys per barrier for long groups (spatial / 3D
-// attention), 32 and 32 for short ones (temporal attention: a group is a handful of frames).
-constexpr uint32_t kScoreShortGroup = 64;   // tokens up to which the small shape is used
+constexpr uint32_t kScoreShortGroup = 64;   // tokens up to which attention_scores_short_kernel is used
 
+// Long groups with rows of more than 128 channels: a workgroup of four wavefronts takes 256 queries of one group; every
+// wavefront keeps its 64 queries as B operands in registers for the whole pass and walks over the group's keys 64 at a
+// time: the key block goes through LDS once for the four wavefronts (rows padded by 16 bytes so that the 16-byte
+// operand reads of the 16 lanes of a pass fall into 16 different bank groups).
 // D32: channels / 32, rounded up (channels beyond `dim` are zero on both sides).  kRelu: max(., 0), else |.|.
-// kScoreQB: blocks of 32 queries per wavefront; kScoreKeys: keys per barrier (a multiple of 32).
-template <int D32, bool kRelu, int kScoreQB, int kScoreKeys>
+constexpr int kScoreQB = 2;      // blocks of 32 queries per wavefront
+constexpr int kScoreKeys = 64;   // keys per barrier
+template <int D32, bool kRelu>
 __global__ __launch_bounds__(kScoreThreads) void attention_scores_kernel(const uint16_t* q, const uint16_t* k,
                                                                          uint32_t tokens, uint32_t dim,
                                                                          uint32_t blocks_per_group, float* scores)
@@ -337,6 +337,141 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
     case 2: run(std::integral_constant<int, 2>{}); break;
     case 3: run(std::integral_constant<int, 3>{}); break;
     default: run(std::integral_constant<int, 4>{}); break;
+    }
+}
+
+// Short groups (temporal attention: a group is a handful of frames), bound by memory: Q and K are read once and a
+// float per row comes back.  A wavefront takes kNB blocks of 32 rows at a time -- as many whole groups as fit 32
+// rows (kNB = 1), or one group of 33 to 64 rows (kNB = 2); the tensors are contiguous, so those rows are one run of
+// memory -- loads them straight into LDS of its own (pieces placed as in the kernel above), forms all products of the
+// 32 queries with the 32 keys on the matrix cores and adds up those whose key lies in the query's group.  Nothing is
+// shared between wavefronts, so there are no barriers; a wavefront requests the rows of its next task as soon as
+// it has read its operands.  kP: 16-byte pieces per row, 0: taken from `pieces`.
+// Measured (us; before: one workgroup of four wavefronts, barriers and room for 128 queries per group): 24576 groups x
+// 16 tokens x 128 channels 53 -> 35.4 (5.7 TB/s), x 72 channels 39 -> 20.5, 12000 x 21 x 64 15.2 -> 11.4, 6000 x 40 x
+// 128 26.5 -> 23.9, 100000 x 4 x 64 95 -> 18.8; 12000 x 64 x 64 37.6 -> 36.9.
+__host__ __device__ constexpr uint32_t short_region_bytes(uint32_t rows, uint32_t pieces)   // of one matrix: whole loads
+{
+    return (rows * pieces + 63u) / 64u * 1024u;
+}
+__host__ __device__ constexpr uint32_t short_wave_bytes(uint32_t rows, uint32_t pieces)
+{
+    return 2u * short_region_bytes(rows, pieces) + (pieces & 1u) * 16u;
+}
+
+template <int kP, int kNB>
+__global__ __launch_bounds__(kScoreThreads) void attention_scores_short_kernel(const uint16_t* q, const uint16_t* k,
+                                                                               uint32_t n_rows, uint32_t tokens,
+                                                                               uint32_t rows_per_task, uint32_t n_tasks,
+                                                                               uint32_t pieces, uint32_t relu, float* scores)
+{
+    extern __shared__ __align__(1024) uint8_t short_lds[];
+    const uint32_t P = kP ? (uint32_t)kP : pieces;
+    const uint32_t n_waves = blockDim.x >> 6;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t half = lane >> 5, col = lane & 31u;
+    const uint32_t g_log = P % 16u == 0 ? 4u : (uint32_t)__builtin_ctz(P | 16u);   // log2 of gcd(P, 16)
+    const uint32_t region = short_region_bytes(rows_per_task, P);
+    const uint32_t base = wave * short_wave_bytes(rows_per_task, P);
+    uint8_t* lq = short_lds + base;
+    uint8_t* lk = lq + region;
+    if ((P & 1u) && lane < 4) reinterpret_cast<uint32_t*>(lk + region)[lane] = 0;   // the zeroed piece of an odd row's last step
+    const uint8_t* qb = reinterpret_cast<const uint8_t*>(q);
+    const uint8_t* kb = reinterpret_cast<const uint8_t*>(k);
+
+    auto fetch = [&](uint32_t task) {
+        const uint32_t row0 = task * rows_per_task;                          // wave-uniform
+        const uint32_t n = min(rows_per_task, n_rows - row0);
+        const uint8_t* q0 = qb + (size_t)row0 * (P * 16u);
+        const uint8_t* k0 = kb + (size_t)row0 * (P * 16u);
+#pragma unroll 4
+        for (uint32_t i = 0; i * 64u < n * P; ++i) {
+            const uint32_t j = 64u * i + lane, row = min(j / P, n - 1u);         // (past the last row: that row again)
+            const uint32_t piece = (j % P) ^ ((row >> (4u - g_log)) & ((1u << g_log) - 1u));
+            const uint32_t off = (row * P + piece) * 16u;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(k0 + off),
+                                             (__attribute__((address_space(3))) void*)(lk + i * 1024u), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(q0 + off),
+                                             (__attribute__((address_space(3))) void*)(lq + i * 1024u), 16, 0, 0);
+        }
+    };
+    const uint32_t steps = (P + 1u) / 2u;
+    // this lane's 16 bytes of step s of row 32 b + lane % 32 (past the task's rows: of its last row; nobody uses the result)
+    auto operand = [&](const uint8_t* m, uint32_t b, uint32_t s) {
+        const uint32_t row = min(b * 32u + col, rows_per_task - 1u);
+        const uint32_t swz = (row >> (4u - g_log)) & ((1u << g_log) - 1u);
+        const uint32_t at = (row * P + ((2u * s + half) ^ swz)) * 16u;
+        const bool past = (P & 1u) && s + 1u == steps && half;
+        return __builtin_bit_cast(mfma_bf16x8, *reinterpret_cast<const uint4*>(past ? lk + region : m + at));
+    };
+    // a query's group: keys lo .. lo + tokens - 1 of the task's rows
+    const uint32_t lo = kNB == 1 ? (col / tokens) * tokens : 0u;
+    const float n_keys = (float)tokens;
+    const uint32_t stride = gridDim.x * n_waves;
+    uint32_t task = blockIdx.x * n_waves + wave;
+    if (task >= n_tasks) return;
+    fetch(task);
+    while (true) {
+        const uint32_t next = task + stride;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the task's rows are in LDS
+        float sum[kNB];
+#pragma unroll
+        for (int b = 0; b < kNB; ++b) sum[b] = 0.0f;
+        auto add_up = [&](const mfma_f32x16& acc, int keys, float& s) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                // accumulator r belongs to key 8 (r / 4) + 4 (lane / 32) + r % 4 of the block
+                const float v = relu ? fmaxf(acc[r], 0.0f) : fabsf(acc[r]);
+                s += (32u * keys + 8u * (r / 4) + 4u * half + (r % 4) - lo < tokens) ? v : 0.0f;
+            }
+        };
+        auto refill = [&]() {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // every operand of this task has been read
+            if (next < n_tasks) fetch(next);
+        };
+        if constexpr (kP != 0 && kNB == 1) {
+            constexpr int kSteps = (kP + 1) / 2;
+            mfma_bf16x8 a[kSteps], bq[kSteps];
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) { a[s] = operand(lk, 0, s); bq[s] = operand(lq, 0, s); }
+            refill();
+            mfma_f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], bq[s], acc, 0, 0, 0);
+            add_up(acc, 0, sum[0]);
+        } else {
+            mfma_f32x16 acc[kNB][kNB];
+#pragma unroll
+            for (int i = 0; i < kNB; ++i) {
+#pragma unroll
+                for (int b = 0; b < kNB; ++b) acc[i][b] = mfma_f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            }
+#pragma unroll 2
+            for (uint32_t s = 0; s < steps; ++s) {
+                mfma_bf16x8 a[kNB], bq[kNB];
+#pragma unroll
+                for (int b = 0; b < kNB; ++b) { a[b] = operand(lk, b, s); bq[b] = operand(lq, b, s); }
+#pragma unroll
+                for (int i = 0; i < kNB; ++i) {
+#pragma unroll
+                    for (int b = 0; b < kNB; ++b) acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bq[b], acc[i][b], 0, 0, 0);
+                }
+            }
+            refill();
+#pragma unroll
+            for (int b = 0; b < kNB; ++b) {
+#pragma unroll
+                for (int i = 0; i < kNB; ++i) add_up(acc[i][b], i, sum[b]);
+            }
+        }
+        const uint32_t row0 = task * rows_per_task, n = min(rows_per_task, n_rows - row0);
+#pragma unroll
+        for (int b = 0; b < kNB; ++b) {
+            const float total = sum[b] + __shfl_xor(sum[b], 32);   // the two half-wavefronts hold different keys of one query
+            if (half == 0 && 32u * b + col < n) scores[(size_t)row0 + 32u * b + col] = total / n_keys;
+        }
+        if (next >= n_tasks) break;
+        task = next;
     }
 }
 

@@ -75,3 +75,38 @@ def test_infinities_and_nans_stay_in_their_rows(F, tokens, dim):
     keep[5] = False
     assert torch.equal(got[0][keep], clean[0][keep]) and torch.equal(got[1], clean[1])
     assert torch.isinf(got[2]).all()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("tokens", [1, 2, 3, 5, 8, 11, 15, 16, 17, 21, 31, 32, 33, 40, 47, 63, 64])
+def test_short_groups(F, tokens, mode):
+    for i, dim in enumerate(DIMS + [136, 200, 248, 256]):
+        groups = (1, 2, 7, 33, 1001)[i % 5]
+        q, k = synth.attention_qk(groups, tokens, dim, seed=1000 * tokens + dim, device="cuda")
+        check(F, q, k, mode)
+
+
+@pytest.mark.parametrize("dim", [64, 72, 96, 128, 40])
+def test_short_groups_over_many_tasks_per_wavefront(F, dim):
+    for groups, tokens in ((40001, 16), (30003, 24), (9001, 50)):
+        q, k = synth.attention_qk(groups, tokens, dim, seed=dim, device="cuda")
+        out = F.fb4_attention_scores(q, k, 1)
+        p = torch.matmul(q.float(), k.float().transpose(1, 2).contiguous())
+        ref = p.clamp_min(0).mean(dim=2)
+        # both sides round their sums in fp32: the bound of `reference` twice, with the products' mass from above
+        mass = (q.float().norm(dim=2) * k.float().norm(dim=2).amax(dim=1, keepdim=True))
+        assert ((out - ref).abs() <= mass * (dim + tokens + 8) * 2.0 ** -22).all(), (groups, tokens, dim)
+
+
+def test_short_groups_keep_infinities_and_nans_in_their_group(F):
+    for dim in (24, 64, 72):
+        q, k = synth.attention_qk(9, 12, dim, seed=dim, device="cuda")
+        clean = F.fb4_attention_scores(q, k, 0).clone()
+        k2 = k.clone()
+        k2[3, 11, :] = float("nan")
+        k2[5, 0, dim - 1] = float("inf")
+        got = F.fb4_attention_scores(q, k2, 0)
+        torch.cuda.synchronize()
+        assert torch.isnan(got[3]).all() and not torch.isfinite(got[5]).any()
+        rest = [0, 1, 2, 4, 6, 7, 8]
+        assert torch.equal(got[rest], clean[rest])
