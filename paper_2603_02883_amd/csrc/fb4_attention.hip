@@ -157,21 +157,32 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
     if (frames * tokens > 0x7FFFFFFFll || n_anchors > 0x7FFFFFFFll || tokens * dim > 0x7FFFFFFFll) return FB4_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint32_t n = (uint32_t)(frames * tokens);
-    hipLaunchKernelGGL(seda_fill_kernel, dim3((n + 255) / 256), dim3(256), 0, s, token_group, anchor_group, n);
+    const uint32_t gh = (uint32_t)grid_h, gw = (uint32_t)grid_w, th = (uint32_t)tile_h, tw = (uint32_t)tile_w;
+    const uint32_t n_prepare = (n + kPrepareRows - 1) / kPrepareRows;
+    if ((int64_t)n_prepare * n_anchors <= kPrepareMaxVisits) {
+        hipLaunchKernelGGL(seda_prepare_kernel, dim3(n_prepare), dim3(kAssignThreads), 0, s, anchors, (uint32_t)n_anchors, n,
+                           (uint32_t)tokens, gw, th, tw, token_group, anchor_group);
+    } else {
+        hipLaunchKernelGGL(seda_fill_kernel, dim3((n + kAssignThreads - 1) / kAssignThreads), dim3(kAssignThreads), 0, s, token_group,
+                           anchor_group, n);
+        hipLaunchKernelGGL(seda_anchor_kernel, dim3((unsigned)((n_anchors + kAssignThreads - 1) / kAssignThreads)), dim3(kAssignThreads),
+                           0, s, anchors, (uint32_t)n_anchors, (uint32_t)frames, gh, gw, th, tw, token_group, anchor_group);
+    }
     if (n_anchors > 0) {
         AssignParams p = {};
-        p.frames = (uint32_t)frames; p.heads = (uint32_t)heads; p.grid_h = (uint32_t)grid_h; p.grid_w = (uint32_t)grid_w;
-        p.dim = (uint32_t)dim; p.tile_h = (uint32_t)tile_h; p.tile_w = (uint32_t)tile_w;
+        p.frames = (uint32_t)frames; p.heads = (uint32_t)heads; p.grid_h = gh; p.grid_w = gw;
+        p.dim = (uint32_t)dim; p.tile_h = th; p.tile_w = tw;
         p.window = (uint32_t)window; p.window_t = (uint32_t)window_t;
         p.stride_f = joint ? (uint64_t)tokens : (uint64_t)heads * tokens;
         p.stride_h = joint ? (uint64_t)frames * tokens : (uint64_t)tokens;
         p.threshold = threshold;
-        hipLaunchKernelGGL(seda_mark_kernel, dim3((unsigned)n_anchors, (unsigned)window_t), dim3(kAssignThreads), 0, s,
-                           static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group,
-                           window_scores);
-        hipLaunchKernelGGL(seda_anchor_kernel, dim3((unsigned)((n_anchors + 255) / 256)), dim3(256), 0, s, anchors,
-                           (uint32_t)n_anchors, (uint32_t)frames, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h,
-                           (uint32_t)tile_w, token_group, anchor_group);
+        const dim3 grid((unsigned)n_anchors, (unsigned)window_t);
+#define FB4_MARK_LAUNCH(quads) hipLaunchKernelGGL(seda_mark_kernel<quads>, grid, dim3(kAssignThreads), 0, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group, anchor_group, window_scores)
+        if (window <= 3) FB4_MARK_LAUNCH(3);
+        else if (window <= 5) FB4_MARK_LAUNCH(7);
+        else if (window <= 7) FB4_MARK_LAUNCH(13);
+        else FB4_MARK_LAUNCH(16);
+#undef FB4_MARK_LAUNCH
     }
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }

@@ -577,20 +577,12 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
 // K[token], averaged over the heads -- exceeds a threshold.  The group of an anchor is the row-major number of the
 // spatial tile it lies in (the per-frame candidates of a tile share one sub-formatbook); a token marked by anchors
 // of several groups belongs to the highest group number (App. D: the subsequent anchor), an anchor to its own
-// group.  Three small launches: fill with -1, mark (one workgroup per anchor and frame of the window: 64 window
-// slots x 4 shares of the heads, a maximum on the group number), anchors.
+// group.  Two small launches: the anchors' own groups and -1 elsewhere (seda_prepare_kernel; with very many anchors
+// seda_fill_kernel and seda_anchor_kernel instead), then the marks -- a maximum on the group number of every token
+// that is no anchor (seda_mark_kernel, one workgroup per anchor and frame of the window).
 // Token (frame f, head h, token t) of Q / K sits at ((f * stride_f + h * stride_h) + t) * dim: factorized
 // attention [frames][heads][tokens][dim], 3D attention [heads][frames * tokens][dim].
-constexpr int kAssignThreads = 256;   // 64 window slots x 4 groups of heads
-
-__global__ __launch_bounds__(256) void seda_fill_kernel(int32_t* a, int32_t* b, uint32_t n)
-{
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i < n) {
-        a[i] = -1;
-        if (b) b[i] = -1;
-    }
-}
+constexpr int kAssignThreads = 256;
 
 __device__ __forceinline__ uint32_t tile_of(uint32_t token, uint32_t grid_w, uint32_t tile_h, uint32_t tile_w)
 {
@@ -598,34 +590,51 @@ __device__ __forceinline__ uint32_t tile_of(uint32_t token, uint32_t grid_w, uin
     return (y / tile_h) * ((grid_w + tile_w - 1) / tile_w) + x / tile_w;
 }
 
-// Dot product of two bf16 rows of `dim` channels (a multiple of 8) in fp32: four chains over the 16-byte pieces
-// c, c + 1, c + 2, c + 3 (mod 4), added as (0 + 1) + (2 + 3).
-__device__ __forceinline__ float dot_bf16_rows(const uint16_t* qrow, const uint16_t* krow, uint32_t dim)
+// A workgroup writes kPrepareRows rows and looks through all anchors for those among them: no second launch has to
+// wait for the first (the launcher takes it up to kPrepareMaxVisits visits of an anchor by a workgroup).
+constexpr uint32_t kPrepareRows = 1024;
+constexpr int64_t kPrepareMaxVisits = 1ll << 22;
+
+__global__ __launch_bounds__(kAssignThreads) void seda_prepare_kernel(const int32_t* anchors, uint32_t n_anchors, uint32_t n_rows,
+                                                                      uint32_t tokens, uint32_t grid_w, uint32_t tile_h,
+                                                                      uint32_t tile_w, int32_t* token_group, int32_t* anchor_group)
 {
-    const uint4* qr = reinterpret_cast<const uint4*>(qrow);
-    const uint4* kr = reinterpret_cast<const uint4*>(krow);
-    const uint32_t n16 = dim / 8;
-    float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (uint32_t c = 0; c < n16; c += 4) {
-        uint4 qa[4], kb[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {   // (a piece past the row's end re-reads the last one and is skipped)
-            qa[j] = qr[min(c + j, n16 - 1u)];
-            kb[j] = kr[min(c + j, n16 - 1u)];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (c + j < n16) {
-                const uint32_t qs[4] = {qa[j].x, qa[j].y, qa[j].z, qa[j].w}, ks[4] = {kb[j].x, kb[j].y, kb[j].z, kb[j].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    part[j] = __builtin_fmaf(__uint_as_float(qs[i] << 16), __uint_as_float(ks[i] << 16), part[j]);
-                    part[j] = __builtin_fmaf(__uint_as_float(qs[i] & 0xFFFF0000u), __uint_as_float(ks[i] & 0xFFFF0000u), part[j]);
-                }
-            }
-        }
+    __shared__ int32_t group[kPrepareRows];
+    const uint32_t first = blockIdx.x * kPrepareRows, n = min(kPrepareRows, n_rows - first);
+    for (uint32_t i = threadIdx.x; i < kPrepareRows; i += kAssignThreads) group[i] = -1;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n_anchors; i += kAssignThreads) {
+        const uint32_t at = (uint32_t)anchors[i] - first;   // (a negative entry lies past any row)
+        if (anchors[i] >= 0 && at < n) group[at] = (int32_t)tile_of((uint32_t)anchors[i] % tokens, grid_w, tile_h, tile_w);
     }
-    return (part[0] + part[1]) + (part[2] + part[3]);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += kAssignThreads) {
+        token_group[first + i] = group[i];
+        anchor_group[first + i] = group[i];
+    }
+}
+
+__global__ __launch_bounds__(kAssignThreads) void seda_fill_kernel(int32_t* a, int32_t* b, uint32_t n)
+{
+    const uint32_t i = blockIdx.x * (uint32_t)kAssignThreads + threadIdx.x;
+    if (i < n) {
+        a[i] = -1;
+        b[i] = -1;
+    }
+}
+
+__global__ __launch_bounds__(kAssignThreads) void seda_anchor_kernel(const int32_t* anchors, uint32_t n, uint32_t frames,
+                                                                     uint32_t grid_h, uint32_t grid_w, uint32_t tile_h,
+                                                                     uint32_t tile_w, int32_t* token_group, int32_t* anchor_group)
+{
+    const uint32_t i = blockIdx.x * (uint32_t)kAssignThreads + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t tokens = grid_h * grid_w;
+    const int64_t row = anchors[i];
+    if (row < 0 || row >= (int64_t)frames * tokens) return;
+    const int32_t g = (int32_t)tile_of((uint32_t)row % tokens, grid_w, tile_h, tile_w);
+    token_group[row] = g;    // (two entries naming one row write the same value)
+    anchor_group[row] = g;
 }
 
 struct AssignParams {
@@ -634,57 +643,103 @@ struct AssignParams {
     float threshold;
 };
 
-__global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_t* q, const uint16_t* k,
-                                                                   const int32_t* anchors, AssignParams p,
-                                                                   int32_t* token_group, float* scores)
+// Adds up the 16 lanes of a row of lanes (every lane ends with the sum; a fixed order).
+__device__ __forceinline__ float row_of_lanes_sum(float v)
 {
-    __shared__ float partial[4][64];
-    const uint32_t tokens = p.grid_h * p.grid_w;
-    const uint32_t i = blockIdx.x, wt = blockIdx.y;
-    const int64_t row = anchors[i];
-    const uint32_t w = threadIdx.x & 63u, hq = threadIdx.x >> 6;
-    // (no early exit: every thread reaches the barrier)
-    const bool slot = w < p.window * p.window;
-    const bool anchor_ok = row >= 0 && row < (int64_t)p.frames * tokens;   // otherwise: no token of the clip, marks nothing
-    const uint32_t rc = anchor_ok ? (uint32_t)row : 0u;
-    const uint32_t fa = rc / tokens, ac = rc - fa * tokens;
-    const uint32_t g = tile_of(ac, p.grid_w, p.tile_h, p.tile_w);
-    const int32_t ay = (int32_t)(ac / p.grid_w), ax = (int32_t)(ac % p.grid_w);
-    const int32_t f = (int32_t)fa + (int32_t)wt - (int32_t)(p.window_t / 2);
-    const int32_t y = ay + (int32_t)(w / p.window) - (int32_t)(p.window / 2), x = ax + (int32_t)(w % p.window) - (int32_t)(p.window / 2);
-    const bool inside = slot && anchor_ok && f >= 0 && f < (int32_t)p.frames && y >= 0 && y < (int32_t)p.grid_h && x >= 0 &&
-                        x < (int32_t)p.grid_w;
-    const uint32_t t = inside ? (uint32_t)y * p.grid_w + (uint32_t)x : 0u;
-    const uint32_t fc = inside ? (uint32_t)f : 0u;
-    float acc = 0.0f;
-    if (inside) {
-        for (uint32_t h = hq; h < p.heads; h += 4)   // this thread's share of the heads
-            acc += dot_bf16_rows(q + (fa * p.stride_f + h * p.stride_h + ac) * p.dim,
-                                 k + (fc * p.stride_f + h * p.stride_h + t) * p.dim, p.dim);
-    }
-    partial[hq][w] = acc;
-    __syncthreads();
-    if (hq == 0 && slot) {
-        const size_t per = (size_t)p.window_t * p.window * p.window;
-        float* out = scores ? scores + (size_t)i * per + (size_t)wt * p.window * p.window + w : nullptr;
-        const float sc = (partial[0][w] + partial[1][w] + partial[2][w] + partial[3][w]) / (float)p.heads;   // fixed order
-        if (out) *out = inside ? sc : __builtin_nanf("");
-        if (inside && sc > p.threshold) atomicMax(token_group + (size_t)fc * tokens + t, (int32_t)g);
-    }
+    auto moved = [](float x, auto ctrl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    v += moved(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+    v += moved(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+    v += moved(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    v += moved(v, std::integral_constant<int, 0x140>{});   // row_mirror
+    return v;
 }
 
-__global__ __launch_bounds__(256) void seda_anchor_kernel(const int32_t* anchors, uint32_t n, uint32_t frames,
-                                                          uint32_t grid_h, uint32_t grid_w, uint32_t tile_h, uint32_t tile_w,
-                                                          int32_t* token_group, int32_t* anchor_group)
+// 16 lanes share a row of K, 16 bytes each, four window slots at a time, so that a load covers whole rows (and
+// neighbouring slots are neighbouring rows); a wavefront takes every fourth head with the loads of two heads in
+// flight, and a lane keeps its channels' sums over its heads: lanes and wavefronts are added up once at the end.
+// kQuads: window slots / 4, rounded up.  16 frames x 24 heads x 1024 tokens x 128 channels, 1024 anchors, 5 x 5
+// windows: 45 us with a thread per slot, which read its row 16 bytes at a time, 16.7 now (9.4 TB/s of gathered rows; they
+// overlap, so part of them comes from the caches).
+template <int kQuads>
+__global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_t* q, const uint16_t* k,
+                                                                   const int32_t* anchors, AssignParams p,
+                                                                   int32_t* token_group, const int32_t* anchor_group,
+                                                                   float* scores)
 {
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t tokens = grid_h * grid_w;
+    __shared__ float partial[kAssignThreads / 64][4 * kQuads];
+    const uint32_t tokens = p.grid_h * p.grid_w;
+    const uint32_t i = blockIdx.x, wt = blockIdx.y, slots = p.window * p.window;
     const int64_t row = anchors[i];
-    if (row < 0 || row >= (int64_t)frames * tokens) return;
-    const int32_t g = (int32_t)tile_of((uint32_t)row % tokens, grid_w, tile_h, tile_w);
-    token_group[row] = g;    // (two entries naming one row write the same value)
-    anchor_group[row] = g;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, sub = lane >> 4, piece = lane & 15u;
+    const bool anchor_ok = row >= 0 && row < (int64_t)p.frames * tokens;   // otherwise: no token of the clip, marks nothing
+    if (!anchor_ok && !scores) return;   // (the same for the whole workgroup)
+    const uint32_t rc = anchor_ok ? (uint32_t)row : 0u;
+    const uint32_t fa = rc / tokens, ac = rc - fa * tokens;
+    const int32_t ay = (int32_t)(ac / p.grid_w), ax = (int32_t)(ac % p.grid_w);
+    const int32_t f = (int32_t)fa + (int32_t)wt - (int32_t)(p.window_t / 2);
+    const bool frame_ok = anchor_ok && f >= 0 && f < (int32_t)p.frames;
+    const uint32_t fc = frame_ok ? (uint32_t)f : fa;
+    auto place = [&](uint32_t slot, uint32_t& t) {   // the slot's token; false (and the anchor's own) outside the clip
+        const int32_t y = ay + (int32_t)(slot / p.window) - (int32_t)(p.window / 2);
+        const int32_t x = ax + (int32_t)(slot % p.window) - (int32_t)(p.window / 2);
+        const bool inside = slot < slots && frame_ok && y >= 0 && y < (int32_t)p.grid_h && x >= 0 && x < (int32_t)p.grid_w;
+        t = inside ? (uint32_t)y * p.grid_w + (uint32_t)x : ac;
+        return inside;
+    };
+    float acc[kQuads];
+    uint32_t off[kQuads];   // of the slots' rows, in elements (the launcher checks tokens * dim < 2^31)
+#pragma unroll
+    for (int j = 0; j < kQuads; ++j) {
+        acc[j] = 0.0f;
+        uint32_t t;
+        place(4u * j + sub, t);
+        off[j] = t * p.dim;
+    }
+    if (frame_ok) {
+        const uint32_t n16 = p.dim / 8u;
+        for (uint32_t c = piece; c < n16; c += 16) {
+#pragma unroll 2
+            for (uint32_t h = wave; h < p.heads; h += kAssignThreads / 64) {
+                const uint4 qv = *reinterpret_cast<const uint4*>(q + (fa * p.stride_f + h * p.stride_h + ac) * p.dim + c * 8u);
+                const uint16_t* kh = k + (fc * p.stride_f + h * p.stride_h) * p.dim + c * 8u;
+                uint4 kv[kQuads];
+#pragma unroll
+                for (int j = 0; j < kQuads; ++j) kv[j] = *reinterpret_cast<const uint4*>(kh + off[j]);
+                const uint32_t qs[4] = {qv.x, qv.y, qv.z, qv.w};
+#pragma unroll
+                for (int j = 0; j < kQuads; ++j) {
+                    const uint32_t ks[4] = {kv[j].x, kv[j].y, kv[j].z, kv[j].w};
+                    float d0 = 0.0f, d1 = 0.0f;   // (short chains: their rounding errors stay those of small sums)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        d0 = __builtin_fmaf(__uint_as_float(qs[e] << 16), __uint_as_float(ks[e] << 16), d0);
+                        d1 = __builtin_fmaf(__uint_as_float(qs[e] & 0xFFFF0000u), __uint_as_float(ks[e] & 0xFFFF0000u), d1);
+                    }
+                    acc[j] += d0 + d1;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kQuads; ++j) {
+        const float v = row_of_lanes_sum(acc[j]);
+        if (piece == 0) partial[wave][4 * j + sub] = v;
+    }
+    __syncthreads();
+    const uint32_t w = threadIdx.x;
+    if (w < slots) {
+        uint32_t t;
+        const bool inside = place(w, t);
+        // (in a fixed order; the four sums of a wavefront's heads are the largest terms: added in double)
+        const float sc = (float)(((double)partial[0][w] + (double)partial[1][w]) + ((double)partial[2][w] + (double)partial[3][w])) / (float)p.heads;
+        const size_t per = (size_t)p.window_t * slots;
+        if (scores) scores[(size_t)i * per + (size_t)wt * slots + w] = inside ? sc : __builtin_nanf("");
+        const size_t at = (size_t)fc * tokens + t;
+        if (inside && sc > p.threshold && anchor_group[at] < 0)
+            atomicMax(token_group + at, (int32_t)tile_of(ac, p.grid_w, p.tile_h, p.tile_w));
+    }
 }
 
 // Sec. 3.4, factorized attention, step 2: one workgroup per spatial tile, one wavefront per frame at a time.  Per

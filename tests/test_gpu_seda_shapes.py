@@ -1,0 +1,81 @@
+"""The SeDA refresh at the edges of its kernels' tiles and rules, against the CPU oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+from fb4_inputs import DEFAULT_FORMATBOOK, synth
+from oracle import fb4_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_02883_amd as F
+    return F
+
+
+@pytest.mark.parametrize("window", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("dim,heads,joint,window_t", [(8, 1, False, 1), (72, 5, False, 1), (136, 3, True, 2), (256, 9, True, 3)])
+def test_seda_assign_windows_and_row_lengths(F, window, dim, heads, joint, window_t):
+    frames, gh, gw = 3, 7, 9
+    tokens = gh * gw
+    q, k = synth.attention_qk(frames * heads, tokens, dim, seed=window * 1000 + dim, device="cuda")
+    shape = (heads, frames * tokens, dim) if joint else (frames, heads, tokens, dim)
+    q, k = q.reshape(shape).contiguous(), k.reshape(shape).contiguous()
+    anchors = np.random.default_rng(dim + window).choice(frames * tokens, size=23, replace=False).astype(np.int32)
+    anchors[::5] = -1
+    tgr, agr, sr = O.seda_assign(synth.bf16_bits(q), synth.bf16_bits(k), anchors, frames, gh, gw, window=window,
+                                 window_t=window_t, threshold=0.0, joint=joint)
+    inside = ~np.isnan(sr)
+    threshold = float(np.median(sr[inside]))
+    tgr, agr, sr = O.seda_assign(synth.bf16_bits(q), synth.bf16_bits(k), anchors, frames, gh, gw, window=window,
+                                 window_t=window_t, threshold=threshold, joint=joint)
+    tg, ag, sc = F.fb4_seda_assign(q, k, torch.from_numpy(anchors).cuda(), frames, gh, gw, window=window, window_t=window_t,
+                                   threshold=threshold, joint=joint, want_scores=True)
+    torch.cuda.synchronize()
+    sc = sc.cpu().numpy()
+    assert np.array_equal(np.isnan(sc), ~inside)
+    # fp32 sums of exact products: at most dim * heads + 8 additions, 2^-23 each of the sum of absolute values, which is at
+    # most the product of the largest row norms
+    qn = float(q.float().norm(dim=-1).max() * k.float().norm(dim=-1).max())
+    bound = (dim * heads + 8) * 2.0 ** -23 * qn
+    assert np.abs(sc[inside] - sr[inside]).max() <= bound
+    if (np.abs(sr[inside] - threshold) > bound).sum() >= inside.sum() - 1:   # (the median itself may fall on either side)
+        near = np.abs(sr - threshold) <= bound
+        if not near.any():
+            assert np.array_equal(tg.cpu().numpy(), tgr)
+    assert np.array_equal(ag.cpu().numpy(), agr)
+    # the groups follow from the compared scores exactly
+    expect = np.full(frames * tokens, -1, dtype=np.int32)
+    for a, row in enumerate(anchors):
+        if row < 0:
+            continue
+        f, t = divmod(int(row), tokens)
+        g = (t // gw // 4) * ((gw + 3) // 4) + (t % gw) // 4
+        for s in range(window_t * window * window):
+            if sc[a, s] > np.float32(threshold):
+                ft = f + s // (window * window) - window_t // 2
+                y, x = t // gw + s % (window * window) // window - window // 2, t % gw + s % window - window // 2
+                at = ft * tokens + y * gw + x
+                expect[at] = max(expect[at], g)
+    expect[agr >= 0] = agr[agr >= 0]
+    assert np.array_equal(tg.cpu().numpy(), expect)
+
+
+def test_seda_assign_with_very_many_anchor_entries(F):
+    # more entries than the one-launch preparation takes: the same groups as from the list without repetitions
+    frames, gh, gw, heads, dim = 8, 64, 64, 1, 8
+    tokens = gh * gw
+    q, k = synth.attention_qk(frames * heads, tokens, dim, seed=3, device="cuda")
+    q, k = q.view(frames, heads, tokens, dim), k.view(frames, heads, tokens, dim)
+    few = torch.from_numpy(np.random.default_rng(1).choice(frames * tokens, size=400, replace=False).astype(np.int32)).cuda()
+    many = few.repeat(400)                                   # 32 workgroups x 160000 entries
+    a = F.fb4_seda_assign(q, k, few, frames, gh, gw, window=3, threshold=1.0)
+    b = F.fb4_seda_assign(q, k, many, frames, gh, gw, window=3, threshold=1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert int((a[1] >= 0).sum()) == 400
