@@ -749,21 +749,26 @@ __global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_
 // score from the main anchor to it -- Qt[p*][h][f*] . Kt[p*][h][f], head mean in fp32 -- exceeds the threshold.
 // Every entry of `kept` is written exactly once: by the workgroup of the tile the entry lies in (an entry that is
 // no candidate of its frame by the workgroup of tile 0), so no launch has to clear it first.
-constexpr int kMainThreads = 256;
+// Bound by its chain of dependent loads (list, temporal scores, the two rows of every head): a wavefront per frame up
+// to 16, the loads of four heads in flight, the best frame found by the lanes of one wavefront.  64 tiles x 16 frames x
+// 24 heads x 128 channels: 30 us with four wavefronts, serial head sums and one frame after the other, 9.8 now.
+constexpr int kMainThreads = 256;       // seda_main_anchor_3d_kernel
+constexpr int kMainMaxThreads = 1024;   // seda_main_anchor_kernel: 64 per frame, at most these
 constexpr uint32_t kMainMaxFrames = 1024;
 
-__global__ __launch_bounds__(kMainThreads) void seda_main_anchor_kernel(
+__global__ __launch_bounds__(kMainMaxThreads) void seda_main_anchor_kernel(
     const float* temporal_scores, const uint16_t* qt, const uint16_t* kt, uint32_t frames, uint32_t heads, uint32_t grid_h,
     uint32_t grid_w, uint32_t dim, const int32_t* cand, uint32_t n_per_frame, uint32_t tile_h, uint32_t tile_w,
     float prune_threshold, int32_t* main_anchor, int32_t* kept, float* prune_scores)
 {
     __shared__ double score[kMainMaxFrames];
-    __shared__ int32_t slot[kMainMaxFrames];
+    __shared__ int32_t slot[kMainMaxFrames], row_of[kMainMaxFrames];
     __shared__ int32_t best_frame;
-    constexpr uint32_t kWaves = kMainThreads / 64, kNone = 0xFFFFFFFFu;
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    const uint32_t n_waves = blockDim.x >> 6;
     const uint32_t tokens = grid_h * grid_w, tile = blockIdx.x, tiles = gridDim.x;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    for (uint32_t f = wave; f < frames; f += kWaves) {
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint32_t f = wave; f < frames; f += n_waves) {
         const int32_t* list = cand + (size_t)f * n_per_frame;
         int32_t* out = kept + (size_t)f * n_per_frame;
         uint32_t found = kNone;
@@ -782,47 +787,59 @@ __global__ __launch_bounds__(kMainThreads) void seda_main_anchor_kernel(
             if (found == kNone) found = first;
         }
         double v = 0.0;
+        int32_t row = -1;
         if (found != kNone) {
-            const uint32_t pos = (uint32_t)(list[found] - (int32_t)(f * tokens));
+            row = list[found];
+            const uint32_t pos = (uint32_t)(row - (int32_t)(f * tokens));
             for (uint32_t h0 = 0; h0 < heads; h0 += 64) {
                 const uint32_t cnt = min(64u, heads - h0);
                 const float own = lane < cnt ? temporal_scores[((size_t)pos * heads + h0 + lane) * frames + f] : 0.0f;
-                for (uint32_t i = 0; i < cnt; ++i) v += (double)__shfl(own, (int)i);
+                for (uint32_t i = 0; i < cnt; ++i)   // head by head
+                    v += (double)__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, own), (int)i));
             }
             v /= (double)heads;
             if (v != v) v = -__builtin_inf();
         }
         if (lane == 0) {
             slot[f] = found == kNone ? -1 : (int32_t)found;
+            row_of[f] = row;
             score[f] = v;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (wave == 0) {
         int32_t bf = -1;
         double bv = 0.0;
-        for (uint32_t f = 0; f < frames; ++f) {
-            if (slot[f] < 0) continue;
-            if (bf < 0 || score[f] > bv) { bf = (int32_t)f; bv = score[f]; }
+        auto offer = [&](int32_t f, double v) {   // the earliest frame on ties
+            if (f >= 0 && (bf < 0 || v > bv || (v == bv && f < bf))) { bf = f; bv = v; }
+        };
+        for (uint32_t f = lane; f < frames; f += 64) offer(slot[f] >= 0 ? (int32_t)f : -1, score[f]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const int32_t of = __shfl_xor(bf, o);
+            const double ov = __shfl_xor(bv, o);
+            offer(of, ov);
         }
-        best_frame = bf;
-        main_anchor[tile] = bf < 0 ? -1 : cand[(size_t)bf * n_per_frame + slot[bf]];
+        if (lane == 0) {
+            best_frame = bf;
+            main_anchor[tile] = bf < 0 ? -1 : row_of[bf];
+        }
     }
     __syncthreads();
-    const int32_t bf = best_frame;
+    const int32_t bf = __builtin_amdgcn_readfirstlane(best_frame);
     const uint32_t n16 = dim / 8;
-    for (uint32_t f = wave; f < frames; f += kWaves) {
+    for (uint32_t f = wave; f < frames; f += n_waves) {
         float sc = __builtin_nanf("");
         if (slot[f] >= 0) {   // (then the tile has a main anchor)
-            const uint32_t pos = (uint32_t)(cand[(size_t)bf * n_per_frame + slot[bf]] - (int32_t)((uint32_t)bf * tokens));
+            const uint32_t pos = (uint32_t)(row_of[bf] - (int32_t)((uint32_t)bf * tokens));
             // 16 lanes share a row's 16-byte pieces, four heads at a time; the wavefront's sum in a fixed order
             float acc = 0.0f;
-            for (uint32_t h = lane >> 4; h < heads; h += 4) {
-                const size_t base = ((size_t)pos * heads + h) * frames;
-                const uint4* qr = reinterpret_cast<const uint4*>(qt + (base + (uint32_t)bf) * dim);
-                const uint4* kr = reinterpret_cast<const uint4*>(kt + (base + f) * dim);
-                for (uint32_t c = lane & 15u; c < n16; c += 16) {
-                    const uint4 a = qr[c], b = kr[c];
+            const size_t base = (size_t)pos * heads * frames;
+            for (uint32_t c = lane & 15u; c < n16; c += 16) {
+#pragma unroll 4
+                for (uint32_t h = lane >> 4; h < heads; h += 4) {
+                    const uint4 a = reinterpret_cast<const uint4*>(qt + (base + (size_t)h * frames + (uint32_t)bf) * dim)[c];
+                    const uint4 b = reinterpret_cast<const uint4*>(kt + (base + (size_t)h * frames + f) * dim)[c];
                     const uint32_t qs[4] = {a.x, a.y, a.z, a.w}, ks[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -834,10 +851,8 @@ __global__ __launch_bounds__(kMainThreads) void seda_main_anchor_kernel(
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
             sc = acc / (float)heads;
-            if (lane == 0) {
-                const int32_t row = cand[(size_t)f * n_per_frame + slot[f]];
-                kept[(size_t)f * n_per_frame + slot[f]] = ((int32_t)f == bf || sc > prune_threshold) ? row : -1;
-            }
+            if (lane == 0)
+                kept[(size_t)f * n_per_frame + slot[f]] = ((int32_t)f == bf || sc > prune_threshold) ? row_of[f] : -1;
         }
         if (lane == 0 && prune_scores) prune_scores[(size_t)f * tiles + tile] = sc;
     }

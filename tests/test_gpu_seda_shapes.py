@@ -79,3 +79,34 @@ def test_seda_assign_with_very_many_anchor_entries(F):
     torch.cuda.synchronize()
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     assert int((a[1] >= 0).sum()) == 400
+
+
+@pytest.mark.parametrize("frames,heads,dim", [(1, 1, 8), (2, 70, 136), (17, 3, 72), (64, 2, 8), (70, 5, 16), (200, 1, 8)])
+def test_seda_main_anchor_frames_heads_and_ties(F, frames, heads, dim):
+    gh, gw = 4, 8                                            # two tiles
+    tokens = gh * gw
+    rng = np.random.default_rng(frames)
+    ts = rng.integers(0, 3, size=(tokens, heads, frames)).astype(np.float32)       # few values: ties are the rule
+    ts[rng.random(ts.shape) < 0.02] = np.nan
+    cand = np.stack([np.array([f * tokens + rng.integers(0, 4), f * tokens + 4 + rng.integers(0, 4)]) for f in range(frames)])
+    cand[rng.random(cand.shape) < 0.1] = -1
+    qt, kt = synth.attention_qk(tokens * heads, frames, dim, seed=frames, device="cuda")
+    qt, kt = qt.view(tokens, heads, frames, dim), kt.view(tokens, heads, frames, dim)
+    cand = cand.astype(np.int32)
+    main, kept, ps = F.fb4_seda_main_anchor(torch.from_numpy(ts).cuda(), qt, kt, torch.from_numpy(cand).cuda(), gh, gw,
+                                            prune_threshold=1.0, want_scores=True)
+    torch.cuda.synchronize()
+    main_r, kept_r, ps_r = O.seda_main_anchor(ts, synth.bf16_bits(qt), synth.bf16_bits(kt), cand, gh, gw, prune_threshold=1.0)
+    assert np.array_equal(main.cpu().numpy(), main_r)
+    got = ps.cpu().numpy()
+    inside = ~np.isnan(ps_r)
+    assert np.array_equal(np.isnan(got), ~inside)
+    bound = (dim * heads + 8) * 2.0 ** -23 * float(qt.float().norm(dim=-1).max() * kt.float().norm(dim=-1).max())
+    if inside.any():
+        assert np.abs(got[inside] - ps_r[inside]).max() <= bound
+    # the kept list follows from the compared scores exactly
+    for f in range(frames):
+        for tile in range(2):
+            if inside[f, tile]:
+                keep = got[f, tile] > np.float32(1.0) or cand[f, tile] == main_r[tile]
+                assert kept.cpu().numpy()[f, tile] == (cand[f, tile] if keep else -1)
