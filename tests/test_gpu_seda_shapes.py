@@ -110,3 +110,14 @@ def test_seda_main_anchor_frames_heads_and_ties(F, frames, heads, dim):
             if inside[f, tile]:
                 keep = got[f, tile] > np.float32(1.0) or cand[f, tile] == main_r[tile]
                 assert kept.cpu().numpy()[f, tile] == (cand[f, tile] if keep else -1)
+
+
+@pytest.mark.parametrize("frames,heads,gh,gw,th,tw", [(1, 1, 1, 1, 4, 4), (3, 24, 32, 32, 4, 4), (2, 25, 7, 9, 4, 4), (2, 33, 64, 128, 4, 4),
+                                                      (2, 7, 90, 91, 5, 7), (1, 3, 33, 31, 40, 40), (2, 50, 13, 17, 1, 1), (2, 2, 64, 64, 64, 1)])
+def test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th, tw):
+    rng = np.random.default_rng(gh * gw + heads)
+    s = rng.integers(0, 4, size=(frames, heads, gh * gw)).astype(np.float32)       # few values: ties are the rule
+    s[rng.random(s.shape) < 0.3 / heads] = np.nan
+    got = F.fb4_select_salient_tokens(torch.from_numpy(s).cuda(), gh, gw, th, tw)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), O.select_salient_tokens(s, gh, gw, th, tw))
