@@ -121,3 +121,28 @@ def test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th,
     got = F.fb4_select_salient_tokens(torch.from_numpy(s).cuda(), gh, gw, th, tw)
     torch.cuda.synchronize()
     assert np.array_equal(got.cpu().numpy(), O.select_salient_tokens(s, gh, gw, th, tw))
+
+
+# (rows, blocks per row, groups, share of anchors): one launch, and on both sides of its limits the three launches
+@pytest.mark.parametrize("rows,nb,groups,share", [(0, 5, 8, 1.0), (1, 1, 8, 1.0), (63, 7, 8, 1.0), (1030, 129, 9, 0.7), (8193, 96, 64, 0.1),
+                                                  (32768, 3, 256, 0.1), (32769, 3, 16, 0.1), (300, 40, 7, 0.5), (4096, 1025, 16, 0.05)])
+def test_seda_profile_shapes(F, rows, nb, groups, share):
+    rng = np.random.default_rng(rows + nb)
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    meta = (rng.integers(0, 34, size=(rows, nb)) | (rng.integers(0, 255, size=(rows, nb)) << 8)).astype(np.uint16)   # (32, 33: no dialect)
+    group = rng.integers(0, groups, size=rows).astype(np.int32)
+    group[rng.random(rows) >= share] = rng.choice([-1, groups, groups + 100])
+    counts = torch.full((groups, 32), 77, dtype=torch.int32, device="cuda")
+    counts, sub = F.fb4_seda_profile(luts, torch.from_numpy(meta.view(np.int16)).cuda(), torch.from_numpy(group).cuda(), groups, counts=counts)
+    torch.cuda.synchronize()
+    cr = np.zeros((groups, 32), dtype=np.int64)
+    for g in range(groups):
+        d = (meta[group == g] & 0xFF).ravel()
+        cr[g] = np.bincount(d[d < 32], minlength=32)
+    assert np.array_equal(counts.cpu().numpy(), cr)
+    for g in range(groups):
+        for k in range(8):
+            ds = [d for d in range(32) if DEFAULT_FORMATBOOK[d][7] == 8 + k]
+            best = min(ds, key=lambda d: (-cr[g][d], d)) if ds else 255
+            assert int(sub[g, k]) == best
+    luts.free()
