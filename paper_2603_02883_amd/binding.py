@@ -109,13 +109,20 @@ def workspace_bytes():
 
 
 def _dp(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# The handle of a device's current stream without the Stream object around it: torch.cuda.current_stream() takes 2.8 us
+# of an 8 us call, this 0.3 us (fb4_quantize on 300 x 1152, where the launch itself takes 4.2).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(rc, where):
