@@ -4,6 +4,7 @@
 // every entry point are in include/fb4.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <new>
 
@@ -78,10 +79,10 @@ int launch_quant(const fb4_opts* o, int grid, hipStream_t s, const QuantParams& 
 template <int kBlock, int G, bool kFlat, int kMode, int kThreads = kFastThreads, bool kSedaToo = true>
 void launch_fast_variant(bool ts, bool seda, int n_cu, hipStream_t s, const FastParams& f)
 {
-    constexpr int kWaves = kThreads / 64;
-    long long g = ((long long)f.n_tiles + kWaves - 1) / kWaves;
-    if (g > n_cu) g = n_cu;
-    const unsigned groups = (unsigned)g;
+    // (fewer tiles than the chip has wavefronts are spread over the compute units, not packed into full workgroups:
+    // 300 x 1152 4.03 us packed, 3.47 spread; exhaustive, 500 x 3072, 8.5 and 6.35; block 16 with SeDA lists and the
+    // range filter, 2000 x 1152, 5.47 and 5.25; 1000 x 3072 4.24 and 4.28; same from 3000 x 3072 on)
+    const unsigned groups = std::min(f.n_tiles, (unsigned)n_cu);
     // (the leading arguments repeat fields of f: see the kernel)
 #define FB4_FAST_ARGS f.blob, f.x, f.n_blocks, f.n_tiles, f.div_mul, f.div_shift, f.nb, groups, f.row_stride, f.salient, f
     if (seda) {

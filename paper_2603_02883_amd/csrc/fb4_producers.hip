@@ -1,5 +1,6 @@
 // C ABI of the FB4 quantizer library, the producer-fused entry points (App. E.2): the quantizer behind a
 // LayerNorm and behind a GeLU.  Declarations and contracts are in include/fb4.h.
+#include <algorithm>
 #include <cstring>
 
 #include "fb4_common.hpp"
@@ -75,10 +76,8 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
     if (B == 0) { B = (int)((nb + 63) / 64); rw = 1; }
     if (rw > (uint32_t)rows) rw = (uint32_t)rows;
     const uint32_t n_bundles = (uint32_t)((rows + rw - 1) / rw);
-    const int kLnWaves = ln_threads(B, opts->num_groups) / 64;
-    long long g = ((long long)n_bundles + kLnWaves - 1) / kLnWaves;
-    if (g > luts->n_cu) g = luts->n_cu;
-    const unsigned groups = (unsigned)g;
+    // (a bundle per compute unit before a second one on any: 300 x 1152 14.7 -> 8.9 us)
+    const unsigned groups = std::min(n_bundles, (unsigned)luts->n_cu);
     LayerNormParams p = {};
     p.rows = (uint32_t)rows;
     p.cols = (uint32_t)cols;
@@ -147,9 +146,8 @@ int fb4_gelu_quantize(const fb4_luts* luts, const fb4_opts* opts, const void* x,
     while ((1ull << l) < nb) ++l;
     const uint32_t div_shift = 31 + l;
     const uint32_t div_mul = (uint32_t)(((1ull << div_shift) + nb - 1) / nb);
-    long long g = ((long long)n_tiles + kGeluThreads / 64 - 1) / (kGeluThreads / 64);
-    if (g > luts->n_cu) g = luts->n_cu;
-    const unsigned groups = (unsigned)g;
+    // (a tile per compute unit before a second one on any: 300 x 1152 7.0 -> 4.7 us, 1000 x 3072 7.2 -> 5.75)
+    const unsigned groups = std::min(n_tiles, (unsigned)luts->n_cu);
     GeluParams p = {codes, meta, token_group, sub_formatbooks, (uint32_t)n_groups, (uint32_t)luts->n_dialects};
     const bool seda = token_group != nullptr, ts = (opts->flags & FB4_FLAG_TWO_STAGE) != 0;
     const uint16_t* table = reinterpret_cast<const uint16_t*>(luts->dev_blob + kBlobBytes + (approximate ? kGeluTableBytes : 0));
