@@ -66,21 +66,45 @@ __device__ __forceinline__ void layernorm_tables_to_lds(uint8_t* lds, const uint
     constexpr int kLdsSeda = kLdsLnTables + 2 * kGbFloats * 4;
     float* lds_gamma = reinterpret_cast<float*>(lds + kLdsLnTables);
     float* lds_beta = lds_gamma + kGbFloats;
-    // ---- tables (layout of the streaming kernel) and the scale / shift vectors
-    for (int i = threadIdx.x; i < 64 * kRowCopies; i += kThreads) {
-        const int bin = i / (2 * kRowCopies), half = (i / kRowCopies) & 1;
-        reinterpret_cast<uint4*>(lds + kLdsRows)[i] = *reinterpret_cast<const uint4*>(blob + kOffQerror8 + bin * 32 + half * 16);
+    // ---- tables (layout of the streaming kernel) and the scale / shift vectors: everything is requested before anything
+    // is waited for (indices are clamped, not predicated: a thread past the end loads a piece that it does not write).
+    // In a loop over the channels, whose every round waited for its loads: 16384 x 3072 35.5 us instead of 34.1, 16384 x
+    // 1152 21.05 instead of 20.4, 4000 x 12288 51.9 instead of 43.4.
+    constexpr int kRowIt = (64 * kRowCopies + kThreads - 1) / kThreads, kGbIt = (kGbFloats / 4 + kThreads - 1) / kThreads;
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // (the vectors are 4-byte aligned only)
+    uint4 rowv[kRowIt];
+    f32x4u gv[kGbIt], bv[kGbIt];
+#pragma unroll
+    for (int k = 0; k < kRowIt; ++k) {
+        const int i = min((int)threadIdx.x + k * kThreads, 64 * kRowCopies - 1);
+        rowv[k] = *reinterpret_cast<const uint4*>(blob + kOffQerror8 + (i / (2 * kRowCopies)) * 32 + ((i / kRowCopies) & 1) * 16);
     }
-    for (int i = threadIdx.x; i < 256; i += kThreads)
-        reinterpret_cast<uint32_t*>(lds + kLdsNibT)[i] = reinterpret_cast<const uint32_t*>(blob + kOffQvalueT)[i];
-    if (kTwoStage && threadIdx.x < 64)
-        reinterpret_cast<uint32_t*>(lds + kLdsRange)[threadIdx.x] = reinterpret_cast<const uint32_t*>(blob + kOffRangeExcl)[threadIdx.x];
+    const uint32_t nibv = reinterpret_cast<const uint32_t*>(blob + kOffQvalueT)[threadIdx.x & 255u];
+    const uint32_t rngv = kTwoStage ? reinterpret_cast<const uint32_t*>(blob + kOffRangeExcl)[threadIdx.x & 63u] : 0u;
+    const uint32_t n4 = p.cols / 4u;
+#pragma unroll
+    for (int k = 0; k < kGbIt; ++k) {
+        const uint32_t c4 = min(threadIdx.x + (uint32_t)(k * kThreads), n4 - 1u);
+        gv[k] = f32x4u{1.0f, 1.0f, 1.0f, 1.0f};
+        bv[k] = f32x4u{0.0f, 0.0f, 0.0f, 0.0f};
+        if (gamma) gv[k] = *reinterpret_cast<const f32x4u*>(gamma + 4u * c4);
+        if (beta) bv[k] = *reinterpret_cast<const f32x4u*>(beta + 4u * c4);
+    }
+#pragma unroll
+    for (int k = 0; k < kRowIt; ++k)
+        if ((int)threadIdx.x + k * kThreads < 64 * kRowCopies) reinterpret_cast<uint4*>(lds + kLdsRows)[threadIdx.x + k * kThreads] = rowv[k];
+    if (threadIdx.x < 256) reinterpret_cast<uint32_t*>(lds + kLdsNibT)[threadIdx.x] = nibv;
+    if (kTwoStage && threadIdx.x < 64) reinterpret_cast<uint32_t*>(lds + kLdsRange)[threadIdx.x] = rngv;
     // scale / shift: the four channels (4q .. 4q+3) of chunk cb at [q][64 B][4], so that the 16-byte reads of
     // neighbouring lanes (neighbouring chunks, same q) fall into different banks and q is a constant offset
-    for (uint32_t c = threadIdx.x; c < p.cols; c += kThreads) {
-        const uint32_t at = (((c & 31u) >> 2) * (64u * B) + (c >> 5)) * 4u + (c & 3u);
-        lds_gamma[at] = gamma ? gamma[c] : 1.0f;
-        lds_beta[at] = beta ? beta[c] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < kGbIt; ++k) {
+        const uint32_t c4 = threadIdx.x + (uint32_t)(k * kThreads);
+        if (c4 < n4) {
+            const uint32_t at = (c4 & 7u) * (64u * B) + (c4 >> 3);
+            reinterpret_cast<float4*>(lds_gamma)[at] = make_float4(gv[k].x, gv[k].y, gv[k].z, gv[k].w);
+            reinterpret_cast<float4*>(lds_beta)[at] = make_float4(bv[k].x, bv[k].y, bv[k].z, bv[k].w);
+        }
     }
     if (kSeda) build_seda_rows(lds, kLdsSeda, p.sub, p.n_groups, p.n_dialects, kThreads);
     __syncthreads();
