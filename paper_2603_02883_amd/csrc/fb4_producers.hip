@@ -62,21 +62,32 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
         return FB4_ERR_UNSUPPORTED;
     if ((uint64_t)rows * (uint64_t)nb >= 0x7F000000ull) return FB4_ERR_UNSUPPORTED;
     if ((rc = check_device(luts)) != FB4_OK) return rc;
-    // Chunks per lane B and rows per bundle: the fullest wavefront among B <= 4, the fewest chunks among equals;
-    // rows longer than 8192 need 5 or 6.
+    // Chunks per lane B and rows per bundle.  If with the fewest chunks that hold a row every wavefront gets one bundle at
+    // most, these: the shortest chain (us, 1 / 2 / 3 / 4 chunks: 300 x 1152 5.0 / 7.1 / 8.7 / 10.9, 3000 x 1024 6.4 / 7.7 /
+    // 9.7 / 11.9, 60000 x 96 13.3 / 19.6 / 22.9 / 33.1; 1000 x 3072 8.1 with 2 and 9.5 with 3).  Otherwise the fullest
+    // wavefront among B <= 4, the fewest chunks among equals (40000 x 1152 43.8 / 39.6 / 36.6 / 41.4); rows longer than
+    // 8192 need 5 or 6.
+    const int fewest = (int)((nb + 63) / 64);
     int B = 0;
     uint32_t rw = 0;
+    if (fewest <= 4) {
+        const int64_t r = 64 * fewest / nb;
+        if ((rows + r - 1) / r <= (int64_t)luts->n_cu * (ln_threads(fewest, opts->num_groups) / 64)) {
+            B = fewest;
+            rw = (uint32_t)r;
+        }
+    }
     double best = 0.0;
-    for (int b = 1; b <= 4; ++b) {
-        if (nb > 64 * b) continue;
+    for (int b = fewest; b <= 4 && rw == 0; ++b) {
         const uint32_t r = (uint32_t)(64 * b / nb);
         const double fill = (double)(r * nb) / (64.0 * b) - (b == 4 ? 0.05 : 0.0);
-        if (fill > best + 1e-9) { best = fill; B = b; rw = r; }
+        if (fill > best + 1e-9) { best = fill; B = b; }
     }
-    if (B == 0) { B = (int)((nb + 63) / 64); rw = 1; }
+    if (B == 0) B = fewest;
+    if (rw == 0) rw = (uint32_t)(64 * B / nb);
     if (rw > (uint32_t)rows) rw = (uint32_t)rows;
     const uint32_t n_bundles = (uint32_t)((rows + rw - 1) / rw);
-    // (a bundle per compute unit before a second one on any: 300 x 1152 14.7 -> 8.9 us)
+    // (a bundle per compute unit before a second one on any: 300 x 1152 in bundles of five rows 14.7 -> 8.9 us)
     const unsigned groups = std::min(n_bundles, (unsigned)luts->n_cu);
     LayerNormParams p = {};
     p.rows = (uint32_t)rows;
