@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kProfileThreads) void profile_count_kernel(const ui
 // rows.  Where 6 % of the rows are anchors (us, three launches against this one): 16384 rows x 96 blocks, 64 groups
 // 9.0 and 7.3, 200 groups 9.4 and 7.1; 32768 rows, 64 groups 10.0 and 9.7, 256 groups 10.0 and 9.1; 1000 rows, 20 groups
 // 7.8 and 5.7; 65536 rows x 36, 64 groups 11.2 and 12.8; half of 16384 rows in 8 groups 26.9 and 26.2, all of them in
-// one group 193 and 241.  So: a few groups at least, and limits on the rows and on what is read in all.
+// one group 193 and 241.  Behind the launch that writes anchor_group (cold caches) 12.8 and 12.1.  So: a few groups at least, and limits on the rows and on what is read in all.
 constexpr int kProfileGroupThreads = 1024;
 inline bool profile_in_one_launch(long long rows, long long nb, int n_groups)
 {
