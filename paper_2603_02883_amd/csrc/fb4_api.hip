@@ -613,11 +613,6 @@ int fb4_seda_profile(const fb4_luts* luts, const uint16_t* meta, int64_t rows, i
         return FB4_ERR_UNSUPPORTED;
     if (int rc = check_device(luts)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (blocks_per_row > 0 && blocks_per_row <= (1 << 22) && profile_in_one_launch(rows, blocks_per_row, n_groups)) {
-        hipLaunchKernelGGL(profile_group_kernel, dim3((unsigned)n_groups), dim3(kProfileGroupThreads), 0, s, meta, (long long)rows,
-                           (long long)blocks_per_row, anchor_group, luts->dev_blob, counts, sub_formatbooks);
-        return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
-    }
     const uint32_t n = (uint32_t)n_groups * 32u;
     // cleared by a kernel (not a memset node), so the call can be captured into a HIP graph
     hipLaunchKernelGGL(profile_clear_kernel, dim3((n + kProfileThreads - 1) / kProfileThreads), dim3(kProfileThreads),

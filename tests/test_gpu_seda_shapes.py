@@ -123,7 +123,7 @@ def test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th,
     assert np.array_equal(got.cpu().numpy(), O.select_salient_tokens(s, gh, gw, th, tw))
 
 
-# (rows, blocks per row, groups, share of anchors): one launch, and on both sides of its limits the three launches
+# (rows, blocks per row, groups, share of anchors)
 @pytest.mark.parametrize("rows,nb,groups,share", [(0, 5, 8, 1.0), (1, 1, 8, 1.0), (63, 7, 8, 1.0), (1030, 129, 9, 0.7), (8193, 96, 64, 0.1),
                                                   (32768, 3, 256, 0.1), (32769, 3, 16, 0.1), (300, 40, 7, 0.5), (4096, 1025, 16, 0.05)])
 def test_seda_profile_shapes(F, rows, nb, groups, share):
@@ -145,4 +145,21 @@ def test_seda_profile_shapes(F, rows, nb, groups, share):
             ds = [d for d in range(32) if DEFAULT_FORMATBOOK[d][7] == 8 + k]
             best = min(ds, key=lambda d: (-cr[g][d], d)) if ds else 255
             assert int(sub[g, k]) == best
+    luts.free()
+
+
+@pytest.mark.parametrize("rows", [0, 1])
+def test_seda_profile_with_as_many_groups_as_a_launch_of_large_workgroups_refuses(F, rows):
+    # (a workgroup of 1024 threads per group would be 2^32 threads here, one more than a launch takes)
+    groups = 1 << 22
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    meta = torch.full((rows, 3), 5, dtype=torch.int16, device="cuda")
+    group = torch.full((rows,), groups - 1, dtype=torch.int32, device="cuda")
+    counts = torch.full((groups, 32), 77, dtype=torch.int32, device="cuda")
+    counts, sub = F.fb4_seda_profile(luts, meta, group, groups, counts=counts)
+    torch.cuda.synchronize()
+    assert int(counts.sum()) == 3 * rows and int(counts[-1, 5]) == 3 * rows
+    # without anchors the lowest dialect of every range
+    lowest = [min(d for d in range(32) if DEFAULT_FORMATBOOK[d][7] == 8 + k) for k in range(8)]
+    assert (sub[:-1] == torch.tensor(lowest, dtype=torch.uint8, device="cuda")).all()
     luts.free()
