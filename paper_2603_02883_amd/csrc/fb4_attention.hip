@@ -133,8 +133,13 @@ int fb4_select_salient_tokens(const float* scores, int64_t frames, int heads, in
     const int64_t tokens = (int64_t)grid_h * grid_w;
     if (tokens > (int64_t)kSelectMaxTokens || frames * tokens > 0x7FFFFFFFll || !aligned(scores, 4) || !aligned(rows_out, 4))
         return FB4_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(select_salient_kernel, dim3((unsigned)frames), dim3(kSelectThreads), 0, static_cast<hipStream_t>(stream),
-                       scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, rows_out);
+    const int64_t th = std::min(tile_h, grid_h), tw = std::min(tile_w, grid_w);
+    const SelectShape shape = select_shape(frames, ((grid_h + th - 1) / th) * ((grid_w + tw - 1) / tw), th * tw);
+#define FB4_SELECT_LAUNCH(t, l) hipLaunchKernelGGL((select_salient_kernel<t, l>), dim3((unsigned)frames), dim3(t), 0, static_cast<hipStream_t>(stream), scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, rows_out)
+    if (shape.threads == 1024) FB4_SELECT_LAUNCH(1024, 16);
+    else if (shape.lanes == 16) FB4_SELECT_LAUNCH(256, 16);
+    else FB4_SELECT_LAUNCH(256, 1);
+#undef FB4_SELECT_LAUNCH
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }
 

@@ -510,11 +510,22 @@ __global__ __launch_bounds__(256) void probe_mfma_rate_kernel(float* out, uint32
     out[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
-// Bound by its dependent steps (a frame's scores are 100 KB): one workgroup of 16 wavefronts per frame, up to 24 head
-// loads in flight, 16 lanes per tile.  16 frames x 24 heads x 1024 tokens: 11.4 us with four wavefronts, 6.7 now.
-constexpr int kSelectThreads = 1024;
+// One workgroup per frame, up to 24 head loads in flight.  kSelectThreads / kLanes (lanes per tile), chosen by
+// select_shape: a few frames are bound by the dependent steps of one workgroup, so 16 wavefronts with 16 lanes per tile;
+// with more frames than compute units the instructions count, and a thread per tile takes the fewest, unless one round of
+// 16 lanes holds all tiles.  us with 1024 x 16 / 256 x 16 / 256 x 1, tiles of 4 x 4: 16 frames x 24 heads x 1024 tokens
+// 5.45 / 7.99 / 6.70, 1024 frames x 8 heads x 1024 tokens 15.9 / 14.5 / 10.9, 1024 x 8 x 256 9.8 / 6.3 / 7.4, 16 x 8 x 16
+// 3.8 / 3.5 / 4.0; one token per frame, 65536 frames 458 / 246 / 177.
+struct SelectShape { int threads, lanes; };
+inline SelectShape select_shape(int64_t frames, int64_t tiles, int64_t tile_tokens)
+{
+    if (tile_tokens > 4 && tiles * 16 <= 256) return {256, 16};
+    if (tile_tokens > 4 && frames <= 256) return {1024, 16};   // (256 compute units)
+    return {256, 1};
+}
 constexpr uint32_t kSelectMaxTokens = 8192;   // per frame (the head means sit in LDS)
 
+template <int kSelectThreads, int kLanes>
 __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const float* scores, uint32_t heads,
                                                                         uint32_t grid_h, uint32_t grid_w, uint32_t tile_h,
                                                                         uint32_t tile_w, int32_t* rows_out)
@@ -537,7 +548,9 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
             for (int j = 0; j < N; ++j) m += (double)v[j];
             h += N;
         };
-        while (h + 24 <= heads) some(std::integral_constant<int, 24>{});
+        if (kLanes > 1) {
+            while (h + 24 <= heads) some(std::integral_constant<int, 24>{});
+        }
         while (h + 8 <= heads) some(std::integral_constant<int, 8>{});
         while (h < heads) some(std::integral_constant<int, 1>{});
         mean[t] = m / (double)heads;
@@ -545,27 +558,30 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
     }
     __syncthreads();
     const uint32_t th = (grid_h + tile_h - 1) / tile_h, tw = (grid_w + tile_w - 1) / tile_w;
-    const uint32_t part = threadIdx.x & 15u;
-    for (uint32_t tile = threadIdx.x >> 4; tile < th * tw; tile += kSelectThreads / 16) {
+    const uint32_t part = threadIdx.x % kLanes;
+    for (uint32_t tile = threadIdx.x / kLanes; tile < th * tw; tile += kSelectThreads / kLanes) {
         const uint32_t ty = tile / tw, tx = tile - ty * tw;
         const uint32_t y0 = ty * tile_h, x0 = tx * tile_w;
         const uint32_t hh = min(tile_h, grid_h - y0), ww = min(tile_w, grid_w - x0);
         uint32_t best = 0xFFFFFFFFu;
         double best_v = 0.0;
-        auto offer = [&](uint32_t at, double v) {   // the lowest token on ties
-            if (at != 0xFFFFFFFFu && (best == 0xFFFFFFFFu || v > best_v || (v == best_v && at < best))) { best = at; best_v = v; }
-        };
-        for (uint32_t i = part; i < hh * ww; i += 16) {
-            const uint32_t at = (y0 + i / ww) * grid_w + x0 + i % ww;
+        auto look = [&](uint32_t at) {   // (in ascending order: the first of equals stays)
             double v = mean[at];
             if (v != v) v = -__builtin_inf();
-            offer(at, v);
+            if (best == 0xFFFFFFFFu || v > best_v) { best = at; best_v = v; }
+        };
+        if (kLanes == 1) {
+            for (uint32_t y = y0; y < y0 + hh; ++y)
+                for (uint32_t x = x0; x < x0 + ww; ++x) look(y * grid_w + x);
+        } else {
+            for (uint32_t i = part; i < hh * ww; i += kLanes) look((y0 + i / ww) * grid_w + x0 + i % ww);
         }
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {   // (the 16 lanes of a tile stay together)
-            const uint32_t oat = (uint32_t)__shfl_xor((int)best, o);
-            const double ov = __shfl_xor(best_v, o);
-            offer(oat, ov);
+        for (int o = kLanes / 2; o > 0; o >>= 1) {   // (the lanes of a tile stay together)
+            const uint32_t at = (uint32_t)__shfl_xor((int)best, o);
+            const double v = __shfl_xor(best_v, o);
+            // the lowest token on ties
+            if (at != 0xFFFFFFFFu && (best == 0xFFFFFFFFu || v > best_v || (v == best_v && at < best))) { best = at; best_v = v; }
         }
         if (part == 0) chosen[best] = 1;   // (tiles are disjoint: no two threads write the same byte)
     }
@@ -584,8 +600,12 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
     if ((threadIdx.x & 63) == 63) wave_total[threadIdx.x >> 6] = incl;
     __syncthreads();
     uint32_t at = incl - count;
+    if (kWaves > 4) {   // (many: all read at once)
 #pragma unroll
-    for (uint32_t w = 0; w < kWaves; ++w) at += w < (threadIdx.x >> 6) ? wave_total[w] : 0u;
+        for (uint32_t w = 0; w < kWaves; ++w) at += w < (threadIdx.x >> 6) ? wave_total[w] : 0u;
+    } else {
+        for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) at += wave_total[w];
+    }
     int32_t* out = rows_out + (size_t)frame * th * tw;
     for (uint32_t t = first; t < last; ++t)
         if (chosen[t]) out[at++] = (int32_t)(frame * tokens + t);

@@ -113,7 +113,9 @@ def test_seda_main_anchor_frames_heads_and_ties(F, frames, heads, dim):
 
 
 @pytest.mark.parametrize("frames,heads,gh,gw,th,tw", [(1, 1, 1, 1, 4, 4), (3, 24, 32, 32, 4, 4), (2, 25, 7, 9, 4, 4), (2, 33, 64, 128, 4, 4),
-                                                      (2, 7, 90, 91, 5, 7), (1, 3, 33, 31, 40, 40), (2, 50, 13, 17, 1, 1), (2, 2, 64, 64, 64, 1)])
+                                                      (2, 7, 90, 91, 5, 7), (1, 3, 33, 31, 40, 40), (2, 50, 13, 17, 1, 1), (2, 2, 64, 64, 64, 1),
+                                                      (256, 3, 18, 20, 4, 4), (257, 25, 18, 20, 4, 4), (257, 9, 16, 16, 4, 4), (1, 9, 16, 17, 4, 4),
+                                                      (300, 2, 65, 66, 3, 2), (3, 5, 9, 9, 2, 2)])
 def test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th, tw):
     rng = np.random.default_rng(gh * gw + heads)
     s = rng.integers(0, 4, size=(frames, heads, gh * gw)).astype(np.float32)       # few values: ties are the rule
@@ -121,6 +123,14 @@ def test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th,
     got = F.fb4_select_salient_tokens(torch.from_numpy(s).cuda(), gh, gw, th, tw)
     torch.cuda.synchronize()
     assert np.array_equal(got.cpu().numpy(), O.select_salient_tokens(s, gh, gw, th, tw))
+
+
+def test_salient_token_choice_of_as_many_frames_as_a_launch_of_large_workgroups_refuses(F):
+    # (a workgroup of 1024 threads per frame would be 2^32 threads here, one more than a launch takes)
+    frames = 1 << 22
+    got = F.fb4_select_salient_tokens(torch.zeros((frames, 1, 1), device="cuda"), 1, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(-1), torch.arange(frames, dtype=torch.int32, device="cuda"))
 
 
 # (rows, blocks per row, groups, share of anchors)
