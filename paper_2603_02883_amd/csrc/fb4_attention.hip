@@ -210,7 +210,12 @@ int fb4_seda_main_anchor(const float* temporal_scores, const void* qt, const voi
         return FB4_ERR_UNSUPPORTED;
     if (frames * tokens > 0x7FFFFFFFll || n_cand > 0x7FFFFFFFll || frames * dim > 0x7FFFFFFFll) return FB4_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const unsigned threads = (unsigned)std::min<int64_t>(std::max<int64_t>(frames, 4) * 64, kMainMaxThreads);
+    // A wavefront per frame, four at least.  Up to 16 while two workgroups per compute unit hold all tiles, else up to 8,
+    // so that the next tiles do not wait for a whole workgroup of 16 (us with 4 / 8 / 16, 8 heads x 128 channels x 16
+    // frames: 64 tiles 10.4 / 6.9 / 5.7, 256 tiles 14.5 / 9.2 / 7.3, 1024 tiles 45.5 / 36.6 / 44.2); a launch takes fewer
+    // than 2^32 threads, so from 2^22 tiles on 4.
+    const int64_t most = tiles <= 512 ? kMainMaxThreads : tiles <= (1 << 22) ? 512 : 256;
+    const unsigned threads = (unsigned)std::min<int64_t>(std::max<int64_t>(frames, 4) * 64, most);
     hipLaunchKernelGGL(seda_main_anchor_kernel, dim3((unsigned)tiles), dim3(threads), 0, s, temporal_scores,
                        static_cast<const uint16_t*>(qt), static_cast<const uint16_t*>(kt), (uint32_t)frames, (uint32_t)heads,
                        (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)dim, candidates, (uint32_t)n_per_frame, (uint32_t)tile_h,

@@ -792,7 +792,7 @@ __global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_
 // to 16, the loads of four heads in flight, the best frame found by the lanes of one wavefront.  64 tiles x 16 frames x
 // 24 heads x 128 channels: 30 us with four wavefronts, serial head sums and one frame after the other, 9.8 now.
 constexpr int kMainThreads = 256;       // seda_main_anchor_3d_kernel
-constexpr int kMainMaxThreads = 1024;   // seda_main_anchor_kernel: 64 per frame, at most these
+constexpr int kMainMaxThreads = 1024;   // seda_main_anchor_kernel: 64 per frame, at most these (the launcher says when)
 constexpr uint32_t kMainMaxFrames = 1024;
 
 __global__ __launch_bounds__(kMainMaxThreads) void seda_main_anchor_kernel(
@@ -853,10 +853,9 @@ __global__ __launch_bounds__(kMainMaxThreads) void seda_main_anchor_kernel(
             if (f >= 0 && (bf < 0 || v > bv || (v == bv && f < bf))) { bf = f; bv = v; }
         };
         for (uint32_t f = lane; f < frames; f += 64) offer(slot[f] >= 0 ? (int32_t)f : -1, score[f]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const int32_t of = __shfl_xor(bf, o);
-            const double ov = __shfl_xor(bv, o);
+        for (uint32_t o = 1; o < frames && o < 64; o <<= 1) {   // (lane 0 needs no more: lanes from `frames` on hold none)
+            const int32_t of = __shfl_xor(bf, (int)o);
+            const double ov = __shfl_xor(bv, (int)o);
             offer(of, ov);
         }
         if (lane == 0) {

@@ -112,6 +112,29 @@ def test_seda_main_anchor_frames_heads_and_ties(F, frames, heads, dim):
                 assert kept.cpu().numpy()[f, tile] == (cand[f, tile] if keep else -1)
 
 
+@pytest.mark.parametrize("gh,gw", [(16, 32), (19, 27), (2049, 2048)])
+def test_seda_main_anchor_with_many_tiles(F, gh, gw):
+    # on both sides of the number of tiles that two workgroups per compute unit hold, and (16 frames) more tiles than a
+    # launch takes workgroups of 1024 threads
+    frames, heads, dim = 16, 1, 8
+    tokens = gh * gw
+    rng = np.random.default_rng(gw)
+    at = rng.choice(tokens, size=5, replace=False)                                  # tiles of one token
+    cand = np.array([f * tokens + at for f in range(frames)], dtype=np.int32)
+    qt, kt = torch.ones((tokens, heads, frames, dim), dtype=torch.bfloat16, device="cuda"), torch.ones((tokens, heads, frames, dim), dtype=torch.bfloat16, device="cuda")
+    kt[torch.from_numpy(at).cuda(), :, 3] = 0.25                                    # frame 3: score 2, the others 8
+    ts = torch.zeros((tokens, heads, frames), device="cuda")
+    best = rng.integers(0, frames, size=5)
+    ts[torch.from_numpy(at).cuda(), 0, torch.from_numpy(best).cuda()] = 1.0
+    main, kept = F.fb4_seda_main_anchor(ts, qt, kt, torch.from_numpy(cand).cuda(), gh, gw, 1, 1, prune_threshold=3.0)
+    torch.cuda.synchronize()
+    want = np.full(tokens, -1, dtype=np.int32)
+    want[at] = best * tokens + at
+    assert np.array_equal(main.cpu().numpy(), want)
+    cand[3] = np.where(best == 3, cand[3], -1)
+    assert np.array_equal(kept.cpu().numpy(), cand)
+
+
 @pytest.mark.parametrize("frames,heads,gh,gw,th,tw", [(1, 1, 1, 1, 4, 4), (3, 24, 32, 32, 4, 4), (2, 25, 7, 9, 4, 4), (2, 33, 64, 128, 4, 4),
                                                       (2, 7, 90, 91, 5, 7), (1, 3, 33, 31, 40, 40), (2, 50, 13, 17, 1, 1), (2, 2, 64, 64, 64, 1),
                                                       (256, 3, 18, 20, 4, 4), (257, 25, 18, 20, 4, 4), (257, 9, 16, 16, 4, 4), (1, 9, 16, 17, 4, 4),
