@@ -164,14 +164,19 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
     const uint32_t n = (uint32_t)(frames * tokens);
     const uint32_t gh = (uint32_t)grid_h, gw = (uint32_t)grid_w, th = (uint32_t)tile_h, tw = (uint32_t)tile_w;
     const uint32_t n_prepare = (n + kPrepareRows - 1) / kPrepareRows;
+    const bool one_buffer = token_group == anchor_group;
+    auto own_groups = [&]() {
+        if (n_anchors == 0) return;
+        hipLaunchKernelGGL(seda_anchor_kernel, dim3((unsigned)((n_anchors + kAssignThreads - 1) / kAssignThreads)), dim3(kAssignThreads),
+                           0, s, anchors, (uint32_t)n_anchors, (uint32_t)frames, gh, gw, th, tw, token_group, anchor_group);
+    };
     if ((int64_t)n_prepare * n_anchors <= kPrepareMaxVisits) {
         hipLaunchKernelGGL(seda_prepare_kernel, dim3(n_prepare), dim3(kAssignThreads), 0, s, anchors, (uint32_t)n_anchors, n,
                            (uint32_t)tokens, gw, th, tw, token_group, anchor_group);
     } else {
         hipLaunchKernelGGL(seda_fill_kernel, dim3((n + kAssignThreads - 1) / kAssignThreads), dim3(kAssignThreads), 0, s, token_group,
                            anchor_group, n);
-        hipLaunchKernelGGL(seda_anchor_kernel, dim3((unsigned)((n_anchors + kAssignThreads - 1) / kAssignThreads)), dim3(kAssignThreads),
-                           0, s, anchors, (uint32_t)n_anchors, (uint32_t)frames, gh, gw, th, tw, token_group, anchor_group);
+        own_groups();
     }
     if (n_anchors > 0) {
         AssignParams p = {};
@@ -182,12 +187,13 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
         p.stride_h = joint ? (uint64_t)frames * tokens : (uint64_t)tokens;
         p.threshold = threshold;
         const dim3 grid((unsigned)n_anchors, (unsigned)window_t);
-#define FB4_MARK_LAUNCH(quads) hipLaunchKernelGGL(seda_mark_kernel<quads>, grid, dim3(kAssignThreads), 0, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group, anchor_group, window_scores)
+#define FB4_MARK_LAUNCH(quads) hipLaunchKernelGGL(seda_mark_kernel<quads>, grid, dim3(kAssignThreads), 0, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group, one_buffer ? nullptr : anchor_group, window_scores)
         if (window <= 3) FB4_MARK_LAUNCH(3);
         else if (window <= 5) FB4_MARK_LAUNCH(7);
         else if (window <= 7) FB4_MARK_LAUNCH(13);
         else FB4_MARK_LAUNCH(16);
 #undef FB4_MARK_LAUNCH
+        if (one_buffer) own_groups();
     }
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }

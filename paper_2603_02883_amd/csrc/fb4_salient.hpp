@@ -618,7 +618,9 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
 // of several groups belongs to the highest group number (App. D: the subsequent anchor), an anchor to its own
 // group.  Two small launches: the anchors' own groups and -1 elsewhere (seda_prepare_kernel; with very many anchors
 // seda_fill_kernel and seda_anchor_kernel instead), then the marks -- a maximum on the group number of every token
-// that is no anchor (seda_mark_kernel, one workgroup per anchor and frame of the window).
+// that is no anchor (seda_mark_kernel, one workgroup per anchor and frame of the window).  Where one buffer is passed
+// for both results its marks are no sign of an anchor: every token is marked then (anchor_group null), and
+// seda_anchor_kernel puts the anchors' own groups back at the end.
 // Token (frame f, head h, token t) of Q / K sits at ((f * stride_f + h * stride_h) + t) * dim: factorized
 // attention [frames][heads][tokens][dim], 3D attention [heads][frames * tokens][dim].
 constexpr int kAssignThreads = 256;
@@ -776,7 +778,7 @@ __global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_
         const size_t per = (size_t)p.window_t * slots;
         if (scores) scores[(size_t)i * per + (size_t)wt * slots + w] = inside ? sc : __builtin_nanf("");
         const size_t at = (size_t)fc * tokens + t;
-        if (inside && sc > p.threshold && anchor_group[at] < 0)
+        if (inside && sc > p.threshold && (!anchor_group || anchor_group[at] < 0))
             atomicMax(token_group + at, (int32_t)tile_of(ac, p.grid_w, p.tile_h, p.tile_w));
     }
 }

@@ -81,6 +81,22 @@ def test_seda_assign_with_very_many_anchor_entries(F):
     assert int((a[1] >= 0).sum()) == 400
 
 
+@pytest.mark.parametrize("n_anchors", [150, 70000])
+def test_seda_assign_into_one_buffer(F, n_anchors):
+    # a caller without use for the anchors' groups may pass one buffer for both: it holds the tokens' groups
+    frames, gh, gw, heads, dim = 3, 40, 41, 2, 16
+    tokens = gh * gw
+    q, k = synth.attention_qk(frames * heads, tokens, dim, seed=9, device="cuda")
+    q, k = q.view(frames, heads, tokens, dim), k.view(frames, heads, tokens, dim)
+    few = torch.from_numpy(np.random.default_rng(2).choice(frames * tokens, size=150, replace=False).astype(np.int32)).cuda()
+    anchors = few.repeat(n_anchors // 150 + 1)[:max(n_anchors, 150)]
+    want, _ = F.fb4_seda_assign(q, k, few, frames, gh, gw, window=8, threshold=-1e9)   # every window whole: marks meet everywhere
+    one = torch.empty(frames * tokens, dtype=torch.int32, device="cuda")
+    F.fb4_seda_assign(q, k, anchors, frames, gh, gw, window=8, threshold=-1e9, token_group=one, anchor_group=one)
+    torch.cuda.synchronize()
+    assert torch.equal(one, want)
+
+
 @pytest.mark.parametrize("frames,heads,dim", [(1, 1, 8), (2, 70, 136), (17, 3, 72), (64, 2, 8), (70, 5, 16), (200, 1, 8)])
 def test_seda_main_anchor_frames_heads_and_ties(F, frames, heads, dim):
     gh, gw = 4, 8                                            # two tiles
