@@ -170,7 +170,7 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
         hipLaunchKernelGGL(seda_anchor_kernel, dim3((unsigned)((n_anchors + kAssignThreads - 1) / kAssignThreads)), dim3(kAssignThreads),
                            0, s, anchors, (uint32_t)n_anchors, (uint32_t)frames, gh, gw, th, tw, token_group, anchor_group);
     };
-    if ((int64_t)n_prepare * n_anchors <= kPrepareMaxVisits) {
+    if (n_anchors <= (int64_t)kPrepareMaxAnchors) {
         hipLaunchKernelGGL(seda_prepare_kernel, dim3(n_prepare), dim3(kAssignThreads), 0, s, anchors, (uint32_t)n_anchors, n,
                            (uint32_t)tokens, gw, th, tw, token_group, anchor_group);
     } else {

@@ -616,7 +616,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
 // K[token], averaged over the heads -- exceeds a threshold.  The group of an anchor is the row-major number of the
 // spatial tile it lies in (the per-frame candidates of a tile share one sub-formatbook); a token marked by anchors
 // of several groups belongs to the highest group number (App. D: the subsequent anchor), an anchor to its own
-// group.  Two small launches: the anchors' own groups and -1 elsewhere (seda_prepare_kernel; with very many anchors
+// group.  Two small launches: the anchors' own groups and -1 elsewhere (seda_prepare_kernel; with many anchors
 // seda_fill_kernel and seda_anchor_kernel instead), then the marks -- a maximum on the group number of every token
 // that is no anchor (seda_mark_kernel, one workgroup per anchor and frame of the window).  Where one buffer is passed
 // for both results its marks are no sign of an anchor: every token is marked then (anchor_group null), and
@@ -631,10 +631,12 @@ __device__ __forceinline__ uint32_t tile_of(uint32_t token, uint32_t grid_w, uin
     return (y / tile_h) * ((grid_w + tile_w - 1) / tile_w) + x / tile_w;
 }
 
-// A workgroup writes kPrepareRows rows and looks through all anchors for those among them: no second launch has to
-// wait for the first (the launcher takes it up to kPrepareMaxVisits visits of an anchor by a workgroup).
+// A workgroup writes kPrepareRows rows and looks through all anchors for those among them, eight entries per thread: no
+// second launch has to wait for the first.  More anchors cost more than that launch: the whole call with these / with
+// seda_fill_kernel and seda_anchor_kernel, 16 frames x 1024 tokens, windows of one token: 1024 anchors 6.9 / 7.8 us, 2048
+// 8.5 / 8.8, 3000 10.6 / 9.8, 16384 31.9 / 22.5; 64 x 4096 tokens, 2048 anchors 7.7 / 9.1, 16384 26.1 / 22.9.
 constexpr uint32_t kPrepareRows = 1024;
-constexpr int64_t kPrepareMaxVisits = 1ll << 22;
+constexpr uint32_t kPrepareMaxAnchors = 2048;
 
 __global__ __launch_bounds__(kAssignThreads) void seda_prepare_kernel(const int32_t* anchors, uint32_t n_anchors, uint32_t n_rows,
                                                                       uint32_t tokens, uint32_t grid_w, uint32_t tile_h,
@@ -644,9 +646,16 @@ __global__ __launch_bounds__(kAssignThreads) void seda_prepare_kernel(const int3
     const uint32_t first = blockIdx.x * kPrepareRows, n = min(kPrepareRows, n_rows - first);
     for (uint32_t i = threadIdx.x; i < kPrepareRows; i += kAssignThreads) group[i] = -1;
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n_anchors; i += kAssignThreads) {
-        const uint32_t at = (uint32_t)anchors[i] - first;   // (a negative entry lies past any row)
-        if (anchors[i] >= 0 && at < n) group[at] = (int32_t)tile_of((uint32_t)anchors[i] % tokens, grid_w, tile_h, tile_w);
+    if (n_anchors > 0) {
+        constexpr uint32_t kRead = kPrepareMaxAnchors / kAssignThreads;   // entries per thread, all in flight
+        int32_t row[kRead];
+#pragma unroll
+        for (uint32_t j = 0; j < kRead; ++j) row[j] = anchors[min(threadIdx.x + j * kAssignThreads, n_anchors - 1u)];   // (past the end: the last one again)
+#pragma unroll
+        for (uint32_t j = 0; j < kRead; ++j) {
+            const uint32_t at = (uint32_t)row[j] - first;   // (a negative entry lies past any row)
+            if (row[j] >= 0 && at < n) group[at] = (int32_t)tile_of((uint32_t)row[j] % tokens, grid_w, tile_h, tile_w);
+        }
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n; i += kAssignThreads) {

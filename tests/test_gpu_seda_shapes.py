@@ -73,12 +73,29 @@ def test_seda_assign_with_very_many_anchor_entries(F):
     q, k = synth.attention_qk(frames * heads, tokens, dim, seed=3, device="cuda")
     q, k = q.view(frames, heads, tokens, dim), k.view(frames, heads, tokens, dim)
     few = torch.from_numpy(np.random.default_rng(1).choice(frames * tokens, size=400, replace=False).astype(np.int32)).cuda()
-    many = few.repeat(400)                                   # 32 workgroups x 160000 entries
+    many = few.repeat(400)
     a = F.fb4_seda_assign(q, k, few, frames, gh, gw, window=3, threshold=1.0)
     b = F.fb4_seda_assign(q, k, many, frames, gh, gw, window=3, threshold=1.0)
     torch.cuda.synchronize()
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     assert int((a[1] >= 0).sum()) == 400
+
+
+@pytest.mark.parametrize("n_anchors", [0, 1, 255, 256, 257, 2047, 2048, 2049, 5000])
+def test_seda_assign_own_groups_by_the_number_of_anchor_entries(F, n_anchors):
+    frames, gh, gw, dim = 5, 21, 34, 8                       # 3570 rows: the last of four workgroups is short
+    rows = frames * gh * gw
+    q, k = synth.attention_qk(frames, gh * gw, dim, seed=4, device="cuda")
+    q, k = q.view(frames, 1, gh * gw, dim), k.view(frames, 1, gh * gw, dim)
+    anchors = np.random.default_rng(n_anchors).integers(-2, rows + 2, size=n_anchors).astype(np.int32)
+    anchors[:3] = [0, rows - 1, 0x7FFFFFFF][:n_anchors]
+    tg, ag = F.fb4_seda_assign(q, k, torch.from_numpy(anchors).cuda(), frames, gh, gw, window=1, threshold=1e30)
+    torch.cuda.synchronize()
+    want = np.full(rows, -1, dtype=np.int32)
+    for r in anchors[(anchors >= 0) & (anchors < rows)]:
+        y, x = divmod(int(r) % (gh * gw), gw)
+        want[r] = (y // 4) * ((gw + 3) // 4) + x // 4
+    assert np.array_equal(ag.cpu().numpy(), want) and np.array_equal(tg.cpu().numpy(), want)
 
 
 @pytest.mark.parametrize("n_anchors", [150, 70000])
