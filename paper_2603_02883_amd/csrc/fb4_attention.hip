@@ -187,11 +187,25 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
         p.stride_h = joint ? (uint64_t)frames * tokens : (uint64_t)tokens;
         p.threshold = threshold;
         const dim3 grid((unsigned)n_anchors, (unsigned)window_t);
-#define FB4_MARK_LAUNCH(quads) hipLaunchKernelGGL(seda_mark_kernel<quads>, grid, dim3(kAssignThreads), 0, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group, one_buffer ? nullptr : anchor_group, window_scores)
-        if (window <= 3) FB4_MARK_LAUNCH(3);
-        else if (window <= 5) FB4_MARK_LAUNCH(7);
-        else if (window <= 7) FB4_MARK_LAUNCH(13);
-        else FB4_MARK_LAUNCH(16);
+        // As many lanes as a row has 16-byte pieces; with fewer heads than wavefronts at most 4, so that the wavefronts
+        // that have a head take fewer steps.  us with 16 lanes for every row / now, 1024 anchors of 16 x 1024 tokens, 8 x 8
+        // windows: 24 heads x 8 channels 25.9 / 10.0, x 32 channels 25.3 / 18.2, one head x 128 channels x 16 frames 77 / 27.
+        int lanes = dim > 64 ? 16 : dim > 32 ? 8 : dim > 16 ? 4 : dim > 8 ? 2 : 1;
+        if (heads < kAssignThreads / 64) lanes = std::min(lanes, 4);
+#define FB4_MARK_LAUNCH(w, l) hipLaunchKernelGGL((seda_mark_kernel<w, l>), grid, dim3(kAssignThreads), 0, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group, one_buffer ? nullptr : anchor_group, window_scores)
+#define FB4_MARK_CASE(w)                                     \
+        case w:                                              \
+            if (lanes == 16) FB4_MARK_LAUNCH(w, 16);         \
+            else if (lanes == 8) FB4_MARK_LAUNCH(w, 8);      \
+            else if (lanes == 4) FB4_MARK_LAUNCH(w, 4);      \
+            else if (lanes == 2) FB4_MARK_LAUNCH(w, 2);      \
+            else FB4_MARK_LAUNCH(w, 1);                      \
+            break;
+        switch (window) {
+            FB4_MARK_CASE(1) FB4_MARK_CASE(2) FB4_MARK_CASE(3) FB4_MARK_CASE(4)
+            FB4_MARK_CASE(5) FB4_MARK_CASE(6) FB4_MARK_CASE(7) FB4_MARK_CASE(8)
+        }
+#undef FB4_MARK_CASE
 #undef FB4_MARK_LAUNCH
         if (one_buffer) own_groups();
     }

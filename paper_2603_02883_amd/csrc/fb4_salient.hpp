@@ -693,73 +693,77 @@ struct AssignParams {
     float threshold;
 };
 
-// Adds up the 16 lanes of a row of lanes (every lane ends with the sum; a fixed order).
-__device__ __forceinline__ float row_of_lanes_sum(float v)
+// Adds up groups of kLanes neighbouring lanes (every lane ends with its group's sum; a fixed order).
+template <int kLanes>
+__device__ __forceinline__ float group_of_lanes_sum(float v)
 {
     auto moved = [](float x, auto ctrl) {
         return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true));
     };
-    v += moved(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
-    v += moved(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
-    v += moved(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
-    v += moved(v, std::integral_constant<int, 0x140>{});   // row_mirror
+    if (kLanes >= 2) v += moved(v, std::integral_constant<int, 0xB1>{});     // quad_perm [1,0,3,2]
+    if (kLanes >= 4) v += moved(v, std::integral_constant<int, 0x4E>{});     // quad_perm [2,3,0,1]
+    if (kLanes >= 8) v += moved(v, std::integral_constant<int, 0x141>{});    // row_half_mirror
+    if (kLanes >= 16) v += moved(v, std::integral_constant<int, 0x140>{});   // row_mirror
     return v;
 }
 
-// 16 lanes share a row of K, 16 bytes each, four window slots at a time, so that a load covers whole rows (and
+// kLanes lanes share a row of K, 16 bytes each, 64 / kLanes window slots at a time, so that a load covers whole rows (and
 // neighbouring slots are neighbouring rows); a wavefront takes every fourth head with the loads of two heads in
 // flight, and a lane keeps its channels' sums over its heads: lanes and wavefronts are added up once at the end.
-// kQuads: window slots / 4, rounded up.  16 frames x 24 heads x 1024 tokens x 128 channels, 1024 anchors, 5 x 5
-// windows: 45 us with a thread per slot, which read its row 16 bytes at a time, 16.7 now (9.4 TB/s of gathered rows; they
-// overlap, so part of them comes from the caches).
-template <int kQuads>
+// kWindow: the window's side (slots and their places are then constants).  16 frames x 24 heads x 1024 tokens x 128
+// channels, 1024 random anchors, 5 x 5 windows, with the preparation: 45.5 us with a thread per slot, which read its row 16
+// bytes at a time, 26.5 so.
+template <int kWindow, int kLanes>
 __global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_t* q, const uint16_t* k,
                                                                    const int32_t* anchors, AssignParams p,
                                                                    int32_t* token_group, const int32_t* anchor_group,
                                                                    float* scores)
 {
-    __shared__ float partial[kAssignThreads / 64][4 * kQuads];
+    constexpr uint32_t slots = kWindow * kWindow, kRows = 64 / kLanes;
+    constexpr int kSteps = (slots + kRows - 1) / kRows;
+    __shared__ float partial[kAssignThreads / 64][kSteps * kRows];
     const uint32_t tokens = p.grid_h * p.grid_w;
-    const uint32_t i = blockIdx.x, wt = blockIdx.y, slots = p.window * p.window;
+    const uint32_t i = blockIdx.x, wt = blockIdx.y;
     const int64_t row = anchors[i];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, sub = lane >> 4, piece = lane & 15u;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t sub = lane / kLanes, piece = lane % kLanes;
     const bool anchor_ok = row >= 0 && row < (int64_t)p.frames * tokens;   // otherwise: no token of the clip, marks nothing
-    if (!anchor_ok && !scores) return;   // (the same for the whole workgroup)
     const uint32_t rc = anchor_ok ? (uint32_t)row : 0u;
     const uint32_t fa = rc / tokens, ac = rc - fa * tokens;
     const int32_t ay = (int32_t)(ac / p.grid_w), ax = (int32_t)(ac % p.grid_w);
     const int32_t f = (int32_t)fa + (int32_t)wt - (int32_t)(p.window_t / 2);
     const bool frame_ok = anchor_ok && f >= 0 && f < (int32_t)p.frames;
+    if (!frame_ok && !scores) return;   // (the same for the whole workgroup)
     const uint32_t fc = frame_ok ? (uint32_t)f : fa;
     auto place = [&](uint32_t slot, uint32_t& t) {   // the slot's token; false (and the anchor's own) outside the clip
-        const int32_t y = ay + (int32_t)(slot / p.window) - (int32_t)(p.window / 2);
-        const int32_t x = ax + (int32_t)(slot % p.window) - (int32_t)(p.window / 2);
+        const int32_t y = ay + (int32_t)(slot / kWindow) - kWindow / 2;
+        const int32_t x = ax + (int32_t)(slot % kWindow) - kWindow / 2;
         const bool inside = slot < slots && frame_ok && y >= 0 && y < (int32_t)p.grid_h && x >= 0 && x < (int32_t)p.grid_w;
         t = inside ? (uint32_t)y * p.grid_w + (uint32_t)x : ac;
         return inside;
     };
-    float acc[kQuads];
-    uint32_t off[kQuads];   // of the slots' rows, in elements (the launcher checks tokens * dim < 2^31)
+    float acc[kSteps];
+    uint32_t off[kSteps];   // of the slots' rows, in elements (the launcher checks tokens * dim < 2^31)
 #pragma unroll
-    for (int j = 0; j < kQuads; ++j) {
+    for (int j = 0; j < kSteps; ++j) {
         acc[j] = 0.0f;
         uint32_t t;
-        place(4u * j + sub, t);
+        place(kRows * j + sub, t);
         off[j] = t * p.dim;
     }
-    if (frame_ok) {
+    if (frame_ok && wave < p.heads) {
         const uint32_t n16 = p.dim / 8u;
-        for (uint32_t c = piece; c < n16; c += 16) {
+        for (uint32_t c = piece; c < n16; c += kLanes) {
 #pragma unroll 2
             for (uint32_t h = wave; h < p.heads; h += kAssignThreads / 64) {
                 const uint4 qv = *reinterpret_cast<const uint4*>(q + (fa * p.stride_f + h * p.stride_h + ac) * p.dim + c * 8u);
                 const uint16_t* kh = k + (fc * p.stride_f + h * p.stride_h) * p.dim + c * 8u;
-                uint4 kv[kQuads];
+                uint4 kv[kSteps];
 #pragma unroll
-                for (int j = 0; j < kQuads; ++j) kv[j] = *reinterpret_cast<const uint4*>(kh + off[j]);
+                for (int j = 0; j < kSteps; ++j) kv[j] = *reinterpret_cast<const uint4*>(kh + off[j]);
                 const uint32_t qs[4] = {qv.x, qv.y, qv.z, qv.w};
 #pragma unroll
-                for (int j = 0; j < kQuads; ++j) {
+                for (int j = 0; j < kSteps; ++j) {
                     const uint32_t ks[4] = {kv[j].x, kv[j].y, kv[j].z, kv[j].w};
                     float d0 = 0.0f, d1 = 0.0f;   // (short chains: their rounding errors stay those of small sums)
 #pragma unroll
@@ -773,9 +777,9 @@ __global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_
         }
     }
 #pragma unroll
-    for (int j = 0; j < kQuads; ++j) {
-        const float v = row_of_lanes_sum(acc[j]);
-        if (piece == 0) partial[wave][4 * j + sub] = v;
+    for (int j = 0; j < kSteps; ++j) {
+        const float v = group_of_lanes_sum<kLanes>(acc[j]);
+        if (piece == 0) partial[wave][kRows * j + sub] = v;
     }
     __syncthreads();
     const uint32_t w = threadIdx.x;

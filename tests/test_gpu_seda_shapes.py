@@ -19,7 +19,9 @@ def F():
 
 
 @pytest.mark.parametrize("window", [1, 2, 3, 4, 5, 6, 7, 8])
-@pytest.mark.parametrize("dim,heads,joint,window_t", [(8, 1, False, 1), (72, 5, False, 1), (136, 3, True, 2), (256, 9, True, 3)])
+@pytest.mark.parametrize("dim,heads,joint,window_t", [(8, 1, False, 1), (72, 5, False, 1), (136, 3, True, 2), (256, 9, True, 3),
+                                                          (8, 6, True, 2), (16, 4, False, 1), (24, 5, True, 2), (32, 9, False, 1), (40, 4, False, 1),
+                                                          (64, 7, True, 3), (48, 2, False, 1), (128, 1, True, 2)])
 def test_seda_assign_windows_and_row_lengths(F, window, dim, heads, joint, window_t):
     frames, gh, gw = 3, 7, 9
     tokens = gh * gw
