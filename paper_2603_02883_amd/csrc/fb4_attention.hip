@@ -48,6 +48,12 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
     const int64_t bpg = (tokens + per_wg - 1) / per_wg;
     if (tokens * dim > 0x7FFFFFFFll || groups * bpg > 0x7FFFFFFFll) return FB4_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
+#define FB4_SCORE_LAUNCH(d, relu, qb, keys) hipLaunchKernelGGL((attention_scores_kernel<d, relu, qb, keys>), grid, dim3(kScoreThreads), 0, s, qs, ks, (uint32_t)tokens, (uint32_t)dim, (uint32_t)bpg, out)
+#define FB4_SCORE_CASE(d, qb, keys)                          \
+    case d:                                                  \
+        if (mode) FB4_SCORE_LAUNCH(d, true, qb, keys);       \
+        else FB4_SCORE_LAUNCH(d, false, qb, keys);           \
+        break;
     if (small) {
         const uint32_t pieces = (uint32_t)(dim / 8);
         const uint32_t rows_per_task = tokens > 32 ? (uint32_t)tokens : (32u / (uint32_t)tokens) * (uint32_t)tokens;
@@ -60,29 +66,52 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
             const uint32_t n = std::min(163840u / (w * per_wave), 8u / w);
             if (n * w > most) { most = n * w; waves = w; }
         }
-        // (row numbers are 32 bits in the kernel: longer inputs take several launches)
-        const int64_t at_once = ((1ll << 30) / rows_per_task) * rows_per_task / tokens;
+        const bool one_wave = scores_short_in_one_wave(groups, tokens, dim, most);
+        // (row numbers are 32 bits in the one kernel, a launch takes fewer than 2^24 workgroups of the other: longer inputs
+        // take several launches)
+        const int64_t at_once = one_wave ? ((1ll << 30) / rows_per_task) * rows_per_task / tokens : 1ll << 23;
         for (int64_t g0 = 0; g0 < groups; g0 += at_once) {
-            const uint32_t n_rows = (uint32_t)(std::min(at_once, groups - g0) * tokens);
-            const uint32_t n_tasks = (n_rows + rows_per_task - 1) / rows_per_task;
-            // every wavefront with the same number of tasks (6000 x 48 x 72: 16.3 us; with the last round ragged 17.5)
-            const uint32_t rounds = (n_tasks + 256u * most - 1) / (256u * most);
-            const dim3 sgrid((n_tasks + rounds * waves - 1) / (rounds * waves));
+            const int64_t n_groups = std::min(at_once, groups - g0);
             const uint16_t* qs = static_cast<const uint16_t*>(q) + (size_t)(g0 * tokens * dim);
             const uint16_t* ks = static_cast<const uint16_t*>(k) + (size_t)(g0 * tokens * dim);
             float* out = scores + g0 * tokens;
-#define FB4_SHORT_LAUNCH(p, n) hipLaunchKernelGGL((attention_scores_short_kernel<p, n>), sgrid, dim3(64 * waves), waves * per_wave, s, qs, ks, n_rows, (uint32_t)tokens, rows_per_task, n_tasks, pieces, (uint32_t)mode, out)
-#define FB4_SHORT_CASE(n)                               \
-            switch (pieces) {                           \
-            case 8: FB4_SHORT_LAUNCH(8, n); break;      \
-            case 9: FB4_SHORT_LAUNCH(9, n); break;      \
-            case 12: FB4_SHORT_LAUNCH(12, n); break;    \
-            case 16: FB4_SHORT_LAUNCH(16, n); break;    \
-            default: FB4_SHORT_LAUNCH(0, n); break;     \
+            if (!one_wave) {
+                const dim3 grid((unsigned)n_groups);   // (bpg is 1)
+                switch ((int)((dim + 31) / 32)) {
+                    FB4_SCORE_CASE(1, 1, 32) FB4_SCORE_CASE(2, 1, 32) FB4_SCORE_CASE(3, 1, 32) FB4_SCORE_CASE(4, 1, 32)
+                    FB4_SCORE_CASE(5, 1, 32) FB4_SCORE_CASE(6, 1, 32) FB4_SCORE_CASE(7, 1, 32) FB4_SCORE_CASE(8, 1, 32)
+                }
+                if (hipGetLastError() != hipSuccess) return FB4_ERR_HIP;
+                continue;
             }
-            if (tokens <= 32) { FB4_SHORT_CASE(1) } else { FB4_SHORT_CASE(2) }
+            const uint32_t n_rows = (uint32_t)(n_groups * tokens);
+            const uint32_t n_tasks = (n_rows + rows_per_task - 1) / rows_per_task;
+            if (n_tasks <= 256u) waves = 1;   // (a compute unit each: 64 groups x 32 x 112 2.90 us with four, 2.66 so)
+            // every wavefront with the same number of tasks (6000 x 48 x 72: 16.3 us; with the last round ragged 17.5)
+            const uint32_t rounds = (n_tasks + 256u * most - 1) / (256u * most);
+            const dim3 sgrid((n_tasks + rounds * waves - 1) / (rounds * waves));
+#define FB4_SHORT_CASE(p, n) case p: hipLaunchKernelGGL((attention_scores_short_kernel<p, n>), sgrid, dim3(64 * waves), waves * per_wave, s, qs, ks, n_rows, (uint32_t)tokens, rows_per_task, n_tasks, (uint32_t)mode, out); break;
+#define FB4_SHORT_CASES(n)                                                                                                          \
+    FB4_SHORT_CASE(1, n) FB4_SHORT_CASE(2, n) FB4_SHORT_CASE(3, n) FB4_SHORT_CASE(4, n) FB4_SHORT_CASE(5, n) FB4_SHORT_CASE(6, n)   \
+    FB4_SHORT_CASE(7, n) FB4_SHORT_CASE(8, n) FB4_SHORT_CASE(9, n) FB4_SHORT_CASE(10, n) FB4_SHORT_CASE(11, n)                      \
+    FB4_SHORT_CASE(12, n) FB4_SHORT_CASE(13, n) FB4_SHORT_CASE(14, n) FB4_SHORT_CASE(15, n) FB4_SHORT_CASE(16, n)
+            if (tokens <= 32) {
+                switch (pieces) {
+                    FB4_SHORT_CASES(1)
+                    FB4_SHORT_CASE(17, 1) FB4_SHORT_CASE(18, 1) FB4_SHORT_CASE(19, 1) FB4_SHORT_CASE(20, 1) FB4_SHORT_CASE(21, 1)
+                    FB4_SHORT_CASE(22, 1) FB4_SHORT_CASE(23, 1) FB4_SHORT_CASE(24, 1) FB4_SHORT_CASE(25, 1) FB4_SHORT_CASE(26, 1)
+                    FB4_SHORT_CASE(27, 1) FB4_SHORT_CASE(28, 1) FB4_SHORT_CASE(29, 1) FB4_SHORT_CASE(30, 1) FB4_SHORT_CASE(31, 1)
+                    FB4_SHORT_CASE(32, 1)
+                    default: return FB4_ERR_UNSUPPORTED;
+                }
+            } else {
+                switch (pieces) {
+                    FB4_SHORT_CASES(2)
+                    default: return FB4_ERR_UNSUPPORTED;
+                }
+            }
+#undef FB4_SHORT_CASES
 #undef FB4_SHORT_CASE
-#undef FB4_SHORT_LAUNCH
             if (hipGetLastError() != hipSuccess) return FB4_ERR_HIP;
         }
         return FB4_OK;
@@ -109,18 +138,14 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
         return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
     }
     const dim3 grid((unsigned)(groups * bpg));
-#define FB4_SCORE_ARGS static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), (uint32_t)tokens, (uint32_t)dim, (uint32_t)bpg, scores
-#define FB4_SCORE_CASE(d)                                                                                                          \
-    case d:                                                                                                                        \
-        if (mode) hipLaunchKernelGGL((attention_scores_kernel<d, true>), grid, dim3(kScoreThreads), 0, s, FB4_SCORE_ARGS);         \
-        else hipLaunchKernelGGL((attention_scores_kernel<d, false>), grid, dim3(kScoreThreads), 0, s, FB4_SCORE_ARGS);             \
-        break;
+    const uint16_t *qs = static_cast<const uint16_t*>(q), *ks = static_cast<const uint16_t*>(k);
+    float* out = scores;
     switch ((int)((dim + 31) / 32)) {
-        FB4_SCORE_CASE(5) FB4_SCORE_CASE(6) FB4_SCORE_CASE(7) FB4_SCORE_CASE(8)
+        FB4_SCORE_CASE(5, 2, 64) FB4_SCORE_CASE(6, 2, 64) FB4_SCORE_CASE(7, 2, 64) FB4_SCORE_CASE(8, 2, 64)
         default: return FB4_ERR_UNSUPPORTED;
     }
 #undef FB4_SCORE_CASE
-#undef FB4_SCORE_ARGS
+#undef FB4_SCORE_LAUNCH
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }
 

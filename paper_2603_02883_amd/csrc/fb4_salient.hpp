@@ -38,16 +38,16 @@ __device__ __forceinline__ uint32_t xcd_local_position(uint32_t b, uint32_t n)
     const uint32_t chunk = n / 8u;
     return b < chunk * 8u ? (b % 8u) * chunk + b / 8u : b;
 }
-constexpr uint32_t kScoreShortGroup = 64;   // tokens up to which attention_scores_short_kernel is used
+constexpr uint32_t kScoreShortGroup = 64;   // tokens of a short group at most
 
-// Long groups with rows of more than 128 channels: a workgroup of four wavefronts takes 256 queries of one group; every
-// wavefront keeps its 64 queries as B operands in registers for the whole pass and walks over the group's keys 64 at a
-// time: the key block goes through LDS once for the four wavefronts (rows padded by 16 bytes so that the 16-byte
-// operand reads of the 16 lanes of a pass fall into 16 different bank groups).
+// A workgroup of four wavefronts takes 128 * kScoreQB queries of one group; every wavefront keeps its queries as B
+// operands in registers for the whole pass and walks over the group's keys kScoreKeys at a time: the key block goes
+// through LDS once for the four wavefronts (rows padded by 16 bytes so that the 16-byte operand reads of the 16 lanes
+// of a pass fall into 16 different bank groups).  Long groups with rows of more than 128 channels: 64 queries per
+// wavefront and 64 keys per barrier; short groups (scores_short_in_one_wave says which): 32 and 32.
 // D32: channels / 32, rounded up (channels beyond `dim` are zero on both sides).  kRelu: max(., 0), else |.|.
-constexpr int kScoreQB = 2;      // blocks of 32 queries per wavefront
-constexpr int kScoreKeys = 64;   // keys per barrier
-template <int D32, bool kRelu>
+// kScoreQB: blocks of 32 queries per wavefront; kScoreKeys: keys per barrier (a multiple of 32).
+template <int D32, bool kRelu, int kScoreQB, int kScoreKeys>
 __global__ __launch_bounds__(kScoreThreads) void attention_scores_kernel(const uint16_t* q, const uint16_t* k,
                                                                          uint32_t tokens, uint32_t dim,
                                                                          uint32_t blocks_per_group, float* scores)
@@ -359,10 +359,22 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
 // memory -- loads them straight into LDS of its own (pieces placed as in the kernel above), forms all products of the
 // 32 queries with the 32 keys on the matrix cores and adds up those whose key lies in the query's group.  Nothing is
 // shared between wavefronts, so there are no barriers; a wavefront requests the rows of its next task as soon as
-// it has read its operands.  kP: 16-byte pieces per row, 0: taken from `pieces`.
-// Measured (us; before: one workgroup of four wavefronts, barriers and room for 128 queries per group): 24576 groups x
-// 16 tokens x 128 channels 53 -> 35.4 (5.7 TB/s), x 72 channels 39 -> 20.5, 12000 x 21 x 64 15.2 -> 11.4, 6000 x 40 x
-// 128 26.5 -> 23.9, 100000 x 4 x 64 95 -> 18.8; 12000 x 64 x 64 37.6 -> 36.9.
+// it has read its operands.  kP: 16-byte pieces per row; every row length is compiled, because dividing each load's
+// position by a number not known before costs more than the products (8 groups x 32 tokens x 112 channels 3.34 us so, 2.73
+// compiled; 16384 x 16 x 80 14.5 and 13.8).
+// Measured (us; before: the first kernel above): 24576 groups x 16 tokens x 128 channels 53 -> 35.4 (5.7 TB/s), x 72
+// channels 39 -> 20.5, 12000 x 21 x 64 15.2 -> 11.4, 6000 x 40 x 128 26.5 -> 23.9, 100000 x 4 x 64 95 -> 18.8.
+// Which of the two: up to 32 tokens this one, except where the rows of five wavefronts fill a compute unit's LDS (8192 x
+// 32 x 256: 44.2 against 37.8; with six, 13107 x 20 x 256: 40.0 against 45.7).  From 33 tokens on one wavefront's chain
+// of loads and products is longer than four wavefronts' in the first kernel, and only many groups hide it (40 tokens x
+// 72 channels, 6 / 409 / 1638 / 6553 groups: 3.4 / 3.6 / 4.4 / 14.9 us against 3.0 / 3.4 / 5.8 / 17.4), the less the
+// fuller its two blocks of 32 are (4681 x 56 x 112: 20.7 against 18.7) and not for rows of more than 128 channels
+// (5461 x 48 x 160: 29.2 against 26.7).
+inline bool scores_short_in_one_wave(int64_t groups, int64_t tokens, int64_t dim, uint32_t waves_per_cu)
+{
+    if (tokens <= 32) return waves_per_cu > 5;
+    return tokens <= 48 && dim <= 128 && groups >= 1024;
+}
 __host__ __device__ constexpr uint32_t short_region_bytes(uint32_t rows, uint32_t pieces)   // of one matrix: whole loads
 {
     return (rows * pieces + 63u) / 64u * 1024u;
@@ -376,14 +388,14 @@ template <int kP, int kNB>
 __global__ __launch_bounds__(kScoreThreads) void attention_scores_short_kernel(const uint16_t* q, const uint16_t* k,
                                                                                uint32_t n_rows, uint32_t tokens,
                                                                                uint32_t rows_per_task, uint32_t n_tasks,
-                                                                               uint32_t pieces, uint32_t relu, float* scores)
+                                                                               uint32_t relu, float* scores)
 {
     extern __shared__ __align__(1024) uint8_t short_lds[];
-    const uint32_t P = kP ? (uint32_t)kP : pieces;
+    constexpr uint32_t P = kP;
     const uint32_t n_waves = blockDim.x >> 6;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t half = lane >> 5, col = lane & 31u;
-    const uint32_t g_log = P % 16u == 0 ? 4u : (uint32_t)__builtin_ctz(P | 16u);   // log2 of gcd(P, 16)
+    constexpr uint32_t g_log = (uint32_t)__builtin_ctz(P | 16u);   // log2 of gcd(P, 16)
     const uint32_t region = short_region_bytes(rows_per_task, P);
     const uint32_t base = wave * short_wave_bytes(rows_per_task, P);
     uint8_t* lq = short_lds + base;
@@ -408,7 +420,7 @@ __global__ __launch_bounds__(kScoreThreads) void attention_scores_short_kernel(c
                                              (__attribute__((address_space(3))) void*)(lq + i * 1024u), 16, 0, 0);
         }
     };
-    const uint32_t steps = (P + 1u) / 2u;
+    constexpr uint32_t steps = (P + 1u) / 2u;
     // this lane's 16 bytes of step s of row 32 b + lane % 32 (past the task's rows: of its last row; nobody uses the result)
     auto operand = [&](const uint8_t* m, uint32_t b, uint32_t s) {
         const uint32_t row = min(b * 32u + col, rows_per_task - 1u);
@@ -442,15 +454,14 @@ __global__ __launch_bounds__(kScoreThreads) void attention_scores_short_kernel(c
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // every operand of this task has been read
             if (next < n_tasks) fetch(next);
         };
-        if constexpr (kP != 0 && kNB == 1) {
-            constexpr int kSteps = (kP + 1) / 2;
-            mfma_bf16x8 a[kSteps], bq[kSteps];
+        if constexpr (kNB == 1) {
+            mfma_bf16x8 a[steps], bq[steps];
 #pragma unroll
-            for (int s = 0; s < kSteps; ++s) { a[s] = operand(lk, 0, s); bq[s] = operand(lq, 0, s); }
+            for (uint32_t s = 0; s < steps; ++s) { a[s] = operand(lk, 0, s); bq[s] = operand(lq, 0, s); }
             refill();
             mfma_f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-            for (int s = 0; s < kSteps; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], bq[s], acc, 0, 0, 0);
+            for (uint32_t s = 0; s < steps; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], bq[s], acc, 0, 0, 0);
             add_up(acc, 0, sum[0]);
         } else {
             mfma_f32x16 acc[kNB][kNB];

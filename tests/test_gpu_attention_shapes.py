@@ -98,6 +98,26 @@ def test_short_groups_over_many_tasks_per_wavefront(F, dim):
         assert ((out - ref).abs() <= mass * (dim + tokens + 8) * 2.0 ** -22).all(), (groups, tokens, dim)
 
 
+def close_to_fp32(F, groups, tokens, dim, mode):
+    q, k = synth.attention_qk(groups, tokens, dim, seed=groups + dim, device="cuda")
+    out = torch.full((groups * tokens + 64,), -7.0, device="cuda")
+    F.fb4_attention_scores(q, k, mode, scores=out[:groups * tokens].view(groups, tokens))
+    assert (out[groups * tokens:] == -7.0).all()
+    p = torch.matmul(q.float(), k.float().transpose(1, 2).contiguous())
+    ref = (p.clamp_min(0) if mode else p.abs()).mean(dim=2)
+    # both sides round their sums in fp32: the bound of `reference` twice, with the products' mass from above
+    mass = (q.float().norm(dim=2) * k.float().norm(dim=2).amax(dim=1, keepdim=True))
+    assert ((out[:groups * tokens].view(groups, tokens) - ref).abs() <= mass * (dim + tokens + 8) * 2.0 ** -22).all(), (groups, tokens, dim)
+
+
+@pytest.mark.parametrize("dim", range(8, 257, 8))
+def test_short_groups_of_every_row_length(F, dim):
+    # one wavefront per task and several tasks per wavefront; up to 128 channels groups of 33 to 48 tokens on both sides of
+    # the number of groups from which one wavefront takes a group, and always of 49 and more, which four take
+    for groups, tokens in ((40, 32), (9001, 16), (1023, 48), (1024, 48), (5003, 33), (1100, 49), (1100, 64)):
+        close_to_fp32(F, groups, tokens, dim, (dim // 8 + tokens) % 2)
+
+
 def test_short_groups_keep_infinities_and_nans_in_their_group(F):
     for dim in (24, 64, 72):
         q, k = synth.attention_qk(9, 12, dim, seed=dim, device="cuda")
