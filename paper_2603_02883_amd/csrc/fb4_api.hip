@@ -519,9 +519,14 @@ int fb4_dequantize(const fb4_luts* luts, const uint8_t* codes1, const uint16_t* 
             f.salient = salient_rows;
             f.n_sal = (uint32_t)n_sal;
             f.rows = (uint32_t)rows;
+            const bool early = f.n_sal <= f.rows / kDeqEarlyShare &&
+                               n_blocks * 8 >= (uint64_t)groups * kDeqThreads * kDeqWords * kDeqEarlyHalfRounds;
             if (out_dtype == FB4_DTYPE_F32) {
                 if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
                 else hipLaunchKernelGGL((dequantize_fast_kernel<false, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
+            } else if (early) {
+                if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, false, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
+                else hipLaunchKernelGGL((dequantize_fast_kernel<false, false, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
             } else {
                 if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, false, true>), dg, db, 0, s, FB4_DEQ_ARGS);
                 else hipLaunchKernelGGL((dequantize_fast_kernel<false, false, true>), dg, db, 0, s, FB4_DEQ_ARGS);

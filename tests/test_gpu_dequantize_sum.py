@@ -1,5 +1,5 @@
-"""Decoding with a second plane: lists around the limits of the kernel's rules (when a list is requested early, when the
-first round is written ahead of the tables) and salient rows at the ends, against float64."""
+"""Decoding with a second plane: lists and sizes around the limits of the kernel's rules (when the first round is written
+ahead of the tables, how much of the list is requested with it) and salient rows at the ends, against float64."""
 
 import numpy as np
 import pytest
@@ -15,6 +15,18 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("rows,cols,n_sal", [(1, 32, 1), (7, 64, 1), (8, 64, 1), (64, 96, 8), (64, 96, 9), (600, 1152, 75), (600, 1152, 600),
                                              (20000, 320, 2048), (20000, 320, 2049), (20000, 320, 2500), (20000, 320, 2501), (65536, 32, 9000)])
 def test_dequantize_with_a_second_plane(rows, cols, n_sal, block, f32):
+    check(rows, cols, n_sal, block, f32)
+
+
+@pytest.mark.parametrize("block", [32, 16])
+@pytest.mark.parametrize("rows,cols,n_sal", [(61440, 512, 1), (61440, 512, 2048), (61440, 512, 7680), (61440, 512, 7681), (61439, 512, 2049),
+                                             (20000, 1600, 2049), (20000, 1600, 2501)])
+def test_dequantize_of_as_many_rounds_as_write_the_first_one_early(rows, cols, n_sal, block):
+    # (2.5 rounds of 768 workgroups x 512 threads x 4 words of 8 elements are 61440 x 512)
+    check(rows, cols, n_sal, block, False)
+
+
+def check(rows, cols, n_sal, block, f32):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2603_02883_amd as F
