@@ -50,12 +50,45 @@ def test_long_groups(F, tokens, mode):
         check(F, q, k, mode)
 
 
-@pytest.mark.parametrize("blocks", [1, 2, 3, 4])
-def test_long_groups_with_every_number_of_query_blocks(F, blocks):
-    # launches whose size makes the launcher take 1, 2, 3 and 4 blocks of queries per wavefront
-    groups, tokens = {1: (16, 390), 2: (8, 1500), 3: (24, 999), 4: (130, 480)}[blocks]
-    q, k = synth.attention_qk(groups, tokens, 72, seed=blocks, device="cuda")
-    check(F, q, k, 0)
+def query_blocks(groups, tokens):
+    """The launcher's choice: blocks of 32 queries per wavefront, and those of the two wavefront pairs of the last
+    workgroup of a group (0, 0 where the whole workgroups take all)."""
+    n_blk, best, best_cost = (tokens + 31) // 32, 4, 0.0
+    for b in (4, 3, 2, 1):
+        full, rest = divmod(n_blk, 2 * b)
+        units = full * (b + 0.7) + ((rest + 1) // 2 + 0.7 if rest else 0.0)
+        load = groups * units / ((b + 0.7) * 256)
+        cost = (b + 0.7) * (0.2 + 0.8 * (int(load + 0.999) if load > 1 else 1))
+        if b == 4 or cost < best_cost:
+            best, best_cost = b, cost
+    rest = n_blk % (2 * best)
+    return best, (rest + 1) // 2, rest // 2
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("groups,tokens,blocks", [(1, 97, (1, 0, 0)), (1, 65, (1, 1, 0)), (16, 390, (1, 1, 0)), (134, 97, (2, 0, 0)),
+                                                  (92, 129, (2, 1, 0)), (92, 161, (2, 1, 1)), (134, 65, (2, 2, 1)), (24, 999, (2, 0, 0)),
+                                                  (176, 161, (3, 0, 0)), (260, 97, (3, 2, 2)), (176, 129, (3, 3, 2)), (130, 480, (3, 2, 1)),
+                                                  (197, 225, (4, 0, 0)), (155, 257, (4, 1, 0)), (386, 65, (4, 2, 1)), (260, 161, (4, 3, 3)),
+                                                  (197, 193, (4, 4, 3))])
+def test_long_groups_with_every_number_of_query_blocks(F, groups, tokens, blocks, mode):
+    # whole workgroups of 1, 2, 3 and 4 blocks per wavefront and last workgroups with every number of them, in the variants
+    # with three wavefronts per SIMD (up to 72 channels) and with two
+    assert query_blocks(groups, tokens) == blocks
+    for dim in (64, 72, 96, 128):
+        q, k = synth.attention_qk(groups, tokens, dim, seed=groups + dim, device="cuda")
+        check(F, q, k, mode)
+
+
+@pytest.mark.parametrize("groups,tokens,dim", [(272, 1350, 72), (384, 1024, 128)])
+def test_long_groups_of_a_whole_clip(F, groups, tokens, dim):
+    assert query_blocks(groups, tokens)[0] == 4
+    q, k = synth.attention_qk(groups, tokens, dim, seed=dim, device="cuda")
+    got = F.fb4_attention_scores(q, k, 0)
+    torch.cuda.synchronize()
+    for g in (0, 1, groups // 2, groups - 2, groups - 1):
+        ref, bound = reference(q[g:g + 1], k[g:g + 1], 0)
+        assert ((got[g:g + 1].double().cpu() - ref).abs() <= bound).all(), g
 
 
 @pytest.mark.parametrize("dim", [24, 64, 72, 128])
