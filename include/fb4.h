@@ -281,7 +281,11 @@ int fb4_repack_mxfp8(const fb4_luts* luts, const uint8_t* codes, const uint16_t*
  * are exactly fb4_quantize of that bf16 tensor.  Rows outside the
  * range of fp32 sums (an Inf or NaN, squares beyond 2^100, var + eps below
  * 2^-100) are evaluated in double instead.  x is read as plain IEEE bf16 (a
- * row with an Inf or NaN normalizes to NaN throughout).
+ * row with an Inf or NaN normalizes to NaN throughout).  A row's sums are formed
+ * in an order that depends on cols, on the number of rows and groups in the call
+ * and on the row's place in it (the same call always gives the same results):
+ * a value next to the middle of two bf16 values may be rounded one way in a call
+ * of few rows and the other way in one of many, and its code with it.
  *   opts        FB4_SEL_LUT with 8 or 16 groups, block 32 or 16 (Sec. 4.1),
  *               FB4_FLAG_TWO_STAGE allowed; the exhaustive selector and 32 groups
  *               FB4_ERR_UNSUPPORTED

@@ -64,3 +64,71 @@ def test_layernorm(F, rows, cols):
         cr, mr = O.quantize(DEFAULT_FORMATBOOK, yb)
         assert np.array_equal(c.cpu().numpy(), cr) and np.array_equal(m.cpu().numpy().view(np.uint16), mr), (rows, cols, shift)
     luts.free()
+
+
+def layernorm_bundles(rows, cols, num_groups):
+    """The launcher's choice: (chunks per lane, rows per bundle, whether every wavefront gets one bundle at most)."""
+    nb, cu = cols // 32, torch.cuda.get_device_properties(0).multi_processor_count
+    fewest = (nb + 63) // 64
+    wavefronts = lambda b: cu * (12 if b <= 4 and not (num_groups > 8 and b >= 2) else 8)
+    if fewest <= 4 and -(-rows // (64 * fewest // nb)) <= wavefronts(fewest):
+        return fewest, min(64 * fewest // nb, rows), True
+    best, B = 0.0, fewest
+    for b in range(fewest, 5):
+        fill = (64 * b // nb) * nb / (64.0 * b) - (0.05 if b == 4 else 0.0)
+        if fill > best + 1e-9:
+            best, B = fill, b
+    return B, min(64 * B // nb, rows), -(-rows // (64 * B // nb)) <= wavefronts(B)
+
+
+@pytest.mark.parametrize("block,g", [(32, 8), (16, 8), (32, 16), (16, 16)])
+@pytest.mark.parametrize("rows,cols,chunks,rows_per_bundle", [(6501, 1024, 1, 2), (3300, 2048, 1, 1), (3301, 4096, 2, 1), (16001, 1152, 3, 5),
+                                                              (6501, 3072, 3, 2), (3100, 6176, 4, 1), (2100, 9216, 5, 1), (2101, 12288, 6, 1)])
+def test_layernorm_of_more_bundles_than_wavefronts(F, rows, cols, chunks, rows_per_bundle, block, g):
+    assert layernorm_bundles(rows, cols, g) == (chunks, rows_per_bundle, False)
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    x = synth.vdit_activation(rows=rows, cols=cols, seed=cols, device="cuda")
+    gamma, beta = synth.layernorm_affine(cols, seed=cols)
+    y = torch.empty_like(x)
+    o = F.opts(block=block, num_groups=g)
+    c, m = F.fb4_layernorm_quantize(luts, o, x, torch.from_numpy(gamma).cuda(), torch.from_numpy(beta).cuda(), 1e-6, y_out=y)
+    c0, m0 = F.fb4_quantize(luts, o, y)                       # (against the oracle in tests of its own)
+    torch.cuda.synchronize()
+    assert torch.equal(c, c0) and torch.equal(m, m0)
+    assert_layernorm(x, y, gamma, beta)
+    luts.free()
+
+
+def assert_layernorm(x, y, gamma, beta):
+    """y is the LayerNorm of x within one bf16 step, or within 2^-19 (|gamma| (|t| + |mean| rstd + 1) + |beta|) where the
+    terms cancel, t = (x - mean) rstd."""
+    xd, g, b = x.double(), torch.from_numpy(gamma).cuda().double(), torch.from_numpy(beta).cuda().double()
+    mean = xd.mean(dim=1, keepdim=True)
+    rstd = ((xd - mean).square().mean(dim=1, keepdim=True) + 1e-6).rsqrt()
+    t = (xd - mean) * rstd
+    ref = t * g + b
+    step = torch.ldexp(torch.ones_like(ref), torch.frexp(ref.abs().clamp_min(2.0 ** -126))[1] - 8)   # (8 significant bits)
+    err = (y.double() - ref).abs()
+    assert (err <= torch.maximum(step, 2.0 ** -19 * (g.abs() * (t.abs() + mean.abs() * rstd + 1) + b.abs()) + step / 2)).all()
+    return (err <= step / 2).double().mean().item()
+
+
+@pytest.mark.parametrize("cols", [1152, 3072])
+def test_layernorm_of_the_same_rows_in_a_short_and_a_long_call(F, cols):
+    # how many chunks a lane takes, and with it the order of a row's sums, goes with the number of rows: a value next to the
+    # middle of two bf16 values may be rounded to either
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    x = synth.vdit_activation(rows=16384, cols=cols, seed=3, device="cuda")
+    gamma, beta = (torch.from_numpy(a).cuda() for a in synth.layernorm_affine(cols))
+    ys = []
+    for rows in (16384, 300):
+        y = torch.empty_like(x[:rows])
+        F.fb4_layernorm_quantize(luts, F.opts(), x[:rows], gamma, beta, 1e-6, y_out=y)
+        ys.append(y[:300].float())
+    torch.cuda.synchronize()
+    assert layernorm_bundles(300, cols, 8)[0] != layernorm_bundles(16384, cols, 8)[0]
+    # one bf16 step apart, or (gamma t and beta cancel) within 2^-18 of terms of a few units
+    off = (ys[0] - ys[1]).abs()
+    assert (off <= torch.maximum(ys[0].abs() * 2.0 ** -7, torch.full_like(off, 2.0 ** -15))).all()
+    assert (off != 0).float().mean() < 1e-4
+    luts.free()
