@@ -11,11 +11,14 @@ using namespace fb4;
 namespace {
 
 // Blocks of 32 queries per wavefront of the long-group kernel.  A workgroup's time goes with b + 0.7 (0.7: what a step
-// costs whatever the number of blocks; 24 groups x 16384 tokens x 128 channels take 1157 / 1255 / 1337 / 1657 us with
+// costs whatever the number of blocks; 24 groups x 16384 tokens x 128 channels take 1124 / 1215 / 1261 / 1555 us with
 // 4 / 3 / 2 / 1), m workgroups on a compute unit take about 0.2 + 0.8 m times as long as one, and the last workgroup
 // of a group has only the blocks that are left.  So long launches take 4 and short ones fewer, to reach more
-// compute units: 16 x 400 x 72 channels 4.0 us with 1 and 7.1 with 4, 8 x 3000 x 72 16 and 27, 24 x 4000 x 64 45
-// with 3 and 50 with 4; 272 x 1350 x 64 62 with 4 and 65 with 3.
+// compute units.  us with 1 / 2 / 3 / 4, the choice starred: 16 x 400 x 72 4.4* / 5.4 / 6.4 / 7.7, 8 x 3000 x 72 16.6 / 17.8* /
+// 22.4 / 27.6, 130 x 480 x 72 9.5 / 8.7 / 8.9* / 10.5, 24 x 4000 x 64 52.8 / 44.7 / 44.9* / 51.0, 272 x 1350 x 72 86.4 / 69.8 /
+// 66.9 / 66.1*, 384 x 1024 x 128 120.8 / 96.7 / 90.5 / 84.5*.  (256 compute units as on this card: the choice decides
+// speed only.  That rows of up to 72 channels run three workgroups per compute unit and longer ones two is left out: the
+// figures above come from both.)
 uint32_t dma_blocks_per_wave(int64_t groups, uint32_t n_blk)
 {
     constexpr double kCus = 256.0, kStep = 0.7;
@@ -87,7 +90,8 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
             const uint32_t n_rows = (uint32_t)(n_groups * tokens);
             const uint32_t n_tasks = (n_rows + rows_per_task - 1) / rows_per_task;
             if (n_tasks <= 256u) waves = 1;   // (a compute unit each: 64 groups x 32 x 112 2.90 us with four, 2.66 so)
-            // every wavefront with the same number of tasks (6000 x 48 x 72: 16.3 us; with the last round ragged 17.5)
+            // every wavefront with the same number of tasks (6000 x 48 x 72: 16.3 us; with the last round ragged 17.5; for
+            // 256 compute units, which decides speed only)
             const uint32_t rounds = (n_tasks + 256u * most - 1) / (256u * most);
             const dim3 sgrid((n_tasks + rounds * waves - 1) / (rounds * waves));
 #define FB4_SHORT_CASE(p, n) case p: hipLaunchKernelGGL((attention_scores_short_kernel<p, n>), sgrid, dim3(64 * waves), waves * per_wave, s, qs, ks, n_rows, (uint32_t)tokens, rows_per_task, n_tasks, (uint32_t)mode, out); break;

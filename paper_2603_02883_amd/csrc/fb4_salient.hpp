@@ -158,15 +158,15 @@ __global__ __launch_bounds__(kScoreThreads) void attention_scores_kernel(const u
 // w % 2 and walks the keys of half w / 2 of the group, 64 per barrier, from that half's own double-buffered LDS
 // region; the two halves' sums meet in LDS at the end (always half 0 + half 1).  Queries that do not fill a workgroup
 // are taken by one short workgroup per group; those are the last of the launch, so that they fill up its end.
-// Measured (us; before: every row through registers into padded LDS rows, channels padded to 32, two MFMAs per
-// operand read): 272 groups x 1350 tokens x 72 channels 132 -> 70.5 (71.4 GFLOP: 1.0 PFLOP/s), 64 channels 91 -> 62,
-// 300 x 1000 x 96 81 -> 60, 300 x 1000 x 40 41 -> 28.6; 384 x 1024 x 128, which had a kernel of this kind, 95 -> 93.
+// Measured (us in a graph; before: every row through registers into padded LDS rows, channels padded to 32, two MFMAs per
+// operand read): 272 groups x 1350 tokens x 72 channels 120 -> 66 (71.4 GFLOP: 1.07 PFLOP/s), 64 channels 81 -> 58,
+// 300 x 1000 x 96 74 -> 53, 300 x 1000 x 40 43 -> 28; 384 x 1024 x 128, which had a kernel of this kind, 88 -> 86.
 constexpr int kDmaQB = 4;                  // blocks of 32 queries per wavefront at most
 constexpr int kDmaKeys = 64;               // per barrier and half
 constexpr int kDmaMaxPieces = 16;
 // Wavefronts per SIMD: three where 168 registers hold the kernel (up to 72 channels), else two.  With three the sums
 // of 32 keys are kept from being moved among the next 32 keys' MFMAs, which would need a second set of accumulators
-// (272 groups x 1350 tokens x 72 channels: 76.6 us with two, 70.5 with three; 64 channels 67 and 62).
+// (272 groups x 1350 tokens x 72 channels, inputs changing: 76.6 us with two, 70.5 with three; 64 channels 67 and 62).
 constexpr int dma_waves(int pieces) { return pieces <= 9 ? 3 : 2; }
 
 template <int kP, bool kRelu>
