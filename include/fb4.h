@@ -408,6 +408,7 @@ int fb4_select_salient_tokens(const float* scores, int64_t frames, int heads, in
  *   anchor_group   device, int32 [frames * tokens]: the group on anchor rows,
  *                  -1 elsewhere -- the anchor_group argument of
  *                  fb4_seda_profile (whose n_groups is the number of tiles)
+ *                  (the same buffer as token_group: it then holds token_group)
  *   window_scores  device, float [n_anchors][window_t * window * window] or
  *                  NULL: the scores that were compared, frame offset major (NaN
  *                  outside the clip)
