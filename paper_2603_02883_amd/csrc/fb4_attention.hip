@@ -16,21 +16,22 @@ namespace {
 // of a group has only the blocks that are left.  So long launches take 4 and short ones fewer, to reach more
 // compute units.  us with 1 / 2 / 3 / 4, the choice starred: 16 x 400 x 72 4.4* / 5.4 / 6.4 / 7.7, 8 x 3000 x 72 16.6 / 17.8* /
 // 22.4 / 27.6, 130 x 480 x 72 9.5 / 8.7 / 8.9* / 10.5, 24 x 4000 x 64 52.8 / 44.7 / 44.9* / 51.0, 272 x 1350 x 72 86.4 / 69.8 /
-// 66.9 / 66.1*, 384 x 1024 x 128 120.8 / 96.7 / 90.5 / 84.5*.  (256 compute units as on this card: the choice decides
+// 66.9 / 66.1*, 384 x 1024 x 128 120.8 / 96.7 / 90.5 / 84.5*; with up to six (`most`, 80 to 96 channels): 1000 x 300 x 96,
+// which takes 5, 24.3 against 29.4 with 4.  (256 compute units as on this card: the choice decides
 // speed only.  That rows of up to 72 channels run three workgroups per compute unit and longer ones two is left out: the
 // figures above come from both.)
-uint32_t dma_blocks_per_wave(int64_t groups, uint32_t n_blk)
+uint32_t dma_blocks_per_wave(int64_t groups, uint32_t n_blk, uint32_t most)
 {
     constexpr double kCus = 256.0, kStep = 0.7;
-    uint32_t best = kDmaQB;
+    uint32_t best = most;
     double best_cost = 0.0;
-    for (uint32_t b = kDmaQB; b >= 1; --b) {
+    for (uint32_t b = most; b >= 1; --b) {
         const uint32_t full = n_blk / (2 * b), rest = n_blk - full * 2 * b;
         const double units = full * (b + kStep) + (rest ? (rest + 1) / 2 + kStep : 0.0);
         const double load = (double)groups * units / ((b + kStep) * kCus);
         const double m = load > 1.0 ? (double)(int64_t)(load + 0.999) : 1.0;
         const double cost = (b + kStep) * (0.2 + 0.8 * m);
-        if (b == (uint32_t)kDmaQB || cost < best_cost) { best_cost = cost; best = b; }
+        if (b == most || cost < best_cost) { best_cost = cost; best = b; }
     }
     return best;
 }
@@ -122,7 +123,7 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
     }
     if (dim <= 8 * kDmaMaxPieces) {   // (longer rows: too many registers for four blocks of queries)
         const uint32_t n_blk = (uint32_t)((tokens + 31) / 32);
-        uint32_t bpw = dma_blocks_per_wave(groups, n_blk);
+        const uint32_t bpw = dma_blocks_per_wave(groups, n_blk, (uint32_t)dma_max_blocks((int)(dim / 8)));
         const uint32_t n_full = n_blk / (2 * bpw), n_wg = n_full + (n_blk % (2 * bpw) ? 1 : 0);
         const dim3 dgrid((unsigned)(groups * n_wg));
 #define FB4_DMA_ARGS static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), (uint32_t)groups, (uint32_t)tokens, n_full, bpw, scores

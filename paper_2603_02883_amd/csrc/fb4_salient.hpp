@@ -146,8 +146,8 @@ __global__ __launch_bounds__(kScoreThreads) void attention_scores_kernel(const u
     }
 }
 
-// Long groups of up to 128 channels: four blocks of 32 queries per wavefront, so that one 16-byte operand read from
-// LDS feeds four MFMAs.  Channels are taken in steps of 16, not padded to 32: 72 channels are 5 steps.
+// Long groups of up to 128 channels: four blocks of 32 queries per wavefront (80 to 96 channels: six), so that one 16-byte
+// operand read from LDS feeds as many MFMAs.  Channels are taken in steps of 16, not padded to 32: 72 channels are 5 steps.
 // kP: 16-byte pieces per row (dim / 8).  Queries as B operands (16 registers per step) and four accumulator blocks
 // leave no room to stage key blocks through registers: `global_load_lds_dwordx4` writes a wavefront's 64 x 16 bytes
 // straight into LDS.  Those 1 KiB land contiguously, so rows cannot be padded; instead piece p of key row r sits at
@@ -161,13 +161,20 @@ __global__ __launch_bounds__(kScoreThreads) void attention_scores_kernel(const u
 // Measured (us in a graph; before: every row through registers into padded LDS rows, channels padded to 32, two MFMAs per
 // operand read): 272 groups x 1350 tokens x 72 channels 120 -> 66 (71.4 GFLOP: 1.07 PFLOP/s), 64 channels 81 -> 58,
 // 300 x 1000 x 96 74 -> 53, 300 x 1000 x 40 43 -> 28; 384 x 1024 x 128, which had a kernel of this kind, 88 -> 86.
-constexpr int kDmaQB = 4;                  // blocks of 32 queries per wavefront at most
+// Then the sums of a block of queries moved beside the next block's MFMAs, and up to six blocks for 80 to 96 channels: 16 x
+// 2000 x 72 12.6 -> 11.7, 8 x 8000 x 64 61.5 -> 55.4, 1000 x 300 x 96 30.3 -> 24.3, 12 x 16000 x 96 436 -> 403; 272 x 1350 x
+// 72 67.4 -> 66.7, 384 x 1024 x 128 83.5 -> 82.5: full launches on ordinary data are held by the power limit, not by the
+// schedule (2176 x 1350 x 72 510 us, the same on zeros 385).
+constexpr int dma_max_blocks(int pieces) { return pieces >= 10 && pieces <= 12 ? 6 : 4; }   // of 32 queries per wavefront
 constexpr int kDmaKeys = 64;               // per barrier and half
 constexpr int kDmaMaxPieces = 16;
-// Wavefronts per SIMD: three where 168 registers hold the kernel (up to 72 channels), else two.  With three the sums
-// of 32 keys are kept from being moved among the next 32 keys' MFMAs, which would need a second set of accumulators
-// (272 groups x 1350 tokens x 72 channels, inputs changing: 76.6 us with two, 70.5 with three; 64 channels 67 and 62).
+// Wavefronts per SIMD: three where 168 registers hold the kernel (up to 72 channels; 272 groups x 1350 tokens x 72, inputs
+// changing: 76.6 us with two when all sums followed all MFMAs, 70.5 with three), else two, with up to six blocks of
+// queries for 80 to 96 channels.
 constexpr int dma_waves(int pieces) { return pieces <= 9 ? 3 : 2; }
+// An operand of the next 32 keys is read right behind the last MFMA that uses the present one; 65 to 72 channels on three
+// wavefronts per SIMD have no registers for that (14 would spill): theirs are read between two runs of 32 keys.
+constexpr bool dma_reads_early(int pieces) { return pieces != 9; }
 
 template <int kP, bool kRelu>
 __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(dma_waves(kP), dma_waves(kP))))
@@ -264,7 +271,7 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
         const uint32_t at = row_at + ((((uint32_t)(2 * s) + half) ^ swz) << 4) + kk * 32u * kRowBytes;
         return (kP % 2 && s == kSteps - 1 && half) ? 2u * kHalfBytes : at;
     };
-    float* meet = reinterpret_cast<float*>(lds_a);               // [query set][32 * kDmaQB]
+    float* meet = reinterpret_cast<float*>(lds_a);               // [query set][32 * dma_max_blocks(kP)]
 
     auto run = [&](auto blocks) {
         constexpr int NB = decltype(blocks)::value;
@@ -283,30 +290,44 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
         float sum[NB > 0 ? NB : 1];
 #pragma unroll
         for (int b = 0; b < NB; ++b) sum[b] = 0.0f;
+        // Blocks of queries one after the other: the sums of one block's products (vector ALU) are formed while the next
+        // block's MFMAs run, and two blocks' accumulators are enough.  `done`: the block whose sums are still to be formed
+        // (zeros at first, which add nothing).
+        mfma_f32x16 done = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        auto add_up = [&](float& s) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s += kRelu ? fmaxf(done[r], 0.0f) : fabsf(done[r]);
+        };
         auto compute = [&](const uint8_t* buffer, uint32_t step) {
             if (NB == 0 || step >= my_steps) return;
-            // the operand of the next step is read while this step's MFMAs run
-            uint4 a_next = *reinterpret_cast<const uint4*>(buffer + operand(0, 0));
+            constexpr bool kEarly = dma_reads_early(kP);
+            mfma_bf16x8 a[kSteps];   // operands of 32 keys
+            auto read = [&](int s, int kk) { a[s] = __builtin_bit_cast(mfma_bf16x8, *reinterpret_cast<const uint4*>(buffer + operand(s, kk))); };
 #pragma unroll
             for (int kk = 0; kk < kDmaKeys / 32; ++kk) {
-                mfma_f32x16 acc[NB > 0 ? NB : 1];
+                if (!kEarly || kk == 0) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) acc[b] = mfma_f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < kSteps; ++s) {
-                    const uint4 a = a_next;
-                    const int ns = (s + 1) % kSteps, nk = kk + (s + 1) / kSteps;
-                    if (nk < kDmaKeys / 32) a_next = *reinterpret_cast<const uint4*>(buffer + operand(ns, nk));
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mfma_bf16x8, a), qf[b][s], acc[b], 0, 0, 0);
+                    for (int s = 0; s < kSteps; ++s) read(s, kk);
                 }
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
+                    const bool last = kEarly && b == NB - 1 && kk + 1 < kDmaKeys / 32;   // (an operand's last use with these keys)
+                    mfma_f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) sum[b] += kRelu ? fmaxf(acc[b][r], 0.0f) : fabsf(acc[b][r]);
+                    for (int s = 0; s < kSteps; ++s) {
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], qf[b][s], acc, 0, 0, 0);
+                        if (last) read(s, kk + 1);
+                    }
+                    add_up(sum[(b + NB - 1) % (NB > 0 ? NB : 1)]);
+                    done = acc;
+#pragma unroll
+                    for (int s = 0; s < kSteps; ++s) {   // the order: MFMA, operand read, a share of the sums
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        if (last) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        if (s > 0 || kSteps == 1) __builtin_amdgcn_sched_group_barrier(0x002, (16 + kSteps - 1) / kSteps + 1, 0);
+                    }
+                    if (kEarly) __builtin_amdgcn_sched_barrier(0);
                 }
-                if (dma_waves(kP) > 2) __builtin_amdgcn_sched_barrier(0);
             }
         };
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the first step's keys are in LDS
@@ -323,19 +344,20 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
                 __syncthreads();
             }
         }
+        if (NB > 0) add_up(sum[NB > 0 ? NB - 1 : 0]);
         // ---- the two key halves meet: half 1 through LDS, then half 0 + half 1
 #pragma unroll
         for (int b = 0; b < NB; ++b) sum[b] += __shfl_xor(sum[b], 32);   // the two half-wavefronts hold different keys
         if (kh == 1 && half == 0) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) meet[qset * (32u * kDmaQB) + 32u * b + col] = sum[b];
+            for (int b = 0; b < NB; ++b) meet[qset * (32u * dma_max_blocks(kP)) + 32u * b + col] = sum[b];
         }
         __syncthreads();
         if (kh == 0 && half == 0) {
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const uint32_t qi = (first + b) * 32u + col;
-                if (qi < tokens) scores[(size_t)g * tokens + qi] = (sum[b] + meet[qset * (32u * kDmaQB) + 32u * b + col]) / (float)tokens;
+                if (qi < tokens) scores[(size_t)g * tokens + qi] = (sum[b] + meet[qset * (32u * dma_max_blocks(kP)) + 32u * b + col]) / (float)tokens;
             }
         }
     };
@@ -349,6 +371,8 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
     case 1: run(std::integral_constant<int, 1>{}); break;
     case 2: run(std::integral_constant<int, 2>{}); break;
     case 3: run(std::integral_constant<int, 3>{}); break;
+    case 5: if constexpr (dma_max_blocks(kP) > 4) run(std::integral_constant<int, 5>{}); break;
+    case 6: if constexpr (dma_max_blocks(kP) > 4) run(std::integral_constant<int, 6>{}); break;
     default: run(std::integral_constant<int, 4>{}); break;
     }
 }
