@@ -84,30 +84,31 @@ __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b)
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
                                                                   __builtin_bit_cast(u16x2, b)));
 }
-__device__ __forceinline__ uint32_t pk_sub(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b));
-}
-// max(a - b, 0) in both halves
-__device__ __forceinline__ uint32_t pk_sub_sat(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, a),
-                                                                      __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ uint32_t pk_shl(uint32_t a, uint32_t n)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) << __builtin_bit_cast(u16x2, n));
-}
-__device__ __forceinline__ uint32_t pk_shr(uint32_t v, uint32_t s)   // per half: v >> s, s <= 15
-{
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, v) >> __builtin_bit_cast(u16x2, s));
-}
 __device__ __forceinline__ uint32_t halves_max(uint32_t v) { return max(v & 0xFFFFu, v >> 16); }
 __device__ __forceinline__ uint32_t halves_min(uint32_t v) { return min(v & 0xFFFFu, v >> 16); }
 // a.lo*b.lo + a.hi*b.hi + c
 __device__ __forceinline__ uint32_t dot2_u16(uint32_t a, uint32_t b, uint32_t c)
 {
     return __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b), c, false);
+}
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_add_f16(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, a) + __builtin_bit_cast(f16x2, b));
+}
+__device__ __forceinline__ uint32_t pk_sub_f16(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, a) - __builtin_bit_cast(f16x2, b));
+}
+__device__ __forceinline__ uint32_t pk_fma_f16(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b),
+                                                                  __builtin_bit_cast(f16x2, c)));
+}
+// per half: a * k + c mod 2^16 (one instruction if k is no power of two to the optimizer: sgpr_const)
+__device__ __forceinline__ uint32_t pk_mad_u16(uint32_t a, uint32_t k, uint32_t c)
+{
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) * __builtin_bit_cast(u16x2, k) + __builtin_bit_cast(u16x2, c)));
 }
 // A constant the optimizer cannot fold back into an instruction literal: keeps
 // three-operand instructions encodable with the constant in a register.
@@ -309,25 +310,46 @@ struct MatrixConsts {
     i32x4 wq[4];          // online selector with 32 groups: this lane's pieces of the (negated) Qerror matrix
 };
 
+// A bin b is held as the 16-bit pattern kBinBias + b (the fp16 number 1024 + b: see compute_tile); every table address
+// that is formed from one takes the bias off with its constant part, modulo 2^32.
+constexpr uint32_t kBinBias = 0x6400u;
+
 struct TileConsts {
-    uint32_t k7f, k80, kpair, row_base;
-    uint32_t kdid[16];   // DID pairs of the 16 key registers: (4i, 4i+2) and (4i+1, 4i+3)
+    uint32_t k8, khalf;  // both halves: 8; the fp16 number 1023.5
+    uint32_t k1001, k128, k1024;   // exhaustive selector: the fp16 numbers 1 + 2^-10, 128 and 1024
+    uint32_t kpair, row_base;
+    uint32_t sel_e, sel_o;   // byte selectors of the keys of dialects (4i, 4i+2) and (4i+1, 4i+3)
+    uint32_t kdid4[8];       // 8 groups: DIDs 4i .. 4i+3, a byte each
+    uint32_t kdid[16];       // 16 groups: DID pairs of the 16 key registers, (4i, 4i+2) and (4i+1, 4i+3)
     uint32_t gm_off;     // exhaustive selector: LDS offset of its table
     MatrixConsts mx;     // only set by a kernel that runs the exhaustive selector on the matrix cores
 };
 
+// G: the number of groups the kernel runs with
+template <int G>
 __device__ __forceinline__ TileConsts make_tile_consts(uint32_t lane, uint32_t gm_off)
 {
     TileConsts K;
     K.gm_off = gm_off;
-    K.row_base = kLdsRows + (lane & (kRowCopies - 1u)) * 16u;
-    K.k7f = sgpr_const(0x007F007Fu);
-    K.k80 = vgpr_const(0x00800080u);
+    K.row_base = kLdsRows + (lane & (kRowCopies - 1u)) * 16u - kBinBias * (32u * kRowCopies);
+    K.k8 = sgpr_const(0x00080008u);
+    K.khalf = sgpr_const(0x63FF63FFu);
     K.kpair = sgpr_const(32u | (1024u << 16));   // lo bin * 32 + hi bin * 1024
+    if (G == 0) {   // (two constants of one instruction: one of them in a vector register)
+        K.k1001 = vgpr_const(0x3C013C01u);
+        K.k128 = vgpr_const(0x58005800u);
+        K.k1024 = sgpr_const(0x64006400u);
+    } else if (G == 8) {
+        K.sel_e = vgpr_const(0x06020400u);
+        K.sel_o = vgpr_const(0x07030501u);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        K.kdid[2 * i] = sgpr_const((4u * i) | ((4u * i + 2u) << 16));
-        K.kdid[2 * i + 1] = sgpr_const((4u * i + 1u) | ((4u * i + 3u) << 16));
+        for (int i = 0; i < 8; ++i) K.kdid4[i] = sgpr_const(0x03020100u + 0x04040404u * i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            K.kdid[2 * i] = sgpr_const((4u * i) | ((4u * i + 2u) << 16));
+            K.kdid[2 * i + 1] = sgpr_const((4u * i + 1u) | ((4u * i + 3u) << 16));
+        }
     }
     return K;
 }
@@ -335,10 +357,11 @@ __device__ __forceinline__ TileConsts make_tile_consts(uint32_t lane, uint32_t g
 // Sec. 3.2 online selection for one block from the bins of its R group maxima: sum the Qerror rows, drop the
 // excluded candidates, argmin with the lowest DID on ties.  Rows hold one byte per dialect; eight of them
 // (8 x 31 = 248) still fit the byte, so rows are summed eight at a time and widened to 16 bits in between.
-// excl_a: LDS offset of this block's SeDA exclusion row (kSeda only).
+// gbin: with kBinBias.  excl_a: LDS offset of this block's SeDA exclusion row (kSeda only); range_row: of the row of its
+// range (kTwoStage only: the first stage keeps the dialects whose top magnitude is the integer part of the block maximum).
 template <int R, bool kTwoStage, bool kSeda>
 __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], const uint8_t* lds,
-                                                    const TileConsts& K, uint32_t excl_a)
+                                                    const TileConsts& K, uint32_t excl_a, uint32_t range_row)
 {
     static_assert(R % 8 == 0, "rows are summed eight at a time");
     uint32_t ev[8], od[8];   // 16-bit sums of dialects (4i, 4i+2) and (4i+1, 4i+3); R == 8 keeps bytes in ev
@@ -350,13 +373,8 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
         xa1 = *reinterpret_cast<const uint4*>(lds + excl_a + 16);
     }
     if (kTwoStage) {
-        // first stage: keep the dialects whose top magnitude is the integer part of the block maximum
-        uint32_t binmax = 0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) binmax = max(binmax, gbin[r]);
-        const uint32_t roff = kLdsRange + (min(max(binmax >> 1, 8u), 15u) - 8u) * 32u;
-        xr0 = *reinterpret_cast<const uint4*>(lds + roff);
-        xr1 = *reinterpret_cast<const uint4*>(lds + roff + 16);
+        xr0 = *reinterpret_cast<const uint4*>(lds + range_row);
+        xr1 = *reinterpret_cast<const uint4*>(lds + range_row + 16);
     }
 #pragma unroll
     for (int c = 0; c < R / 8; ++c) {
@@ -387,44 +405,58 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
             }
         }
     }
-    uint32_t ea[8] = {xa0.x, xa0.y, xa0.z, xa0.w, xa1.x, xa1.y, xa1.z, xa1.w};
-    if (kTwoStage) {
-        const uint32_t eb2[8] = {ea[0] | xr0.x, ea[1] | xr0.y, ea[2] | xr0.z, ea[3] | xr0.w,
-                                 ea[4] | xr1.x, ea[5] | xr1.y, ea[6] | xr1.z, ea[7] | xr1.w};
-        // ... unless that leaves nothing (possible only together with a SeDA list)
-        const bool none = kSeda && ((eb2[0] & eb2[1] & eb2[2] & eb2[3] & eb2[4] & eb2[5] & eb2[6] & eb2[7]) == 0xFFFFFFFFu);
+    const uint32_t ea[8] = {xa0.x, xa0.y, xa0.z, xa0.w, xa1.x, xa1.y, xa1.z, xa1.w};
+    const uint32_t er[8] = {xr0.x, xr0.y, xr0.z, xr0.w, xr1.x, xr1.y, xr1.z, xr1.w};
+    // the range applies unless that leaves nothing (possible only together with a SeDA list)
+    bool none = false;
+    if (kSeda && kTwoStage) {
+        uint32_t all = ea[0] | er[0];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ea[i] = none ? ea[i] : eb2[i];
+        for (int i = 1; i < 8; ++i) all &= ea[i] | er[i];
+        none = all == 0xFFFFFFFFu;
     }
-    // ---- argmin with lowest DID on ties: 16-bit keys (sum << 5 | DID), 32 of them in 16 registers.  An
-    // excluded dialect gets a key no real sum reaches.
+    // ---- argmin with lowest DID on ties: 16-bit keys, 32 of them in 16 registers; an excluded dialect gets a key that no
+    // real sum reaches.  8 groups: sum << 8 | DID, a byte each (0xFF > 248 >= any real sum), put together by one byte
+    // permutation per two keys; more: sum << 5 | DID.
     uint32_t best = 0xFFFFFFFFu;
+    if (R == 8) {
+        uint32_t a[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        uint32_t e, o;
-        if (R == 8) {
-            const uint32_t a = (kSeda || kTwoStage) ? (ev[i] | ea[i]) : ev[i];   // 0xFF > 248 >= any real sum
-            e = a & 0x00FF00FFu;                                  // dialects 4i, 4i+2
-            o = __builtin_amdgcn_perm(0u, a, 0x0C030C01u);        // dialects 4i+1, 4i+3
-        } else {
-            e = ev[i];
-            o = od[i];
+        for (int i = 0; i < 8; ++i) {
+            a[i] = ev[i];
+            if (kSeda) a[i] |= ea[i];
+            if (kTwoStage) a[i] |= er[i];
         }
-        uint32_t ke = (e << 5) | K.kdid[2 * i];
-        uint32_t ko = (o << 5) | K.kdid[2 * i + 1];
-        if (R != 8 && (kSeda || kTwoStage)) {
-            const uint32_t xe = ea[i] & 0x00FF00FFu;
-            const uint32_t xo = __builtin_amdgcn_perm(0u, ea[i], 0x0C030C01u);
-            ke |= xe | (xe << 8);                                 // 0xFFFF > (992 << 5 | 31)
-            ko |= xo | (xo << 8);
+        if (kSeda && kTwoStage && __builtin_amdgcn_ballot_w64(none) != 0) {   // (rare)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a[i] = none ? (ev[i] | ea[i]) : a[i];
         }
-        best = pk_min(best, pk_min(ke, ko));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t ke = __builtin_amdgcn_perm(a[i], K.kdid4[i], K.sel_e);   // dialects 4i, 4i+2
+            const uint32_t ko = __builtin_amdgcn_perm(a[i], K.kdid4[i], K.sel_o);   // dialects 4i+1, 4i+3
+            best = pk_min(best, pk_min(ke, ko));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            uint32_t ke = (ev[i] << 5) | K.kdid[2 * i];
+            uint32_t ko = (od[i] << 5) | K.kdid[2 * i + 1];
+            if (kSeda || kTwoStage) {
+                const uint32_t x = kTwoStage ? (none ? ea[i] : (ea[i] | er[i])) : ea[i];
+                const uint32_t xe = x & 0x00FF00FFu;
+                const uint32_t xo = __builtin_amdgcn_perm(0u, x, 0x0C030C01u);
+                ke |= xe | (xe << 8);                                 // 0xFFFF > (992 << 5 | 31)
+                ko |= xo | (xo << 8);
+            }
+            best = pk_min(best, pk_min(ke, ko));
+        }
     }
     return halves_min(best) & 31u;
 }
 
 // Exhaustive selection (Sec. 3.2, first paragraph) for the blocks of a wavefront, whose elements sit in registers
-// b2[first .. first + RB) (bins, two per register) and x2 (256 * xhat, two per register).  With X = 256 * xhat =
+// b2[first .. first + RB) (bins, two per register) and f2 (fractions), both biased by kBinBias.  With X = 256 * xhat =
 // 128 * bin + frac and m the nearest magnitude of a dialect, (X - 256 m)^2 = X^2 - 512 Z with
 // Z = 128 * m * (bin - m) + frac * m: the smallest error is the largest Z_d = sum over the elements of
 // 128 * gain[bin][d] + frac * mag[bin][d] (< 2^20, every quantity an exact integer).
@@ -458,20 +490,19 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
 //     not, and if the range excludes all candidates the best of them still wins, which is the rule
 //     ("unless it leaves no candidate").  |key| < 2^25 before that.
 template <int RB, bool kTwoStage, bool kSeda>
-__device__ __forceinline__ uint32_t select_sse_matrix(const uint32_t (&b2)[16], const uint32_t (&x2)[16], int first,
+__device__ __forceinline__ uint32_t select_sse_matrix(const uint32_t (&b2)[16], const uint32_t (&f2)[16], int first,
                                                       uint8_t* lds, const MatrixConsts& M, uint32_t lane,
                                                       uint32_t range_row, uint32_t seda_row)
 {
     const uint32_t k_lo = sgpr_const(256u), k_hi = sgpr_const(256u << 16);   // 256 * bin from either half
     const uint32_t one_lo = sgpr_const(1u), one_hi = sgpr_const(1u << 16);   // the fraction of either half
-    const uint32_t k_cnt = vgpr_const(0x01000000u);
+    const uint32_t k_cnt = vgpr_const(0x01000000u - kBinBias);
 #pragma unroll
     for (int k = first; k < first + RB; ++k) {
-        const uint32_t f2 = x2[k] & 0x007F007Fu;
-        uint32_t* a0 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_lo, M.row));
-        uint32_t* a1 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_hi, M.row));
-        __hip_atomic_fetch_add(a0, dot2_u16(f2, one_lo, k_cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        __hip_atomic_fetch_add(a1, dot2_u16(f2, one_hi, k_cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        uint32_t* a0 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_lo, M.row - 256u * kBinBias));
+        uint32_t* a1 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_hi, M.row - 256u * kBinBias));
+        __hip_atomic_fetch_add(a0, dot2_u16(f2[k], one_lo, k_cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        __hip_atomic_fetch_add(a1, dot2_u16(f2[k], one_hi, k_cnt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -591,8 +622,8 @@ __device__ __forceinline__ uint32_t select_lut32_matrix(const uint32_t (&b2)[16]
     const uint32_t one = vgpr_const(1u);
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        uint32_t* a0 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_lo, M.row));
-        uint32_t* a1 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_hi, M.row));
+        uint32_t* a0 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_lo, M.row - 256u * kBinBias));
+        uint32_t* a1 = reinterpret_cast<uint32_t*>(lds + dot2_u16(b2[k], k_hi, M.row - 256u * kBinBias));
         __hip_atomic_fetch_add(a0, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         __hip_atomic_fetch_add(a1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
@@ -757,32 +788,54 @@ __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint
         }
     } else {
         uint32_t b2[16];
-        uint32_t x2[16];   // exhaustive selector: 256 * xhat
+        uint32_t f2[16];   // exhaustive selector: fractions
         uint32_t did[NB];
         meta = 0;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            // ---- shared exponent (Sec. 3.1) and bins (Sec. 3.2), two elements per instruction
+            // ---- shared exponent (Sec. 3.1) and bins (Sec. 3.2), two elements per instruction.  v = 2 * xhat in [0, 32) as
+            // an fp16 number: exponent field ef - ec + 19, the mantissa's seven bits on top of ten; its integer part is the
+            // bin.  v + 1023.5 rounds to 1024 + floor(v) wherever v is no integer and above 0.25, so half a bf16 step is added
+            // first (which reaches no further integer), and what is below 0.5, bin 0 anyway, is lifted to the binade of 0.5.
+            // Three instructions a register where shifting the mantissa by the exponents' difference took five.  The kernels
+            // that the vector ALU bounds (us, with this and the byte permutations below): block 16 with range filter and lists,
+            // 13000 x 1152, 12.4 -> 11.6; LayerNorm 16384 x 3072 33.3 -> 31.7; GeLU 4096 x 12288 27.5 -> 26.5; exhaustive
+            // 12288 x 3072 26.5 -> 25.7; the memory-bound quantizer, 16384 x 3072, 21.8 -> 21.4.
             const uint32_t ebm = bm[b] >> 7;
             const uint32_t eb = max(ebm, 4u);                       // stored exponent byte
-            const uint32_t ec = (max(ebm, 5u) + 3u) * 0x00010001u;  // shift base in both halves
+            const uint32_t ec = max(ebm, 5u);
+            const uint32_t low = (ec - 5u) * 0x00800080u;
+            const uint32_t off = ((19u - ec) & 63u) * 0x04000400u + (kSse ? 0u : 0x00040004u);
+            // (four registers at a time: an instruction on packed halves is not followed at once by one that needs it)
 #pragma unroll
-            for (int k = b * RB; k < (b + 1) * RB; ++k) {
-                const uint32_t ef = pk_shr(a[k], 0x00070007u);                 // exponent fields
-                const uint32_t sh = pk_min(pk_sub(ec, ef), 0x000F000Fu);       // >= 3; >= 8 means bin 0
-                const uint32_t sig = (a[k] & K.k7f) | K.k80;                   // 1.m as 8-bit integers
-                b2[k] = pk_shr(sig, sh);                                       // floor(2*xhat), 0..31
-                // 256 * xhat = sig << (7 - sh); an element with sh > 7 is in bin 0 and its value is not used
-                if (kSse) x2[k] = pk_shl(sig, pk_sub_sat(0x00070007u, sh));
+            for (int k0 = b * RB; k0 < (b + 1) * RB; k0 += 4) {
+                uint32_t v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = pk_max(a[k0 + i], low);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = pk_mad_u16(v[i], K.k8, off);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (!kSse) b2[k0 + i] = pk_add_f16(v[i], K.khalf);
+                    else b2[k0 + i] = pk_fma_f16(v[i], K.k1001, K.khalf);   // (the fraction is needed without that half step: one rounding)
+                }
+                if (kSse) {
+                    uint32_t t[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) t[i] = pk_sub_f16(b2[k0 + i], K.k1024);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) t[i] = pk_sub_f16(v[i], t[i]);                      // v - bin, exact
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) f2[k0 + i] = pk_fma_f16(t[i], K.k128, K.k1024);     // 1024 + 128 * that, exact
+                }
             }
+            // the block's range row: its largest element has bin 16 + (top three mantissa bits), range = bin / 2
+            // (an all-zero block: range row 0, as from its bins)
+            const uint32_t range_row = kLdsRange + ((bm[b] >> 4) & 7u) * 32u;
             if (kSse) {
-                // the block's range row: its largest element has bin 16 + (top three mantissa bits), range = bin / 2
-                // (an all-zero block: range row 0, as from its bins)
-                const uint32_t range_row = kLdsRange + ((bm[b] >> 4) & 7u) * 32u;
-                did[b] = select_sse_matrix<RB, kTwoStage, kSeda>(b2, x2, b * RB, const_cast<uint8_t*>(lds), K.mx,
+                did[b] = select_sse_matrix<RB, kTwoStage, kSeda>(b2, f2, b * RB, const_cast<uint8_t*>(lds), K.mx,
                                                                  threadIdx.x & 63u, range_row, excl_a);
             } else if (kCounts && G == 32) {
-                const uint32_t range_row = kLdsRange + ((bm[b] >> 4) & 7u) * 32u;
                 did[b] = select_lut32_matrix<kTwoStage, kSeda>(b2, const_cast<uint8_t*>(lds), K.mx, threadIdx.x & 63u,
                                                                range_row, excl_a);
             } else {
@@ -794,18 +847,20 @@ __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint
                     else if (PER == 2) gbin[r] = halves_max(b2[b * RB + r]);
                     else gbin[r] = (r & 1) ? (b2[b * RB + r / 2] >> 16) : (b2[b * RB + r / 2] & 0xFFFFu);
                 }
-                did[b] = select_lut_rows<GG, kTwoStage, kSeda>(gbin, lds, K, excl_a);
+                did[b] = select_lut_rows<GG, kTwoStage, kSeda>(gbin, lds, K, excl_a, range_row);
             }
             meta |= (did[b] | (eb << 8)) << (16 * b);
         }
         // ---- emit: every element through Qvalue of the chosen dialect, two elements per pair-table lookup
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const uint32_t pbase = kLdsPair + did[c / (4 / NB)];
+            const uint32_t pbase = kLdsPair - kBinBias * (32u + 1024u) + did[c / (4 / NB)];
             uint32_t byte[4];
 #pragma unroll
             for (int m = 0; m < 4; ++m) byte[m] = lds[dot2_u16(b2[4 * c + m], K.kpair, pbase)];
-            uint32_t v = byte[0] | (byte[1] << 8) | (byte[2] << 16) | (byte[3] << 24);
+            // (byte permutations: shifts and ors would be regrouped into more instructions)
+            uint32_t v = __builtin_amdgcn_perm(__builtin_amdgcn_perm(byte[3], byte[2], 0x0C0C0400u),
+                                               __builtin_amdgcn_perm(byte[1], byte[0], 0x0C0C0400u), 0x05040100u);
             // sign bits: element 2m -> bit 8m+3, element 2m+1 -> bit 8m+7
             const uint32_t x01 = __builtin_amdgcn_perm(w[4 * c + 1], w[4 * c + 0], 0x07030501u);  // b1(w0) b1(w1) b3(w0) b3(w1)
             const uint32_t x23 = __builtin_amdgcn_perm(w[4 * c + 3], w[4 * c + 2], 0x07030501u);
@@ -1211,7 +1266,7 @@ __global__ __launch_bounds__(kThreads) void quantize_lut_kernel(
         }
         __syncthreads();
     }
-    TileConsts K = make_tile_consts(lane, kLdsGm);
+    TileConsts K = make_tile_consts<G>(lane, kLdsGm);
     if (kCounts) K.mx = make_count_consts(lds, lds_count_offset(kSeda, kRes, 0) + wave * kHistWaveBytes, lane);
     if (kSse)
         K.mx = make_matrix_consts(lds, kLdsGm, lds_matrix_offset(kSeda, kRes),

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kGeluThreads) void gelu_quantize_kernel(
         dst[1] = make_uint4(l1.x | (h1.x << 4), l1.y | (h1.y << 4), l1.z | (h1.z << 4), l1.w | (h1.w << 4));
     }
     __syncthreads();
-    const TileConsts K = make_tile_consts(lane, 0);
+    const TileConsts K = make_tile_consts<G>(lane, 0);
     const bool meta_aligned = (reinterpret_cast<uintptr_t>(p.meta) & 15u) == 0;
     const uint32_t kclamp = sgpr_const(kGeluClamp | (kGeluClamp << 16));
 

@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
     int32_t gbuf[2] = {-1, -1};
     request(u, 0, buf[0], gbuf[0]);
     layernorm_tables_to_lds<B, kTwoStage && !kWriteY, kSeda && !kWriteY, kThreads>(lds, blob, gamma, beta, p);
-    const TileConsts K = make_tile_consts(lane, 0);
+    const TileConsts K = make_tile_consts<G>(lane, 0);
     FastParams sp = {};
     sp.codes = p.codes;
     sp.meta = p.meta;
