@@ -359,39 +359,66 @@ __device__ __forceinline__ TileConsts make_tile_consts(uint32_t lane, uint32_t g
 // (8 x 31 = 248) still fit the byte, so rows are summed eight at a time and widened to 16 bits in between.
 // gbin: with kBinBias.  excl_a: LDS offset of this block's SeDA exclusion row (kSeda only); range_row: of the row of its
 // range (kTwoStage only: the first stage keeps the dialects whose top magnitude is the integer part of the block maximum).
-template <int R, bool kTwoStage, bool kSeda>
+// kLean: half of the row reads at a time and the exclusion rows behind them, for kernels that are short of registers.
+template <int R, bool kTwoStage, bool kSeda, bool kLean>
 __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], const uint8_t* lds,
                                                     const TileConsts& K, uint32_t excl_a, uint32_t range_row)
 {
     static_assert(R % 8 == 0, "rows are summed eight at a time");
     uint32_t ev[8], od[8];   // 16-bit sums of dialects (4i, 4i+2) and (4i+1, 4i+3); R == 8 keeps bytes in ev
     // ---- candidate restrictions (Sec. 3.4 SeDA, Sec. 3.2 two-stage) as rows of bytes, 0xFF = excluded.  Their
-    // reads go out together with the first batch of Qerror rows.
+    // reads go out together with the first batch of Qerror rows, or behind the sums where registers are short: with 16
+    // groups and one restriction (GeLU, 16 wavefronts, 8000 x 3072, block 16: 104 us so and 27 with late reads; with both
+    // restrictions the early ones fit).
+    constexpr bool kLate = kLean || (R != 8 && !(kSeda && kTwoStage));
     uint4 xa0 = make_uint4(0, 0, 0, 0), xa1 = xa0, xr0 = xa0, xr1 = xa0;
-    if (kSeda) {
-        xa0 = *reinterpret_cast<const uint4*>(lds + excl_a);
-        xa1 = *reinterpret_cast<const uint4*>(lds + excl_a + 16);
-    }
-    if (kTwoStage) {
-        xr0 = *reinterpret_cast<const uint4*>(lds + range_row);
-        xr1 = *reinterpret_cast<const uint4*>(lds + range_row + 16);
-    }
+    auto exclusions = [&]() {
+        if (kSeda) {
+            xa0 = *reinterpret_cast<const uint4*>(lds + excl_a);
+            xa1 = *reinterpret_cast<const uint4*>(lds + excl_a + 16);
+        }
+        if (kTwoStage) {
+            xr0 = *reinterpret_cast<const uint4*>(lds + range_row);
+            xr1 = *reinterpret_cast<const uint4*>(lds + range_row + 16);
+        }
+    };
+    // the dialects excluded by the list, and those that the range excludes too, unless that leaves nothing (possible only
+    // together with a list)
+    uint32_t x[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    auto excluded = [&]() {
+        const uint32_t ea[8] = {xa0.x, xa0.y, xa0.z, xa0.w, xa1.x, xa1.y, xa1.z, xa1.w};
+        const uint32_t er[8] = {xr0.x, xr0.y, xr0.z, xr0.w, xr1.x, xr1.y, xr1.z, xr1.w};
+        uint32_t range = 0xFFFFFFFFu;
+        if (kSeda && kTwoStage) {   // (a mask, not a branch: that would split the routine and cost registers)
+            uint32_t all = ea[0] | er[0];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) all &= ea[i] | er[i];
+            range = all == 0xFFFFFFFFu ? 0u : 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = ea[i] | (er[i] & range);
+    };
+    if (!kLate) exclusions();
 #pragma unroll
     for (int c = 0; c < R / 8; ++c) {
         uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         // all row reads are issued before the first sum: with two wavefronts per SIMD their latency shows
-        uint4 r0[8], r1[8];
+        constexpr int kAtOnce = kLean ? 4 : 8;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint8_t* row = lds + K.row_base + gbin[8 * c + j] * (32u * kRowCopies);
-            r0[j] = *reinterpret_cast<const uint4*>(row);
-            r1[j] = *reinterpret_cast<const uint4*>(row + 16 * kRowCopies);
-        }
-        asm volatile("" ::: "memory");
+        for (int j0 = 0; j0 < 8; j0 += kAtOnce) {
+            uint4 r0[kAtOnce], r1[kAtOnce];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            acc[0] += r0[j].x; acc[1] += r0[j].y; acc[2] += r0[j].z; acc[3] += r0[j].w;
-            acc[4] += r1[j].x; acc[5] += r1[j].y; acc[6] += r1[j].z; acc[7] += r1[j].w;
+            for (int j = 0; j < kAtOnce; ++j) {
+                const uint8_t* row = lds + K.row_base + gbin[8 * c + j0 + j] * (32u * kRowCopies);
+                r0[j] = *reinterpret_cast<const uint4*>(row);
+                r1[j] = *reinterpret_cast<const uint4*>(row + 16 * kRowCopies);
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) {
+                acc[0] += r0[j].x; acc[1] += r0[j].y; acc[2] += r0[j].z; acc[3] += r0[j].w;
+                acc[4] += r1[j].x; acc[5] += r1[j].y; acc[6] += r1[j].z; acc[7] += r1[j].w;
+            }
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -405,36 +432,18 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
             }
         }
     }
-    const uint32_t ea[8] = {xa0.x, xa0.y, xa0.z, xa0.w, xa1.x, xa1.y, xa1.z, xa1.w};
-    const uint32_t er[8] = {xr0.x, xr0.y, xr0.z, xr0.w, xr1.x, xr1.y, xr1.z, xr1.w};
-    // the range applies unless that leaves nothing (possible only together with a SeDA list)
-    bool none = false;
-    if (kSeda && kTwoStage) {
-        uint32_t all = ea[0] | er[0];
-#pragma unroll
-        for (int i = 1; i < 8; ++i) all &= ea[i] | er[i];
-        none = all == 0xFFFFFFFFu;
-    }
     // ---- argmin with lowest DID on ties: 16-bit keys, 32 of them in 16 registers; an excluded dialect gets a key that no
     // real sum reaches.  8 groups: sum << 8 | DID, a byte each (0xFF > 248 >= any real sum), put together by one byte
     // permutation per two keys; more: sum << 5 | DID.
+    if (kLate) exclusions();
+    excluded();
     uint32_t best = 0xFFFFFFFFu;
     if (R == 8) {
-        uint32_t a[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            a[i] = ev[i];
-            if (kSeda) a[i] |= ea[i];
-            if (kTwoStage) a[i] |= er[i];
-        }
-        if (kSeda && kTwoStage && __builtin_amdgcn_ballot_w64(none) != 0) {   // (rare)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = none ? (ev[i] | ea[i]) : a[i];
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t ke = __builtin_amdgcn_perm(a[i], K.kdid4[i], K.sel_e);   // dialects 4i, 4i+2
-            const uint32_t ko = __builtin_amdgcn_perm(a[i], K.kdid4[i], K.sel_o);   // dialects 4i+1, 4i+3
+            const uint32_t a = (kSeda || kTwoStage) ? (ev[i] | x[i]) : ev[i];
+            const uint32_t ke = __builtin_amdgcn_perm(a, K.kdid4[i], K.sel_e);   // dialects 4i, 4i+2
+            const uint32_t ko = __builtin_amdgcn_perm(a, K.kdid4[i], K.sel_o);   // dialects 4i+1, 4i+3
             best = pk_min(best, pk_min(ke, ko));
         }
     } else {
@@ -443,9 +452,8 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
             uint32_t ke = (ev[i] << 5) | K.kdid[2 * i];
             uint32_t ko = (od[i] << 5) | K.kdid[2 * i + 1];
             if (kSeda || kTwoStage) {
-                const uint32_t x = kTwoStage ? (none ? ea[i] : (ea[i] | er[i])) : ea[i];
-                const uint32_t xe = x & 0x00FF00FFu;
-                const uint32_t xo = __builtin_amdgcn_perm(0u, x, 0x0C030C01u);
+                const uint32_t xe = x[i] & 0x00FF00FFu;
+                const uint32_t xo = __builtin_amdgcn_perm(0u, x[i], 0x0C030C01u);
                 ke |= xe | (xe << 8);                                 // 0xFFFF > (992 << 5 | 31)
                 ko |= xo | (xo << 8);
             }
@@ -720,7 +728,7 @@ __device__ __forceinline__ MatrixConsts make_count_consts(uint8_t* lds, uint32_t
 // (code1, meta1), which the plain routine recomputes from x.  stage: 16 words of the lane's private memory when w
 // is not in global memory at all (xb is then ignored).
 // kCounts: the calling kernel has the LDS counts that select_lut32_matrix needs (32 groups only).
-template <int kBlock, int G, bool kTwoStage, bool kSeda, bool kResidual = false, bool kCounts = false>
+template <int kBlock, int G, bool kTwoStage, bool kSeda, bool kResidual = false, bool kCounts = false, bool kLean = false>
 __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint8_t* lds, const TileConsts& K,
                                              const uint16_t* xb, bool in_range, uint32_t excl_a,
                                              uint32_t (&code)[4], uint32_t& meta,
@@ -847,7 +855,7 @@ __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint
                     else if (PER == 2) gbin[r] = halves_max(b2[b * RB + r]);
                     else gbin[r] = (r & 1) ? (b2[b * RB + r / 2] >> 16) : (b2[b * RB + r / 2] & 0xFFFFu);
                 }
-                did[b] = select_lut_rows<GG, kTwoStage, kSeda>(gbin, lds, K, excl_a, range_row);
+                did[b] = select_lut_rows<GG, kTwoStage, kSeda, kLean>(gbin, lds, K, excl_a, range_row);
             }
             meta |= (did[b] | (eb << 8)) << (16 * b);
         }

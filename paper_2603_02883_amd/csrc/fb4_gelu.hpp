@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kGeluThreads) void gelu_quantize_kernel(
         uint32_t code[4], meta;
         bool tile_special;
         const uint32_t no_code[4] = {0, 0, 0, 0};
-        compute_tile<kBlock, G, kTwoStage, kSeda>(y, lds, K, nullptr, gb < n_blocks, excl, code, meta, no_code, 0u, tile_special, stage);
+        compute_tile<kBlock, G, kTwoStage, kSeda, false, false, G == 8>(y, lds, K, nullptr, gb < n_blocks, excl, code, meta, no_code, 0u, tile_special, stage);
         store_tile<kBlock>(sp, gb, lane, make_uint4(code[0], code[1], code[2], code[3]), meta, meta_aligned);
         t = t_next;
         t_next = t_after;
