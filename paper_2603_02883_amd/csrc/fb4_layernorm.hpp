@@ -194,11 +194,12 @@ __device__ __noinline__ RowNorm layernorm_row_plain(const uint16_t* xrow, uint32
 // B: chunks per lane (the host picks it from the row length); gamma / beta may be null (1 / 0).
 // kWriteY: the producer alone -- writes the normalized bf16 tensor to p.y_out and nothing else (for checking the
 // producer against its definition; production launches never use it).
-// One chunk per lane is in registers at a time: a first walk over the bundle's chunks forms the sums, a last walk
-// reads the chunks again (from the L2 cache: the wavefront has just read them) and normalizes and quantizes
-// them; two chunk buffers alternate, the chunk of the next step is always in flight.  (Holding the bundle in
-// registers instead reads x once but leaves room for 8 wavefronts per CU only, or spills: 42-62 us on a
-// 16384x3072 tensor.)
+// A first walk over the bundle's chunks forms the sums, a last walk normalizes and quantizes them.  Two chunk buffers per
+// lane: the last two chunks of the first walk stay in them, so that up to two chunks per lane x is read once, and of B
+// chunks B - 2 again.  (All of them again, from the L2 cache as far as it holds the bundles of all wavefronts, 4.7 MB of an
+// XCD's 4: 16384 x 3072 32.8 us instead of 30.7, 8000 x 8192 50.8 and 41.9, 4000 x 12288 41.7 and 38.6.  Fewer vector
+// instructions, or the second reads requested earlier, change nothing: the memory traffic is the bound.  Holding the whole bundle in registers leaves
+// room for 8 wavefronts per CU only, or spills: 42-62 us.)
 // kBlock, G: block size (32 or 16) and number of groups of the online selector (Sec. 3.2, Sec. 4.1).
 template <int B, int kBlock, int G, bool kTwoStage, bool kSeda, bool kWriteY, int kThreads = ln_threads(B, G)>
 __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
@@ -241,11 +242,14 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
     uint32_t u = blockIdx.x + wave * W;
     uint32_t u_next = blockIdx.x + (kWaves + wave) * W;
     if (threadIdx.x == 0) wg_next = 2 * kWaves;
-    // Two chunk buffers used in turn: step s of a bundle works on buf[s & 1] while the chunk of step s + 1 is on
-    // its way into the other one.  A bundle takes 2 B steps (B chunks summed, B chunks normalized and quantized).
+    // Two chunk buffers.  The first walk reads chunk j from buf[j & 1] and leaves the last two chunks there, with which the
+    // last walk begins: only the other B - 2 are read again.  A buffer is requested anew as soon as its chunk has been read
+    // for the last time; the last walk's order (B - 2, B - 1, 0 .. B - 3) frees buf[0], then buf[1], at its end for the next
+    // bundle's first two chunks.
     uint32_t buf[2][16];
     int32_t gbuf[2] = {-1, -1};
     request(u, 0, buf[0], gbuf[0]);
+    if (B > 1) request(u, 1, buf[1], gbuf[1]);
     layernorm_tables_to_lds<B, kTwoStage && !kWriteY, kSeda && !kWriteY, kThreads>(lds, blob, gamma, beta, p);
     const TileConsts K = make_tile_consts<G>(lane, 0);
     FastParams sp = {};
@@ -270,9 +274,7 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
         float part[B], part2[B];
 #pragma unroll
         for (int j = 0; j < B; ++j) {
-            const int s = j;
-            request(u, (j + 1) % B, buf[(s + 1) & 1], gbuf[(s + 1) & 1]);   // (after the last chunk: the first again)
-            const uint32_t (&w)[16] = buf[s & 1];
+            const uint32_t (&w)[16] = buf[j & 1];
             float a0 = 0.0f, a1 = 0.0f, q0 = 0.0f, q1 = 0.0f;
 #pragma unroll
             for (int k = 0; k < 16; k += 2) {
@@ -283,6 +285,8 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
             }
             part[j] = ok[j] ? a0 + a1 : 0.0f;
             part2[j] = ok[j] ? q0 + q1 : 0.0f;
+            __builtin_amdgcn_sched_barrier(0);
+            if (j + 2 < B) request(u, j + 2, buf[j & 1], gbuf[j & 1]);
             __builtin_amdgcn_sched_barrier(0);
         }
         // ---- per row: both sums over the wavefront's chunks of that row; mean, and the variance as the mean
@@ -314,17 +318,14 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
                 if (rloc[j] == r) { mean[j] = m; rn[j].nms = -m; rn[j].r = rstd; }
             }
         }
-        // (after B steps the bundle's first chunk is on its way into buf[B & 1])
         if (centered) {
             // ---- another walk (rows whose mean is not small against their spread): squared deviations from the mean
 #pragma unroll
             for (int j = 0; j < B; ++j) {
-                const int s = B + j;
-                // keeps the buffer parity of the path that skips this walk: with an odd number of chunks the first
-                // chunk comes back into the buffer this step works on, requested after its arithmetic
-                const bool late = (B & 1) && j == B - 1;
-                if (!late) request(u, (j + 1) % B, buf[(s + 1) & 1], gbuf[(s + 1) & 1]);
-                const uint32_t (&w)[16] = buf[s & 1];
+                uint32_t again[16];
+                int32_t unused = 0;
+                if (j + 2 < B) request(u, j, again, unused);
+                const uint32_t (&w)[16] = j + 2 < B ? again : buf[j & 1];
                 float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
 #pragma unroll
                 for (int k = 0; k < 16; k += 2) {
@@ -337,7 +338,6 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
                 }
                 part2[j] = ok[j] ? (a0 + a1) + (a2 + a3) : 0.0f;
                 __builtin_amdgcn_sched_barrier(0);
-                if (late) request(u, 0, buf[s & 1], gbuf[s & 1]);
             }
             in_range = true;
             for (uint32_t r = 0; r < rw; ++r) {
@@ -369,13 +369,11 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
         }
         // ---- last walk: normalize, scale and shift, round to bf16, quantize, store
 #pragma unroll
-        for (int j = 0; j < B; ++j) {
+        for (int s = 0; s < B; ++s) {
             typedef float f32x2 __attribute__((ext_vector_type(2)));
-            const int s = B + j;
-            const int32_t grp = gbuf[s & 1];
-            if (j + 1 < B) request(u, j + 1, buf[(s + 1) & 1], gbuf[(s + 1) & 1]);
-            else request(u_next, 0, buf[(s + 1) & 1], gbuf[(s + 1) & 1]);   // first chunk of the next bundle
-            const uint32_t (&w)[16] = buf[s & 1];
+            const int j = B == 1 ? 0 : s < 2 ? B - 2 + s : s - 2, at = B == 1 ? 0 : (B + s) & 1;
+            const int32_t grp = gbuf[at];
+            const uint32_t (&w)[16] = buf[at];
             const float4* g4 = reinterpret_cast<const float4*>(lds_gamma) + cb[j];
             const float4* b4 = reinterpret_cast<const float4*>(lds_beta) + cb[j];
             const uint32_t gb = u * per_bundle + lane + 64u * j;
@@ -392,6 +390,10 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
                 y[2 * q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(y01, bf16x2));
                 y[2 * q + 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(y23, bf16x2));
             }
+            __builtin_amdgcn_sched_barrier(0);
+            if (B == 1) request(u_next, 0, buf[at], gbuf[at]);
+            else if (s + 2 < B) request(u, s, buf[at], gbuf[at]);
+            else request(u_next, s + 2 - B, buf[at], gbuf[at]);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (kWriteY) {
                 if (ok[j]) {
@@ -414,7 +416,7 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
                 uint32_t code[4], meta;
                 bool tile_special;
                 const uint32_t no_code[4] = {0, 0, 0, 0};
-                compute_tile<kBlock, G, kTwoStage, kSeda>(y, lds, K, nullptr, ok[j], excl, code, meta, no_code, 0u, tile_special, stage);
+                compute_tile<kBlock, G, kTwoStage, kSeda, false, false, G == 8>(y, lds, K, nullptr, ok[j], excl, code, meta, no_code, 0u, tile_special, stage);
                 const bool al = meta_aligned && (((gb - lane) & 7u) == 0u);
                 store_tile<kBlock>(sp, gb, lane, make_uint4(code[0], code[1], code[2], code[3]), meta, al, ok[j]);
             }

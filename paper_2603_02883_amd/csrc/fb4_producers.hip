@@ -64,9 +64,12 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
     if ((rc = check_device(luts)) != FB4_OK) return rc;
     // Chunks per lane B and rows per bundle.  If with the fewest chunks that hold a row every wavefront gets one bundle at
     // most, these: the shortest chain (us, 1 / 2 / 3 / 4 chunks: 300 x 1152 5.0 / 7.1 / 8.7 / 10.9, 3000 x 1024 6.4 / 7.7 /
-    // 9.7 / 11.9, 60000 x 96 13.3 / 19.6 / 22.9 / 33.1; 1000 x 3072 8.1 with 2 and 9.5 with 3).  Otherwise the fullest
-    // wavefront among B <= 4, the fewest chunks among equals (40000 x 1152 43.8 / 39.6 / 36.6 / 41.4); rows longer than
-    // 8192 need 5 or 6.
+    // 9.7 / 11.9, 60000 x 96 13.0 / 19.3 / 23.6 / 31.6).  Otherwise the least cost among B <= 4: instructions of a bundle
+    // (500 per chunk, 45 + 10 B per row, 60), more from two chunks on, which are not all kept from the first walk to the
+    // last (kReread), times the rounds of bundles that the chip's wavefronts take, half of it as if the last round were
+    // full; rows longer than 8192 need 5 or 6.  us with 1 / 2 / 3 / 4 chunks, the choice starred: 16384 x 1152 19.1 / 19.1* / 19.4 / 21.0,
+    // 40000 x 1152 40.5 / 36.9 / 33.6* / 38.1, 9000 x 1600 14.2* / 15.4 / 16.3 / 17.0, 65536 x 320 19.6* / 24.6 / 24.8 / 27.8,
+    // 40000 x 2400 - / 76.3 / 68.4* / 70.8, 16384 x 3072 - / 36.3 / 31.6* / 38.7, 5000 x 3072 - / 14.6 / 15.6* / 18.2.
     const int fewest = (int)((nb + 63) / 64);
     int B = 0;
     uint32_t rw = 0;
@@ -79,9 +82,12 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
     }
     double best = 0.0;
     for (int b = fewest; b <= 4 && rw == 0; ++b) {
-        const uint32_t r = (uint32_t)(64 * b / nb);
-        const double fill = (double)(r * nb) / (64.0 * b) - (b == 4 ? 0.05 : 0.0);
-        if (fill > best + 1e-9) { best = fill; B = b; }
+        const int64_t r = 64 * b / nb, bundles = (rows + r - 1) / r;
+        const int threads = ln_threads(b, opts->num_groups);
+        const double rounds = (double)bundles / ((double)luts->n_cu * (threads / 64)), whole = (double)(int64_t)rounds + 1.0;
+        constexpr double kReread[5] = {0.0, 1.0, 1.1, 1.14, 1.22};
+        const double cost = (500.0 * b + (45.0 + 10.0 * b) * r + 60.0) * kReread[b] * (0.5 * (whole + rounds) + 0.2) * threads;
+        if (B == 0 || cost < best) { best = cost; B = b; }
     }
     if (B == 0) B = fewest;
     if (rw == 0) rw = (uint32_t)(64 * B / nb);

@@ -70,19 +70,23 @@ def layernorm_bundles(rows, cols, num_groups):
     """The launcher's choice: (chunks per lane, rows per bundle, whether every wavefront gets one bundle at most)."""
     nb, cu = cols // 32, torch.cuda.get_device_properties(0).multi_processor_count
     fewest = (nb + 63) // 64
-    wavefronts = lambda b: cu * (12 if b <= 4 and not (num_groups > 8 and b >= 2) else 8)
+    threads = lambda b: 768 if b <= 4 and not (num_groups > 8 and b >= 2) else 512
+    wavefronts = lambda b: cu * (threads(b) // 64)
     if fewest <= 4 and -(-rows // (64 * fewest // nb)) <= wavefronts(fewest):
         return fewest, min(64 * fewest // nb, rows), True
-    best, B = 0.0, fewest
+    best, B = 0.0, 0
     for b in range(fewest, 5):
-        fill = (64 * b // nb) * nb / (64.0 * b) - (0.05 if b == 4 else 0.0)
-        if fill > best + 1e-9:
-            best, B = fill, b
+        r = 64 * b // nb
+        rounds = -(-rows // r) / wavefronts(b)
+        cost = (500 * b + (45 + 10 * b) * r + 60) * (1, 1.1, 1.14, 1.22)[b - 1] * (0.5 * (int(rounds) + 1 + rounds) + 0.2) * threads(b)
+        if B == 0 or cost < best:
+            best, B = cost, b
+    B = B or fewest
     return B, min(64 * B // nb, rows), -(-rows // (64 * B // nb)) <= wavefronts(B)
 
 
 @pytest.mark.parametrize("block,g", [(32, 8), (16, 8), (32, 16), (16, 16)])
-@pytest.mark.parametrize("rows,cols,chunks,rows_per_bundle", [(6501, 1024, 1, 2), (3300, 2048, 1, 1), (3301, 4096, 2, 1), (16001, 1152, 3, 5),
+@pytest.mark.parametrize("rows,cols,chunks,rows_per_bundle", [(9001, 960, 1, 2), (6501, 1600, 1, 1), (3301, 4096, 2, 1), (16001, 1152, 2, 3), (30001, 1152, 3, 5),
                                                               (6501, 3072, 3, 2), (3100, 6176, 4, 1), (2100, 9216, 5, 1), (2101, 12288, 6, 1)])
 def test_layernorm_of_more_bundles_than_wavefronts(F, rows, cols, chunks, rows_per_bundle, block, g):
     assert layernorm_bundles(rows, cols, g) == (chunks, rows_per_bundle, False)
@@ -93,6 +97,26 @@ def test_layernorm_of_more_bundles_than_wavefronts(F, rows, cols, chunks, rows_p
     o = F.opts(block=block, num_groups=g)
     c, m = F.fb4_layernorm_quantize(luts, o, x, torch.from_numpy(gamma).cuda(), torch.from_numpy(beta).cuda(), 1e-6, y_out=y)
     c0, m0 = F.fb4_quantize(luts, o, y)                       # (against the oracle in tests of its own)
+    torch.cuda.synchronize()
+    assert torch.equal(c, c0) and torch.equal(m, m0)
+    assert_layernorm(x, y, gamma, beta)
+    luts.free()
+
+
+@pytest.mark.parametrize("rows,cols,chunks", [(9001, 960, 1), (16001, 1152, 2), (20001, 2400, 3), (3301, 5120, 3), (3100, 6176, 4),
+                                              (2100, 9216, 5), (2101, 12288, 6)])
+def test_layernorm_of_large_means_and_overflowing_rows(F, rows, cols, chunks):
+    # rows that take the walk over squared deviations, and some that are redone in double, between ordinary ones
+    assert layernorm_bundles(rows, cols, 8)[0] == chunks
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    x = synth.vdit_activation(rows=rows, cols=cols, seed=cols, device="cuda").float()
+    x[3::7] += 40.0
+    x[11::1001] *= 2.0 ** 70
+    x = x.bfloat16()
+    gamma, beta = synth.layernorm_affine(cols, seed=cols)
+    y = torch.empty_like(x)
+    c, m = F.fb4_layernorm_quantize(luts, F.opts(), x, torch.from_numpy(gamma).cuda(), torch.from_numpy(beta).cuda(), 1e-6, y_out=y)
+    c0, m0 = F.fb4_quantize(luts, F.opts(), y)
     torch.cuda.synchronize()
     assert torch.equal(c, c0) and torch.equal(m, m0)
     assert_layernorm(x, y, gamma, beta)
