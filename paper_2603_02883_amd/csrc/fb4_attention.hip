@@ -163,14 +163,26 @@ int fb4_select_salient_tokens(const float* scores, int64_t frames, int heads, in
     const int64_t tokens = (int64_t)grid_h * grid_w;
     if (tokens > (int64_t)kSelectMaxTokens || frames * tokens > 0x7FFFFFFFll || !aligned(scores, 4) || !aligned(rows_out, 4))
         return FB4_ERR_UNSUPPORTED;
-    const int64_t th = std::min(tile_h, grid_h), tw = std::min(tile_w, grid_w);
-    const SelectShape shape = select_shape(frames, ((grid_h + th - 1) / th) * ((grid_w + tw - 1) / tw), th * tw);
-#define FB4_SELECT_LAUNCH(t, l) hipLaunchKernelGGL((select_salient_kernel<t, l>), dim3((unsigned)frames), dim3(t), 0, static_cast<hipStream_t>(stream), scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, rows_out)
-    if (shape.threads == 1024) FB4_SELECT_LAUNCH(1024, 16);
-    else if (shape.lanes == 16) FB4_SELECT_LAUNCH(256, 16);
-    else FB4_SELECT_LAUNCH(256, 1);
+    const int64_t th = std::min(tile_h, grid_h), tw = std::min(tile_w, grid_w), tile_rows = (grid_h + th - 1) / th;
+    const uint32_t tile_columns = (uint32_t)((grid_w + tw - 1) / tw);
+    const SelectShape shape = select_shape(frames, tile_rows, tile_columns, th * tw, th * grid_w);
+    const int64_t per_frame = (tile_rows + shape.rows - 1) / shape.rows, workgroups = frames * per_frame;
+    const bool small = std::min(shape.rows * th, (int64_t)grid_h) * grid_w <= 2048;   // (less LDS: more workgroups per compute unit)
+    const int64_t at_once = 0xFFFFFFFFll / shape.threads;   // (a launch takes fewer than 2^32 threads)
+    for (int64_t first = 0; first < workgroups; first += at_once) {
+        const dim3 grid((unsigned)std::min(at_once, workgroups - first));
+#define FB4_SELECT_LAUNCH(t, l, m) hipLaunchKernelGGL((select_salient_kernel<t, l, m>), grid, dim3(t), 0, static_cast<hipStream_t>(stream), scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, (uint32_t)tile_rows, tile_columns, (uint32_t)shape.rows, (uint32_t)per_frame, (uint32_t)first, rows_out)
+#define FB4_SELECT_CASE(t, m)                               \
+        if (shape.lanes == 16) FB4_SELECT_LAUNCH(t, 16, m); \
+        else FB4_SELECT_LAUNCH(t, 1, m);
+        if (shape.threads == 128) { FB4_SELECT_CASE(128, 2048) }
+        else if (shape.threads == 256) { if (small) { FB4_SELECT_CASE(256, 2048) } else { FB4_SELECT_CASE(256, kSelectMaxTokens) } }
+        else { if (small) { FB4_SELECT_CASE(1024, 2048) } else { FB4_SELECT_CASE(1024, kSelectMaxTokens) } }
+#undef FB4_SELECT_CASE
 #undef FB4_SELECT_LAUNCH
-    return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
+        if (hipGetLastError() != hipSuccess) return FB4_ERR_HIP;
+    }
+    return FB4_OK;
 }
 
 int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int heads, int grid_h, int grid_w,

@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 namespace fb4 {
@@ -558,33 +559,43 @@ __global__ __launch_bounds__(256) void probe_mfma_rate_kernel(float* out, uint32
     out[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
-// One workgroup per frame, up to 24 head loads in flight.  kSelectThreads / kLanes (lanes per tile), chosen by
-// select_shape: a few frames are bound by the dependent steps of one workgroup, so 16 wavefronts with 16 lanes per tile;
-// with more frames than compute units the instructions count, and a thread per tile takes the fewest, unless one round of
-// 16 lanes holds all tiles.  us with 1024 x 16 / 256 x 16 / 256 x 1, tiles of 4 x 4: 16 frames x 24 heads x 1024 tokens
-// 5.45 / 7.99 / 6.70, 1024 frames x 8 heads x 1024 tokens 15.9 / 14.5 / 10.9, 1024 x 8 x 256 9.8 / 6.3 / 7.4, 16 x 8 x 16
-// 3.8 / 3.5 / 4.0; one token per frame, 65536 frames 458 / 246 / 177.
-struct SelectShape { int threads, lanes; };
-inline SelectShape select_shape(int64_t frames, int64_t tiles, int64_t tile_tokens)
+// A workgroup takes some rows of tiles of a frame: their tokens are one run of memory, their chosen tokens one run of the
+// ascending list.  Up to 24 head loads in flight, kLanes lanes per tile.  Bound by its chain of dependent steps -- loads,
+// maxima, compaction --, so a few frames are spread over the compute units, one row of tiles each (but 64 tokens at least):
+// 16 frames x 24 heads x 1024 tokens 5.3 us with a workgroup per frame, 3.5 so, 128 x 24 x 1350 6.6 and 5.1.  With more frames
+// the instructions count and a workgroup takes a frame (256 x 24 x 1350 8.3 against 9.4): 1024 threads with 16 lanes per tile up
+// to 256 frames, else 256 and a thread per tile, unless one round of 16 lanes holds all tiles (1024 frames x 8 heads x 1024
+// tokens with 1024 x 16 / 256 x 16 / 256 x 1 15.9 / 14.5 / 10.9, 1024 x 8 x 256 9.8 / 6.3 / 7.4).
+struct SelectShape { int threads, lanes; int64_t rows; };   // rows: of tiles per workgroup
+inline SelectShape select_shape(int64_t frames, int64_t tile_rows, int64_t tile_columns, int64_t tile_tokens, int64_t row_tokens)
 {
-    if (tile_tokens > 4 && tiles * 16 <= 256) return {256, 16};
-    if (tile_tokens > 4 && frames <= 256) return {1024, 16};   // (256 compute units)
-    return {256, 1};
+    const bool wide = tile_tokens > 4;   // 16 lanes per tile
+    const int64_t rows = std::min((64 + row_tokens - 1) / row_tokens, tile_rows);
+    if (frames * ((tile_rows + rows - 1) / rows) <= 1600 && (rows < tile_rows || frames <= 256)) {
+        const int64_t n = rows * row_tokens;
+        return {n <= 128 ? 128 : n <= 512 ? 256 : 1024, wide ? 16 : 1, rows};
+    }
+    if (wide && tile_rows * tile_columns * 16 <= 256) return {256, 16, tile_rows};
+    if (wide && frames <= 256) return {1024, 16, tile_rows};   // (256 compute units)
+    return {256, 1, tile_rows};
 }
-constexpr uint32_t kSelectMaxTokens = 8192;   // per frame (the head means sit in LDS)
 
-template <int kSelectThreads, int kLanes>
+template <int kSelectThreads, int kLanes, int kMaxTokens>
 __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const float* scores, uint32_t heads,
                                                                         uint32_t grid_h, uint32_t grid_w, uint32_t tile_h,
-                                                                        uint32_t tile_w, int32_t* rows_out)
+                                                                        uint32_t tile_w, uint32_t th, uint32_t tw, uint32_t rows_per_workgroup,
+                                                                        uint32_t per_frame, uint32_t first_workgroup, int32_t* rows_out)
 {
     constexpr uint32_t kWaves = kSelectThreads / 64;
-    __shared__ double mean[kSelectMaxTokens];
-    __shared__ uint8_t chosen[kSelectMaxTokens];
+    __shared__ double mean[kMaxTokens];
+    __shared__ uint8_t chosen[kMaxTokens];
     __shared__ uint32_t wave_total[kWaves];
-    const uint32_t tokens = grid_h * grid_w, frame = blockIdx.x;
-    const float* sf = scores + (size_t)frame * heads * tokens;
-    for (uint32_t t = threadIdx.x; t < tokens; t += kSelectThreads) {
+    const uint32_t tokens = grid_h * grid_w;
+    const uint32_t wg = first_workgroup + blockIdx.x, frame = per_frame == 1 ? wg : wg / per_frame, row0 = (wg - frame * per_frame) * rows_per_workgroup;
+    const uint32_t y0 = row0 * tile_h, hh = min(rows_per_workgroup * tile_h, grid_h - y0), n = hh * grid_w;   // tokens of these rows of tiles
+    const uint32_t n_tiles = min(rows_per_workgroup, th - row0) * tw;
+    const float* sf = scores + (size_t)frame * heads * tokens + (size_t)y0 * grid_w;
+    for (uint32_t t = threadIdx.x; t < n; t += kSelectThreads) {
         double m = 0.0;
         uint32_t h = 0;
         auto some = [&](auto count) {   // that many loads in flight, added in head order
@@ -596,21 +607,17 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
             for (int j = 0; j < N; ++j) m += (double)v[j];
             h += N;
         };
-        if (kLanes > 1) {
-            while (h + 24 <= heads) some(std::integral_constant<int, 24>{});
-        }
+        while (h + 24 <= heads) some(std::integral_constant<int, 24>{});
         while (h + 8 <= heads) some(std::integral_constant<int, 8>{});
         while (h < heads) some(std::integral_constant<int, 1>{});
         mean[t] = m / (double)heads;
         chosen[t] = 0;
     }
     __syncthreads();
-    const uint32_t th = (grid_h + tile_h - 1) / tile_h, tw = (grid_w + tile_w - 1) / tile_w;
     const uint32_t part = threadIdx.x % kLanes;
-    for (uint32_t tile = threadIdx.x / kLanes; tile < th * tw; tile += kSelectThreads / kLanes) {
-        const uint32_t ty = tile / tw, tx = tile - ty * tw;
-        const uint32_t y0 = ty * tile_h, x0 = tx * tile_w;
-        const uint32_t hh = min(tile_h, grid_h - y0), ww = min(tile_w, grid_w - x0);
+    for (uint32_t tile = threadIdx.x / kLanes; tile < n_tiles; tile += kSelectThreads / kLanes) {
+        const uint32_t ty = tile < tw ? 0u : tile / tw, yt = ty * tile_h, x0 = (tile - ty * tw) * tile_w;
+        const uint32_t ht = min(tile_h, hh - yt), ww = min(tile_w, grid_w - x0);
         uint32_t best = 0xFFFFFFFFu;
         double best_v = 0.0;
         auto look = [&](uint32_t at) {   // (in ascending order: the first of equals stays)
@@ -619,10 +626,10 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
             if (best == 0xFFFFFFFFu || v > best_v) { best = at; best_v = v; }
         };
         if (kLanes == 1) {
-            for (uint32_t y = y0; y < y0 + hh; ++y)
+            for (uint32_t y = yt; y < yt + ht; ++y)
                 for (uint32_t x = x0; x < x0 + ww; ++x) look(y * grid_w + x);
         } else {
-            for (uint32_t i = part; i < hh * ww; i += kLanes) look((y0 + i / ww) * grid_w + x0 + i % ww);
+            for (uint32_t i = part; i < ht * ww; i += kLanes) look((yt + i / ww) * grid_w + x0 + i % ww);
         }
 #pragma unroll
         for (int o = kLanes / 2; o > 0; o >>= 1) {   // (the lanes of a tile stay together)
@@ -635,8 +642,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
     }
     __syncthreads();
     // ascending compaction: thread t owns a contiguous run of tokens
-    const uint32_t per = (tokens + kSelectThreads - 1) / kSelectThreads;
-    const uint32_t first = min(tokens, threadIdx.x * per), last = min(tokens, first + per);
+    const uint32_t per = (n + kSelectThreads - 1) / kSelectThreads;
+    const uint32_t first = min(n, threadIdx.x * per), last = min(n, first + per);
     uint32_t count = 0;
     for (uint32_t t = first; t < last; ++t) count += chosen[t];
     uint32_t incl = count;
@@ -648,16 +655,13 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
     if ((threadIdx.x & 63) == 63) wave_total[threadIdx.x >> 6] = incl;
     __syncthreads();
     uint32_t at = incl - count;
-    if (kWaves > 4) {   // (many: all read at once)
 #pragma unroll
-        for (uint32_t w = 0; w < kWaves; ++w) at += w < (threadIdx.x >> 6) ? wave_total[w] : 0u;
-    } else {
-        for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) at += wave_total[w];
-    }
-    int32_t* out = rows_out + (size_t)frame * th * tw;
+    for (uint32_t w = 0; w < kWaves; ++w) at += w < (threadIdx.x >> 6) ? wave_total[w] : 0u;
+    int32_t* out = rows_out + ((size_t)frame * th + row0) * tw;
     for (uint32_t t = first; t < last; ++t)
-        if (chosen[t]) out[at++] = (int32_t)(frame * tokens + t);
+        if (chosen[t]) out[at++] = (int32_t)(frame * tokens + y0 * grid_w + t);
 }
+constexpr uint32_t kSelectMaxTokens = 8192;   // per frame (the head means sit in LDS)
 
 // Sec. 3.4 ("Attention-Guided Semantic Relatedness Extraction"), the marking step: every anchor marks the tokens
 // of a window x window (x window_t frames) box around it whose raw attention score from the anchor -- Q[anchor] .

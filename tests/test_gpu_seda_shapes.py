@@ -183,6 +183,15 @@ def test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th,
     assert np.array_equal(got.cpu().numpy(), O.select_salient_tokens(s, gh, gw, th, tw))
 
 
+# (several rows of tiles per workgroup with a ragged last one, one row of 128 / 512 / 1024 threads with both LDS sizes, a thread
+# per tile, and both sides of the number of workgroups from which each takes a frame)
+@pytest.mark.parametrize("frames,heads,gh,gw,th,tw", [(5, 3, 40, 6, 4, 4), (7, 9, 13, 3, 4, 4), (2, 2, 30, 100, 4, 4), (3, 2, 40, 200, 4, 4),
+                                                      (1, 2, 90, 91, 30, 7), (2, 2, 64, 128, 1, 2), (2, 3, 16, 500, 2, 2),
+                                                      (200, 2, 32, 32, 4, 4), (201, 2, 32, 32, 4, 4), (1700, 2, 5, 5, 4, 4)])
+def test_salient_token_choice_of_rows_of_tiles(F, frames, heads, gh, gw, th, tw):
+    test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th, tw)
+
+
 def test_salient_token_choice_of_as_many_frames_as_a_launch_of_large_workgroups_refuses(F):
     # (a workgroup of 1024 threads per frame would be 2^32 threads here, one more than a launch takes)
     frames = 1 << 22
