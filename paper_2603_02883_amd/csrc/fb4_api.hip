@@ -618,6 +618,14 @@ int fb4_seda_profile(const fb4_luts* luts, const uint16_t* meta, int64_t rows, i
         return FB4_ERR_UNSUPPORTED;
     if (int rc = check_device(luts)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const int words = blocks_per_row % 8 == 0 && aligned(meta, 16) ? 8 : blocks_per_row % 4 == 0 && aligned(meta, 8) ? 4
+                          : blocks_per_row % 2 == 0 && aligned(meta, 4) ? 2 : 1;
+    if (rows > 0 && blocks_per_row > 0 && profile_by_group(rows, blocks_per_row, n_groups, words)) {
+#define FB4_PROFILE_CASE(w) case w: hipLaunchKernelGGL((profile_group_kernel<w>), dim3((unsigned)n_groups), dim3(kProfileGroupThreads), 0, s, meta, (uint32_t)rows, (uint32_t)blocks_per_row, anchor_group, luts->dev_blob, counts, sub_formatbooks); break;
+        switch (words) { FB4_PROFILE_CASE(8) FB4_PROFILE_CASE(4) FB4_PROFILE_CASE(2) FB4_PROFILE_CASE(1) }
+#undef FB4_PROFILE_CASE
+        return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
+    }
     const uint32_t n = (uint32_t)n_groups * 32u;
     // cleared by a kernel (not a memset node), so the call can be captured into a HIP graph
     hipLaunchKernelGGL(profile_clear_kernel, dim3((n + kProfileThreads - 1) / kProfileThreads), dim3(kProfileThreads),

@@ -67,4 +67,95 @@ __global__ __launch_bounds__(kProfileThreads) void profile_select_kernel(const u
     sub[i] = (uint8_t)best;
 }
 
+// The same in one launch: a workgroup per group looks through all rows for its anchors (a list in LDS), counts their
+// dialects into 64 histograms, one per lane of a wavefront, so that neither many equal dialects nor many rows of one group
+// meet in one address, and picks the group's dialects.
+// kWords: metadata words per load, which divide the blocks of a row.
+// us, three launches / this (rows x blocks, groups, share of anchors): 16384 x 96, 64, 1/16 9.8 / 5.4, the same with all rows
+// anchors 13.6 / 7.9, with one dialect everywhere 14.1 / 7.8, with a tenth of the rows anchors of one group 26.8 / 15.3; 1000 x
+// 36, 64 8.7 / 4.9.  Every workgroup looks through all rows (65536 x 96, 512 groups 12.5 / 15.3), and one that gets all anchors
+// takes 0.0041 a word and 0.0143 a load of the time that the atomics of three launches take for them (16384 x 97, a word a load,
+// 26.7 / 47.3; 65536 x 384, eight words, 86 / 202): profile_by_group keeps this below 1.
+inline bool profile_by_group(int64_t rows, int64_t blocks_per_row, int64_t n_groups, int words)
+{
+    return n_groups <= 512 && rows <= 32768 && rows * n_groups <= (1 << 23) && blocks_per_row * (2 * words + 7) <= 400 * words;
+}
+constexpr int kProfileGroupThreads = 1024;
+constexpr uint32_t kProfileGroupRows = 16384;   // per look
+
+template <int kWords>
+__global__ __launch_bounds__(kProfileGroupThreads) void profile_group_kernel(const uint16_t* meta, uint32_t rows, uint32_t nb,
+                                                                             const int32_t* anchor_group, const uint8_t* blob,
+                                                                             uint32_t* counts, uint8_t* sub)
+{
+    __shared__ uint32_t hist[32][64];
+    __shared__ uint16_t list[kProfileGroupRows];
+    __shared__ uint32_t n_list, total[32];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, g = blockIdx.x;
+    const uint32_t d = tid & 31u;
+    const int n_dialects = *reinterpret_cast<const int32_t*>(blob + kOffCount);
+    const uint32_t top = blob[kOffTop + d];
+    for (uint32_t i = tid; i < 32 * 64; i += kProfileGroupThreads) hist[0][i] = 0;
+    auto add = [&](uint32_t word) {
+        const uint32_t did = word & 0xFFu;
+        if (did < 32u) atomicAdd(&hist[did][lane], 1u);
+    };
+    for (uint32_t row0 = 0; row0 < rows; row0 += kProfileGroupRows) {
+        constexpr uint32_t kRead = kProfileGroupRows / kProfileGroupThreads;
+        int32_t group[kRead];
+#pragma unroll
+        for (uint32_t k = 0; k < kRead; ++k) group[k] = anchor_group[min(row0 + tid + k * kProfileGroupThreads, rows - 1u)];
+        if (tid == 0) n_list = 0;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t k = 0; k < kRead; ++k) {
+            const uint32_t off = tid + k * kProfileGroupThreads;
+            const bool mine = row0 + off < rows && (uint32_t)group[k] == g;   // (g < 2^31: a negative entry is none)
+            const unsigned long long m = __ballot(mine);
+            if (m) {   // (wave-uniform)
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&n_list, (uint32_t)__builtin_popcountll(m));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (mine) list[at + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = (uint16_t)off;
+            }
+        }
+        __syncthreads();
+        const uint32_t per_row = nb / kWords, items = n_list * per_row;   // (the launcher bounds rows * nb)
+#pragma unroll 2
+        for (uint32_t i = tid; i < items; i += kProfileGroupThreads) {
+            const uint32_t r = i / per_row;
+            const uint16_t* at = meta + ((size_t)row0 + list[r]) * nb + (size_t)(i - r * per_row) * kWords;
+            if constexpr (kWords == 1) {
+                add(*at);
+            } else {
+                typedef uint32_t words __attribute__((ext_vector_type(kWords / 2)));
+                const words v = *reinterpret_cast<const words*>(at);
+#pragma unroll
+                for (int j = 0; j < kWords / 2; ++j) { add(v[j]); add(v[j] >> 16); }
+            }
+        }
+        __syncthreads();
+    }
+    {
+        uint32_t c = hist[tid >> 5][d] + hist[tid >> 5][d + 32u];
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) c += (uint32_t)__shfl_xor((int)c, o);
+        if (d == 0) {
+            total[tid >> 5] = c;
+            counts[(size_t)g * 32 + (tid >> 5)] = c;
+        }
+    }
+    __syncthreads();
+    if (tid < 256) {   // 32 lanes per range bucket: the most frequent dialect, lowest DID on ties
+        const bool in = (int)d < n_dialects && top == 8u + (tid >> 5);
+        unsigned long long key = in ? (((unsigned long long)total[d] + 1ull) << 5) | (31u - d) : 0ull;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+            const unsigned long long other = __shfl_xor(key, o);
+            key = other > key ? other : key;
+        }
+        if (d == 0) sub[(size_t)g * 8 + (tid >> 5)] = key ? (uint8_t)(31u - (uint32_t)(key & 31u)) : 255u;
+    }
+}
+
 }  // namespace fb4

@@ -200,6 +200,31 @@ def test_salient_token_choice_of_as_many_frames_as_a_launch_of_large_workgroups_
     assert torch.equal(got.view(-1), torch.arange(frames, dtype=torch.int32, device="cuda"))
 
 
+# Both sides of the limits of the kernel with a workgroup per group (rows, rows x groups, groups, blocks per row for 8, 4, 2
+# and 1 metadata words per load), more rows than it looks through at a time, every row in one group, one dialect everywhere
+@pytest.mark.parametrize("rows,nb,groups,share", [(1, 1, 1, 1.0), (16385, 8, 3, 1.0), (32768, 136, 256, 0.05), (32768, 144, 8, 0.05), (32769, 96, 5, 0.2),
+                                                  (16384, 8, 512, 0.3), (16384, 8, 513, 0.3), (3000, 104, 9, 0.5), (3000, 108, 9, 0.5), (999, 70, 2, 0.9),
+                                                  (999, 74, 2, 0.9), (777, 43, 4, 0.6), (777, 45, 4, 0.6), (5000, 36, 1, 1.0), (40, 41, 60, 0.5)])
+def test_seda_profile_by_group(F, rows, nb, groups, share):
+    test_seda_profile_shapes(F, rows, nb, groups, share)
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 4])
+def test_seda_profile_alignment_and_concentration(F, offset):
+    # metadata that start 0, 2, 4 and 8 bytes past a 16-byte boundary; every block the same dialect, every row the same group
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    rows, nb = 2000, 96
+    buf = torch.full((rows * nb + 8,), 9 | (130 << 8), dtype=torch.int32).to(torch.int16).cuda()
+    group = torch.full((rows,), 3, dtype=torch.int32, device="cuda")
+    counts, sub = F.fb4_seda_profile(luts, buf[offset:offset + rows * nb].view(rows, nb), group, 5)
+    torch.cuda.synchronize()
+    assert int(counts[3, 9]) == rows * nb and int(counts.sum()) == rows * nb
+    want = [min(d for d in range(32) if DEFAULT_FORMATBOOK[d][7] == 8 + k) for k in range(8)]
+    want[DEFAULT_FORMATBOOK[9][7] - 8] = 9
+    assert sub[3].tolist() == want
+    luts.free()
+
+
 # (rows, blocks per row, groups, share of anchors)
 @pytest.mark.parametrize("rows,nb,groups,share", [(0, 5, 8, 1.0), (1, 1, 8, 1.0), (63, 7, 8, 1.0), (1030, 129, 9, 0.7), (8193, 96, 64, 0.1),
                                                   (32768, 3, 256, 0.1), (32769, 3, 16, 0.1), (300, 40, 7, 0.5), (4096, 1025, 16, 0.05)])
