@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libfb4.so: the same entry points as include/fb4.h.
+"""Thin binding of libfb4.so: the same entry points as include/fb4.h, the ones that a program calls per layer through a small
+C module (csrc/fb4_pycall.c), the others through ctypes.
 
 Argument marshalling only -- every step of the quantizer runs in the library's
 HIP kernels.  PyTorch tensors are used for device memory and for the current
@@ -42,7 +43,7 @@ class fb4_opts(ctypes.Structure):
 
 
 def _load():
-    if not os.path.exists(_build.LIB):
+    if not os.path.exists(_build.LIB) or not os.path.exists(_build.CALL):
         # nothing built yet (fresh checkout): compile once; an existing library is loaded as it is
         try:
             _build.build(force=True)
@@ -83,6 +84,8 @@ def _load():
 
 _lib = _load()
 
+from . import _fb4call as _call  # noqa: E402  (linked against libfb4.so, which _load has built if need be)
+
 EXPORTS = ["fb4_version", "fb4_strerror", "fb4_workspace_bytes", "fb4_build_luts", "fb4_build_luts_host",
            "fb4_free_luts", "fb4_quantize", "fb4_quantize_seda", "fb4_decompose", "fb4_dequantize",
            "fb4_quantize_decompose", "fb4_seda_profile",
@@ -112,9 +115,10 @@ def _dp(t):
     return None if t is None else t.data_ptr()
 
 
-# The handle of a device's current stream without the Stream object around it: torch.cuda.current_stream() takes 2.8 us
-# of an 8 us call, this 0.3 us (fb4_quantize on 300 x 1152, where the launch itself takes 4.2).
+# The handle of a device's current stream without the Stream object around it: torch.cuda.current_stream() takes 2.8 us,
+# torch.cuda.current_device() and the raw handle 0.36, both from torch._C 0.2.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
 def _stream(stream):
@@ -122,7 +126,7 @@ def _stream(stream):
         return stream.cuda_stream
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_get_device())
 
 
 def _check(rc, where):
@@ -180,14 +184,13 @@ def fb4_free_luts(luts):
 
 def fb4_quantize(luts, o, x, codes=None, meta=None, stream=None):
     """x: bf16 cuda tensor [rows][cols] (row stride allowed).  Returns (codes, meta)."""
-    rows, cols = x.shape
-    if codes is None:
-        codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
-    if meta is None:
-        meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
-    rc = _lib.fb4_quantize(luts.handle, ctypes.byref(o), _dp(x), rows, cols, x.stride(0) if rows > 1 else cols,
-                           _dp(codes), _dp(meta), _stream(stream))
-    _check(rc, "fb4_quantize")
+    if codes is None or meta is None:
+        rows, cols = x.shape
+        if codes is None:
+            codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
+        if meta is None:
+            meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
+    _check(_call.quantize(luts.handle, o, x, codes, meta, _stream(stream)), "fb4_quantize")
     return codes, meta
 
 
@@ -196,28 +199,23 @@ def fb4_layernorm_quantize(luts, o, x, gamma=None, beta=None, eps=1e-6, codes=No
     """LayerNorm over the channels of each row (gamma, beta: float32 cuda [cols] or None), then quantize, in one
     pass; token_group / sub_formatbooks as in fb4_quantize_seda (optional); y_out: bf16 cuda [rows][cols] that
     receives the producer's result (checks only).  Returns (codes, meta)."""
-    rows, cols = x.shape
-    if codes is None:
-        codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
-    if meta is None:
-        meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
-    rc = _lib.fb4_layernorm_quantize(luts.handle, ctypes.byref(o), _dp(x), rows, cols,
-                                     x.stride(0) if rows > 1 else cols, _dp(gamma), _dp(beta), float(eps),
-                                     _dp(token_group), _dp(sub_formatbooks),
-                                     0 if sub_formatbooks is None else sub_formatbooks.shape[0],
-                                     _dp(codes), _dp(meta), _dp(y_out), _stream(stream))
-    _check(rc, "fb4_layernorm_quantize")
+    if codes is None or meta is None:
+        rows, cols = x.shape
+        if codes is None:
+            codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
+        if meta is None:
+            meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
+    _check(_call.layernorm_quantize(luts.handle, o, x, gamma, beta, eps, token_group, sub_formatbooks, codes, meta, y_out,
+                                    _stream(stream)), "fb4_layernorm_quantize")
     return codes, meta
 
 
 def fb4_attention_scores(q, k, mode=0, scores=None, stream=None):
     """q, k: bf16 cuda [groups][tokens][dim].  mode 0: mean |Q.K^T| over the keys, 1: mean max(Q.K^T, 0).
     Returns float32 [groups][tokens]."""
-    groups, tokens, dim = q.shape
     if scores is None:
-        scores = torch.empty((groups, tokens), dtype=torch.float32, device=q.device)
-    _check(_lib.fb4_attention_scores(_dp(q), _dp(k), groups, tokens, dim, int(mode), _dp(scores), _stream(stream)),
-           "fb4_attention_scores")
+        scores = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
+    _check(_call.attention_scores(q, k, int(mode), scores, _stream(stream)), "fb4_attention_scores")
     return scores
 
 
@@ -304,30 +302,26 @@ def fb4_gelu_quantize(luts, o, x, approximate=0, codes=None, meta=None, stream=N
                       sub_formatbooks=None):
     """GeLU of every element (approximate: 0 = x Phi(x), 1 = the tanh form), then quantize, in one pass;
     token_group / sub_formatbooks as in fb4_quantize_seda (optional).  Returns (codes, meta)."""
-    rows, cols = x.shape
-    if codes is None:
-        codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
-    if meta is None:
-        meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
-    rc = _lib.fb4_gelu_quantize(luts.handle, ctypes.byref(o), _dp(x), rows, cols, x.stride(0) if rows > 1 else cols,
-                                int(approximate), _dp(token_group), _dp(sub_formatbooks),
-                                0 if sub_formatbooks is None else sub_formatbooks.shape[0],
-                                _dp(codes), _dp(meta), _stream(stream))
-    _check(rc, "fb4_gelu_quantize")
+    if codes is None or meta is None:
+        rows, cols = x.shape
+        if codes is None:
+            codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
+        if meta is None:
+            meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
+    _check(_call.gelu_quantize(luts.handle, o, x, int(approximate), token_group, sub_formatbooks, codes, meta, _stream(stream)),
+           "fb4_gelu_quantize")
     return codes, meta
 
 
 def fb4_quantize_seda(luts, o, x, token_group, sub_formatbooks, codes=None, meta=None, stream=None):
     """token_group: int32 cuda [rows]; sub_formatbooks: uint8 cuda [n_groups][8]."""
-    rows, cols = x.shape
-    if codes is None:
-        codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
-    if meta is None:
-        meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
-    rc = _lib.fb4_quantize_seda(luts.handle, ctypes.byref(o), _dp(x), rows, cols,
-                                x.stride(0) if rows > 1 else cols, _dp(token_group), _dp(sub_formatbooks),
-                                sub_formatbooks.shape[0], _dp(codes), _dp(meta), _stream(stream))
-    _check(rc, "fb4_quantize_seda")
+    if codes is None or meta is None:
+        rows, cols = x.shape
+        if codes is None:
+            codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
+        if meta is None:
+            meta = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
+    _check(_call.quantize_seda(luts.handle, o, x, token_group, sub_formatbooks, codes, meta, _stream(stream)), "fb4_quantize_seda")
     return codes, meta
 
 
@@ -351,51 +345,40 @@ def fb4_decompose(luts, o, x, codes1, meta1, salient_rows, token_group=None, sub
 def fb4_quantize_decompose(luts, o, x, salient_rows, token_group=None, sub_formatbooks=None,
                            codes1=None, meta1=None, codes2=None, meta2=None, stream=None):
     """Both planes in one call.  Returns (codes1, meta1, codes2, meta2)."""
-    rows, cols = x.shape
-    n_sal = salient_rows.numel()
-    if codes1 is None:
-        codes1 = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
-    if meta1 is None:
-        meta1 = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
-    if codes2 is None:
-        codes2 = torch.empty((n_sal, cols // 2), dtype=torch.uint8, device=x.device)
-    if meta2 is None:
-        meta2 = torch.empty((n_sal, cols // o.block), dtype=torch.int16, device=x.device)
-    rc = _lib.fb4_quantize_decompose(luts.handle, ctypes.byref(o), _dp(x), rows, cols,
-                                     x.stride(0) if rows > 1 else cols, _dp(token_group), _dp(sub_formatbooks),
-                                     0 if sub_formatbooks is None else sub_formatbooks.shape[0],
-                                     _dp(salient_rows), n_sal, _dp(codes1), _dp(meta1), _dp(codes2), _dp(meta2),
-                                     _stream(stream))
-    _check(rc, "fb4_quantize_decompose")
+    if codes1 is None or meta1 is None or codes2 is None or meta2 is None:
+        (rows, cols), n_sal = x.shape, salient_rows.numel()
+        if codes1 is None:
+            codes1 = torch.empty((rows, cols // 2), dtype=torch.uint8, device=x.device)
+        if meta1 is None:
+            meta1 = torch.empty((rows, cols // o.block), dtype=torch.int16, device=x.device)
+        if codes2 is None:
+            codes2 = torch.empty((n_sal, cols // 2), dtype=torch.uint8, device=x.device)
+        if meta2 is None:
+            meta2 = torch.empty((n_sal, cols // o.block), dtype=torch.int16, device=x.device)
+    _check(_call.quantize_decompose(luts.handle, o, x, salient_rows, token_group, sub_formatbooks, codes1, meta1, codes2, meta2,
+                                    _stream(stream)), "fb4_quantize_decompose")
     return codes1, meta1, codes2, meta2
 
 
 def fb4_dequantize(luts, codes1, meta1, block=32, codes2=None, meta2=None, salient_rows=None,
                    out=None, out_dtype=DTYPE_BF16, stream=None):
-    rows, half = codes1.shape
-    cols = half * 2
     if out is None:
-        out = torch.empty((rows, cols), dtype=torch.bfloat16 if out_dtype == DTYPE_BF16 else torch.float32,
-                          device=codes1.device)
-    n_sal = 0 if salient_rows is None else salient_rows.numel()
-    rc = _lib.fb4_dequantize(luts.handle, _dp(codes1), _dp(meta1), rows, cols, block, _dp(codes2), _dp(meta2),
-                             _dp(salient_rows), n_sal, _dp(out), out_dtype, out.stride(0) if rows > 1 else cols,
-                             _stream(stream))
-    _check(rc, "fb4_dequantize")
+        rows, half = codes1.shape
+        out = torch.empty((rows, half * 2), dtype=torch.bfloat16 if out_dtype == DTYPE_BF16 else torch.float32, device=codes1.device)
+    _check(_call.dequantize(luts.handle, codes1, meta1, block, codes2, meta2, salient_rows, out, out_dtype, _stream(stream)),
+           "fb4_dequantize")
     return out
 
 
 def fb4_repack_mxfp8(luts, codes, meta, block=32, elems=None, scales=None, stream=None):
     """One code plane as MXFP8 operands: (E4M3 bytes uint8 [rows][cols], E8M0 scale bytes uint8 [rows][cols/32])."""
-    rows, half = codes.shape
-    cols = half * 2
-    if elems is None:
-        elems = torch.empty((rows, cols), dtype=torch.uint8, device=codes.device)
-    if scales is None:
-        scales = torch.empty((rows, cols // 32), dtype=torch.uint8, device=codes.device)
-    rc = _lib.fb4_repack_mxfp8(luts.handle, _dp(codes), _dp(meta), rows, cols, block, _dp(elems),
-                               elems.stride(0) if rows > 1 else cols, _dp(scales), _stream(stream))
-    _check(rc, "fb4_repack_mxfp8")
+    if elems is None or scales is None:
+        rows, half = codes.shape
+        if elems is None:
+            elems = torch.empty((rows, half * 2), dtype=torch.uint8, device=codes.device)
+        if scales is None:
+            scales = torch.empty((rows, half * 2 // 32), dtype=torch.uint8, device=codes.device)
+    _check(_call.repack_mxfp8(luts.handle, codes, meta, block, elems, scales, _stream(stream)), "fb4_repack_mxfp8")
     return elems, scales
 
 

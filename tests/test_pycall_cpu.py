@@ -1,0 +1,64 @@
+"""The C module behind the binding: what it reads from its arguments and what it refuses, without a GPU (a null handle makes
+every entry point answer before it looks at the device)."""
+
+import ctypes
+
+import pytest
+import torch
+
+import paper_2603_02883_amd as F
+from paper_2603_02883_amd import binding as B
+
+X = torch.zeros((4, 64), dtype=torch.bfloat16)
+
+
+def calls(o, x):
+    c, m = torch.zeros((4, 32), dtype=torch.uint8), torch.zeros((4, 2), dtype=torch.int16)
+    tg, sub = torch.zeros(4, dtype=torch.int32), torch.zeros((1, 8), dtype=torch.uint8)
+    sal = torch.zeros(1, dtype=torch.int32)
+    return {
+        "quantize": lambda h: B._call.quantize(h, o, x, c, m, 0),
+        "quantize_seda": lambda h: B._call.quantize_seda(h, o, x, tg, sub, c, m, 0),
+        "quantize_decompose": lambda h: B._call.quantize_decompose(h, o, x, sal, tg, sub, c, m, c, m, 0),
+        "dequantize": lambda h: B._call.dequantize(h, c, m, 32, None, None, None, x, 0, 0),
+        "repack_mxfp8": lambda h: B._call.repack_mxfp8(h, c, m, 32, x.view(torch.uint8), m, 0),
+        "layernorm_quantize": lambda h: B._call.layernorm_quantize(h, o, x, None, None, 1e-6, tg, sub, c, m, None, 0),
+        "gelu_quantize": lambda h: B._call.gelu_quantize(h, o, x, 1, tg, sub, c, m, 0),
+    }
+
+
+def test_a_null_handle_is_an_invalid_argument():
+    for handle in (None, 0, ctypes.c_void_p(None)):
+        for name, call in calls(F.opts(), X).items():
+            assert call(handle) == F.ERR_INVALID_ARG, name
+    # two dimensions are what the matrices have, three what the scores' operands have
+    q = torch.zeros((1, 0, 8), dtype=torch.bfloat16)
+    assert B._call.attention_scores(q, q, 0, None, 0) == F.OK
+    assert B._call.attention_scores(q, q, 2, None, 0) == F.ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("x,error", [(torch.zeros(64), ValueError), (torch.zeros((1, 4, 64)), ValueError), (object(), AttributeError), (None, AttributeError)])
+def test_what_is_no_matrix_is_refused(x, error):
+    c = torch.zeros((4, 32), dtype=torch.uint8)
+    with pytest.raises(error):
+        B._call.quantize(None, F.opts(), x, c, c, 0)
+    with pytest.raises(error):
+        B._call.attention_scores(x if x is None or not isinstance(x, torch.Tensor) or x.dim() != 3 else x[0], x, 0, c, 0)
+
+
+def test_handles_options_and_counts_are_checked():
+    for name, call in calls(F.opts(), X).items():
+        with pytest.raises(TypeError):
+            call(ctypes.c_int32(1))          # four bytes are no handle
+        with pytest.raises((TypeError, BufferError)):
+            call(X)
+    for name, call in calls(ctypes.c_void_p(1), X).items():
+        if name not in ("dequantize", "repack_mxfp8"):
+            with pytest.raises(TypeError):
+                call(None)                   # eight bytes are no fb4_opts
+    with pytest.raises(TypeError):
+        B._call.quantize(None, F.opts(), X)
+    for call in (lambda h: B._call.quantize_seda(h, F.opts(), X, None, None, None, None, 0),
+                 lambda h: B._call.quantize_decompose(h, F.opts(), X, None, None, None, None, None, None, None, 0)):
+        with pytest.raises(AttributeError):  # these lists have to be there
+            call(None)
