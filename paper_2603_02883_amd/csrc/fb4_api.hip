@@ -75,26 +75,28 @@ int launch_quant(const fb4_opts* o, int grid, hipStream_t s, const QuantParams& 
 // workload with 8 wavefronts each (SeDA: 25.7 against 27.2; 4, 12 or 16 wavefronts are slower too), and the
 // kernels are free to use up to 256 vector registers per lane.  The exhaustive selector without candidate
 // restrictions runs 12 wavefronts (37.7 against 39.1 us).
-// kSedaToo = false: the variants with SeDA lists are not instantiated (`seda` must be false).
-template <int kBlock, int G, bool kFlat, int kMode, int kThreads = kFastThreads, bool kSedaToo = true>
-void launch_fast_variant(bool ts, bool seda, int n_cu, hipStream_t s, const FastParams& f)
+template <int kBlock, int G, bool kFlat, bool kTwoStage, bool kSeda, int kMode, int kThreads>
+void launch_one(int n_cu, hipStream_t s, const FastParams& f)
 {
     // (fewer tiles than the chip has wavefronts are spread over the compute units, not packed into full workgroups:
     // 300 x 1152 4.03 us packed, 3.47 spread; exhaustive, 500 x 3072, 8.5 and 6.35; block 16 with SeDA lists and the
     // range filter, 2000 x 1152, 5.47 and 5.25; 1000 x 3072 4.24 and 4.28; same from 3000 x 3072 on)
     const unsigned groups = std::min(f.n_tiles, (unsigned)n_cu);
     // (the leading arguments repeat fields of f: see the kernel)
-#define FB4_FAST_ARGS f.blob, f.x, f.n_blocks, f.n_tiles, f.div_mul, f.div_shift, f.nb, groups, f.row_stride, f.salient, f
+    hipLaunchKernelGGL((quantize_lut_kernel<kBlock, G, kFlat, kTwoStage, kSeda, kMode, kThreads>), dim3(groups), dim3(kThreads), 0, s, f.blob,
+                       f.x, f.n_blocks, f.n_tiles, f.div_mul, f.div_shift, f.nb, groups, f.row_stride, f.salient, f);
+}
+
+template <int kBlock, int G, bool kFlat, int kMode>
+void launch_fast_variant(bool ts, bool seda, int n_cu, hipStream_t s, const FastParams& f)
+{
     if (seda) {
-        if constexpr (kSedaToo) {
-            if (ts) hipLaunchKernelGGL((quantize_lut_kernel<kBlock, G, kFlat, true, true, kMode, kThreads>), dim3(groups), dim3(kThreads), 0, s, FB4_FAST_ARGS);
-            else hipLaunchKernelGGL((quantize_lut_kernel<kBlock, G, kFlat, false, true, kMode, kThreads>), dim3(groups), dim3(kThreads), 0, s, FB4_FAST_ARGS);
-        }
+        if (ts) launch_one<kBlock, G, kFlat, true, true, kMode, kFastThreads>(n_cu, s, f);
+        else launch_one<kBlock, G, kFlat, false, true, kMode, kFastThreads>(n_cu, s, f);
     } else {
-        if (ts) hipLaunchKernelGGL((quantize_lut_kernel<kBlock, G, kFlat, true, false, kMode, kThreads>), dim3(groups), dim3(kThreads), 0, s, FB4_FAST_ARGS);
-        else hipLaunchKernelGGL((quantize_lut_kernel<kBlock, G, kFlat, false, false, kMode, kThreads>), dim3(groups), dim3(kThreads), 0, s, FB4_FAST_ARGS);
+        if (ts) launch_one<kBlock, G, kFlat, true, false, kMode, kFastThreads>(n_cu, s, f);
+        else launch_one<kBlock, G, kFlat, false, false, kMode, kFastThreads>(n_cu, s, f);
     }
-#undef FB4_FAST_ARGS
 }
 
 // Second-plane outputs of the fused quantize + decompose call.
@@ -163,8 +165,8 @@ bool launch_fast(const fb4_luts* luts, const fb4_opts* opts, const QuantParams& 
                 if (opts->block == 32) launch_fast_variant<32, 0, false, 0>(ts, seda, ng, s, f);
                 else launch_fast_variant<16, 0, false, 0>(ts, seda, ng, s, f);
             } else {
-                if (opts->block == 32) launch_fast_variant<32, 0, false, 0, 768, false>(false, false, ng, s, f);
-                else launch_fast_variant<16, 0, false, 0, 768, false>(false, false, ng, s, f);
+                if (opts->block == 32) launch_one<32, 0, false, false, false, 0, 768>(ng, s, f);
+                else launch_one<16, 0, false, false, false, 0, 768>(ng, s, f);
             }
         }
     } else if (fused) {
@@ -184,7 +186,11 @@ bool launch_fast(const fb4_luts* luts, const fb4_opts* opts, const QuantParams& 
             launch_fast_variant<32, 32, false, 0>(ts, seda, ng, s, f);
         }
     } else {
-        if (opts->num_groups == 8) launch_fast_variant<16, 8, false, 0>(ts, seda, ng, s, f);
+        // (block 16 with lists and the range filter: 12 wavefronts from 10 tiles per compute unit on, us with 8 / 12: 13000 x 1152 11.8 / 11.2, 16384 x 3072 29.0 / 28.0, 65536 x
+        // 3072 101.9 / 97.6, 16000 x 1152 12.65 / 12.95, 3600 x 1152 5.4 / 5.6.  With one of the two, or none, 12 are slower:
+        // 65536 x 3072 with lists 94.9 / 96.8, 40000 x 12288 219 / 232)
+        if (opts->num_groups == 8 && ts && seda && f.n_tiles > 10u * (uint32_t)ng) launch_one<16, 8, false, true, true, 0, 768>(ng, s, f);
+        else if (opts->num_groups == 8) launch_fast_variant<16, 8, false, 0>(ts, seda, ng, s, f);
         else launch_fast_variant<16, 16, false, 0>(ts, seda, ng, s, f);
     }
     *rc = hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;

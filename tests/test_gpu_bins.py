@@ -58,3 +58,18 @@ def test_every_pattern_near_the_block_maximum(F, block, selector, groups, two_st
         c, m = O.quantize(DEFAULT_FORMATBOOK, bits, block=block, selector=sel, num_groups=groups, flags=o.flags, **kw)
         assert np.array_equal(got[1].cpu().numpy().view(np.uint16), m)
         assert np.array_equal(got[0].cpu().numpy(), c)
+
+
+@pytest.mark.parametrize("rows", [2000, 4551, 4552, 9000])
+def test_block_16_lists_and_range_filter_on_both_sides_of_the_wavefront_rule(F, rows):
+    # 36 chunks per row: 2560 tiles of 64 chunks are 10 per compute unit
+    cols = 1152
+    x = synth.mixture_activation(rows=rows, cols=cols, seed=rows, device="cuda", n_components=6)[0]
+    tg = (np.arange(rows) % 7 - 1).astype(np.int32)
+    sub = synth.seda_sub_formatbooks(DEFAULT_FORMATBOOK, n_groups=6, seed=2)
+    o = F.opts(block=16, num_groups=8, flags=F.FLAG_TWO_STAGE)
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    codes, meta = F.fb4_quantize_seda(luts, o, x, torch.from_numpy(tg).cuda(), torch.from_numpy(sub).cuda())
+    torch.cuda.synchronize()
+    c, m = O.quantize(DEFAULT_FORMATBOOK, synth.bf16_bits(x), block=16, num_groups=8, flags=o.flags, token_group=tg, sub_formatbooks=sub)
+    assert np.array_equal(meta.cpu().numpy().view(np.uint16), m) and np.array_equal(codes.cpu().numpy(), c)
