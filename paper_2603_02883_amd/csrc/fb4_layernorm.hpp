@@ -196,10 +196,11 @@ __device__ __noinline__ RowNorm layernorm_row_plain(const uint16_t* xrow, uint32
 // producer against its definition; production launches never use it).
 // A first walk over the bundle's chunks forms the sums, a last walk normalizes and quantizes them.  Two chunk buffers per
 // lane: the last two chunks of the first walk stay in them, so that up to two chunks per lane x is read once, and of B
-// chunks B - 2 again.  (All of them again, from the L2 cache as far as it holds the bundles of all wavefronts, 4.7 MB of an
-// XCD's 4: 16384 x 3072 32.8 us instead of 30.7, 8000 x 8192 50.8 and 41.9, 4000 x 12288 41.7 and 38.6.  Fewer vector
-// instructions, or the second reads requested earlier, change nothing: the memory traffic is the bound.  Holding the whole bundle in registers leaves
-// room for 8 wavefronts per CU only, or spills: 42-62 us.)
+// chunks B - 2 again.  All of them again: 16384 x 3072 32.8 us instead of 30.7, 8000 x 8192 50.8 and 41.9, 4000 x 12288 41.7
+// and 38.6.  (201 MB then went through the L2 caches on 16384 x 3072, now 134; from beyond them 126 MB, now 121: the bundles
+// of an XCD's wavefronts, 4.7 MB, do not fit its 4 MB.  32 of 535 vector instructions less, or the second reads requested a
+// step earlier, changed nothing.  Holding the whole bundle in registers leaves room for 8 wavefronts per CU only, or
+// spills: 42-62 us.)
 // kBlock, G: block size (32 or 16) and number of groups of the online selector (Sec. 3.2, Sec. 4.1).
 template <int B, int kBlock, int G, bool kTwoStage, bool kSeda, bool kWriteY, int kThreads = ln_threads(B, G)>
 __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
