@@ -90,6 +90,19 @@ def layernorm_bundles(rows, cols, num_groups):
                                                               (6501, 3072, 3, 2), (3100, 6176, 4, 1), (2100, 9216, 5, 1), (2101, 12288, 6, 1)])
 def test_layernorm_of_more_bundles_than_wavefronts(F, rows, cols, chunks, rows_per_bundle, block, g):
     assert layernorm_bundles(rows, cols, g) == (chunks, rows_per_bundle, False)
+    layernorm_against_two_steps(F, rows, cols, block, g)
+
+
+# (with 16 groups, whose kernels run fewer wavefronts from two chunks on, one round of longer bundles instead of two)
+@pytest.mark.parametrize("block", [32, 16])
+@pytest.mark.parametrize("rows,cols,g,bundles", [(6501, 1024, 8, (1, 2, False)), (6501, 1024, 16, (2, 4, True)),
+                                                 (3300, 2048, 8, (1, 1, False)), (3300, 2048, 16, (2, 2, True))])
+def test_layernorm_where_the_groups_decide_the_bundles(F, rows, cols, g, bundles, block):
+    assert layernorm_bundles(rows, cols, g) == bundles
+    layernorm_against_two_steps(F, rows, cols, block, g)
+
+
+def layernorm_against_two_steps(F, rows, cols, block, g):
     luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
     x = synth.vdit_activation(rows=rows, cols=cols, seed=cols, device="cuda")
     gamma, beta = synth.layernorm_affine(cols, seed=cols)
