@@ -121,6 +121,66 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _get_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
+class CtypesCall:
+    """The calls of csrc/fb4_pycall.c through ctypes, with the same arguments: the C module hands over here whatever it does not
+    read itself (other types than its own, other shapes, errors)."""
+
+    @staticmethod
+    def _matrix(x):
+        rows, cols = x.shape
+        return _dp(x), rows, cols, x.stride(0) if rows > 1 else cols
+
+    @staticmethod
+    def _lists(token_group, sub_formatbooks):
+        return _dp(token_group), _dp(sub_formatbooks), 0 if sub_formatbooks is None else sub_formatbooks.shape[0]
+
+    @staticmethod
+    def quantize(h, o, x, codes, meta, s):
+        return _lib.fb4_quantize(h, ctypes.byref(o), *CtypesCall._matrix(x), _dp(codes), _dp(meta), s)
+
+    @staticmethod
+    def quantize_seda(h, o, x, token_group, sub_formatbooks, codes, meta, s):
+        return _lib.fb4_quantize_seda(h, ctypes.byref(o), *CtypesCall._matrix(x), _dp(token_group), _dp(sub_formatbooks),
+                                      sub_formatbooks.shape[0], _dp(codes), _dp(meta), s)
+
+    @staticmethod
+    def quantize_decompose(h, o, x, salient_rows, token_group, sub_formatbooks, codes1, meta1, codes2, meta2, s):
+        matrix, n_sal = CtypesCall._matrix(x), salient_rows.numel()
+        return _lib.fb4_quantize_decompose(h, ctypes.byref(o), *matrix, *CtypesCall._lists(token_group, sub_formatbooks),
+                                           _dp(salient_rows), n_sal, _dp(codes1), _dp(meta1), _dp(codes2), _dp(meta2), s)
+
+    @staticmethod
+    def dequantize(h, codes1, meta1, block, codes2, meta2, salient_rows, out, out_dtype, s):
+        rows, half = codes1.shape
+        n_sal = 0 if salient_rows is None else salient_rows.numel()
+        return _lib.fb4_dequantize(h, _dp(codes1), _dp(meta1), rows, half * 2, block, _dp(codes2), _dp(meta2), _dp(salient_rows),
+                                   n_sal, _dp(out), out_dtype, out.stride(0) if rows > 1 else half * 2, s)
+
+    @staticmethod
+    def repack_mxfp8(h, codes, meta, block, elems, scales, s):
+        rows, half = codes.shape
+        return _lib.fb4_repack_mxfp8(h, _dp(codes), _dp(meta), rows, half * 2, block, _dp(elems),
+                                     elems.stride(0) if rows > 1 else half * 2, _dp(scales), s)
+
+    @staticmethod
+    def layernorm_quantize(h, o, x, gamma, beta, eps, token_group, sub_formatbooks, codes, meta, y_out, s):
+        return _lib.fb4_layernorm_quantize(h, ctypes.byref(o), *CtypesCall._matrix(x), _dp(gamma), _dp(beta), float(eps),
+                                           *CtypesCall._lists(token_group, sub_formatbooks), _dp(codes), _dp(meta), _dp(y_out), s)
+
+    @staticmethod
+    def gelu_quantize(h, o, x, approximate, token_group, sub_formatbooks, codes, meta, s):
+        return _lib.fb4_gelu_quantize(h, ctypes.byref(o), *CtypesCall._matrix(x), approximate,
+                                      *CtypesCall._lists(token_group, sub_formatbooks), _dp(codes), _dp(meta), s)
+
+    @staticmethod
+    def attention_scores(q, k, mode, scores, s):
+        groups, tokens, dim = q.shape
+        return _lib.fb4_attention_scores(_dp(q), _dp(k), groups, tokens, dim, mode, _dp(scores), s)
+
+
+_call.bind(fb4_opts, ctypes.c_void_p, CtypesCall)
+
+
 def _stream(stream):
     if stream is not None:
         return stream.cuda_stream

@@ -3,6 +3,7 @@ every entry point answer before it looks at the device)."""
 
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
@@ -46,19 +47,59 @@ def test_what_is_no_matrix_is_refused(x, error):
         B._call.attention_scores(x if x is None or not isinstance(x, torch.Tensor) or x.dim() != 3 else x[0], x, 0, c, 0)
 
 
+class Wider(B.fb4_opts):
+    _fields_ = [("more", ctypes.c_int32)]
+
+
 def test_handles_options_and_counts_are_checked():
+    """By type, as ctypes checks the same arguments: neither any four or eight bytes are a handle nor any sixteen options."""
     for name, call in calls(F.opts(), X).items():
-        with pytest.raises(TypeError):
-            call(ctypes.c_int32(1))          # four bytes are no handle
-        with pytest.raises((TypeError, BufferError)):
-            call(X)
-    for name, call in calls(ctypes.c_void_p(1), X).items():
-        if name not in ("dequantize", "repack_mxfp8"):
-            with pytest.raises(TypeError):
-                call(None)                   # eight bytes are no fb4_opts
+        for wrong in (ctypes.c_int32(1), ctypes.c_int64(0), ctypes.c_double(0.0), np.zeros(1, np.int64), np.int64(0), 0.0, X):
+            with pytest.raises(ctypes.ArgumentError):
+                call(wrong)
+        for null in (False, ctypes.POINTER(ctypes.c_int)()):
+            assert call(null) == F.ERR_INVALID_ARG, name
+    for wrong, error in ((bytes(16), TypeError), (np.zeros(4, np.int32), TypeError), (None, TypeError), (ctypes.byref(F.opts()), TypeError),
+                         ((ctypes.c_int32 * 4)(), ctypes.ArgumentError), (ctypes.pointer(F.opts()), ctypes.ArgumentError)):
+        for name, call in calls(wrong, X).items():
+            if name not in ("dequantize", "repack_mxfp8"):
+                with pytest.raises(error):
+                    call(None)
+    for name, call in calls(Wider(32, F.SEL_LUT, 8, 0, 5), X).items():
+        assert call(None) == F.ERR_INVALID_ARG, name
     with pytest.raises(TypeError):
         B._call.quantize(None, F.opts(), X)
     for call in (lambda h: B._call.quantize_seda(h, F.opts(), X, None, None, None, None, 0),
                  lambda h: B._call.quantize_decompose(h, F.opts(), X, None, None, None, None, None, None, None, 0)):
         with pytest.raises(AttributeError):  # these lists have to be there
             call(None)
+
+
+class Like:
+    """What has a tensor's methods."""
+
+    def __init__(self, shape):
+        self.shape = shape
+
+    def data_ptr(self):
+        return 64
+
+    def stride(self, dim):
+        return 64
+
+
+def test_numbers_and_shapes_are_read_as_before():
+    c, m = torch.zeros((4, 32), dtype=torch.uint8), torch.zeros((4, 2), dtype=torch.int16)
+    for block, error in ((32, None), (np.int64(32), None), (2**70, None), (32.0, ctypes.ArgumentError), (None, ctypes.ArgumentError)):
+        for call in (lambda: B._call.dequantize(None, c, m, block, None, None, None, X, 0, 0), lambda: B._call.repack_mxfp8(None, c, m, block, c, m, 0)):
+            if error is None:
+                assert call() == F.ERR_INVALID_ARG
+            else:
+                with pytest.raises(error):
+                    call()
+    for eps in (1, 1e-6, "1e-6", np.float32(1e-6), torch.tensor(1e-6)):
+        assert B._call.layernorm_quantize(None, F.opts(), X, None, None, eps, None, None, c, m, None, 0) == F.ERR_INVALID_ARG
+    for shape in ((4, 64), [4, 64], np.array([4, 64])):
+        assert B._call.quantize(None, F.opts(), Like(shape), c, m, 0) == F.ERR_INVALID_ARG
+    with pytest.raises(ctypes.ArgumentError):
+        B._call.quantize(None, F.opts(), Like((4.0, 64)), c, m, 0)
