@@ -1,5 +1,5 @@
 """Thin binding of libfb4.so: the same entry points as include/fb4.h, the ones that a program calls per layer through a small
-C module (csrc/fb4_pycall.c), the others through ctypes.
+C module (csrc/fb4_pycall.c) where there is one for this interpreter, the others through ctypes.
 
 Argument marshalling only -- every step of the quantizer runs in the library's
 HIP kernels.  PyTorch tensors are used for device memory and for the current
@@ -9,6 +9,8 @@ this module raises.
 """
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import numpy as np
@@ -43,7 +45,7 @@ class fb4_opts(ctypes.Structure):
 
 
 def _load():
-    if not os.path.exists(_build.LIB) or not os.path.exists(_build.CALL):
+    if not os.path.exists(_build.LIB):
         # nothing built yet (fresh checkout): compile once; an existing library is loaded as it is
         try:
             _build.build(force=True)
@@ -84,8 +86,6 @@ def _load():
 
 _lib = _load()
 
-from . import _fb4call as _call  # noqa: E402  (linked against libfb4.so, which _load has built if need be)
-
 EXPORTS = ["fb4_version", "fb4_strerror", "fb4_workspace_bytes", "fb4_build_luts", "fb4_build_luts_host",
            "fb4_free_luts", "fb4_quantize", "fb4_quantize_seda", "fb4_decompose", "fb4_dequantize",
            "fb4_quantize_decompose", "fb4_seda_profile",
@@ -123,7 +123,7 @@ _get_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 class CtypesCall:
     """The calls of csrc/fb4_pycall.c through ctypes, with the same arguments: the C module hands over here whatever it does not
-    read itself (other types than its own, other shapes, errors)."""
+    read itself (other types than its own, other shapes, errors), and where there is no module every call comes here."""
 
     @staticmethod
     def _matrix(x):
@@ -178,7 +178,24 @@ class CtypesCall:
         return _lib.fb4_attention_scores(_dp(q), _dp(k), groups, tokens, dim, mode, _dp(scores), s)
 
 
-_call.bind(fb4_opts, ctypes.c_void_p, CtypesCall)
+def _load_call():
+    """The C module of this interpreter (by its path: a module of another one is not taken), built if it is missing and can be."""
+    if not os.path.exists(_build.CALL):
+        try:
+            if not _build.can_build_call():
+                return CtypesCall
+            _build.build_call()
+        except (OSError, RuntimeError):   # (a folder that cannot be written, an interpreter that the source does not compile for)
+            return CtypesCall
+    name = __package__ + "._fb4call"
+    loader = importlib.machinery.ExtensionFileLoader(name, _build.CALL)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location(name, _build.CALL, loader=loader))
+    loader.exec_module(module)
+    module.bind(fb4_opts, ctypes.c_void_p, CtypesCall)
+    return module
+
+
+_call = _load_call()
 
 
 def _stream(stream):

@@ -2,6 +2,10 @@
 every entry point answer before it looks at the device)."""
 
 import ctypes
+import os
+import subprocess
+import sys
+import sysconfig
 
 import numpy as np
 import pytest
@@ -103,3 +107,37 @@ def test_numbers_and_shapes_are_read_as_before():
         assert B._call.quantize(None, F.opts(), Like(shape), c, m, 0) == F.ERR_INVALID_ARG
     with pytest.raises(ctypes.ArgumentError):
         B._call.quantize(None, F.opts(), Like((4.0, 64)), c, m, 0)
+
+
+def test_the_module_is_this_interpreters_and_not_needed(tmp_path):
+    """Its file carries the interpreter's tag; without it and without what builds it the same calls go through ctypes, and the
+    library that is there is not compiled again."""
+    assert os.path.basename(B._build.CALL) == "_fb4call" + sysconfig.get_config_var("EXT_SUFFIX") != "_fb4call.so"
+    assert B._call.__name__.endswith("_fb4call") and B._call.__file__ == B._build.CALL
+    package = os.path.dirname(B.__file__)
+    root = tmp_path / "paper_2603_02883_amd"
+    root.mkdir()
+    for f in ("__init__.py", "binding.py", "build.py", "csrc", "libfb4.so"):
+        os.symlink(os.path.join(package, f), root / f)
+    os.symlink(os.path.join(os.path.dirname(package), "include"), tmp_path / "include")
+    (root / "_fb4call.so").write_bytes(b"another interpreter's")
+    program = ("import torch, paper_2603_02883_amd as F; from paper_2603_02883_amd import binding as B; "
+               "print(B._call is B.CtypesCall, B._call.quantize(None, F.opts(), torch.zeros((2, 32)), None, None, 0))")
+    for env, through_ctypes in (({"CC": "no-such-compiler"}, True), ({"CC": "false"}, True), ({}, False)):
+        r = subprocess.run([sys.executable, "-c", program], cwd=tmp_path, capture_output=True, text=True,
+                           env=dict(os.environ, PYTHONPATH=str(tmp_path), HIPCC="false", **env))
+        assert r.returncode == 0 and r.stdout.split() == [str(through_ctypes), str(F.ERR_INVALID_ARG)], r.stderr
+    assert not (root / "_build").exists() and sorted(f.name for f in root.iterdir() if f.name.startswith("_fb4call")) == [
+        os.path.basename(B._build.CALL), "_fb4call.so"]
+
+
+def test_calls_through_ctypes_answer_like_the_modules():
+    for o, h in ((F.opts(), None), (F.opts(), ctypes.c_void_p(1)), (F.opts(block=5), ctypes.c_void_p(1))):
+        for name, call in calls(o, X).items():
+            if h is None or (name not in ("dequantize", "repack_mxfp8") and o.block == 5):
+                got = call(h)
+                try:
+                    B._call, module = B.CtypesCall, B._call
+                    assert call(h) == got == F.ERR_INVALID_ARG, name
+                finally:
+                    B._call = module
