@@ -409,7 +409,7 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
             uint4 r0[kAtOnce], r1[kAtOnce];
 #pragma unroll
             for (int j = 0; j < kAtOnce; ++j) {
-                const uint8_t* row = lds + K.row_base + gbin[8 * c + j0 + j] * (32u * kRowCopies);
+                const uint8_t* row = lds + (K.row_base + gbin[8 * c + j0 + j] * (32u * kRowCopies));   // (row_base: modulo 2^32)
                 r0[j] = *reinterpret_cast<const uint4*>(row);
                 r1[j] = *reinterpret_cast<const uint4*>(row + 16 * kRowCopies);
             }
