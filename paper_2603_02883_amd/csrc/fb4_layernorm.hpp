@@ -247,6 +247,10 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
     // last walk begins: only the other B - 2 are read again.  A buffer is requested anew as soon as its chunk has been read
     // for the last time; the last walk's order (B - 2, B - 1, 0 .. B - 3) frees buf[0], then buf[1], at its end for the next
     // bundle's first two chunks.
+    // Six chunks and 16 groups: behind the selection, whose registers the buffer would take (4 to 14 spilled; 10000 x 12288 with
+    // the range filter 99.8 us and 96.7 so, with lists 102.9 and 97.6, block 16 with lists 141.8 and 125.4; with both restrictions
+    // nothing spills: 93.2 and 98.0 so).
+    constexpr bool kLateRequest = B == 6 && G > 8 && !(kTwoStage && kSeda);
     uint32_t buf[2][16];
     int32_t gbuf[2] = {-1, -1};
     // (Only by a wavefront that has a bundle: requests of the others, all for the last row, stand before the tables' loads.
@@ -379,6 +383,11 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
             const int j = B == 1 ? 0 : s < 2 ? B - 2 + s : s - 2, at = B == 1 ? 0 : (B + s) & 1;
             const int32_t grp = gbuf[at];
             const uint32_t (&w)[16] = buf[at];
+            auto next = [&]() {   // the chunk that this buffer takes
+                if (B == 1) request(u_next, 0, buf[at], gbuf[at]);
+                else if (s + 2 < B) request(u, s, buf[at], gbuf[at]);
+                else request(u_next, s + 2 - B, buf[at], gbuf[at]);
+            };
             const float4* g4 = reinterpret_cast<const float4*>(lds_gamma) + cb[j];
             const float4* b4 = reinterpret_cast<const float4*>(lds_beta) + cb[j];
             const uint32_t gb = u * per_bundle + lane + 64u * j;
@@ -396,10 +405,10 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
                 y[2 * q + 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(y23, bf16x2));
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (B == 1) request(u_next, 0, buf[at], gbuf[at]);
-            else if (s + 2 < B) request(u, s, buf[at], gbuf[at]);
-            else request(u_next, s + 2 - B, buf[at], gbuf[at]);
-            __builtin_amdgcn_sched_barrier(0);
+            if (!kLateRequest) {
+                next();
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if constexpr (kWriteY) {
                 if (ok[j]) {
                     uint32_t v[16];
@@ -425,6 +434,7 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
                 const bool al = meta_aligned && (((gb - lane) & 7u) == 0u);
                 store_tile<kBlock>(sp, gb, lane, make_uint4(code[0], code[1], code[2], code[3]), meta, al, ok[j]);
             }
+            if (kLateRequest) next();
             __builtin_amdgcn_sched_barrier(0);
         }
         u = u_next;
