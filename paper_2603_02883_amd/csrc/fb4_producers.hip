@@ -64,12 +64,14 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
     if ((rc = check_device(luts)) != FB4_OK) return rc;
     // Chunks per lane B and rows per bundle.  If with the fewest chunks that hold a row every wavefront gets one bundle at
     // most, these: the shortest chain (us, 1 / 2 / 3 / 4 chunks: 300 x 1152 5.0 / 7.1 / 8.7 / 10.9, 3000 x 1024 6.4 / 7.7 /
-    // 9.7 / 11.9, 60000 x 96 13.0 / 19.3 / 23.6 / 31.6).  Otherwise the least cost among B <= 4: instructions of a bundle
-    // (500 per chunk, 45 + 10 B per row, 60), more from two chunks on, which are not all kept from the first walk to the
-    // last (kReread), times the rounds of bundles that the chip's wavefronts take, half of it as if the last round were
-    // full; rows longer than 8192 need 5 or 6.  us with 1 / 2 / 3 / 4 chunks, the choice starred: 16384 x 1152 19.1 / 19.1* / 19.4 / 21.0,
-    // 40000 x 1152 40.5 / 36.9 / 33.6* / 38.1, 9000 x 1600 14.2* / 15.4 / 16.3 / 17.0, 65536 x 320 19.6* / 24.6 / 24.8 / 27.8,
-    // 40000 x 2400 - / 76.3 / 68.4* / 70.8, 16384 x 3072 - / 36.3 / 31.6* / 38.7, 5000 x 3072 - / 14.6 / 15.6* / 18.2.
+    // 9.7 / 11.9, 60000 x 96 13.0 / 19.3 / 23.6 / 31.6).  Otherwise the least cost among B <= 4: chunks and rows of a bundle,
+    // times the bundles and a start of every wavefront; a chunk costs more from two on, which are not all kept from the first
+    // walk to the last, and with 16 groups, whose kernels run eight wavefronts instead of twelve then (kChunk, fitted to 806
+    // shapes in four forms: 0.3 and 0.4 % above the best choice on average; at most 10 and 13 %, 12250 x 1536 with one round of
+    // three chunks); rows longer than 8192 need 5 or 6.  us with 1 / 2 / 3 / 4 chunks, the choice starred: 16384 x 1152
+    // 19.6 / 19.3 / 18.2* / 19.7, 25000 x 1152 27.3 / 26.2 / 23.2* / 24.7, 5000 x 4096 - / 16.6* / 18.7 / 18.4, 9000 x 2400
+    // - / 23.8 / 20.6* / 19.6, 37841 x 1600 39.9 / 43.4 / 46.7 / 41.3*; 16 groups: 7000 x 1024 8.6* / 10.1 / 12.5 / 12.4,
+    // 9000 x 2400 - / 27.3 / 24.7 / 21.6*, 25000 x 1152 31.7 / 29.4 / 26.9* / 30.7.
     const int fewest = (int)((nb + 63) / 64);
     int B = 0;
     uint32_t rw = 0;
@@ -82,11 +84,10 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
     }
     double best = 0.0;
     for (int b = fewest; b <= 4 && rw == 0; ++b) {
+        constexpr double kChunk[2][5] = {{0.0, 1.0, 1.05, 1.01, 1.08}, {0.0, 1.0, 1.2, 1.17, 1.18}}, kRow = 0.05, kStart = 0.45;
         const int64_t r = 64 * b / nb, bundles = (rows + r - 1) / r;
-        const int threads = ln_threads(b, opts->num_groups);
-        const double rounds = (double)bundles / ((double)luts->n_cu * (threads / 64)), whole = (double)(int64_t)rounds + 1.0;
-        constexpr double kReread[5] = {0.0, 1.0, 1.1, 1.14, 1.22};
-        const double cost = (500.0 * b + (45.0 + 10.0 * b) * r + 60.0) * kReread[b] * (0.5 * (whole + rounds) + 0.2) * threads;
+        const int wavefronts = luts->n_cu * (ln_threads(b, opts->num_groups) / 64);
+        const double cost = (b + kRow * r) * kChunk[opts->num_groups > 8][b] * (bundles + kStart * wavefronts);
         if (B == 0 || cost < best) { best = cost; B = b; }
     }
     if (B == 0) B = fewest;
