@@ -186,10 +186,14 @@ bool launch_fast(const fb4_luts* luts, const fb4_opts* opts, const QuantParams& 
             launch_fast_variant<32, 32, false, 0>(ts, seda, ng, s, f);
         }
     } else {
-        // (block 16 with lists and the range filter: 12 wavefronts from 10 tiles per compute unit on, us with 8 / 12: 13000 x 1152 11.8 / 11.2, 16384 x 3072 29.0 / 28.0, 65536 x
-        // 3072 101.9 / 97.6, 16000 x 1152 12.65 / 12.95, 3600 x 1152 5.4 / 5.6.  With one of the two, or none, 12 are slower:
+        // (block 16 with lists and the range filter: 12 wavefronts from 10 tiles per compute unit on, where a third round of 8 is
+        // saved, but not from 33 to 44, which 8 take in five or six full rounds and 12 in three or four with the last one short.
+        // us with 8 / 12 by tiles per compute unit, 3072 channels: 8 5.3 / 5.4, 9 6.00 / 6.03, 12 6.2 / 6.2, 14 7.5 / 6.9, 20 9.9 /
+        // 9.6, 30 12.1 / 11.3, 32 12.5 / 12.4, 34 12.8 / 12.9, 40 13.4 / 13.7, 44 14.8 / 14.8, 48 15.6 / 15.3, 64 19.7 / 19.0, 96 26.6 /
+        // 25.2, 200 53.9 / 48.9; the same within 2 % with 1152, 2080, 4096 and 12288.  With one of the two, or none, 12 are slower:
         // 65536 x 3072 with lists 94.9 / 96.8, 40000 x 12288 219 / 232)
-        if (opts->num_groups == 8 && ts && seda && f.n_tiles > 10u * (uint32_t)ng) launch_one<16, 8, false, true, true, 0, 768>(ng, s, f);
+        const uint32_t per_cu = (f.n_tiles + (uint32_t)ng - 1u) / (uint32_t)ng;
+        if (opts->num_groups == 8 && ts && seda && per_cu > 10u && !(per_cu > 32u && per_cu <= 44u)) launch_one<16, 8, false, true, true, 0, 768>(ng, s, f);
         else if (opts->num_groups == 8) launch_fast_variant<16, 8, false, 0>(ts, seda, ng, s, f);
         else launch_fast_variant<16, 16, false, 0>(ts, seda, ng, s, f);
     }

@@ -73,3 +73,19 @@ def test_block_16_lists_and_range_filter_on_both_sides_of_the_wavefront_rule(F, 
     torch.cuda.synchronize()
     c, m = O.quantize(DEFAULT_FORMATBOOK, synth.bf16_bits(x), block=16, num_groups=8, flags=o.flags, token_group=tg, sub_formatbooks=sub)
     assert np.array_equal(meta.cpu().numpy().view(np.uint16), m) and np.array_equal(codes.cpu().numpy(), c)
+
+
+@pytest.mark.parametrize("rows", [14563, 14564, 20024, 20025])
+def test_block_16_lists_and_range_filter_where_eight_wavefronts_take_over_again(F, rows):
+    # 32, 33, 44 and 45 tiles per compute unit of 256, against the same rows in calls of fewer than 10
+    cols = 1152
+    x = synth.mixture_activation(rows=rows, cols=cols, seed=rows, device="cuda", n_components=6)[0]
+    tg = torch.from_numpy((np.arange(rows) % 7 - 1).astype(np.int32)).cuda()
+    sub = torch.from_numpy(synth.seda_sub_formatbooks(DEFAULT_FORMATBOOK, n_groups=6, seed=2)).cuda()
+    o = F.opts(block=16, num_groups=8, flags=F.FLAG_TWO_STAGE)
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    codes, meta = F.fb4_quantize_seda(luts, o, x, tg, sub)
+    for r in range(0, rows, 2000):
+        c, m = F.fb4_quantize_seda(luts, o, x[r:r + 2000], tg[r:r + 2000], sub)
+        assert torch.equal(meta[r:r + 2000], m) and torch.equal(codes[r:r + 2000], c), r
+    luts.free()
