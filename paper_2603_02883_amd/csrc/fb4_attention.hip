@@ -171,10 +171,11 @@ int fb4_select_salient_tokens(const float* scores, int64_t frames, int heads, in
     const int64_t at_once = 0xFFFFFFFFll / shape.threads;   // (a launch takes fewer than 2^32 threads)
     for (int64_t first = 0; first < workgroups; first += at_once) {
         const dim3 grid((unsigned)std::min(at_once, workgroups - first));
-#define FB4_SELECT_LAUNCH(t, l, m) hipLaunchKernelGGL((select_salient_kernel<t, l, m>), grid, dim3(t), 0, static_cast<hipStream_t>(stream), scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, (uint32_t)tile_rows, tile_columns, (uint32_t)shape.rows, (uint32_t)per_frame, (uint32_t)first, rows_out)
-#define FB4_SELECT_CASE(t, m)                               \
-        if (shape.lanes == 16) FB4_SELECT_LAUNCH(t, 16, m); \
-        else FB4_SELECT_LAUNCH(t, 1, m);
+#define FB4_SELECT_LAUNCH(t, l, m, many) hipLaunchKernelGGL((select_salient_kernel<t, l, m, many>), grid, dim3(t), 0, static_cast<hipStream_t>(stream), scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, (uint32_t)tile_rows, tile_columns, (uint32_t)shape.rows, (uint32_t)per_frame, (uint32_t)first, rows_out)
+#define FB4_SELECT_CASE(t, m)                                                              \
+        if (shape.lanes == 16) FB4_SELECT_LAUNCH(t, 16, m, true);                          \
+        else if (m == kSelectMaxTokens && heads < 24) FB4_SELECT_LAUNCH(t, 1, m, (m < kSelectMaxTokens)); \
+        else FB4_SELECT_LAUNCH(t, 1, m, true);
         if (shape.threads == 128) { FB4_SELECT_CASE(128, 2048) }
         else if (shape.threads == 256) { if (small) { FB4_SELECT_CASE(256, 2048) } else { FB4_SELECT_CASE(256, kSelectMaxTokens) } }
         else { if (small) { FB4_SELECT_CASE(1024, 2048) } else { FB4_SELECT_CASE(1024, kSelectMaxTokens) } }

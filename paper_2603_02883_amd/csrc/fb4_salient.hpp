@@ -563,24 +563,31 @@ __global__ __launch_bounds__(256) void probe_mfma_rate_kernel(float* out, uint32
 // ascending list.  Up to 24 head loads in flight, kLanes lanes per tile.  Bound by its chain of dependent steps -- loads,
 // maxima, compaction --, so a few frames are spread over the compute units, one row of tiles each (but 64 tokens at least):
 // 16 frames x 24 heads x 1024 tokens 5.3 us with a workgroup per frame, 3.5 so, 128 x 24 x 1350 6.6 and 5.1.  With more frames
-// the instructions count and a workgroup takes a frame (256 x 24 x 1350 8.3 against 9.4): 1024 threads with 16 lanes per tile up
-// to 256 frames, else 256 and a thread per tile, unless one round of 16 lanes holds all tiles (1024 frames x 8 heads x 1024
-// tokens with 1024 x 16 / 256 x 16 / 256 x 1 15.9 / 14.5 / 10.9, 1024 x 8 x 256 9.8 / 6.3 / 7.4).
+// the instructions count and a workgroup takes a frame (256 x 24 x 1350 8.3 against 9.4), also where more threads than twice
+// the chip holds would come of the split (128 frames of 90 x 90, tiles of 8 x 8, 9.6 against 18.1), past 384 frames (512 x 24 x
+// 13 x 61, 8 x 8, 8.4 against 9.1) and, past 128 frames, where one wavefront takes a frame's tiles at once (256 x 8 x 16 x 16,
+// 8 x 8, 3.5 against 3.7): 1024 threads with 16 lanes per tile up to 256 frames, else 256 and a thread per tile, unless one
+// round of 16 lanes holds all tiles (1024 frames x 8 heads x 1024 tokens with 1024 x 16 / 256 x 16 / 256 x 1 15.9 / 14.5 / 10.9,
+// 1024 x 8 x 256 9.8 / 6.3 / 7.4).
 struct SelectShape { int threads, lanes; int64_t rows; };   // rows: of tiles per workgroup
 inline SelectShape select_shape(int64_t frames, int64_t tile_rows, int64_t tile_columns, int64_t tile_tokens, int64_t row_tokens)
 {
     const bool wide = tile_tokens > 4;   // 16 lanes per tile
-    const int64_t rows = std::min((64 + row_tokens - 1) / row_tokens, tile_rows);
-    if (frames * ((tile_rows + rows - 1) / rows) <= 1600 && (rows < tile_rows || frames <= 256)) {
-        const int64_t n = rows * row_tokens;
-        return {n <= 128 ? 128 : n <= 512 ? 256 : 1024, wide ? 16 : 1, rows};
-    }
+    const int64_t rows = std::min((64 + row_tokens - 1) / row_tokens, tile_rows), n = rows * row_tokens;
+    const int threads = n <= 128 ? 128 : n <= 512 ? 256 : 1024;
+    const int64_t workgroups = frames * ((tile_rows + rows - 1) / rows);
+    const bool one_round = tile_rows * tile_columns * (wide ? 16 : 1) <= 64;   // all tiles of a frame, by one wavefront
+    if (workgroups <= 1600 && workgroups * threads <= 1 << 20 &&
+        (rows < tile_rows ? frames <= 384 && !(one_round && frames > 128) : frames <= 256))
+        return {threads, wide ? 16 : 1, rows};
     if (wide && tile_rows * tile_columns * 16 <= 256) return {256, 16, tile_rows};
     if (wide && frames <= 256) return {1024, 16, tile_rows};   // (256 compute units)
     return {256, 1, tile_rows};
 }
 
-template <int kSelectThreads, int kLanes, int kMaxTokens>
+// kMany: 24 heads at once.  Large frames with a thread per tile have a variant without, for fewer heads than that (64 frames x 8
+// heads x 8100 tokens, tiles of 1 x 1, 27.0 us with and 26.2 without, 24 heads 38.7 and 55.6); elsewhere it costs nothing.
+template <int kSelectThreads, int kLanes, int kMaxTokens, bool kMany>
 __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const float* scores, uint32_t heads,
                                                                         uint32_t grid_h, uint32_t grid_w, uint32_t tile_h,
                                                                         uint32_t tile_w, uint32_t th, uint32_t tw, uint32_t rows_per_workgroup,
@@ -607,7 +614,9 @@ __global__ __launch_bounds__(kSelectThreads) void select_salient_kernel(const fl
             for (int j = 0; j < N; ++j) m += (double)v[j];
             h += N;
         };
-        while (h + 24 <= heads) some(std::integral_constant<int, 24>{});
+        if (kMany) {
+            while (h + 24 <= heads) some(std::integral_constant<int, 24>{});
+        }
         while (h + 8 <= heads) some(std::integral_constant<int, 8>{});
         while (h < heads) some(std::integral_constant<int, 1>{});
         mean[t] = m / (double)heads;

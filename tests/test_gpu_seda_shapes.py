@@ -192,10 +192,27 @@ def test_salient_token_choice_of_rows_of_tiles(F, frames, heads, gh, gw, th, tw)
     test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th, tw)
 
 
+# (both sides of the limits on frames, threads and tiles from which a workgroup takes a frame; large frames with a thread per
+# tile and fewer heads than are added at once, as many, and one more)
+@pytest.mark.parametrize("frames,heads,gh,gw,th,tw", [(384, 2, 13, 61, 8, 8), (385, 2, 13, 61, 8, 8), (128, 3, 16, 16, 8, 8), (129, 3, 16, 16, 8, 8),
+                                                      (129, 3, 16, 16, 2, 2), (85, 1, 90, 90, 8, 8), (86, 1, 90, 90, 8, 8),
+                                                      (260, 23, 47, 46, 2, 2), (260, 24, 47, 46, 2, 2), (260, 25, 47, 46, 2, 2), (2, 8, 4, 1030, 4, 1)])
+def test_salient_token_choice_where_a_workgroup_takes_a_frame(F, frames, heads, gh, gw, th, tw):
+    test_salient_token_choice_shapes_ties_and_nans(F, frames, heads, gh, gw, th, tw)
+
+
 def test_salient_token_choice_of_as_many_frames_as_a_launch_of_large_workgroups_refuses(F):
     # (a workgroup of 1024 threads per frame would be 2^32 threads here, one more than a launch takes)
     frames = 1 << 22
     got = F.fb4_select_salient_tokens(torch.zeros((frames, 1, 1), device="cuda"), 1, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(-1), torch.arange(frames, dtype=torch.int32, device="cuda"))
+
+
+def test_salient_token_choice_of_more_frames_than_one_launch_takes(F):
+    # (a launch has fewer than 2^32 threads, 256 of them per frame here)
+    frames = (1 << 24) + 3
+    got = F.fb4_select_salient_tokens(torch.zeros((frames, 1, 1), device="cuda"), 1, 1, rows_out=torch.full((frames, 1), -1, dtype=torch.int32, device="cuda"))
     torch.cuda.synchronize()
     assert torch.equal(got.view(-1), torch.arange(frames, dtype=torch.int32, device="cuda"))
 
