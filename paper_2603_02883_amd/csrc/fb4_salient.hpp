@@ -174,7 +174,8 @@ constexpr int kDmaMaxPieces = 16;
 // queries for 80 to 96 channels.
 constexpr int dma_waves(int pieces) { return pieces <= 9 ? 3 : 2; }
 // An operand of the next 32 keys is read right behind the last MFMA that uses the present one; 65 to 72 channels on three
-// wavefronts per SIMD have no registers for that (14 would spill): theirs are read between two runs of 32 keys.
+// wavefronts per SIMD have no registers for that with more than two blocks of queries (14 would spill): theirs are read between
+// two runs of 32 keys (with one or two blocks as well, 24 x 1000 x 72 took 7.1 us, now 6.9, and 16 x 1350 8.9 and 8.7).
 constexpr bool dma_reads_early(int pieces) { return pieces != 9; }
 
 template <int kP, bool kRelu>
@@ -301,7 +302,7 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
         };
         auto compute = [&](const uint8_t* buffer, uint32_t step) {
             if (NB == 0 || step >= my_steps) return;
-            constexpr bool kEarly = dma_reads_early(kP);
+            constexpr bool kEarly = dma_reads_early(kP) || NB <= 2;
             mfma_bf16x8 a[kSteps];   // operands of 32 keys
             auto read = [&](int s, int kk) { a[s] = __builtin_bit_cast(mfma_bf16x8, *reinterpret_cast<const uint4*>(buffer + operand(s, kk))); };
 #pragma unroll
