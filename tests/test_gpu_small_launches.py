@@ -118,6 +118,38 @@ def layernorm_against_two_steps(F, rows, cols, block, g):
     luts.free()
 
 
+# Every number of chunks per lane with one bundle per wavefront and with several, whose chunks -- and their rows' groups -- are
+# requested during the bundle before
+LISTED = [(9001, 960, 1), (9001, 2048, 1), (1500, 4096, 2), (3301, 4096, 2), (25001, 768, 2), (6501, 3072, 3), (3301, 5120, 3), (20001, 2400, 3),
+          (300, 8192, 4), (3100, 6176, 4), (20001, 2400, 4), (2100, 9216, 5), (5001, 10240, 5), (300, 12288, 6), (5001, 12288, 6)]
+
+
+@pytest.mark.parametrize("two_stage", [False, True])
+@pytest.mark.parametrize("block,g", [(32, 8), (16, 8), (32, 16), (16, 16)])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 6])
+def test_layernorm_with_lists_over_bundles(F, chunks, block, g, two_stage):
+    shapes = [s for s in LISTED if s[2] == chunks and layernorm_bundles(s[0], s[1], g)[0] == chunks]
+    assert any(not layernorm_bundles(rows, cols, g)[2] for rows, cols, _ in shapes)
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    sub_h = synth.seda_sub_formatbooks(DEFAULT_FORMATBOOK, n_groups=7, seed=chunks)
+    sub_h[2] = np.arange(24, 32)             # dialects of the upper ranges only: the range filter leaves nothing for most blocks
+    sub = torch.from_numpy(sub_h).cuda()
+    o = F.opts(block=block, num_groups=g, flags=F.FLAG_TWO_STAGE if two_stage else 0)
+    for rows, cols, _ in shapes:
+        x = synth.vdit_activation(rows=rows, cols=cols, seed=cols, device="cuda")
+        x[5::97] += 30.0                     # some bundles take the walk over squared deviations as well
+        # another group from row to row, the whole formatbook (-1) and one past the table among them
+        tg = torch.from_numpy((np.random.default_rng(rows).integers(0, 9, size=rows) - 1).astype(np.int32)).cuda()
+        gamma, beta = (torch.from_numpy(a).cuda() for a in synth.layernorm_affine(cols, seed=cols))
+        y = torch.empty_like(x)
+        F.fb4_layernorm_quantize(luts, o, x, gamma, beta, 1e-6, y_out=y)
+        c, m = F.fb4_layernorm_quantize(luts, o, x, gamma, beta, 1e-6, token_group=tg, sub_formatbooks=sub)
+        c0, m0 = F.fb4_quantize_seda(luts, o, y, tg, sub)    # (against the oracle in tests of its own)
+        torch.cuda.synchronize()
+        assert torch.equal(m, m0) and torch.equal(c, c0), (rows, cols)
+    luts.free()
+
+
 @pytest.mark.parametrize("rows,cols,chunks", [(9001, 960, 1), (25001, 768, 2), (20001, 2400, 3), (3301, 5120, 3), (3100, 6176, 4),
                                               (2100, 9216, 5), (2101, 12288, 6)])
 def test_layernorm_of_large_means_and_overflowing_rows(F, rows, cols, chunks):
