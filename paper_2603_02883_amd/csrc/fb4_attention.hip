@@ -17,23 +17,27 @@ namespace {
 // compute units.  us with 1 / 2 / 3 / 4, the choice starred: 16 x 400 x 72 4.4* / 5.4 / 6.4 / 7.7, 8 x 3000 x 72 16.6 / 17.8* /
 // 22.4 / 27.6, 130 x 480 x 72 9.5 / 8.7 / 8.9* / 10.5, 24 x 4000 x 64 52.8 / 44.7 / 44.9* / 51.0, 272 x 1350 x 72 86.4 / 69.8 /
 // 66.9 / 66.1*, 384 x 1024 x 128 120.8 / 96.7 / 90.5 / 84.5*.  With up to six (`most`, 80 to 96 channels) a workgroup's time goes
-// with b + 1.4, m of them take about 0.42 + 0.58 m times as long, and a started round counts 0.6 of a whole one: 1 / .. / 6 300 x
-// 480 x 96 29.1 / 22.7 / 22.4 / 23.5 / 24.2* / 24.2, 130 x 480 x 96 12.7 / 11.9 / 10.5* / 12.3 / 11.6 / 11.2, 130 x 1350 x 96 64.0 / 49.8 /
-// 48.0 / 47.6* / 50.6 / 52.2, 272 x 700 x 96 40.9 / 33.6 / 31.1 / 31.8* / 31.8 / 33.9, 1000 x 300 x 96 with 5 24.3 and with 4 29.4 (646
-// shapes: 1.1 % above the best choice on average, 15 % at 45 x 1744).  (256 compute units as on this card: the choice decides
+// with b + 1.05, m of them take about 0.33 + 0.67 m times as long, and m is 0.48 of the rounds that the load takes, a tenth of
+// those that as many whole workgroups would, and the load itself for the rest: 1 / .. / 6 300 x 480 x 96 29.1 / 22.7 / 22.4 / 23.5 /
+// 24.2* / 24.2, 130 x 480 x 96 12.7 / 11.9 / 10.5* / 12.3 / 11.6 / 11.2, 45 x 1744 x 96 34.9 / 31.7 / 28.6* / 33.2 / 32.8 / 29.4, 130 x
+// 1350 x 96 64.0 / 49.8 / 48.0 / 47.6* / 50.6 / 52.2, 272 x 700 x 96 40.9 / 33.6 / 31.1 / 31.8* / 31.8 / 33.9, 1000 x 300 x 96 with 5 24.3
+// and with 4 29.4 (646 shapes: 1.0 % above the best choice on average).  (256 compute units as on this card: the choice decides
 // speed only.  That rows of up to 72 channels run three workgroups per compute unit and longer ones two is left out: the
 // figures above come from both.)
 uint32_t dma_blocks_per_wave(int64_t groups, uint32_t n_blk, uint32_t most)
 {
     constexpr double kCus = 256.0;
-    const double step = most > 4 ? 1.4 : 0.7, first = most > 4 ? 0.42 : 0.2, started = most > 4 ? 0.6 : 1.0;
+    const bool six = most > 4;
+    const double step = six ? 1.05 : 0.7, first = six ? 0.33 : 0.2;
     uint32_t best = most;
     double best_cost = 0.0;
     for (uint32_t b = most; b >= 1; --b) {
         const uint32_t full = n_blk / (2 * b), rest = n_blk - full * 2 * b;
         const double units = full * (b + step) + (rest ? (rest + 1) / 2 + step : 0.0);
         const double load = (double)groups * units / ((b + step) * kCus);
-        const double m = load > 1.0 ? started * (double)(int64_t)(load + 0.999) + (1.0 - started) * load : 1.0;
+        const double whole = load > 1.0 ? (double)(int64_t)(load + 0.999) : 1.0;
+        const double all = (double)((groups * (full + (rest ? 1 : 0)) + 255) / 256);   // (rounds of workgroups, the short ones too)
+        const double m = six ? std::max(1.0, 0.48 * whole + 0.1 * all + 0.42 * load) : whole;
         const double cost = (b + step) * (first + (1.0 - first) * m);
         if (b == most || cost < best_cost) { best_cost = cost; best = b; }
     }

@@ -170,19 +170,21 @@ def query_blocks_80_to_96(groups, tokens):
     n_blk, best, best_cost = (tokens + 31) // 32, 6, 0.0
     for b in (6, 5, 4, 3, 2, 1):
         full, rest = divmod(n_blk, 2 * b)
-        units = full * (b + 1.4) + ((rest + 1) // 2 + 1.4 if rest else 0.0)
-        load = groups * units / ((b + 1.4) * 256)
-        cost = (b + 1.4) * (0.42 + 0.58 * (0.6 * int(load + 0.999) + 0.4 * load if load > 1 else 1))
+        units = full * (b + 1.05) + ((rest + 1) // 2 + 1.05 if rest else 0.0)
+        load = groups * units / ((b + 1.05) * 256)
+        rounds = -(-groups * (full + (rest > 0)) // 256)
+        m = max(1.0, 0.48 * max(1, int(load + 0.999)) + 0.1 * rounds + 0.42 * load)
+        cost = (b + 1.05) * (0.33 + 0.67 * m)
         if b == 6 or cost < best_cost:
             best, best_cost = b, cost
     rest = n_blk % (2 * best)
     return best, (rest + 1) // 2, rest // 2
 
 
-@pytest.mark.parametrize("groups,tokens,blocks", [(212, 289, (5, 0, 0)), (100, 641, (5, 1, 0)), (149, 385, (5, 2, 1)), (135, 481, (5, 3, 3)),
-                                                  (261, 193, (5, 4, 3)), (212, 257, (5, 5, 4)), (387, 353, (6, 0, 0)), (569, 385, (6, 1, 0)),
-                                                  (513, 481, (6, 2, 2)), (282, 513, (6, 3, 2)), (282, 577, (6, 4, 3)), (289, 257, (6, 5, 4)), (289, 289, (6, 5, 5)),
-                                                  (130, 480, (3, 2, 1)), (130, 1350, (4, 2, 1)), (303, 129, (4, 3, 2)), (261, 161, (2, 1, 1))])
+@pytest.mark.parametrize("groups,tokens,blocks", [(205, 289, (5, 0, 0)), (51, 1281, (5, 1, 0)), (51, 1345, (5, 2, 1)), (79, 801, (5, 3, 3)),
+                                                  (261, 193, (5, 4, 3)), (205, 257, (5, 5, 4)), (387, 353, (6, 0, 0)), (303, 769, (6, 1, 0)),
+                                                  (289, 865, (6, 2, 2)), (121, 1281, (6, 3, 2)), (114, 1345, (6, 4, 3)), (296, 257, (6, 5, 4)), (296, 289, (6, 5, 5)),
+                                                  (130, 480, (3, 2, 1)), (130, 1350, (4, 2, 1)), (310, 129, (4, 3, 2)), (261, 161, (2, 1, 1))])
 def test_long_groups_with_five_and_six_query_blocks(F, groups, tokens, blocks):
     assert query_blocks_80_to_96(groups, tokens) == blocks
     for dim in (80, 88, 96):
