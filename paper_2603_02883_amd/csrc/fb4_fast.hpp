@@ -368,8 +368,8 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
     uint32_t ev[8], od[8];   // 16-bit sums of dialects (4i, 4i+2) and (4i+1, 4i+3); R == 8 keeps bytes in ev
     // ---- candidate restrictions (Sec. 3.4 SeDA, Sec. 3.2 two-stage) as rows of bytes, 0xFF = excluded.  Their
     // reads go out together with the first batch of Qerror rows, or behind the sums where registers are short: with 16
-    // groups and one restriction (GeLU, 16 wavefronts, 8000 x 3072, block 16: 104 us so and 27 with late reads; with both
-    // restrictions the early ones fit).
+    // groups and one restriction (GeLU, 16 wavefronts, 8000 x 3072, block 16: 104 us with early reads, which spill 90 to 107
+    // registers there, 27 with late ones, 7 and 8; with both restrictions early ones spill 2 and late ones 78).
     constexpr bool kLate = kLean || (R != 8 && !(kSeda && kTwoStage));
     uint4 xa0 = make_uint4(0, 0, 0, 0), xa1 = xa0, xr0 = xa0, xr1 = xa0;
     auto exclusions = [&]() {

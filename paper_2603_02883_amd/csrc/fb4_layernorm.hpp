@@ -23,7 +23,7 @@
 // registers (the same channels in every bundle, so its scale / shift addresses
 // are loop invariants), the wavefront reduces the sums per row with butterfly
 // exchanges (a fixed order: results do not change from run to run; it does depend
-// on B and RW, which the launcher picks from the row length and the number of rows), and each
+// on B and RW, which the launcher picks from the row length, the rows and the selector groups), and each
 // lane then normalizes and quantizes its chunks with the streaming kernel's
 // per-chunk routine.  Bundles are dealt like that kernel's tiles: to persistent
 // workgroups round robin, to a workgroup's wavefronts on demand.

@@ -563,13 +563,13 @@ __global__ __launch_bounds__(256) void probe_mfma_rate_kernel(float* out, uint32
 // A workgroup takes some rows of tiles of a frame: their tokens are one run of memory, their chosen tokens one run of the
 // ascending list.  Up to 24 head loads in flight, kLanes lanes per tile.  Bound by its chain of dependent steps -- loads,
 // maxima, compaction --, so a few frames are spread over the compute units, one row of tiles each (but 64 tokens at least):
-// 16 frames x 24 heads x 1024 tokens 5.3 us with a workgroup per frame, 3.5 so, 128 x 24 x 1350 6.6 and 5.1.  With more frames
+// 16 frames x 24 heads x 1024 tokens 5.1 us with a workgroup per frame, 3.1 so, 128 x 24 x 1350 6.4 and 4.8.  With more frames
 // the instructions count and a workgroup takes a frame (256 x 24 x 1350 8.3 against 9.4), also where more threads than twice
 // the chip holds would come of the split (128 frames of 90 x 90, tiles of 8 x 8, 9.6 against 18.1), past 384 frames (512 x 24 x
 // 13 x 61, 8 x 8, 8.4 against 9.1) and, past 128 frames, where one wavefront takes a frame's tiles at once (256 x 8 x 16 x 16,
 // 8 x 8, 3.5 against 3.7): 1024 threads with 16 lanes per tile up to 256 frames, else 256 and a thread per tile, unless one
-// round of 16 lanes holds all tiles (1024 frames x 8 heads x 1024 tokens with 1024 x 16 / 256 x 16 / 256 x 1 15.9 / 14.5 / 10.9,
-// 1024 x 8 x 256 9.8 / 6.3 / 7.4).
+// round of 16 lanes holds all tiles (1024 frames x 8 heads x 1024 tokens with 1024 x 16 / 256 x 16 / 256 x 1 15.5 / 9.5 / 6.8,
+// 1024 x 8 x 256 9.1 / 4.2 / 4.4, 256 x 24 x 1350 7.9 / 11.7 / 9.3).
 struct SelectShape { int threads, lanes; int64_t rows; };   // rows: of tiles per workgroup
 inline SelectShape select_shape(int64_t frames, int64_t tile_rows, int64_t tile_columns, int64_t tile_tokens, int64_t row_tokens)
 {
