@@ -360,7 +360,9 @@ __device__ __forceinline__ TileConsts make_tile_consts(uint32_t lane, uint32_t g
 // gbin: with kBinBias.  excl_a: LDS offset of this block's SeDA exclusion row (kSeda only); range_row: of the row of its
 // range (kTwoStage only: the first stage keeps the dialects whose top magnitude is the integer part of the block maximum).
 // kLean: half of the row reads at a time and the exclusion rows behind them, for kernels that are short of registers.
-template <int R, bool kTwoStage, bool kSeda, bool kLean>
+// kReadsFirst: no sum before the last read of a batch, where the compiler would read two rows at a time and wait for them
+// (LayerNorm of one chunk per lane, 16 groups, both restrictions: see there).
+template <int R, bool kTwoStage, bool kSeda, bool kLean, bool kReadsFirst>
 __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], const uint8_t* lds,
                                                     const TileConsts& K, uint32_t excl_a, uint32_t range_row)
 {
@@ -418,6 +420,7 @@ __device__ __forceinline__ uint32_t select_lut_rows(const uint32_t (&gbin)[R], c
                 r1[j] = *reinterpret_cast<const uint4*>(row + 16 * kRowCopies);
             }
             asm volatile("" ::: "memory");
+            if (kReadsFirst) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < kAtOnce; ++j) {
                 acc[0] += r0[j].x; acc[1] += r0[j].y; acc[2] += r0[j].z; acc[3] += r0[j].w;
@@ -732,7 +735,8 @@ __device__ __forceinline__ MatrixConsts make_count_consts(uint8_t* lds, uint32_t
 // (code1, meta1), which the plain routine recomputes from x.  stage: 16 words of the lane's private memory when w
 // is not in global memory at all (xb is then ignored).
 // kCounts: the calling kernel has the LDS counts that select_lut32_matrix needs (32 groups only).
-template <int kBlock, int G, bool kTwoStage, bool kSeda, bool kResidual = false, bool kCounts = false, bool kLean = false>
+template <int kBlock, int G, bool kTwoStage, bool kSeda, bool kResidual = false, bool kCounts = false, bool kLean = false,
+          bool kReadsFirst = false>
 __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint8_t* lds, const TileConsts& K,
                                              const uint16_t* xb, bool in_range, uint32_t excl_a,
                                              uint32_t (&code)[4], uint32_t& meta,
@@ -859,7 +863,7 @@ __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint
                     else if (PER == 2) gbin[r] = halves_max(b2[b * RB + r]);
                     else gbin[r] = (r & 1) ? (b2[b * RB + r / 2] >> 16) : (b2[b * RB + r / 2] & 0xFFFFu);
                 }
-                did[b] = select_lut_rows<GG, kTwoStage, kSeda, kLean>(gbin, lds, K, excl_a, range_row);
+                did[b] = select_lut_rows<GG, kTwoStage, kSeda, kLean, kReadsFirst>(gbin, lds, K, excl_a, range_row);
             }
             meta |= (did[b] | (eb << 8)) << (16 * b);
         }
