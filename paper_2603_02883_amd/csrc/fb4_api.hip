@@ -36,13 +36,9 @@ int grid_for(const fb4_luts* l, long long n_tiles)
 template <int SEL, int G, int MODE, int LPB>
 void launch_ts(bool two_stage, int grid, hipStream_t s, const QuantParams& p)
 {
-    // (the leading arguments repeat fields of p: see the kernel)
-    if (two_stage)
-        hipLaunchKernelGGL((quantize_kernel<SEL, G, MODE, true, LPB>), dim3(grid), dim3(kThreads), 0, s, p.blob, p.x,
-                           p.salient, p.n_tiles, p.tiles_per_row, grid, p.row_stride, p.cols, p);
-    else
-        hipLaunchKernelGGL((quantize_kernel<SEL, G, MODE, false, LPB>), dim3(grid), dim3(kThreads), 0, s, p.blob, p.x,
-                           p.salient, p.n_tiles, p.tiles_per_row, grid, p.row_stride, p.cols, p);
+    const QuantArgs more = {p.rows, p.codes, p.meta, p.token_group, p.sub, p.codes1, p.meta1, p.n_groups, p.n_dialects};
+    launch(two_stage ? quantize_kernel<SEL, G, MODE, true, LPB> : quantize_kernel<SEL, G, MODE, false, LPB>, dim3(grid), dim3(kThreads), 0, s,
+           p.blob, p.x, p.salient, p.n_tiles, grid, p.row_stride, p.cols, more);
 }
 
 template <int MODE>
@@ -82,9 +78,10 @@ void launch_one(int n_cu, hipStream_t s, const FastParams& f)
     // 300 x 1152 4.03 us packed, 3.47 spread; exhaustive, 500 x 3072, 8.5 and 6.35; block 16 with SeDA lists and the
     // range filter, 2000 x 1152, 5.47 and 5.25; 1000 x 3072 4.24 and 4.28; same from 3000 x 3072 on)
     const unsigned groups = std::min(f.n_tiles, (unsigned)n_cu);
-    // (the leading arguments repeat fields of f: see the kernel)
-    hipLaunchKernelGGL((quantize_lut_kernel<kBlock, G, kFlat, kTwoStage, kSeda, kMode, kThreads>), dim3(groups), dim3(kThreads), 0, s, f.blob,
-                       f.x, f.n_blocks, f.n_tiles, f.div_mul, f.div_shift, f.nb, groups, f.row_stride, f.salient, f);
+    const FastArgs more = {f.rows, f.n_sal, f.codes, f.meta, f.token_group, f.sub, kMode == 2 ? const_cast<uint8_t*>(f.codes1) : f.codes2,
+                           kMode == 2 ? const_cast<uint16_t*>(f.meta1) : f.meta2};
+    launch(quantize_lut_kernel<kBlock, G, kFlat, kTwoStage, kSeda, kMode, kThreads>, dim3(groups), dim3(kThreads), 0, s, f.blob, f.x, f.n_blocks,
+           f.n_tiles, f.div_mul, f.nb, groups, f.n_groups | f.n_dialects << 16, f.row_stride, f.salient, more);
 }
 
 template <int kBlock, int G, bool kFlat, int kMode>
@@ -131,9 +128,7 @@ bool launch_fast(const fb4_luts* luts, const fb4_opts* opts, const QuantParams& 
     f.nb = (uint32_t)nb;
     f.n_blocks = (uint32_t)n_blocks;
     f.n_tiles = (uint32_t)((n_blocks + 63) / 64);
-    uint32_t l = 0;
-    while ((1ull << l) < nb) ++l;
-    f.div_shift = 31 + l;
+    f.div_shift = div_shift_of((uint32_t)nb);
     f.div_mul = (uint32_t)(((1ull << f.div_shift) + nb - 1) / nb);
     f.codes = p.codes;
     f.meta = p.meta;
@@ -220,9 +215,7 @@ bool launch_fast_second_plane(const fb4_luts* luts, const fb4_opts* opts, const 
     f.nb = (uint32_t)nb;
     f.n_blocks = (uint32_t)n_blocks;
     f.n_tiles = (uint32_t)((n_blocks + 63) / 64);
-    uint32_t l = 0;
-    while ((1ull << l) < nb) ++l;
-    f.div_shift = 31 + l;
+    f.div_shift = div_shift_of((uint32_t)nb);
     f.div_mul = (uint32_t)(((1ull << f.div_shift) + nb - 1) / nb);
     f.codes = p.codes;
     f.meta = p.meta;
@@ -250,14 +243,14 @@ bool launch_fast_second_plane(const fb4_luts* luts, const fb4_opts* opts, const 
 }
 
 // Tiling of `out_rows` rows of `cols` columns; false if it does not fit 32-bit tile indices.
-bool tiling(int64_t out_rows, int64_t cols, int block, int* nb, int* tpr, int* n_tiles)
+bool tiling(int64_t out_rows, int64_t cols, int block, int* n_tiles, int* nb = nullptr, int* tiles_per_row = nullptr)
 {
     int64_t b = cols / block;
     int64_t t = (cols + kTileElems - 1) / kTileElems;
     // the kernels step a 32-bit tile index by the grid size: leave room for that last step
     if (b > 0x7FFFFFFF || t * out_rows > 0x7FF00000LL) return false;
-    *nb = (int)b;
-    *tpr = (int)t;
+    if (nb) *nb = (int)b;
+    if (tiles_per_row) *tiles_per_row = (int)t;
     *n_tiles = (int)(t * out_rows);
     return true;
 }
@@ -345,7 +338,7 @@ int fb4_quantize(const fb4_luts* luts, const fb4_opts* opts, const void* x, int6
     if (rc != FB4_OK || rows == 0 || cols == 0) return rc;
     if ((rc = check_device(luts)) != FB4_OK) return rc;
     QuantParams p = {};
-    if (!tiling(rows, cols, opts->block, &p.nb, &p.tiles_per_row, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
+    if (!tiling(rows, cols, opts->block, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
     p.x = static_cast<const uint16_t*>(x);
     p.row_stride = row_stride;
     p.rows = rows;
@@ -371,7 +364,7 @@ int fb4_quantize_seda(const fb4_luts* luts, const fb4_opts* opts, const void* x,
     if (!aligned(token_group, 4)) return FB4_ERR_UNSUPPORTED;
     if ((rc = check_device(luts)) != FB4_OK) return rc;
     QuantParams p = {};
-    if (!tiling(rows, cols, opts->block, &p.nb, &p.tiles_per_row, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
+    if (!tiling(rows, cols, opts->block, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
     p.x = static_cast<const uint16_t*>(x);
     p.row_stride = row_stride;
     p.rows = rows;
@@ -406,7 +399,7 @@ int fb4_decompose(const fb4_luts* luts, const fb4_opts* opts, const void* x, int
     if (n_sal > rows) return FB4_ERR_INVALID_ARG;   // ascending and unique implies n_sal <= rows
     if ((rc = check_device(luts)) != FB4_OK) return rc;
     QuantParams p = {};
-    if (!tiling(n_sal, cols, opts->block, &p.nb, &p.tiles_per_row, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
+    if (!tiling(n_sal, cols, opts->block, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
     p.x = static_cast<const uint16_t*>(x);
     p.row_stride = row_stride;
     p.rows = rows;
@@ -444,7 +437,7 @@ int fb4_quantize_decompose(const fb4_luts* luts, const fb4_opts* opts, const voi
     if (n_sal > 0) {
         // one pass: the second plane is formed from the registers that hold the tile
         QuantParams p = {};
-        if (!tiling(rows, cols, opts->block, &p.nb, &p.tiles_per_row, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
+        if (!tiling(rows, cols, opts->block, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
         p.x = static_cast<const uint16_t*>(x);
         p.row_stride = row_stride;
         p.rows = rows;
@@ -487,7 +480,7 @@ int fb4_dequantize(const fb4_luts* luts, const uint8_t* codes1, const uint16_t* 
     if (int rc = check_device(luts)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     DequantParams p = {};
-    if (!tiling(rows, cols, block, &p.nb, &p.tiles_per_row, &p.n_tiles)) return FB4_ERR_UNSUPPORTED;
+    if (!tiling(rows, cols, block, &p.n_tiles, &p.nb, &p.tiles_per_row)) return FB4_ERR_UNSUPPORTED;
     p.codes1 = codes1;
     p.meta1 = meta1;
     p.rows = rows;
@@ -509,19 +502,15 @@ int fb4_dequantize(const fb4_luts* luts, const uint8_t* codes1, const uint16_t* 
         f.out_row_stride = out_row_stride;
         f.nb = (uint32_t)nb32;
         f.n_blocks = (uint32_t)n_blocks;
-        f.n_tiles = (uint32_t)((n_blocks + 63) / 64);
-        uint32_t l = 0;
-        while ((1ull << l) < nb32) ++l;
-        f.div_shift = 31 + l;
+        f.div_shift = div_shift_of((uint32_t)nb32);
         f.div_mul = (uint32_t)(((1ull << f.div_shift) + nb32 - 1) / nb32);
         f.blob = luts->dev_blob;
-        long long groups = ((long long)f.n_tiles + kDeqWaves - 1) / kDeqWaves;
+        long long groups = ((long long)((n_blocks + 63) / 64) + kDeqWaves - 1) / kDeqWaves;
         const long long cap = (long long)luts->n_cu * 3;   // three workgroups (and their tables) per CU
         if (groups > cap) groups = cap;
         const bool flat = out_row_stride == cols;
         const dim3 dg((unsigned)groups), db(kDeqThreads);
-        // (the leading arguments repeat fields of f: see the kernel)
-#define FB4_DEQ_ARGS f.blob, f.codes, f.meta, f.n_blocks, f.meta_shift, dg.x, f
+#define FB4_DEQ_ARGS f.blob, f.codes, f.meta, f.n_blocks, f.meta_shift, dg.x, DeqFastArgs{f.out, f.out_row_stride, f.nb, f.div_mul, f.div_shift, f.n_sal, f.rows, f.codes2, f.meta2, f.salient}
         if (n_sal > 0 && rows <= (int64_t)kMaxFusedRows) {
             // salient rows get both planes in the same pass
             f.codes2 = codes2;
@@ -532,43 +521,43 @@ int fb4_dequantize(const fb4_luts* luts, const uint8_t* codes1, const uint16_t* 
             const bool early = f.n_sal <= f.rows / kDeqEarlyShare &&
                                n_blocks * 8 >= (uint64_t)groups * kDeqThreads * kDeqWords * kDeqEarlyHalfRounds;
             if (out_dtype == FB4_DTYPE_F32) {
-                if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
-                else hipLaunchKernelGGL((dequantize_fast_kernel<false, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
+                if (flat) launch(dequantize_fast_kernel<true, true, true>, dg, db, 0, s, FB4_DEQ_ARGS);
+                else launch(dequantize_fast_kernel<false, true, true>, dg, db, 0, s, FB4_DEQ_ARGS);
             } else if (early) {
-                if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, false, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
-                else hipLaunchKernelGGL((dequantize_fast_kernel<false, false, true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
+                if (flat) launch(dequantize_fast_kernel<true, false, true, true>, dg, db, 0, s, FB4_DEQ_ARGS);
+                else launch(dequantize_fast_kernel<false, false, true, true>, dg, db, 0, s, FB4_DEQ_ARGS);
             } else {
-                if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, false, true>), dg, db, 0, s, FB4_DEQ_ARGS);
-                else hipLaunchKernelGGL((dequantize_fast_kernel<false, false, true>), dg, db, 0, s, FB4_DEQ_ARGS);
+                if (flat) launch(dequantize_fast_kernel<true, false, true>, dg, db, 0, s, FB4_DEQ_ARGS);
+                else launch(dequantize_fast_kernel<false, false, true>, dg, db, 0, s, FB4_DEQ_ARGS);
             }
             return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
         }
         if (out_dtype == FB4_DTYPE_F32) {
-            if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, true>), dg, db, 0, s, FB4_DEQ_ARGS);
-            else hipLaunchKernelGGL((dequantize_fast_kernel<false, true>), dg, db, 0, s, FB4_DEQ_ARGS);
+            if (flat) launch(dequantize_fast_kernel<true, true>, dg, db, 0, s, FB4_DEQ_ARGS);
+            else launch(dequantize_fast_kernel<false, true>, dg, db, 0, s, FB4_DEQ_ARGS);
         } else {
-            if (flat) hipLaunchKernelGGL((dequantize_fast_kernel<true, false>), dg, db, 0, s, FB4_DEQ_ARGS);
-            else hipLaunchKernelGGL((dequantize_fast_kernel<false, false>), dg, db, 0, s, FB4_DEQ_ARGS);
+            if (flat) launch(dequantize_fast_kernel<true, false>, dg, db, 0, s, FB4_DEQ_ARGS);
+            else launch(dequantize_fast_kernel<false, false>, dg, db, 0, s, FB4_DEQ_ARGS);
         }
 #undef FB4_DEQ_ARGS
     } else if (out_dtype == FB4_DTYPE_F32) {
-        hipLaunchKernelGGL((dequantize_kernel<false, true>), dim3(grid), dim3(kThreads), 0, s, p);
+        launch(dequantize_kernel<false, true>, dim3(grid), dim3(kThreads), 0, s, p, grid);
     } else {
-        hipLaunchKernelGGL((dequantize_kernel<false, false>), dim3(grid), dim3(kThreads), 0, s, p);
+        launch(dequantize_kernel<false, false>, dim3(grid), dim3(kThreads), 0, s, p, grid);
     }
     if (hipGetLastError() != hipSuccess) return FB4_ERR_HIP;
     if (n_sal > 0) {
         // second pass, ordered after the first on the same stream: salient rows = plane 1 + plane 2
         DequantParams p2 = p;
-        if (!tiling(n_sal, cols, block, &p2.nb, &p2.tiles_per_row, &p2.n_tiles)) return FB4_ERR_UNSUPPORTED;
+        if (!tiling(n_sal, cols, block, &p2.n_tiles, &p2.nb, &p2.tiles_per_row)) return FB4_ERR_UNSUPPORTED;
         p2.codes2 = codes2;
         p2.meta2 = meta2;
         p2.salient = salient_rows;
         grid = grid_for(luts, p2.n_tiles);
         if (out_dtype == FB4_DTYPE_F32)
-            hipLaunchKernelGGL((dequantize_kernel<true, true>), dim3(grid), dim3(kThreads), 0, s, p2);
+            launch(dequantize_kernel<true, true>, dim3(grid), dim3(kThreads), 0, s, p2, grid);
         else
-            hipLaunchKernelGGL((dequantize_kernel<true, false>), dim3(grid), dim3(kThreads), 0, s, p2);
+            launch(dequantize_kernel<true, false>, dim3(grid), dim3(kThreads), 0, s, p2, grid);
         if (hipGetLastError() != hipSuccess) return FB4_ERR_HIP;
     }
     return FB4_OK;
@@ -597,9 +586,7 @@ int fb4_repack_mxfp8(const fb4_luts* luts, const uint8_t* codes, const uint16_t*
     f.scales = scales;
     f.nb32 = (uint32_t)nb32;
     f.n_chunks = (uint32_t)n_chunks;
-    uint32_t l = 0;
-    while ((1ull << l) < nb32) ++l;
-    f.div_shift = 31 + l;
+    f.div_shift = div_shift_of((uint32_t)nb32);
     f.div_mul = (uint32_t)(((1ull << f.div_shift) + nb32 - 1) / nb32);
     f.blob = luts->dev_blob;
     long long groups = ((long long)n_chunks * 4 + kRepackThreads - 1) / kRepackThreads;
@@ -608,11 +595,11 @@ int fb4_repack_mxfp8(const fb4_luts* luts, const uint8_t* codes, const uint16_t*
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool flat = elem_row_stride == cols;
     if (block == 16) {
-        if (flat) hipLaunchKernelGGL((repack_mxfp8_kernel<true, true>), dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
-        else hipLaunchKernelGGL((repack_mxfp8_kernel<false, true>), dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
+        if (flat) launch(repack_mxfp8_kernel<true, true>, dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
+        else launch(repack_mxfp8_kernel<false, true>, dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
     } else {
-        if (flat) hipLaunchKernelGGL((repack_mxfp8_kernel<true, false>), dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
-        else hipLaunchKernelGGL((repack_mxfp8_kernel<false, false>), dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
+        if (flat) launch(repack_mxfp8_kernel<true, false>, dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
+        else launch(repack_mxfp8_kernel<false, false>, dim3((unsigned)groups), dim3(kRepackThreads), 0, s, f.blob, f.codes, f.meta, f.n_chunks, (uint32_t)groups, f);
     }
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }
@@ -631,23 +618,23 @@ int fb4_seda_profile(const fb4_luts* luts, const uint16_t* meta, int64_t rows, i
     const int words = blocks_per_row % 8 == 0 && aligned(meta, 16) ? 8 : blocks_per_row % 4 == 0 && aligned(meta, 8) ? 4
                           : blocks_per_row % 2 == 0 && aligned(meta, 4) ? 2 : 1;
     if (rows > 0 && blocks_per_row > 0 && profile_by_group(rows, blocks_per_row, n_groups, words)) {
-#define FB4_PROFILE_CASE(w) case w: hipLaunchKernelGGL((profile_group_kernel<w>), dim3((unsigned)n_groups), dim3(kProfileGroupThreads), 0, s, meta, (uint32_t)rows, (uint32_t)blocks_per_row, anchor_group, luts->dev_blob, counts, sub_formatbooks); break;
+#define FB4_PROFILE_CASE(w) case w: launch(profile_group_kernel<w>, dim3((unsigned)n_groups), dim3(kProfileGroupThreads), 0, s, meta, (uint32_t)rows, (uint32_t)blocks_per_row, anchor_group, luts->dev_blob, counts, sub_formatbooks); break;
         switch (words) { FB4_PROFILE_CASE(8) FB4_PROFILE_CASE(4) FB4_PROFILE_CASE(2) FB4_PROFILE_CASE(1) }
 #undef FB4_PROFILE_CASE
         return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
     }
     const uint32_t n = (uint32_t)n_groups * 32u;
     // cleared by a kernel (not a memset node), so the call can be captured into a HIP graph
-    hipLaunchKernelGGL(profile_clear_kernel, dim3((n + kProfileThreads - 1) / kProfileThreads), dim3(kProfileThreads),
+    launch(profile_clear_kernel, dim3((n + kProfileThreads - 1) / kProfileThreads), dim3(kProfileThreads),
                        0, s, counts, n);
     if (rows > 0 && blocks_per_row > 0) {
         long long groups = (rows + kProfileThreads / 64 - 1) / (kProfileThreads / 64);
         const long long cap = (long long)luts->n_cu * 8;
         if (groups > cap) groups = cap;
-        hipLaunchKernelGGL(profile_count_kernel, dim3((unsigned)groups), dim3(kProfileThreads), 0, s, meta,
-                           (long long)rows, (long long)blocks_per_row, anchor_group, n_groups, counts);
+        launch(profile_count_kernel, dim3((unsigned)groups), dim3(kProfileThreads), 0, s, meta,
+                           (long long)rows, (long long)blocks_per_row, anchor_group, n_groups, counts, (uint32_t)groups);
     }
-    hipLaunchKernelGGL(profile_select_kernel, dim3(((unsigned)n_groups * 8u + kProfileThreads - 1) / kProfileThreads),
+    launch(profile_select_kernel, dim3(((unsigned)n_groups * 8u + kProfileThreads - 1) / kProfileThreads),
                        dim3(kProfileThreads), 0, s, counts, n_groups, luts->dev_blob, sub_formatbooks);
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }

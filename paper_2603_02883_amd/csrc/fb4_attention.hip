@@ -60,7 +60,7 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
     const int64_t bpg = (tokens + per_wg - 1) / per_wg;
     if (tokens * dim > 0x7FFFFFFFll || groups * bpg > 0x7FFFFFFFll) return FB4_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-#define FB4_SCORE_LAUNCH(d, relu, qb, keys) hipLaunchKernelGGL((attention_scores_kernel<d, relu, qb, keys>), grid, dim3(kScoreThreads), 0, s, qs, ks, (uint32_t)tokens, (uint32_t)dim, (uint32_t)bpg, out)
+#define FB4_SCORE_LAUNCH(d, relu, qb, keys) launch(attention_scores_kernel<d, relu, qb, keys>, grid, dim3(kScoreThreads), 0, s, qs, ks, (uint32_t)tokens, (uint32_t)dim, (uint32_t)bpg, grid.x, out)
 #define FB4_SCORE_CASE(d, qb, keys)                          \
     case d:                                                  \
         if (mode) FB4_SCORE_LAUNCH(d, true, qb, keys);       \
@@ -103,7 +103,7 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
             // 256 compute units, which decides speed only)
             const uint32_t rounds = (n_tasks + 256u * most - 1) / (256u * most);
             const dim3 sgrid((n_tasks + rounds * waves - 1) / (rounds * waves));
-#define FB4_SHORT_CASE(p, n) case p: hipLaunchKernelGGL((attention_scores_short_kernel<p, n>), sgrid, dim3(64 * waves), waves * per_wave, s, qs, ks, n_rows, (uint32_t)tokens, rows_per_task, n_tasks, (uint32_t)mode, out); break;
+#define FB4_SHORT_CASE(p, n) case p: launch(attention_scores_short_kernel<p, n>, sgrid, dim3(64 * waves), waves * per_wave, s, qs, ks, n_rows, (uint32_t)tokens, rows_per_task, n_tasks, (uint32_t)mode, waves, sgrid.x, out); break;
 #define FB4_SHORT_CASES(n)                                                                                                          \
     FB4_SHORT_CASE(1, n) FB4_SHORT_CASE(2, n) FB4_SHORT_CASE(3, n) FB4_SHORT_CASE(4, n) FB4_SHORT_CASE(5, n) FB4_SHORT_CASE(6, n)   \
     FB4_SHORT_CASE(7, n) FB4_SHORT_CASE(8, n) FB4_SHORT_CASE(9, n) FB4_SHORT_CASE(10, n) FB4_SHORT_CASE(11, n)                      \
@@ -137,8 +137,8 @@ int fb4_attention_scores(const void* q, const void* k, int64_t groups, int64_t t
 #define FB4_DMA_ARGS static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), (uint32_t)groups, (uint32_t)tokens, n_full, bpw, scores
 #define FB4_DMA_CASE(p)                                                                                                               \
     case p:                                                                                                                           \
-        if (mode) hipLaunchKernelGGL((attention_scores_dma_kernel<p, true>), dgrid, dim3(kScoreThreads), 0, s, FB4_DMA_ARGS);         \
-        else hipLaunchKernelGGL((attention_scores_dma_kernel<p, false>), dgrid, dim3(kScoreThreads), 0, s, FB4_DMA_ARGS);             \
+        if (mode) launch(attention_scores_dma_kernel<p, true>, dgrid, dim3(kScoreThreads), 0, s, FB4_DMA_ARGS);         \
+        else launch(attention_scores_dma_kernel<p, false>, dgrid, dim3(kScoreThreads), 0, s, FB4_DMA_ARGS);             \
         break;
         switch ((int)(dim / 8)) {
             FB4_DMA_CASE(1) FB4_DMA_CASE(2) FB4_DMA_CASE(3) FB4_DMA_CASE(4) FB4_DMA_CASE(5) FB4_DMA_CASE(6) FB4_DMA_CASE(7)
@@ -179,7 +179,7 @@ int fb4_select_salient_tokens(const float* scores, int64_t frames, int heads, in
     const int64_t at_once = 0xFFFFFFFFll / shape.threads;   // (a launch takes fewer than 2^32 threads)
     for (int64_t first = 0; first < workgroups; first += at_once) {
         const dim3 grid((unsigned)std::min(at_once, workgroups - first));
-#define FB4_SELECT_LAUNCH(t, l, m, many) hipLaunchKernelGGL((select_salient_kernel<t, l, m, many>), grid, dim3(t), 0, static_cast<hipStream_t>(stream), scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, (uint32_t)tile_rows, tile_columns, (uint32_t)shape.rows, (uint32_t)per_frame, (uint32_t)first, rows_out)
+#define FB4_SELECT_LAUNCH(t, l, m, many) launch(select_salient_kernel<t, l, m, many>, grid, dim3(t), 0, static_cast<hipStream_t>(stream), scores, (uint32_t)heads, (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, (uint32_t)tile_rows, tile_columns, (uint32_t)shape.rows, (uint32_t)per_frame, (uint32_t)first, rows_out)
 #define FB4_SELECT_CASE(t, m)                                                              \
         if (shape.lanes == 16) FB4_SELECT_LAUNCH(t, 16, m, true);                          \
         else if (m == kSelectMaxTokens && heads < 24) FB4_SELECT_LAUNCH(t, 1, m, (m < kSelectMaxTokens)); \
@@ -218,14 +218,14 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
     const bool one_buffer = token_group == anchor_group;
     auto own_groups = [&]() {
         if (n_anchors == 0) return;
-        hipLaunchKernelGGL(seda_anchor_kernel, dim3((unsigned)((n_anchors + kAssignThreads - 1) / kAssignThreads)), dim3(kAssignThreads),
+        launch(seda_anchor_kernel, dim3((unsigned)((n_anchors + kAssignThreads - 1) / kAssignThreads)), dim3(kAssignThreads),
                            0, s, anchors, (uint32_t)n_anchors, (uint32_t)frames, gh, gw, th, tw, token_group, anchor_group);
     };
     if (n_anchors <= (int64_t)kPrepareMaxAnchors) {
-        hipLaunchKernelGGL(seda_prepare_kernel, dim3(n_prepare), dim3(kAssignThreads), 0, s, anchors, (uint32_t)n_anchors, n,
+        launch(seda_prepare_kernel, dim3(n_prepare), dim3(kAssignThreads), 0, s, anchors, (uint32_t)n_anchors, n,
                            (uint32_t)tokens, gw, th, tw, token_group, anchor_group);
     } else {
-        hipLaunchKernelGGL(seda_fill_kernel, dim3((n + kAssignThreads - 1) / kAssignThreads), dim3(kAssignThreads), 0, s, token_group,
+        launch(seda_fill_kernel, dim3((n + kAssignThreads - 1) / kAssignThreads), dim3(kAssignThreads), 0, s, token_group,
                            anchor_group, n);
         own_groups();
     }
@@ -243,7 +243,7 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
         // windows: 24 heads x 8 channels 25.9 / 10.0, x 32 channels 25.3 / 18.2, one head x 128 channels x 16 frames 77 / 27.
         int lanes = dim > 64 ? 16 : dim > 32 ? 8 : dim > 16 ? 4 : dim > 8 ? 2 : 1;
         if (heads < kAssignThreads / 64) lanes = std::min(lanes, 4);
-#define FB4_MARK_LAUNCH(w, l) hipLaunchKernelGGL((seda_mark_kernel<w, l>), grid, dim3(kAssignThreads), 0, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group, one_buffer ? nullptr : anchor_group, window_scores)
+#define FB4_MARK_LAUNCH(w, l) launch(seda_mark_kernel<w, l>, grid, dim3(kAssignThreads), 0, s, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), anchors, p, token_group, one_buffer ? nullptr : anchor_group, window_scores)
 #define FB4_MARK_CASE(w)                                     \
         case w:                                              \
             if (lanes == 16) FB4_MARK_LAUNCH(w, 16);         \
@@ -287,10 +287,10 @@ int fb4_seda_main_anchor(const float* temporal_scores, const void* qt, const voi
     // than 2^32 threads, so from 2^22 tiles on 4.
     const int64_t most = tiles <= 512 ? kMainMaxThreads : tiles <= (1 << 22) ? 512 : 256;
     const unsigned threads = (unsigned)std::min<int64_t>(std::max<int64_t>(frames, 4) * 64, most);
-    hipLaunchKernelGGL(seda_main_anchor_kernel, dim3((unsigned)tiles), dim3(threads), 0, s, temporal_scores,
+    launch(seda_main_anchor_kernel, dim3((unsigned)tiles), dim3(threads), 0, s, temporal_scores,
                        static_cast<const uint16_t*>(qt), static_cast<const uint16_t*>(kt), (uint32_t)frames, (uint32_t)heads,
                        (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)dim, candidates, (uint32_t)n_per_frame, (uint32_t)tile_h,
-                       (uint32_t)tile_w, prune_threshold, main_anchor, kept, prune_scores);
+                       (uint32_t)tile_w, prune_threshold, main_anchor, kept, prune_scores, threads / 64u, (uint32_t)tiles);
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }
 
@@ -302,7 +302,7 @@ int fb4_seda_main_anchor_3d(const float* scores, int64_t frames, int heads, int 
     const int64_t tokens = (int64_t)grid_h * grid_w;
     const int64_t tiles = (int64_t)((grid_h + tile_h - 1) / tile_h) * ((grid_w + tile_w - 1) / tile_w);
     if (frames * tokens > 0x7FFFFFFFll || !aligned(scores, 4) || !aligned(anchors, 4)) return FB4_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(seda_main_anchor_3d_kernel, dim3((unsigned)tiles), dim3(kMainThreads), 0,
+    launch(seda_main_anchor_3d_kernel, dim3((unsigned)tiles), dim3(kMainThreads), 0,
                        static_cast<hipStream_t>(stream), scores, (uint32_t)frames, (uint32_t)heads, (uint32_t)grid_h,
                        (uint32_t)grid_w, (uint32_t)tile_h, (uint32_t)tile_w, anchors);
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
@@ -312,7 +312,7 @@ int fb4_probe_mfma_rate(int64_t workgroups, int64_t iterations, int random_opera
 {
     if (workgroups < 1 || workgroups > 65536 || iterations < 0 || iterations > 0x7FFFFFFFll || !out) return FB4_ERR_INVALID_ARG;
     if (!aligned(out, 4)) return FB4_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(probe_mfma_rate_kernel, dim3((unsigned)workgroups), dim3(256), 0, static_cast<hipStream_t>(stream), out,
+    launch(probe_mfma_rate_kernel, dim3((unsigned)workgroups), dim3(256), 0, static_cast<hipStream_t>(stream), out,
                        (uint32_t)iterations, (uint32_t)(random_operands != 0));
     // four wavefronts x 8 x 4 MFMAs of 32 x 32 x 16 per iteration, two operations per multiply-add
     if (flop) *flop = (double)workgroups * 4.0 * (double)iterations * 32.0 * (2.0 * 32 * 32 * 16);

@@ -26,7 +26,7 @@ struct DeqFastParams {
     uint32_t meta_shift;      // 2 or 1
     void* out;                // bf16 or fp32, [rows][out_row_stride]
     long long out_row_stride; // elements
-    uint32_t nb, n_blocks, n_tiles, div_mul, div_shift;
+    uint32_t nb, n_blocks, div_mul, div_shift;
     const uint8_t* blob;
     // kSum: second plane of the salient rows (Sec. 3.3), added in fp32
     const uint8_t* codes2;    // [n_sal][nb * 16]
@@ -34,6 +34,17 @@ struct DeqFastParams {
     const int32_t* salient;   // [n_sal] ascending, unique
     uint32_t n_sal;
     uint32_t rows;            // <= kMaxFusedRows
+};
+
+// The arguments of the kernel beyond its leading scalars.
+struct DeqFastArgs {
+    void* out;
+    long long out_row_stride;
+    uint32_t nb, div_mul, div_shift;
+    uint32_t n_sal, rows;
+    const uint8_t* codes2;
+    const uint16_t* meta2;
+    const int32_t* salient;
 };
 
 // Decoded pair (two bf16 patterns) of one code byte: table entry for exponent byte 130 plus the block's
@@ -56,7 +67,7 @@ __device__ __forceinline__ uint32_t decode_pair(const uint32_t* pair, uint32_t b
 // rows salient, to bf16: 16384 x 3072 (4 rounds) 22.4 / 21.3, 65536 x 1152 36.1 / 34.5, 11000 x 3072 (2.7) 16.1 / 15.5,
 // 7000 x 3072 (1.7) 11.8 / 12.5, 1000 x 1152 5.5 / 5.9; 16384 x 3072 with 30 % 30.9 / 32.2; to fp32, where twice the bytes
 // are written twice, 14000 x 3072 76.7 / 81.3.
-// The leading scalar arguments repeat the fields of `p` that the first loads depend on; they arrive in
+// The leading scalar arguments are the ones that the first loads depend on; they arrive in
 // registers when the wavefront starts (kernel-argument preload), the rest by a load.
 constexpr int kDeqWords = 4;   // code words per thread and round
 constexpr uint32_t kDeqEarlyHalfRounds = 5, kDeqEarlyShare = 8;
@@ -64,10 +75,11 @@ constexpr uint32_t kDeqEarlyList = 4 * kDeqThreads;   // entries of the salient 
 template <bool kFlat, bool kF32, bool kSum = false, bool kEarly = false>
 __global__ __launch_bounds__(kDeqThreads) void dequantize_fast_kernel(
     const uint8_t* blob, const uint8_t* codes, const uint16_t* meta, uint32_t n_blocks, uint32_t meta_shift,
-    uint32_t n_workgroups, DeqFastParams p)
+    uint32_t n_workgroups, DeqFastArgs more)
 {
     static_assert(!kEarly || (kSum && !kF32), "written for bf16");
-    p.blob = blob; p.codes = codes; p.meta = meta; p.n_blocks = n_blocks; p.meta_shift = meta_shift;
+    const DeqFastParams p = {codes, meta, meta_shift, more.out, more.out_row_stride, more.nb, n_blocks, more.div_mul, more.div_shift, blob,
+                             more.codes2, more.meta2, more.salient, more.n_sal, more.rows};
     __shared__ __align__(16) uint32_t pair[32 * 256];   // [DID][code byte] -> two bf16 patterns
     __shared__ __align__(16) uint32_t sal_bits[kSum ? kMaxFusedRows / 32 : 4];
     __shared__ uint16_t sal_rank[kSum ? kMaxFusedRows / 32 : 4];

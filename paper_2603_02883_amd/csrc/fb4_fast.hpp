@@ -70,7 +70,24 @@ struct FastParams {
     const uint16_t* meta1;        // [rows][nb * 32 / block]
 };
 
+// The arguments of the streaming kernel beyond its leading scalars (what a launch carries cheaply has no room for FastParams).
+// The pointers begin at the 64th byte: a load across two cache lines of the arguments waits for both (exhaustive, 12288 x 3072,
+// with codes and meta on either side of that line 25.9 us instead of 25.5).
+struct FastArgs {
+    uint32_t rows, n_sal;
+    uint8_t* codes;
+    uint16_t* meta;
+    const int32_t* token_group;
+    const uint8_t* sub;
+    uint8_t* codes2;      // mode 1: the second plane's, which is written; mode 2: the first plane's, which is read
+    uint16_t* meta2;
+};
+
 constexpr uint32_t kMaxFastGroups = 1023;   // SeDA groups whose exclusion rows fit the workgroup's LDS
+
+// Division by nb for dividends below 2^31: (n * div_mul) >> div_shift with div_shift = 31 + ceil(log2 nb) and div_mul =
+// ceil(2^div_shift / nb).
+__host__ __device__ __forceinline__ uint32_t div_shift_of(uint32_t nb) { return nb > 1u ? 63u - (uint32_t)__builtin_clz(nb - 1u) : 31u; }
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
@@ -1047,19 +1064,25 @@ __device__ __forceinline__ void build_seda_rows(uint8_t* lds, int offset, const 
 }
 constexpr uint32_t kMaxFusedProducerGroups = 255;   // SeDA groups the producer-fused kernels hold in LDS
 
-// The leading scalar arguments repeat the fields of `p` that the first loads and the loop bound depend on:
+// The leading scalar arguments are the ones that the first loads and the loop bound depend on:
 // the library is compiled so that the leading argument registers (14 of them on this target: all of these)
 // are filled by the dispatcher when the wavefront starts (the rest of the arguments come by a load, half a microsecond later), and the table and
-// tile requests can then go out at once.
+// tile requests can then go out at once.  counts: n_groups | n_dialects << 16.
 // kMode: 0 = the first plane, 1 = both planes in one pass (rows listed in p.salient get a second plane),
 // 2 = the second plane only, of the rows p.salient lists, from x and a first plane already in memory.
 template <int kBlock, int G, bool kFlat, bool kTwoStage, bool kSeda, int kMode = 0, int kThreads = kFastThreads>
 __global__ __launch_bounds__(kThreads) void quantize_lut_kernel(
-    const uint8_t* blob, const uint16_t* x, uint32_t n_blocks, uint32_t n_tiles, uint32_t div_mul, uint32_t div_shift,
-    uint32_t nb, uint32_t n_workgroups, long long row_stride, const int32_t* salient, FastParams p)
+    const uint8_t* blob, const uint16_t* x, uint32_t n_blocks, uint32_t n_tiles, uint32_t div_mul, uint32_t nb,
+    uint32_t n_workgroups, uint32_t counts, long long row_stride, const int32_t* salient, FastArgs more)
 {
-    p.blob = blob; p.x = x; p.n_blocks = n_blocks; p.n_tiles = n_tiles; p.div_mul = div_mul; p.div_shift = div_shift;
+    FastParams p = {};
+    p.blob = blob; p.x = x; p.n_blocks = n_blocks; p.n_tiles = n_tiles; p.div_mul = div_mul; p.div_shift = div_shift_of(nb);
     p.nb = nb; p.row_stride = row_stride; p.salient = salient;
+    p.codes = more.codes; p.meta = more.meta; p.token_group = more.token_group; p.sub = more.sub;
+    p.n_groups = counts & 0xFFFFu; p.n_dialects = counts >> 16;
+    if (kMode == 2) { p.codes1 = more.codes2; p.meta1 = more.meta2; }
+    else { p.codes2 = more.codes2; p.meta2 = more.meta2; }
+    p.rows = more.rows; p.n_sal = more.n_sal;
     constexpr int kWaves = kThreads / 64;
     constexpr bool kDecomp = kMode == 1, kGather = kMode == 2;
     constexpr bool kRes = kMode != 0;   // residuals are formed: decode tables needed

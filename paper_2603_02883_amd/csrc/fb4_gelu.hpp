@@ -77,14 +77,14 @@ inline void build_gelu_table(bool approximate, uint16_t* table)
 }
 
 // ---- device
-struct GeluParams {
+struct GeluParams {   // (the pointers begin at the 64th byte of the arguments)
+    uint32_t n_groups;            // <= kMaxFusedProducerGroups
+    uint32_t n_dialects;
     uint8_t* codes;
     uint16_t* meta;
     // Sec. 3.4 (optional): candidate lists per token group
     const int32_t* token_group;   // [rows] or null
     const uint8_t* sub;           // [n_groups][8] DIDs
-    uint32_t n_groups;            // <= kMaxFusedProducerGroups
-    uint32_t n_dialects;
 };
 
 // 16 wavefronts per CU (the kernel needs about 100 vector registers): 27.6 us on a 16384x3072 tensor against

@@ -28,9 +28,7 @@ struct QuantParams {
     long long row_stride;    // elements
     long long rows;          // rows of x
     long long cols;          // elements per row (a multiple of the block size)
-    int nb;                  // blocks per row
-    int tiles_per_row;       // ceil(cols / 512)
-    int n_tiles;             // tiles over the OUTPUT rows
+    int n_tiles;             // tiles over the OUTPUT rows, ceil(cols / 512) each
     uint8_t* codes;          // [out_rows][nb*16]
     uint16_t* meta;          // [out_rows][nb]
     const int32_t* token_group;  // [rows] or null
@@ -422,16 +420,32 @@ struct TileInput {
     bool live;        // false: the salient list names a row outside the tensor (wave-uniform)
 };
 
-// The leading scalar arguments repeat the fields of `p` that the first loads depend on; they arrive in
+// The arguments of the kernel beyond its leading scalars.
+struct QuantArgs {
+    long long rows;
+    uint8_t* codes;
+    uint16_t* meta;
+    const int32_t* token_group;
+    const uint8_t* sub;
+    const uint8_t* codes1;
+    const uint16_t* meta1;
+    int n_groups, n_dialects;
+};
+
+// The leading scalar arguments are the ones that the first loads depend on; they arrive in
 // registers when the wavefront starts (kernel-argument preload), the rest by a load.
 template <int SEL, int G, int MODE, bool kTwoStage, int LPB>
 __global__ __launch_bounds__(kThreads) void quantize_kernel(const uint8_t* blob, const uint16_t* x,
-                                                            const int32_t* salient, int n_tiles, int tiles_per_row,
-                                                            int n_workgroups, long long row_stride, long long cols,
-                                                            QuantParams p)
+                                                            const int32_t* salient, int n_tiles, int n_workgroups,
+                                                            long long row_stride, long long cols, QuantArgs more)
 {
-    p.blob = blob; p.x = x; p.salient = salient; p.n_tiles = n_tiles; p.tiles_per_row = tiles_per_row;
+    QuantParams p = {};
+    p.blob = blob; p.x = x; p.salient = salient; p.n_tiles = n_tiles;
     p.row_stride = row_stride; p.cols = cols;
+    p.rows = more.rows; p.codes = more.codes; p.meta = more.meta; p.token_group = more.token_group; p.sub = more.sub;
+    p.codes1 = more.codes1; p.meta1 = more.meta1; p.n_groups = more.n_groups; p.n_dialects = more.n_dialects;
+    const int tiles_per_row = (int)((cols + kTileElems - 1) / kTileElems);
+    const long long nb = cols / (8 * LPB);   // blocks per row
     __shared__ __align__(16) uint8_t lds[kBlobBytes];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -444,8 +458,8 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const uint8_t* blob,
         in.w = make_uint4(0, 0, 0, 0);
         in.c1 = in.m1 = 0;
         in.live = true;
-        const int orow = t / p.tiles_per_row;               // output row (wave-uniform)
-        const int chunk = t - orow * p.tiles_per_row;
+        const int orow = t / tiles_per_row;                 // output row (wave-uniform)
+        const int chunk = t - orow * tiles_per_row;
         in.srow = orow;
         if (MODE == kDecomp) {
             in.srow = p.salient[orow];
@@ -459,7 +473,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const uint8_t* blob,
             in.w = *reinterpret_cast<const uint4*>(p.x + in.srow * p.row_stride + col);
             if (MODE == kDecomp) {
                 in.c1 = *reinterpret_cast<const uint32_t*>(p.codes1 + in.srow * code_pitch + col / 2);
-                in.m1 = p.meta1[in.srow * p.nb + col / (8 * LPB)];
+                in.m1 = p.meta1[in.srow * nb + col / (8 * LPB)];
             }
         }
         return in;
@@ -476,8 +490,8 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const uint8_t* blob,
     for (int t = t_first; t < p.n_tiles; t += stride) {
         if (t != t_first) in = request(t);
         if (!in.live) continue;                             // wave-uniform
-        const int orow = t / p.tiles_per_row;
-        const int chunk = t - orow * p.tiles_per_row;
+        const int orow = t / tiles_per_row;
+        const int chunk = t - orow * tiles_per_row;
         const long long srow = in.srow;
         const long long col = (long long)chunk * kTileElems + lane * 8;
         const bool valid = col < p.cols;                    // the same for all lanes of a block
@@ -547,7 +561,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const uint8_t* blob,
         for (int i = 0; i < 8; ++i) code |= (uint32_t)qv[(e.sign[i] << 5) | e.bin[i]] << (4 * i);
         if (valid) {
             *reinterpret_cast<uint32_t*>(p.codes + (long long)orow * code_pitch + col / 2) = code;
-            if (jb == 0) p.meta[(long long)orow * p.nb + blk] = (uint16_t)(did | (e.ebyte << 8));
+            if (jb == 0) p.meta[(long long)orow * nb + blk] = (uint16_t)(did | (e.ebyte << 8));
         }
     }
 }
@@ -556,7 +570,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const uint8_t* blob,
 // kSum = false: every row from plane 1.  kSum = true: the salient rows again,
 // as the fp32 sum of both planes (Sec. 3.3).
 template <bool kSum, bool kF32>
-__global__ __launch_bounds__(kThreads) void dequantize_kernel(DequantParams p)
+__global__ __launch_bounds__(kThreads) void dequantize_kernel(DequantParams p, int n_workgroups)
 {
     __shared__ __align__(16) uint16_t dec[32 * 8];
     for (int i = threadIdx.x; i < 32 * 8; i += kThreads)
@@ -565,7 +579,7 @@ __global__ __launch_bounds__(kThreads) void dequantize_kernel(DequantParams p)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int stride = gridDim.x * kWavesPerGroup;
+    const int stride = n_workgroups * kWavesPerGroup;
     const long long code_pitch = p.cols / 2;
 
     for (int t = blockIdx.x * kWavesPerGroup + wave; t < p.n_tiles; t += stride) {

@@ -33,10 +33,8 @@
 
 namespace fb4 {
 
-struct LayerNormParams {
+struct LayerNormParams {   // (the pointers begin at the 64th byte of the arguments)
     uint32_t rows;
-    uint32_t cols;
-    uint32_t n_blocks;   // rows * nb
     float eps;
     uint8_t* codes;
     uint16_t* meta;
@@ -61,7 +59,7 @@ constexpr int kLdsLnTables = lds_fast_bytes(false, false, false);
 // a barrier.  kGbFloats: floats reserved per vector; kThreads: threads of the workgroup.
 template <int B, bool kTwoStage, bool kSeda, int kThreads>
 __device__ __forceinline__ void layernorm_tables_to_lds(uint8_t* lds, const uint8_t* blob, const float* gamma,
-                                                        const float* beta, const LayerNormParams& p)
+                                                        const float* beta, uint32_t cols, const LayerNormParams& p)
 {
     constexpr int kGbFloats = 2048 * B;
     constexpr int kLdsSeda = kLdsLnTables + 2 * kGbFloats * 4;
@@ -82,7 +80,7 @@ __device__ __forceinline__ void layernorm_tables_to_lds(uint8_t* lds, const uint
     }
     const uint32_t nibv = reinterpret_cast<const uint32_t*>(blob + kOffQvalueT)[threadIdx.x & 255u];
     const uint32_t rngv = kTwoStage ? reinterpret_cast<const uint32_t*>(blob + kOffRangeExcl)[threadIdx.x & 63u] : 0u;
-    const uint32_t n4 = p.cols / 4u;
+    const uint32_t n4 = cols / 4u;
 #pragma unroll
     for (int k = 0; k < kGbIt; ++k) {
         const uint32_t c4 = min(threadIdx.x + (uint32_t)(k * kThreads), n4 - 1u);
@@ -217,7 +215,7 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t W = n_workgroups;
-    const uint32_t per_bundle = rw * nb;
+    const uint32_t per_bundle = rw * nb, cols = nb * 32u;
 
     uint32_t rloc[B], cb[B];
     bool valid[B];
@@ -259,14 +257,14 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
         request(u, 0, buf[0], gbuf[0]);
         if (B > 1) request(u, 1, buf[1], gbuf[1]);
     }
-    layernorm_tables_to_lds<B, kTwoStage && !kWriteY, kSeda && !kWriteY, kThreads>(lds, blob, gamma, beta, p);
+    layernorm_tables_to_lds<B, kTwoStage && !kWriteY, kSeda && !kWriteY, kThreads>(lds, blob, gamma, beta, cols, p);
     const TileConsts K = make_tile_consts<G>(lane, 0);
     FastParams sp = {};
     sp.codes = p.codes;
     sp.meta = p.meta;
-    sp.n_blocks = p.n_blocks;
+    sp.n_blocks = p.rows * nb;
     const bool meta_aligned = (reinterpret_cast<uintptr_t>(p.meta) & 15u) == 0;
-    const float n_channels = (float)p.cols;
+    const float n_channels = (float)cols;
     const float inv_channels = 1.0f / n_channels;
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
@@ -369,7 +367,7 @@ __global__ __launch_bounds__(kThreads) void layernorm_quantize_kernel(
             for (uint32_t r = 0; r < rw; ++r) {
                 const uint32_t row = u * rw + r;
                 if (row >= p.rows) break;
-                const RowNorm v = layernorm_row_plain(x + (long long)row * row_stride, p.cols, p.eps);
+                const RowNorm v = layernorm_row_plain(x + (long long)row * row_stride, cols, p.eps);
 #pragma unroll
                 for (int j = 0; j < B; ++j) {
                     if (rloc[j] == r) rn[j] = v;

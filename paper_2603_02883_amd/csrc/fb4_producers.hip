@@ -98,8 +98,6 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
     const unsigned groups = std::min(n_bundles, (unsigned)luts->n_cu);
     LayerNormParams p = {};
     p.rows = (uint32_t)rows;
-    p.cols = (uint32_t)cols;
-    p.n_blocks = (uint32_t)(rows * nb);
     p.eps = eps;
     p.codes = codes;
     p.meta = meta;
@@ -112,7 +110,7 @@ int fb4_layernorm_quantize(const fb4_luts* luts, const fb4_opts* opts, const voi
     const bool ts = (opts->flags & FB4_FLAG_TWO_STAGE) != 0;
     const bool seda = token_group != nullptr;
 #define FB4_LN_ARGS luts->dev_blob, static_cast<const uint16_t*>(x), n_bundles, rw, (uint32_t)nb, groups, (long long)row_stride, gamma, beta, p
-#define FB4_LN_LAUNCH(b, blk, g, t, sd, wy) hipLaunchKernelGGL((layernorm_quantize_kernel<b, blk, g, t, sd, wy>), dim3(groups), dim3(ln_threads(b, g)), 0, s, FB4_LN_ARGS)
+#define FB4_LN_LAUNCH(b, blk, g, t, sd, wy) launch(layernorm_quantize_kernel<b, blk, g, t, sd, wy>, dim3(groups), dim3(ln_threads(b, g)), 0, s, FB4_LN_ARGS)
 #define FB4_LN_SHAPE(b, blk, g)                                \
     if (seda) {                                                \
         if (ts) FB4_LN_LAUNCH(b, blk, g, true, true, false);   \
@@ -160,24 +158,22 @@ int fb4_gelu_quantize(const fb4_luts* luts, const fb4_opts* opts, const void* x,
     if (n_blocks >= 0x7F000000ull) return FB4_ERR_UNSUPPORTED;
     if ((rc = check_device(luts)) != FB4_OK) return rc;
     const uint32_t n_tiles = (uint32_t)((n_blocks + 63) / 64);
-    uint32_t l = 0;
-    while ((1ull << l) < nb) ++l;
-    const uint32_t div_shift = 31 + l;
+    const uint32_t div_shift = div_shift_of((uint32_t)nb);
     const uint32_t div_mul = (uint32_t)(((1ull << div_shift) + nb - 1) / nb);
     // (a tile per compute unit before a second one on any: 300 x 1152 7.0 -> 4.7 us, 1000 x 3072 7.2 -> 5.75)
     const unsigned groups = std::min(n_tiles, (unsigned)luts->n_cu);
-    GeluParams p = {codes, meta, token_group, sub_formatbooks, (uint32_t)n_groups, (uint32_t)luts->n_dialects};
+    GeluParams p = {(uint32_t)n_groups, (uint32_t)luts->n_dialects, codes, meta, token_group, sub_formatbooks};
     const bool seda = token_group != nullptr, ts = (opts->flags & FB4_FLAG_TWO_STAGE) != 0;
     const uint16_t* table = reinterpret_cast<const uint16_t*>(luts->dev_blob + kBlobBytes + (approximate ? kGeluTableBytes : 0));
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define FB4_GELU_ARGS luts->dev_blob, static_cast<const uint16_t*>(x), table, (uint32_t)n_blocks, n_tiles, div_mul, div_shift, (uint32_t)nb, groups, (long long)row_stride, p
 #define FB4_GELU_SHAPE(blk, g)                                                                                                        \
     if (seda) {                                                                                                                       \
-        if (ts) hipLaunchKernelGGL((gelu_quantize_kernel<blk, g, true, true>), dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS);  \
-        else hipLaunchKernelGGL((gelu_quantize_kernel<blk, g, false, true>), dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS);    \
+        if (ts) launch(gelu_quantize_kernel<blk, g, true, true>, dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS);  \
+        else launch(gelu_quantize_kernel<blk, g, false, true>, dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS);    \
     } else {                                                                                                                          \
-        if (ts) hipLaunchKernelGGL((gelu_quantize_kernel<blk, g, true, false>), dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS); \
-        else hipLaunchKernelGGL((gelu_quantize_kernel<blk, g, false, false>), dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS);   \
+        if (ts) launch(gelu_quantize_kernel<blk, g, true, false>, dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS); \
+        else launch(gelu_quantize_kernel<blk, g, false, false>, dim3(groups), dim3(kGeluThreads), 0, s, FB4_GELU_ARGS);   \
     }
     if (opts->block == 32) {
         if (opts->num_groups == 8) { FB4_GELU_SHAPE(32, 8) } else { FB4_GELU_SHAPE(32, 16) }

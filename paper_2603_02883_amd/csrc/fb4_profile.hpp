@@ -22,11 +22,11 @@ __global__ __launch_bounds__(kProfileThreads) void profile_clear_kernel(uint32_t
 // One wavefront per row: a 32-bin histogram of the row's DIDs in LDS, then at most 32 global atomics.
 __global__ __launch_bounds__(kProfileThreads) void profile_count_kernel(const uint16_t* meta, long long rows,
                                                                         long long nb, const int32_t* anchor_group,
-                                                                        int n_groups, uint32_t* counts)
+                                                                        int n_groups, uint32_t* counts, uint32_t n_workgroups)
 {
     __shared__ uint32_t hist[kProfileThreads / 64][32];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long stride = (long long)gridDim.x * (kProfileThreads / 64);
+    const long long stride = (long long)n_workgroups * (kProfileThreads / 64);
     for (long long r = (long long)blockIdx.x * (kProfileThreads / 64) + wave; r < rows; r += stride) {
         const int g = anchor_group[r];                    // wave-uniform
         if (g < 0 || g >= n_groups) continue;

@@ -51,14 +51,14 @@ constexpr uint32_t kScoreShortGroup = 64;   // tokens of a short group at most
 template <int D32, bool kRelu, int kScoreQB, int kScoreKeys>
 __global__ __launch_bounds__(kScoreThreads) void attention_scores_kernel(const uint16_t* q, const uint16_t* k,
                                                                          uint32_t tokens, uint32_t dim,
-                                                                         uint32_t blocks_per_group, float* scores)
+                                                                         uint32_t blocks_per_group, uint32_t n_workgroups, float* scores)
 {
     constexpr int kScoreQueries = 128 * kScoreQB;    // per workgroup
     constexpr int kSteps = D32 * 2;                  // MFMA steps of 16 channels
     constexpr int kRowBytes = D32 * 64 + 16;         // one key row in LDS: channels, then 16 bytes of padding
     __shared__ __align__(16) uint8_t lds[2][kScoreKeys * kRowBytes];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t pos = xcd_local_position(blockIdx.x, gridDim.x);
+    const uint32_t pos = xcd_local_position(blockIdx.x, n_workgroups);
     const uint32_t g = pos / blocks_per_group;
     const uint32_t q0 = (pos - g * blocks_per_group) * kScoreQueries + wave * (32u * kScoreQB);
     const uint16_t* qg = q + (size_t)g * tokens * dim;
@@ -414,11 +414,11 @@ template <int kP, int kNB>
 __global__ __launch_bounds__(kScoreThreads) void attention_scores_short_kernel(const uint16_t* q, const uint16_t* k,
                                                                                uint32_t n_rows, uint32_t tokens,
                                                                                uint32_t rows_per_task, uint32_t n_tasks,
-                                                                               uint32_t relu, float* scores)
+                                                                               uint32_t relu, uint32_t n_waves, uint32_t n_workgroups,
+                                                                               float* scores)
 {
     extern __shared__ __align__(1024) uint8_t short_lds[];
     constexpr uint32_t P = kP;
-    const uint32_t n_waves = blockDim.x >> 6;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t half = lane >> 5, col = lane & 31u;
     constexpr uint32_t g_log = (uint32_t)__builtin_ctz(P | 16u);   // log2 of gcd(P, 16)
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(kScoreThreads) void attention_scores_short_kernel(c
     // a query's group: keys lo .. lo + tokens - 1 of the task's rows
     const uint32_t lo = kNB == 1 ? (col / tokens) * tokens : 0u;
     const float n_keys = (float)tokens;
-    const uint32_t stride = gridDim.x * n_waves;
+    const uint32_t stride = n_workgroups * n_waves;
     uint32_t task = blockIdx.x * n_waves + wave;
     if (task >= n_tasks) return;
     fetch(task);
@@ -875,14 +875,13 @@ constexpr uint32_t kMainMaxFrames = 1024;
 __global__ __launch_bounds__(kMainMaxThreads) void seda_main_anchor_kernel(
     const float* temporal_scores, const uint16_t* qt, const uint16_t* kt, uint32_t frames, uint32_t heads, uint32_t grid_h,
     uint32_t grid_w, uint32_t dim, const int32_t* cand, uint32_t n_per_frame, uint32_t tile_h, uint32_t tile_w,
-    float prune_threshold, int32_t* main_anchor, int32_t* kept, float* prune_scores)
+    float prune_threshold, int32_t* main_anchor, int32_t* kept, float* prune_scores, uint32_t n_waves, uint32_t tiles)
 {
     __shared__ double score[kMainMaxFrames];
     __shared__ int32_t slot[kMainMaxFrames], row_of[kMainMaxFrames];
     __shared__ int32_t best_frame;
     constexpr uint32_t kNone = 0xFFFFFFFFu;
-    const uint32_t n_waves = blockDim.x >> 6;
-    const uint32_t tokens = grid_h * grid_w, tile = blockIdx.x, tiles = gridDim.x;
+    const uint32_t tokens = grid_h * grid_w, tile = blockIdx.x;
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (uint32_t f = wave; f < frames; f += n_waves) {
         const int32_t* list = cand + (size_t)f * n_per_frame;

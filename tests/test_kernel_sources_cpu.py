@@ -41,3 +41,14 @@ def test_kernels_keep_their_values_in_registers():
                "layernorm_quantize_kernelILi6ELi16ELi16ELb0ELb1E": 4, "layernorm_quantize_kernelILi1ELi16ELi16ELb1ELb1E": 1}
     over = {k: n for k, n in found.items() if n > max([v for a, v in allowed.items() if a in k], default=0)}
     assert not over
+
+
+def test_kernel_arguments_fit_a_launch():
+    """The runtime carries 112 bytes of kernel arguments with a launch and allocates for more; what a kernel reads of its own launch
+    (its grid's size, say) comes as 256 more."""
+    from paper_2603_02883_amd import build
+    data, sizes = open(build.LIB, "rb").read(), []
+    for m in re.finditer(rb"\.kernarg_segment_size([\x00-\x7f]|\xcc.|\xcd..)", data, re.S):
+        count = m.group(1)
+        sizes.append(int.from_bytes(count[1:], "big") if len(count) > 1 else count[0])
+    assert len(sizes) == len(spills()) > 300 and max(sizes) <= 112
