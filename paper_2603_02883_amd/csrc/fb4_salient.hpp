@@ -322,11 +322,19 @@ void attention_scores_dma_kernel(const uint16_t* q, const uint16_t* k, uint32_t 
                     }
                     add_up(sum[(b + NB - 1) % (NB > 0 ? NB : 1)]);
                     done = acc;
+                    // The order: MFMA, operand read, a share of the sums.  The shares are the sums' instructions and no more: with
+                    // room for others the scheduler filled it with this block's own sums, which wait for its MFMAs with no
+                    // other block's behind them (us, 20 places / 16: 272 x 1350 x 72 65.3 / 64.9, 16 x 8000 x 72 115.8 / 112.7, 24 x
+                    // 1000 x 72 6.84 / 6.55, 15 x 2048 x 112 17.4 / 15.8, 139 x 155 x 56 3.26 / 3.22).  One block of queries per
+                    // wavefront has no other anyway: 20 (1 x 8192 x 96 33.1 / 33.6, 1 x 3600 x 128 19.7 / 20.0).
+                    constexpr int kOps = kRelu ? 32 : 16, kParts = kSteps > 1 ? kSteps - 1 : 1, kEach = kOps / kParts;
+                    constexpr int kFirst = NB == 1 ? (16 + kSteps - 1) / kSteps + 1 : kOps - kEach * (kParts - 1), kRest = NB == 1 ? kFirst : kEach;
 #pragma unroll
-                    for (int s = 0; s < kSteps; ++s) {   // the order: MFMA, operand read, a share of the sums
+                    for (int s = 0; s < kSteps; ++s) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                         if (last) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                        if (s > 0 || kSteps == 1) __builtin_amdgcn_sched_group_barrier(0x002, (16 + kSteps - 1) / kSteps + 1, 0);
+                        if (s == (kSteps > 1 ? 1 : 0)) __builtin_amdgcn_sched_group_barrier(0x002, kFirst, 0);
+                        else if (s > 1) __builtin_amdgcn_sched_group_barrier(0x002, kRest, 0);
                     }
                     if (kEarly) __builtin_amdgcn_sched_barrier(0);
                 }
