@@ -127,6 +127,8 @@ __device__ __forceinline__ uint32_t pk_mad_u16(uint32_t a, uint32_t k, uint32_t 
 {
     return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) * __builtin_bit_cast(u16x2, k) + __builtin_bit_cast(u16x2, c)));
 }
+// (a & b) | c in one instruction whatever stands around it
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0xEA); }
 // A constant the optimizer cannot fold back into an instruction literal: keeps
 // three-operand instructions encodable with the constant in a register.
 __device__ __forceinline__ uint32_t sgpr_const(uint32_t v)
@@ -335,6 +337,7 @@ struct TileConsts {
     uint32_t k8, khalf;  // both halves: 8; the fp16 number 1023.5
     uint32_t k1001, k128, k1024;   // exhaustive selector: the fp16 numbers 1 + 2^-10, 128 and 1024
     uint32_t kpair, row_base;
+    uint32_t k08, k80;   // the sign bits of a code word's even and odd elements
     uint32_t sel_e, sel_o;   // byte selectors of the keys of dialects (4i, 4i+2) and (4i+1, 4i+3)
     uint32_t kdid4[8];       // 8 groups: DIDs 4i .. 4i+3, a byte each
     uint32_t kdid[16];       // 16 groups: DID pairs of the 16 key registers, (4i, 4i+2) and (4i+1, 4i+3)
@@ -351,6 +354,10 @@ __device__ __forceinline__ TileConsts make_tile_consts(uint32_t lane, uint32_t g
     K.row_base = kLdsRows + (lane & (kRowCopies - 1u)) * 16u - kBinBias * (32u * kRowCopies);
     K.k8 = sgpr_const(0x00080008u);
     K.khalf = sgpr_const(0x63FF63FFu);
+    if (G != 16) {
+        K.k08 = sgpr_const(0x08080808u);
+        K.k80 = sgpr_const(0x80808080u);
+    }
     K.kpair = sgpr_const(32u | (1024u << 16));   // lo bin * 32 + hi bin * 1024
     if (G == 0) {   // (two constants of one instruction: one of them in a vector register)
         K.k1001 = vgpr_const(0x3C013C01u);
@@ -894,12 +901,14 @@ __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint
             // (byte permutations: shifts and ors would be regrouped into more instructions)
             uint32_t v = __builtin_amdgcn_perm(__builtin_amdgcn_perm(byte[3], byte[2], 0x0C0C0400u),
                                                __builtin_amdgcn_perm(byte[1], byte[0], 0x0C0C0400u), 0x05040100u);
-            // sign bits: element 2m -> bit 8m+3, element 2m+1 -> bit 8m+7
-            const uint32_t x01 = __builtin_amdgcn_perm(w[4 * c + 1], w[4 * c + 0], 0x07030501u);  // b1(w0) b1(w1) b3(w0) b3(w1)
-            const uint32_t x23 = __builtin_amdgcn_perm(w[4 * c + 3], w[4 * c + 2], 0x07030501u);
-            const uint32_t lo = __builtin_amdgcn_perm(x23, x01, 0x05040100u);   // b1 of w0..w3
-            const uint32_t hi = __builtin_amdgcn_perm(x23, x01, 0x07060302u);   // b3 of w0..w3
-            v |= ((lo >> 4) & 0x08080808u) | (hi & 0x80808080u);
+            // sign bits: element 2m -> bit 8m+3, element 2m+1 -> bit 8m+7.  (selectors 8 to 11 of a byte permutation fill a byte with
+            // the sign of either half: no shift before the masks)
+            const uint32_t x01 = __builtin_amdgcn_perm(w[4 * c + 1], w[4 * c + 0], 0x0B090A08u);   // w0.lo w1.lo w0.hi w1.hi
+            const uint32_t x23 = __builtin_amdgcn_perm(w[4 * c + 3], w[4 * c + 2], 0x0B090A08u);
+            const uint32_t lo = __builtin_amdgcn_perm(x23, x01, 0x05040100u);   // the lower halves of w0..w3
+            const uint32_t hi = __builtin_amdgcn_perm(x23, x01, 0x07060302u);
+            if (G == 16) v |= (lo & 0x08080808u) | (hi & 0x80808080u);   // (no scalar registers left for the masks: GeLU would spill 13)
+            else v = and_or(hi, K.k80, and_or(lo, K.k08, v));
             code[c] = v;
         }
     }
