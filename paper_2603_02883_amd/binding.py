@@ -177,6 +177,34 @@ class CtypesCall:
         groups, tokens, dim = q.shape
         return _lib.fb4_attention_scores(_dp(q), _dp(k), groups, tokens, dim, mode, _dp(scores), s)
 
+    @staticmethod
+    def select_salient_tokens(scores, grid_h, grid_w, tile_h, tile_w, rows_out, s):
+        frames, heads, tokens = scores.shape
+        assert tokens == grid_h * grid_w
+        return _lib.fb4_select_salient_tokens(_dp(scores), frames, heads, grid_h, grid_w, tile_h, tile_w, _dp(rows_out), s)
+
+    @staticmethod
+    def seda_assign(q, k, joint, frames, grid_h, grid_w, anchors, tile_h, tile_w, window, window_t, threshold, token_group,
+                    anchor_group, scores, s):
+        heads, dim = (q.shape[0], q.shape[2]) if joint else (q.shape[1], q.shape[3])
+        n = anchors.numel()
+        return _lib.fb4_seda_assign(_dp(q), _dp(k), 1 if joint else 0, frames, heads, grid_h, grid_w, dim, _dp(anchors), n, tile_h,
+                                    tile_w, window, window_t, float(threshold), _dp(token_group), _dp(anchor_group), _dp(scores), s)
+
+    @staticmethod
+    def seda_main_anchor(temporal_scores, qt, kt, candidates, grid_h, grid_w, tile_h, tile_w, prune_threshold, main_anchor, kept,
+                         prune_scores, s):
+        tokens, heads, frames, dim = qt.shape
+        assert tokens == grid_h * grid_w and candidates.shape[0] == frames
+        return _lib.fb4_seda_main_anchor(_dp(temporal_scores), _dp(qt), _dp(kt), frames, heads, grid_h, grid_w, dim,
+                                         _dp(candidates), candidates.shape[1], tile_h, tile_w, float(prune_threshold),
+                                         _dp(main_anchor), _dp(kept), _dp(prune_scores), s)
+
+    @staticmethod
+    def seda_profile(h, meta, anchor_group, n_groups, counts, sub_formatbooks, s):
+        rows, nb = meta.shape
+        return _lib.fb4_seda_profile(h, _dp(meta), rows, nb, _dp(anchor_group), n_groups, _dp(counts), _dp(sub_formatbooks), s)
+
 
 def _load_call():
     """The C module of this interpreter (by its path: a module of another one is not taken), built if it is missing and can be."""
@@ -191,7 +219,11 @@ def _load_call():
     loader = importlib.machinery.ExtensionFileLoader(name, _build.CALL)
     module = importlib.util.module_from_spec(importlib.util.spec_from_file_location(name, _build.CALL, loader=loader))
     loader.exec_module(module)
+    if not hasattr(module, "read_through"):   # built from an earlier source, without all of the calls
+        return CtypesCall
     module.bind(fb4_opts, ctypes.c_void_p, CtypesCall)
+    # (a torch without the protocol has its tensors read by their methods)
+    module.read_through(torch.Tensor, getattr(torch.Tensor, "__dlpack_c_exchange_api__", None))
     return module
 
 
@@ -299,13 +331,12 @@ def fb4_attention_scores(q, k, mode=0, scores=None, stream=None):
 def fb4_select_salient_tokens(scores, grid_h, grid_w, tile_h=4, tile_w=4, rows_out=None, stream=None):
     """scores: float32 cuda [frames][heads][grid_h * grid_w].  Returns int32 [frames][tiles]: one row per tile,
     ascending within a frame, as rows of the [frames * tokens] tensor."""
-    frames, heads, tokens = scores.shape
-    assert tokens == grid_h * grid_w
-    tiles = ((grid_h + tile_h - 1) // tile_h) * ((grid_w + tile_w - 1) // tile_w)
     if rows_out is None:
+        frames, heads, tokens = scores.shape
+        assert tokens == grid_h * grid_w
+        tiles = ((grid_h + tile_h - 1) // tile_h) * ((grid_w + tile_w - 1) // tile_w)
         rows_out = torch.empty((frames, tiles), dtype=torch.int32, device=scores.device)
-    _check(_lib.fb4_select_salient_tokens(_dp(scores), frames, heads, grid_h, grid_w, tile_h, tile_w, _dp(rows_out),
-                                          _stream(stream)), "fb4_select_salient_tokens")
+    _check(_call.select_salient_tokens(scores, grid_h, grid_w, tile_h, tile_w, rows_out, _stream(stream)), "fb4_select_salient_tokens")
     return rows_out
 
 
@@ -314,15 +345,12 @@ def fb4_seda_assign(q, k, anchors, frames, grid_h, grid_w, tile_h=4, tile_w=4, w
     """q, k: bf16 cuda [frames][heads][tokens][dim] (joint=False) or [heads][frames * tokens][dim] (joint=True);
     anchors: int32 cuda, any shape, rows of the [frames * tokens] activation.  Returns (token_group, anchor_group)
     int32 [frames * tokens] (and the compared scores, float32 [n_anchors][window_t * window^2], if asked)."""
-    heads, dim = (q.shape[0], q.shape[2]) if joint else (q.shape[1], q.shape[3])
     tokens = grid_h * grid_w
-    n = anchors.numel()
     tg = torch.empty(frames * tokens, dtype=torch.int32, device=q.device) if token_group is None else token_group
     ag = torch.empty(frames * tokens, dtype=torch.int32, device=q.device) if anchor_group is None else anchor_group
-    sc = torch.empty((n, window_t * window * window), dtype=torch.float32, device=q.device) if want_scores else None
-    _check(_lib.fb4_seda_assign(_dp(q), _dp(k), 1 if joint else 0, frames, heads, grid_h, grid_w, dim, _dp(anchors), n,
-                                tile_h, tile_w, window, window_t, float(threshold), _dp(tg), _dp(ag), _dp(sc),
-                                _stream(stream)), "fb4_seda_assign")
+    sc = torch.empty((anchors.numel(), window_t * window * window), dtype=torch.float32, device=q.device) if want_scores else None
+    _check(_call.seda_assign(q, k, joint, frames, grid_h, grid_w, anchors, tile_h, tile_w, window, window_t, threshold, tg, ag, sc,
+                             _stream(stream)), "fb4_seda_assign")
     return (tg, ag, sc) if want_scores else (tg, ag)
 
 
@@ -331,16 +359,15 @@ def fb4_seda_main_anchor(temporal_scores, qt, kt, candidates, grid_h, grid_w, ti
     """temporal_scores: float32 cuda [tokens][heads][frames]; qt, kt: bf16 cuda [tokens][heads][frames][dim];
     candidates: int32 cuda [frames][n].  Returns (main_anchor int32 [tiles], kept int32 [frames][n]) and the compared
     scores float32 [frames][tiles] if asked."""
-    tokens, heads, frames, dim = qt.shape
-    assert tokens == grid_h * grid_w and candidates.shape[0] == frames
-    tiles = ((grid_h + tile_h - 1) // tile_h) * ((grid_w + tile_w - 1) // tile_w)
-    main = torch.empty(tiles, dtype=torch.int32, device=qt.device) if main_anchor is None else main_anchor
+    main, ps = main_anchor, None
+    if main is None or want_scores:
+        tiles = ((grid_h + tile_h - 1) // tile_h) * ((grid_w + tile_w - 1) // tile_w)
+        main = torch.empty(tiles, dtype=torch.int32, device=qt.device) if main is None else main
+        ps = torch.empty((qt.shape[2], tiles), dtype=torch.float32, device=qt.device) if want_scores else None
     if kept is None:
         kept = torch.empty_like(candidates)
-    ps = torch.empty((frames, tiles), dtype=torch.float32, device=qt.device) if want_scores else None
-    _check(_lib.fb4_seda_main_anchor(_dp(temporal_scores), _dp(qt), _dp(kt), frames, heads, grid_h, grid_w, dim,
-                                     _dp(candidates), candidates.shape[1], tile_h, tile_w, float(prune_threshold),
-                                     _dp(main), _dp(kept), _dp(ps), _stream(stream)), "fb4_seda_main_anchor")
+    _check(_call.seda_main_anchor(temporal_scores, qt, kt, candidates, grid_h, grid_w, tile_h, tile_w, prune_threshold, main, kept, ps,
+                                  _stream(stream)), "fb4_seda_main_anchor")
     return (main, kept, ps) if want_scores else (main, kept)
 
 
@@ -462,12 +489,9 @@ def fb4_repack_mxfp8(luts, codes, meta, block=32, elems=None, scales=None, strea
 def fb4_seda_profile(luts, meta, anchor_group, n_groups, counts=None, sub_formatbooks=None, stream=None):
     """Sub-formatbooks from the dialects selected on anchor tokens.  Returns (counts int32 [n_groups][32],
     sub_formatbooks uint8 [n_groups][8])."""
-    rows, nb = meta.shape
     if counts is None:
         counts = torch.empty((n_groups, 32), dtype=torch.int32, device=meta.device)
     if sub_formatbooks is None:
         sub_formatbooks = torch.empty((n_groups, 8), dtype=torch.uint8, device=meta.device)
-    rc = _lib.fb4_seda_profile(luts.handle, _dp(meta), rows, nb, _dp(anchor_group), n_groups, _dp(counts),
-                               _dp(sub_formatbooks), _stream(stream))
-    _check(rc, "fb4_seda_profile")
+    _check(_call.seda_profile(luts.handle, meta, anchor_group, n_groups, counts, sub_formatbooks, _stream(stream)), "fb4_seda_profile")
     return counts, sub_formatbooks

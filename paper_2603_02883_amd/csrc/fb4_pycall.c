@@ -1,6 +1,7 @@
-// The Python binding's calls into libfb4.so without ctypes: the entry points that a program calls per layer, with the
-// addresses, sizes and strides read from the tensor objects here.  Bound by the interpreter: a call of fb4_quantize on 300 x
-// 1152 spent 1.6 us of 5.1 in Python and ctypes; 4.1 so, what the launches take one behind the other.
+// The Python binding's calls into libfb4.so without ctypes: the entry points that a program calls per layer and every few
+// steps, with the addresses, sizes and strides read from the tensor objects here.  Bound by the interpreter: a call of fb4_quantize on 300 x
+// 1152 spent 1.6 us of 5.1 in Python and ctypes, 0.9 so, 0.3 where the tensors' own reader answers (look): 4.35 to 3.75-4.05 a call.
+// A refresh of 4 frames of 25 x 55 tokens, four calls: 25.1 us through ctypes, 21.3 so.
 // Only the ordinary argument types are read here.  Whatever else comes -- other types, other shapes, an error on the way -- goes
 // to the same call through ctypes, which converts or refuses it by ctypes' own rules: which arguments are taken and what is
 // raised for the others is decided in one place.
@@ -13,6 +14,25 @@
 
 static PyObject *s_data_ptr, *s_shape, *s_stride, *s_numel, *zero;
 static PyTypeObject *options_type, *handle_type;   // fb4_opts and ctypes.c_void_p (bind)
+
+// What a tensor type lends to C code, by the DLPack C exchange protocol (data layout of its major version 1): a reader of address,
+// sizes and strides that makes no Python objects.  us: the three matrices of fb4_quantize by their methods 0.54, so 0.09.
+typedef struct {
+    void* data;
+    struct { int32_t type, id; } device;
+    int32_t ndim;
+    struct { uint8_t code, bits; uint16_t lanes; } dtype;
+    int64_t *shape, *strides;   // the tensor's own
+    uint64_t byte_offset;
+} dl_tensor;
+typedef struct {
+    struct { uint32_t major, minor; } version;
+    void *previous, *allocator, *from_object, *to_object;
+    int (*read)(void* object, dl_tensor* out);
+    void* current_stream;
+} dl_exchange;
+static PyTypeObject* tensor_type;   // of exactly this type are the objects that `read_tensor` takes
+static int (*read_tensor)(void*, dl_tensor*);
 
 // The readers return 0, or -1 for what they do not read.
 
@@ -45,11 +65,26 @@ static int integer(PyObject* o, int64_t* out)
     return 0;
 }
 
+// 1 and the tensor's fields, or 0 for what its type's reader does not take (no storage, say, whose methods will say so).
+static int look(PyObject* t, dl_tensor* d)
+{
+    if (!read_tensor || Py_TYPE(t) != tensor_type) return 0;
+    if (read_tensor(t, d) == 0) return 1;
+    PyErr_Clear();
+    return 0;
+}
+static void* data_of(const dl_tensor* d) { return d->data ? (char*)d->data + d->byte_offset : NULL; }
+
 // Data pointer of a tensor, null for None.
 static int tensor(PyObject* t, void** out)
 {
     *out = NULL;
     if (t == Py_None) return 0;
+    dl_tensor v;
+    if (look(t, &v)) {
+        *out = data_of(&v);
+        return 0;
+    }
     PyObject* r = PyObject_CallMethodNoArgs(t, s_data_ptr);
     if (!r) return -1;
     const int rc = PyLong_Check(r) ? address(r, out) : -1;
@@ -72,6 +107,11 @@ static int row_stride(PyObject* t, const int64_t* d, int64_t* out)
 {
     *out = d[1];
     if (d[0] <= 1) return 0;
+    dl_tensor v;
+    if (look(t, &v) && v.ndim > 0) {
+        *out = v.strides[0];
+        return 0;
+    }
     PyObject* r = PyObject_CallMethodOneArg(t, s_stride, zero);
     if (!r) return -1;
     const int rc = integer(r, out);
@@ -79,8 +119,40 @@ static int row_stride(PyObject* t, const int64_t* d, int64_t* out)
     return rc;
 }
 
+// Sizes and address of a tensor of n dimensions.
+static int sized(PyObject* t, Py_ssize_t n, int64_t* d, void** out)
+{
+    dl_tensor v;
+    if (look(t, &v) && v.ndim == n) {
+        for (Py_ssize_t i = 0; i < n; ++i) d[i] = v.shape[i];
+        *out = data_of(&v);
+        return 0;
+    }
+    return shape(t, n, d) || tensor(t, out) ? -1 : 0;
+}
+
+// Sizes, row stride and address of a matrix.
+static int matrix(PyObject* t, int64_t* d, int64_t* st, void** out)
+{
+    dl_tensor v;
+    if (look(t, &v) && v.ndim == 2) {
+        d[0] = v.shape[0];
+        d[1] = v.shape[1];
+        *st = d[0] > 1 ? v.strides[0] : d[1];
+        *out = data_of(&v);
+        return 0;
+    }
+    return shape(t, 2, d) || row_stride(t, d, st) || tensor(t, out) ? -1 : 0;
+}
+
 static int numel(PyObject* t, int64_t* out)
 {
+    dl_tensor v;
+    if (look(t, &v)) {
+        *out = 1;
+        for (int32_t i = 0; i < v.ndim; ++i) *out *= v.shape[i];
+        return 0;
+    }
     PyObject* r = PyObject_CallMethodNoArgs(t, s_numel);
     if (!r) return -1;
     const int rc = integer(r, out);
@@ -91,6 +163,11 @@ static int numel(PyObject* t, int64_t* out)
 // Number of groups of a [groups][8] tensor.
 static int groups_of(PyObject* t, int64_t* out)
 {
+    dl_tensor v;
+    if (look(t, &v) && v.ndim > 0) {
+        *out = v.shape[0];
+        return 0;
+    }
     PyObject* s = PyObject_GetAttr(t, s_shape);
     if (!s) return -1;
     PyObject* r = PySequence_GetItem(s, 0);
@@ -109,9 +186,11 @@ static int count_or_none(PyObject* t, int (*count)(PyObject*, int64_t*), int64_t
 }
 
 // The same calls through ctypes (bind).
-enum { k_quantize, k_quantize_seda, k_quantize_decompose, k_dequantize, k_repack_mxfp8, k_layernorm_quantize, k_gelu_quantize, k_attention_scores, kCalls };
+enum { k_quantize, k_quantize_seda, k_quantize_decompose, k_dequantize, k_repack_mxfp8, k_layernorm_quantize, k_gelu_quantize, k_attention_scores,
+       k_select_salient_tokens, k_seda_assign, k_seda_main_anchor, k_seda_profile, kCalls };
 static const char* const call_names[kCalls] = {"quantize", "quantize_seda", "quantize_decompose", "dequantize", "repack_mxfp8",
-                                               "layernorm_quantize", "gelu_quantize", "attention_scores"};
+                                               "layernorm_quantize", "gelu_quantize", "attention_scores",
+                                               "select_salient_tokens", "seda_assign", "seda_main_anchor", "seda_profile"};
 static PyObject* through_ctypes[kCalls];
 
 static PyObject* elsewhere(int call, PyObject* const* a, Py_ssize_t n)
@@ -139,7 +218,7 @@ static PyObject* py_quantize(ARGS)
     void *h, *x, *c, *m, *s;
     fb4_opts o;
     int64_t d[2], st;
-    if (n != 6 || address(a[0], &h) || options(a[1], &o) || shape(a[2], 2, d) || row_stride(a[2], d, &st) || tensor(a[2], &x) ||
+    if (n != 6 || address(a[0], &h) || options(a[1], &o) || matrix(a[2], d, &st, &x) ||
         tensor(a[3], &c) || tensor(a[4], &m) || address(a[5], &s))
         return elsewhere(k_quantize, a, n);
     RETURN_CALL(fb4_quantize(h, &o, x, d[0], d[1], st, c, m, s));
@@ -151,7 +230,7 @@ static PyObject* py_quantize_seda(ARGS)
     void *h, *x, *tg, *sub, *c, *m, *s;
     fb4_opts o;
     int64_t d[2], st, g;
-    if (n != 8 || address(a[0], &h) || options(a[1], &o) || shape(a[2], 2, d) || row_stride(a[2], d, &st) || tensor(a[2], &x) ||
+    if (n != 8 || address(a[0], &h) || options(a[1], &o) || matrix(a[2], d, &st, &x) ||
         tensor(a[3], &tg) || tensor(a[4], &sub) || groups_of(a[4], &g) || tensor(a[5], &c) || tensor(a[6], &m) || address(a[7], &s))
         return elsewhere(k_quantize_seda, a, n);
     RETURN_CALL(fb4_quantize_seda(h, &o, x, d[0], d[1], st, tg, sub, (int)g, c, m, s));
@@ -163,7 +242,7 @@ static PyObject* py_quantize_decompose(ARGS)
     void *h, *x, *sal, *tg, *sub, *c1, *m1, *c2, *m2, *s;
     fb4_opts o;
     int64_t d[2], st, g, n_sal;
-    if (n != 11 || address(a[0], &h) || options(a[1], &o) || shape(a[2], 2, d) || row_stride(a[2], d, &st) || tensor(a[2], &x) ||
+    if (n != 11 || address(a[0], &h) || options(a[1], &o) || matrix(a[2], d, &st, &x) ||
         tensor(a[3], &sal) || numel(a[3], &n_sal) || tensor(a[4], &tg) || tensor(a[5], &sub) || count_or_none(a[5], groups_of, &g) || tensor(a[6], &c1) ||
         tensor(a[7], &m1) || tensor(a[8], &c2) || tensor(a[9], &m2) || address(a[10], &s))
         return elsewhere(k_quantize_decompose, a, n);
@@ -175,7 +254,7 @@ static PyObject* py_dequantize(ARGS)
 {
     void *h, *c1, *m1, *c2, *m2, *sal, *out, *s;
     int64_t d[2], block, n_sal, dtype, st;
-    if (n != 10 || address(a[0], &h) || shape(a[1], 2, d) || tensor(a[1], &c1) || tensor(a[2], &m1) || integer(a[3], &block) ||
+    if (n != 10 || address(a[0], &h) || sized(a[1], 2, d, &c1) || tensor(a[2], &m1) || integer(a[3], &block) ||
         tensor(a[4], &c2) || tensor(a[5], &m2) || tensor(a[6], &sal) || count_or_none(a[6], numel, &n_sal) || tensor(a[7], &out) || integer(a[8], &dtype) ||
         address(a[9], &s))
         return elsewhere(k_dequantize, a, n);
@@ -189,7 +268,7 @@ static PyObject* py_repack_mxfp8(ARGS)
 {
     void *h, *c, *m, *e, *sc, *s;
     int64_t d[2], block, st;
-    if (n != 7 || address(a[0], &h) || shape(a[1], 2, d) || tensor(a[1], &c) || tensor(a[2], &m) || integer(a[3], &block) ||
+    if (n != 7 || address(a[0], &h) || sized(a[1], 2, d, &c) || tensor(a[2], &m) || integer(a[3], &block) ||
         tensor(a[4], &e) || tensor(a[5], &sc) || address(a[6], &s))
         return elsewhere(k_repack_mxfp8, a, n);
     d[1] *= 2;
@@ -203,7 +282,7 @@ static PyObject* py_layernorm_quantize(ARGS)
     void *h, *x, *ga, *be, *tg, *sub, *c, *m, *y, *s;
     fb4_opts o;
     int64_t d[2], st, g;
-    if (n != 12 || !PyFloat_Check(a[5]) || address(a[0], &h) || options(a[1], &o) || shape(a[2], 2, d) || row_stride(a[2], d, &st) || tensor(a[2], &x) ||
+    if (n != 12 || !PyFloat_Check(a[5]) || address(a[0], &h) || options(a[1], &o) || matrix(a[2], d, &st, &x) ||
         tensor(a[3], &ga) || tensor(a[4], &be) || tensor(a[6], &tg) || tensor(a[7], &sub) || count_or_none(a[7], groups_of, &g) || tensor(a[8], &c) ||
         tensor(a[9], &m) || tensor(a[10], &y) || address(a[11], &s))
         return elsewhere(k_layernorm_quantize, a, n);
@@ -217,7 +296,7 @@ static PyObject* py_gelu_quantize(ARGS)
     void *h, *x, *tg, *sub, *c, *m, *s;
     fb4_opts o;
     int64_t d[2], st, g, approximate;
-    if (n != 9 || address(a[0], &h) || options(a[1], &o) || shape(a[2], 2, d) || row_stride(a[2], d, &st) || tensor(a[2], &x) ||
+    if (n != 9 || address(a[0], &h) || options(a[1], &o) || matrix(a[2], d, &st, &x) ||
         integer(a[3], &approximate) || tensor(a[4], &tg) || tensor(a[5], &sub) || count_or_none(a[5], groups_of, &g) || tensor(a[6], &c) || tensor(a[7], &m) ||
         address(a[8], &s))
         return elsewhere(k_gelu_quantize, a, n);
@@ -229,9 +308,67 @@ static PyObject* py_attention_scores(ARGS)
 {
     void *q, *k, *out, *s;
     int64_t d[3], mode;
-    if (n != 5 || shape(a[0], 3, d) || tensor(a[0], &q) || tensor(a[1], &k) || integer(a[2], &mode) || tensor(a[3], &out) || address(a[4], &s))
+    if (n != 5 || sized(a[0], 3, d, &q) || tensor(a[1], &k) || integer(a[2], &mode) || tensor(a[3], &out) || address(a[4], &s))
         return elsewhere(k_attention_scores, a, n);
     RETURN_CALL(fb4_attention_scores(q, k, d[0], d[1], d[2], (int)mode, out, s));
+}
+
+// The refresh of the attention-guided choices, from tensors that their type's reader takes (the others: by ctypes).
+
+// (scores, grid_h, grid_w, tile_h, tile_w, rows_out, stream)
+static PyObject* py_select_salient_tokens(ARGS)
+{
+    dl_tensor v;
+    void *out, *s;
+    int64_t gh, gw, th, tw;
+    if (n != 7 || !look(a[0], &v) || v.ndim != 3 || integer(a[1], &gh) || integer(a[2], &gw) || integer(a[3], &th) || integer(a[4], &tw) ||
+        tensor(a[5], &out) || address(a[6], &s) || v.shape[2] != gh * gw)
+        return elsewhere(k_select_salient_tokens, a, n);
+    RETURN_CALL(fb4_select_salient_tokens(data_of(&v), v.shape[0], (int)v.shape[1], (int)gh, (int)gw, (int)th, (int)tw, out, s));
+}
+
+// (q, k, joint, frames, grid_h, grid_w, anchors, tile_h, tile_w, window, window_t, threshold, token_group, anchor_group, scores, stream)
+static PyObject* py_seda_assign(ARGS)
+{
+    dl_tensor v;
+    void *k, *anchors, *tg, *ag, *sc, *s;
+    int64_t frames, gh, gw, th, tw, w, wt, n_anchors;
+    if (n != 16 || !PyBool_Check(a[2]) || !PyFloat_Check(a[11]) || !look(a[0], &v) || v.ndim != (a[2] == Py_True ? 3 : 4) || tensor(a[1], &k) ||
+        integer(a[3], &frames) || integer(a[4], &gh) || integer(a[5], &gw) || tensor(a[6], &anchors) || numel(a[6], &n_anchors) || integer(a[7], &th) ||
+        integer(a[8], &tw) || integer(a[9], &w) || integer(a[10], &wt) || tensor(a[12], &tg) || tensor(a[13], &ag) || tensor(a[14], &sc) ||
+        address(a[15], &s))
+        return elsewhere(k_seda_assign, a, n);
+    const int joint = a[2] == Py_True;
+    const float threshold = (float)PyFloat_AS_DOUBLE(a[11]);
+    RETURN_CALL(fb4_seda_assign(data_of(&v), k, joint, frames, (int)v.shape[joint ? 0 : 1], (int)gh, (int)gw, v.shape[joint ? 2 : 3], anchors, n_anchors,
+                                (int)th, (int)tw, (int)w, (int)wt, threshold, tg, ag, sc, s));
+}
+
+// (temporal_scores, qt, kt, candidates, grid_h, grid_w, tile_h, tile_w, prune_threshold, main_anchor, kept, prune_scores, stream)
+static PyObject* py_seda_main_anchor(ARGS)
+{
+    dl_tensor q, c;
+    void *ts, *k, *main, *kept, *ps, *s;
+    int64_t gh, gw, th, tw;
+    if (n != 13 || !PyFloat_Check(a[8]) || tensor(a[0], &ts) || !look(a[1], &q) || q.ndim != 4 || tensor(a[2], &k) || !look(a[3], &c) || c.ndim != 2 ||
+        integer(a[4], &gh) || integer(a[5], &gw) || integer(a[6], &th) || integer(a[7], &tw) || tensor(a[9], &main) || tensor(a[10], &kept) ||
+        tensor(a[11], &ps) || address(a[12], &s) || q.shape[0] != gh * gw || c.shape[0] != q.shape[2])
+        return elsewhere(k_seda_main_anchor, a, n);
+    const float threshold = (float)PyFloat_AS_DOUBLE(a[8]);
+    RETURN_CALL(fb4_seda_main_anchor(ts, data_of(&q), k, q.shape[2], (int)q.shape[1], (int)gh, (int)gw, q.shape[3], data_of(&c), (int)c.shape[1], (int)th,
+                                     (int)tw, threshold, main, kept, ps, s));
+}
+
+// (luts, meta, anchor_group, n_groups, counts, sub_formatbooks, stream)
+static PyObject* py_seda_profile(ARGS)
+{
+    dl_tensor v;
+    void *h, *ag, *counts, *sub, *s;
+    int64_t g;
+    if (n != 7 || address(a[0], &h) || !look(a[1], &v) || v.ndim != 2 || tensor(a[2], &ag) || integer(a[3], &g) || tensor(a[4], &counts) ||
+        tensor(a[5], &sub) || address(a[6], &s))
+        return elsewhere(k_seda_profile, a, n);
+    RETURN_CALL(fb4_seda_profile(h, data_of(&v), v.shape[0], v.shape[1], ag, (int)g, counts, sub, s));
 }
 
 // (fb4_opts, c_void_p, object with the same calls through ctypes)
@@ -257,9 +394,25 @@ static PyObject* py_bind(ARGS)
     Py_RETURN_NONE;
 }
 
+// (tensor type, its exchange capsule): True if tensors of exactly this type are read through it from now on
+static PyObject* py_read_through(ARGS)
+{
+    const dl_exchange* lent = NULL;
+    if (n == 2 && PyType_Check(a[0]) && PyCapsule_IsValid(a[1], "dlpack_exchange_api"))
+        lent = (const dl_exchange*)PyCapsule_GetPointer(a[1], "dlpack_exchange_api");
+    read_tensor = lent && lent->version.major == 1 ? lent->read : NULL;   // (a type need not have one)
+    if (read_tensor) {
+        Py_INCREF(a[0]);
+        Py_XSETREF(tensor_type, (PyTypeObject*)a[0]);
+    }
+    return PyBool_FromLong(read_tensor != NULL);
+}
+
 #define METHOD(name) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL, NULL}
 static PyMethodDef methods[] = {METHOD(quantize), METHOD(quantize_seda), METHOD(quantize_decompose), METHOD(dequantize), METHOD(repack_mxfp8),
-                                METHOD(layernorm_quantize), METHOD(gelu_quantize), METHOD(attention_scores), METHOD(bind), {NULL, NULL, 0, NULL}};
+                                METHOD(layernorm_quantize), METHOD(gelu_quantize), METHOD(attention_scores), METHOD(select_salient_tokens),
+                                METHOD(seda_assign), METHOD(seda_main_anchor), METHOD(seda_profile), METHOD(bind),
+                                METHOD(read_through), {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fb4call", NULL, -1, methods, NULL, NULL, NULL, NULL};
 
 PyMODINIT_FUNC PyInit__fb4call(void)

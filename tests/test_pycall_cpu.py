@@ -2,6 +2,8 @@
 every entry point answer before it looks at the device)."""
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 import subprocess
 import sys
@@ -141,3 +143,187 @@ def test_calls_through_ctypes_answer_like_the_modules():
                     assert call(h) == got == F.ERR_INVALID_ARG, name
                 finally:
                     B._call = module
+
+
+RECORDER = r"""
+#include <stdint.h>
+#include "fb4.h"
+int64_t seen[16];
+#define P(i, v) seen[i] = (int64_t)(uintptr_t)(v)
+#define N(i, v) seen[i] = (int64_t)(v)
+int fb4_quantize(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, uint8_t* co, uint16_t* m, void* s)
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, co); P(5, m); return 0; }
+int fb4_quantize_seda(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, const int32_t* tg, const uint8_t* sub, int g,
+                      uint8_t* co, uint16_t* m, void* s)
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, tg); P(5, sub); N(6, g); P(7, co); P(8, m); return 0; }
+int fb4_quantize_decompose(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, const int32_t* tg, const uint8_t* sub, int g,
+                           const int32_t* sal, int64_t n, uint8_t* c1, uint16_t* m1, uint8_t* c2, uint16_t* m2, void* s)
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, tg); P(5, sub); N(6, g); P(7, sal); N(8, n); P(9, c1); P(10, m1); P(11, c2); P(12, m2); return 0; }
+int fb4_dequantize(const fb4_luts* l, const uint8_t* c1, const uint16_t* m1, int64_t r, int64_t c, int b, const uint8_t* c2, const uint16_t* m2,
+                   const int32_t* sal, int64_t n, void* out, int dt, int64_t st, void* s)
+{ P(0, c1); P(1, m1); N(2, r); N(3, c); N(4, b); P(5, c2); P(6, m2); P(7, sal); N(8, n); P(9, out); N(10, dt); N(11, st); return 0; }
+int fb4_repack_mxfp8(const fb4_luts* l, const uint8_t* co, const uint16_t* m, int64_t r, int64_t c, int b, uint8_t* e, int64_t st, uint8_t* sc, void* s)
+{ P(0, co); P(1, m); N(2, r); N(3, c); N(4, b); P(5, e); N(6, st); P(7, sc); return 0; }
+int fb4_layernorm_quantize(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, const float* ga, const float* be, float eps,
+                           const int32_t* tg, const uint8_t* sub, int g, uint8_t* co, uint16_t* m, void* y, void* s)
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, ga); P(5, be); P(6, tg); P(7, sub); N(8, g); P(9, co); P(10, m); P(11, y); return 0; }
+int fb4_gelu_quantize(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, int a, const int32_t* tg, const uint8_t* sub, int g,
+                      uint8_t* co, uint16_t* m, void* s)
+{ P(0, x); N(1, r); N(2, c); N(3, st); N(4, a); P(5, tg); P(6, sub); N(7, g); P(8, co); P(9, m); return 0; }
+int fb4_attention_scores(const void* q, const void* k, int64_t g, int64_t t, int64_t d, int mode, float* out, void* s)
+{ P(0, q); P(1, k); N(2, g); N(3, t); N(4, d); N(5, mode); P(6, out); return 0; }
+int fb4_select_salient_tokens(const float* sc, int64_t f, int h, int gh, int gw, int th, int tw, int32_t* out, void* s)
+{ P(0, sc); N(1, f); N(2, h); N(3, gh); N(4, gw); N(5, th); N(6, tw); P(7, out); return 0; }
+int fb4_seda_assign(const void* q, const void* k, int j, int64_t f, int h, int gh, int gw, int64_t d, const int32_t* an, int64_t n, int th, int tw, int w,
+                    int wt, float t, int32_t* tg, int32_t* ag, float* sc, void* s)
+{ P(0, q); P(1, k); N(2, j); N(3, f); N(4, h); N(5, gh * 1000 + gw); N(6, d); P(7, an); N(8, n); N(9, th * 1000 + tw); N(10, w * 1000 + wt);
+  N(11, t * 4096); P(12, tg); P(13, ag); P(14, sc); return 0; }
+int fb4_seda_main_anchor(const float* ts, const void* q, const void* k, int64_t f, int h, int gh, int gw, int64_t d, const int32_t* c, int n, int th, int tw,
+                         float t, int32_t* m, int32_t* kept, float* ps, void* s)
+{ P(0, ts); P(1, q); P(2, k); N(3, f); N(4, h); N(5, gh); N(6, gw); N(7, d); P(8, c); N(9, n); N(10, th); N(11, tw); N(12, t * 4096); P(13, m);
+  P(14, kept); P(15, ps); return 0; }
+int fb4_seda_profile(const fb4_luts* l, const uint16_t* m, int64_t r, int64_t nb, const int32_t* ag, int g, uint32_t* c, uint8_t* sub, void* s)
+{ P(0, m); N(1, r); N(2, nb); P(3, ag); N(4, g); P(5, c); P(6, sub); return 0; }
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory, request):
+    """The module on a library that notes down what its calls get: (module, function that returns and clears the notes)."""
+    if not hasattr(torch.Tensor, "__dlpack_c_exchange_api__") or not B._build.can_build_call():
+        pytest.skip("tensors without a reader, or nothing to build the module with")
+    d = tmp_path_factory.mktemp("recorder")
+    (d / "recorder.c").write_text(RECORDER)
+    lib, so = d / "libfb4_recorder.so", d / "_fb4call_recorder.so"
+    include = os.path.join(os.path.dirname(os.path.dirname(B.__file__)), "include")
+    cc = B._build.HOST_CC.split()
+    subprocess.run(cc + ["-shared", "-fPIC", "-I" + include, "-o", str(lib), str(d / "recorder.c")], check=True)
+    subprocess.run(cc + ["-O1", "-shared", "-fPIC", "-I" + B._build.PYTHON_INCLUDE, "-o", str(so), B._build.CALL_SOURCE, "-L" + str(d),
+                         "-l:" + lib.name, "-Wl,-rpath,$ORIGIN"], check=True)
+    loader = importlib.machinery.ExtensionFileLoader("_fb4call", str(so))
+    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_fb4call", str(so), loader=loader))
+    loader.exec_module(module)
+    module.bind(B.fb4_opts, ctypes.c_void_p, B.CtypesCall)
+    recording = ctypes.CDLL(str(lib))
+    seen = (ctypes.c_int64 * 16).in_dll(recording, "seen")
+    for call in B.EXPORTS:   # (what the module hands over to ctypes gets there too)
+        if hasattr(recording, call):
+            getattr(recording, call).argtypes = getattr(B.lib(), call).argtypes
+    real, B._lib = B._lib, recording
+    request.addfinalizer(lambda: setattr(B, "_lib", real))
+
+    def notes():
+        out = list(seen)
+        ctypes.memset(seen, 0xEE, ctypes.sizeof(seen))
+        return out
+
+    return module, notes
+
+
+def matrices():
+    big = torch.zeros((6, 192), dtype=torch.bfloat16)
+    return {"plain": big, "columns": big[:, 64:128], "rows": big[1:5], "every other row": big[::2], "one row": big[2:3], "one row, strided": big[::6],
+            "no rows": big[:0], "no columns": big[:, :0], "transposed": big.t(), "stride 0": big[:1].expand(6, 192), "gradient": torch.zeros((4, 64), requires_grad=True),
+            "parameter": torch.nn.Parameter(torch.zeros((4, 64))), "lazy copy": torch._lazy_clone(big), "float8": torch.zeros((4, 64), dtype=torch.float8_e4m3fn),
+            "conjugate": torch.zeros((4, 64), dtype=torch.complex64).conj(), "meta": torch.zeros((4, 64), device="meta")}
+
+
+@pytest.mark.parametrize("name", list(matrices()))
+def test_tensors_are_read_as_by_their_methods(recorder, name):
+    module, notes = recorder
+    x = matrices()[name]
+    o, h = F.opts(), ctypes.c_void_p(64)
+    c, m = torch.zeros((4, 32), dtype=torch.uint8), torch.zeros((9, 2), dtype=torch.int16)[3:]
+    tg, sub, sal = torch.zeros(4, dtype=torch.int32), torch.zeros((3, 8), dtype=torch.uint8), torch.zeros((2, 3), dtype=torch.int32)
+    cube = x[None].expand(2, *x.shape)
+    calls = [lambda: module.quantize(h, o, x, c, x, 0), lambda: module.quantize_seda(h, o, x, tg, sub, c, m, 0), lambda: module.quantize_seda(h, o, x, tg, x, c, m, 0),
+             lambda: module.quantize_decompose(h, o, x, sal, None, None, c, m, c[1:], m, 0), lambda: module.quantize_decompose(h, o, x, x, tg, sub, c, m, c, m, 0),
+             lambda: module.dequantize(h, c, m, 32, None, None, None, x, 0, 0), lambda: module.dequantize(h, x, m, 16, c, m, sal, x, 1, 0),
+             lambda: module.repack_mxfp8(h, x, m, 32, x, c, 0), lambda: module.repack_mxfp8(h, c, m, 32, x, c, 0),
+             lambda: module.layernorm_quantize(h, o, x, tg[1:], None, 1e-6, tg, sub, c, m, x, 0),
+             lambda: module.gelu_quantize(h, o, x, 1, None, None, c, m, 0), lambda: module.attention_scores(cube, cube, 1, x, 0)]
+
+    def results():
+        notes()
+        return [(call(), notes()) for call in calls]
+
+    assert not module.read_through(torch.Tensor, None)
+    want = results()
+    assert module.read_through(torch.Tensor, torch.Tensor.__dlpack_c_exchange_api__)
+    assert results() == want
+
+
+def test_tensors_without_storage_are_refused_as_before(recorder):
+    module, _ = recorder
+    c = torch.zeros((4, 32), dtype=torch.uint8)
+    for through in (None, torch.Tensor.__dlpack_c_exchange_api__):
+        module.read_through(torch.Tensor, through)
+        for transform in (torch.vmap, lambda f: torch.func.grad(lambda x: f(x).sum())):
+            with pytest.raises(RuntimeError, match="data pointer"):
+                transform(lambda x: (module.quantize(ctypes.c_void_p(64), F.opts(), x, c, c, 0), x)[1])(torch.zeros((2, 4, 64))[0] if transform is not torch.vmap else torch.zeros((2, 4, 64)))
+        with pytest.raises(ValueError):
+            module.quantize(ctypes.c_void_p(64), F.opts(), torch.zeros((1, 4, 64)), c, c, 0)
+
+
+def refresh_calls(module, kind):
+    """The refresh's calls with tensors and numbers of one kind."""
+    frames, heads, gh, gw, dim = 3, 5, 4, 6, 16
+    sc, ts = torch.zeros((frames, heads, gh * gw)), torch.zeros((gh * gw, heads, frames))
+    q, qt = torch.zeros((frames, heads, gh * gw, dim), dtype=torch.bfloat16), torch.zeros((gh * gw, heads, frames, dim), dtype=torch.bfloat16)
+    qj = torch.zeros((heads, frames * gh * gw, dim), dtype=torch.bfloat16)
+    cand, out, meta = torch.zeros((frames, 2), dtype=torch.int32), torch.zeros(72, dtype=torch.int32), torch.zeros((72, 9), dtype=torch.int16)
+    t, joint, i = 1.5, (False, True), int
+    if kind == "views":
+        sc, ts, q, qt, cand, meta = sc.transpose(0, 1).contiguous().transpose(0, 1), ts[1:2].expand(gh * gw, heads, frames), q.transpose(1, 2).contiguous().transpose(1, 2), qt.flip(0), cand[:, :1], meta[:, 3:]
+    elif kind == "parameters":
+        sc, ts, q, qj, qt = (torch.nn.Parameter(v) for v in (sc, ts, q, qj, qt))
+    elif kind == "numbers":
+        t, joint, i = np.float32(1.5), (0, 1), np.int32
+    elif kind == "no scores":
+        sc, ts, q, qt, qj, cand, meta = sc[:0], ts[:, :, :0], q[:0], qt[:, :, :0], qj[:, :0], cand[:0], meta[:0]
+        frames = 0
+    h = ctypes.c_void_p(64)
+    return [lambda: module.select_salient_tokens(sc, i(gh), gw, 4, i(2), out, 0), lambda: module.select_salient_tokens(sc, gh, gw, 4, 4, None, None),
+            lambda: module.seda_assign(q, q, joint[0], frames, gh, i(gw), cand, 4, 2, 5, i(1), t, out, out, None, 0),
+            lambda: module.seda_assign(qj, q, joint[1], i(frames), gh, gw, out, 4, 4, 3, 2, 2, out, out[1:], ts, 0),
+            lambda: module.seda_main_anchor(ts, qt, qt, cand, gh, gw, i(4), 2, t, out, cand, None, 0),
+            lambda: module.seda_main_anchor(ts, qt, q, cand, gh, gw, 4, 4, 3, out, cand, sc, 0),
+            lambda: module.seda_profile(h, meta, out, i(7), out, cand, 0), lambda: module.seda_profile(h, q[0, 0], out, 7, out, cand, 0) if frames else None,
+            # sizes and shapes that are refused
+            lambda: module.select_salient_tokens(sc, gh, gw + 1, 4, 4, out, 0), lambda: module.select_salient_tokens(q, gh, gw, 4, 4, out, 0),
+            lambda: module.seda_main_anchor(ts, qt, qt, torch.zeros((9, 2), dtype=torch.int32), gh, gw, 4, 2, t, out, cand, None, 0),
+            lambda: module.seda_main_anchor(ts, qj, qt, cand, gh, gw, 4, 2, t, out, cand, None, 0),
+            lambda: module.seda_assign(qj, q, False, 3, gh, gw, cand, 4, 2, 5, 1, t, out, out, None, 0),
+            lambda: module.seda_assign(q, q, False, 3, gh, gw, None, 4, 2, 5, 1, t, out, out, None, 0),
+            lambda: module.seda_assign(q, q, False, 3, gh, gw, cand, 4, 2, 5, 1, None, out, out, None, 0),
+            lambda: module.seda_profile(h, meta, out, 7.5, out, cand, 0), lambda: module.seda_profile(h, sc, out, 7, out, cand, 0)]
+
+
+@pytest.mark.parametrize("kind", ["plain", "views", "parameters", "numbers", "no scores"])
+def test_the_refresh_is_called_as_through_ctypes(recorder, kind):
+    module, notes = recorder
+
+    def results(calls):
+        out = []
+        for call in calls:
+            notes()
+            try:
+                out.append((call(), notes()))
+            except Exception as e:
+                out.append((type(e), str(e)))
+        return out
+
+    # (the same tensors on both sides: the module to ask is looked up at the call)
+    class Asked:
+        which = B.CtypesCall
+
+        def __getattr__(self, name):
+            return getattr(Asked.which, name)
+
+    calls = refresh_calls(Asked(), kind)
+    want = results(calls)
+    Asked.which = module
+    assert module.read_through(torch.Tensor, torch.Tensor.__dlpack_c_exchange_api__)
+    assert results(calls) == want
+    assert not module.read_through(torch.Tensor, None)
+    assert results(calls) == want
