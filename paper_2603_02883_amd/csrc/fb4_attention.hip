@@ -288,17 +288,19 @@ int fb4_seda_main_anchor(const float* temporal_scores, const void* qt, const voi
     const int64_t most = tiles <= 512 ? kMainMaxThreads : tiles <= (1 << 22) ? 512 : 256;
     const unsigned threads = (unsigned)std::min<int64_t>(std::max<int64_t>(frames, 4) * 64, most);
     // A tile's frames in parts, each with a workgroup that finds the tile's main anchor for itself, while a compute unit gets no
-    // second one: what a compute unit has of the rows' loads in flight is what the pruning takes (us, one part / so, inputs
-    // changing: 64 tiles x 16 frames x 24 heads x 128 channels 8.6 / 7.8, 16 tiles 8.3 / 6.9, 64 x 32 x 16 x 64 10.8 / 9.2, 96 x 17 x
-    // 16 x 72 8.7 / 8.1; two workgroups per compute unit: 256 tiles x 8 frames x 24 x 64 8.2 / 9.0).  Not where `kept` overwrites
-    // the list that the other parts still read.
+    // second one: what a compute unit has of loads in flight is what the pruning takes.  us, one part / so (graph, inputs changing):
+    // 64 tiles x 16 frames x 24 heads x 128 channels 7.85 / 7.05, 16 tiles 7.25 / 6.4, 64 x 32 x 16 x 64 10.4 / 8.5, 4 x 32 x 8 x 128 7.8 /
+    // 6.6.  Not for short rows (64 x 16 x 8 x 72 5.4 / 5.7, 65 x 12 x 12 x 64 5.65 / 6.2) nor where many tiles' parts come to different
+    // XCDs (121 x 16 x 24 x 128 8.8 / 8.9), and not where `kept` overwrites the list that the other parts still read.
     const uintptr_t from = reinterpret_cast<uintptr_t>(candidates), to = reinterpret_cast<uintptr_t>(kept);
     const bool in_place = from < to + n_cand * sizeof(int32_t) && to < from + n_cand * sizeof(int32_t);
-    const int64_t parts = in_place ? 1 : std::max<int64_t>(std::min<int64_t>(256 / tiles, frames), 1);   // (256 compute units)
-    launch(seda_main_anchor_kernel, dim3((unsigned)(tiles * parts)), dim3(threads), 0, s, temporal_scores,
+    const bool worth = heads * dim >= 1024 && (tiles % 8 == 0 || tiles <= 32) && !in_place;
+    const int64_t parts = worth ? std::max<int64_t>(std::min<int64_t>(256 / tiles, frames), 1) : 1;   // (256 compute units)
+    launch(parts > 1 ? seda_main_anchor_kernel<true> : seda_main_anchor_kernel<false>, dim3((unsigned)tiles, (unsigned)parts), dim3(threads), 0, s, temporal_scores,
                        static_cast<const uint16_t*>(qt), static_cast<const uint16_t*>(kt), (uint32_t)frames, (uint32_t)heads,
                        (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)dim, candidates, (uint32_t)n_per_frame, (uint32_t)tile_h,
-                       (uint32_t)tile_w, prune_threshold, main_anchor, kept, prune_scores, threads / 64u, (uint32_t)tiles, (uint32_t)parts);
+                       (uint32_t)tile_w, prune_threshold, main_anchor, kept, prune_scores, threads / 64u, (uint32_t)tiles,
+                       main_anchor_split((uint32_t)frames, (uint32_t)parts, threads / 64u, (uint32_t)heads));
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }
 

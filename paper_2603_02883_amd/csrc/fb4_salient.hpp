@@ -876,50 +876,56 @@ __global__ __launch_bounds__(kAssignThreads) void seda_mark_kernel(const uint16_
 // no candidate of its frame by the workgroup of tile 0), so no launch has to clear it first.
 // Bound by its chain of dependent loads (list, temporal scores, the two rows of every head): a wavefront per frame up
 // to 16, the loads of four heads in flight, the best frame found by the lanes of one wavefront.  64 tiles x 16 frames x
-// 24 heads x 128 channels: 30 us with four wavefronts, serial head sums and one frame after the other, 8.6
-// so, 7.8 in four parts (inputs changing).
+// 24 heads x 128 channels: 30 us with four wavefronts, serial head sums and one frame after the other, 7.85 so, 7.05 in four parts
+// (in a graph, inputs changing).
 constexpr int kMainThreads = 256;       // seda_main_anchor_3d_kernel
 constexpr int kMainMaxThreads = 1024;   // seda_main_anchor_kernel: 64 per frame, at most these (the launcher says when)
 constexpr uint32_t kMainMaxFrames = 1024;
+// How the pruning of a tile's frames is split: frames per part (of a tile: blockIdx.y), wavefronts per frame, and 256 / those, rounded
+// up, which divides a wavefront's number (a division would take as long as a load).
+inline uint32_t main_anchor_split(uint32_t frames, uint32_t parts, uint32_t n_waves, uint32_t heads)
+{
+    const uint32_t per_part = std::max((frames + parts - 1) / parts, 1u);
+    const uint32_t shares = parts > 1 ? std::min(std::max(n_waves / per_part, 1u), (heads + 3) / 4) : 1u;
+    return per_part | shares << 11 | ((256 + shares - 1) / shares) << 16;
+}
 
+// kParts: several workgroups per tile (blockIdx.y).
+template <bool kParts>
 __global__ __launch_bounds__(kMainMaxThreads) void seda_main_anchor_kernel(
     const float* temporal_scores, const uint16_t* qt, const uint16_t* kt, uint32_t frames, uint32_t heads, uint32_t grid_h,
     uint32_t grid_w, uint32_t dim, const int32_t* cand, uint32_t n_per_frame, uint32_t tile_h, uint32_t tile_w,
-    float prune_threshold, int32_t* main_anchor, int32_t* kept, float* prune_scores, uint32_t n_waves, uint32_t tiles, uint32_t parts)
+    float prune_threshold, int32_t* main_anchor, int32_t* kept, float* prune_scores, uint32_t n_waves, uint32_t tiles, uint32_t split)
 {
     __shared__ double score[kMainMaxFrames];
     __shared__ int32_t slot[kMainMaxFrames], row_of[kMainMaxFrames];
     __shared__ int32_t best_frame;
     __shared__ float share_sum[kMainMaxThreads / 64];
     constexpr uint32_t kNone = 0xFFFFFFFFu;
-    // (the parts of a tile a multiple of `tiles` apart: on one XCD where that is a multiple of eight)
-    const uint32_t tokens = grid_h * grid_w, part = blockIdx.x / tiles, tile = blockIdx.x - part * tiles;
+    const uint32_t tokens = grid_h * grid_w, tile = blockIdx.x, part = kParts ? blockIdx.y : 0u;
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (uint32_t f = wave; f < frames; f += n_waves) {
         const int32_t* list = cand + (size_t)f * n_per_frame;
         int32_t* out = kept + (size_t)f * n_per_frame;
         uint32_t found = kNone;
-        int32_t row = -1;
         for (uint32_t j0 = 0; j0 < n_per_frame; j0 += 64) {
             const uint32_t j = j0 + lane;
             bool mine = false;
-            int32_t at = -1;
             if (j < n_per_frame) {
-                at = list[j];
-                const bool valid = at >= (int64_t)f * tokens && at < (int64_t)(f + 1) * tokens;
-                mine = valid && tile_of((uint32_t)at - f * tokens, grid_w, tile_h, tile_w) == tile;
+                const int64_t row = list[j];
+                const bool valid = row >= (int64_t)f * tokens && row < (int64_t)(f + 1) * tokens;
+                mine = valid && tile_of((uint32_t)(row - (int64_t)f * tokens), grid_w, tile_h, tile_w) == tile;
                 if (!valid && tile == 0 && part == 0) out[j] = -1;
             }
             const unsigned long long m = __ballot(mine);
             const uint32_t first = m ? j0 + (uint32_t)__builtin_ctzll(m) : kNone;
             if (mine && part == 0 && (found != kNone || j != first)) out[j] = -1;   // a later entry of the same tile
-            if (found == kNone && m) {
-                found = first;
-                row = __builtin_amdgcn_readlane(at, (int)(first - j0));
-            }
+            if (found == kNone) found = first;
         }
         double v = 0.0;
+        int32_t row = -1;
         if (found != kNone) {
+            row = list[found];
             const uint32_t pos = (uint32_t)(row - (int32_t)(f * tokens));
             for (uint32_t h0 = 0; h0 < heads; h0 += 64) {
                 const uint32_t cnt = min(64u, heads - h0);
@@ -957,40 +963,72 @@ __global__ __launch_bounds__(kMainMaxThreads) void seda_main_anchor_kernel(
     __syncthreads();
     const int32_t bf = __builtin_amdgcn_readfirstlane(best_frame);
     const uint32_t n16 = dim / 8;
-    // this workgroup's frames; where it has more wavefronts than those, several take a frame, every fourth of its heads in turn
-    const uint32_t per_part = max((frames + parts - 1u) / parts, 1u), f0 = min(part * per_part, frames), f1 = min(f0 + per_part, frames);
-    const uint32_t shares = min(max(n_waves / per_part, 1u), (heads + 3u) / 4u), at_once = n_waves / shares;
-    const uint32_t mine = wave / shares, share = wave - mine * shares;
-    for (uint32_t base = f0; base < f1; base += at_once) {   // (once where frames are shared)
-        const uint32_t f = base + mine;
-        const bool ok = mine < at_once && f < f1;
-        float sc = __builtin_nanf("");
-        const bool anchored = ok && slot[f] >= 0;   // (then the tile has a main anchor)
-        if (anchored) {
-            const uint32_t pos = (uint32_t)(row_of[bf] - (int32_t)((uint32_t)bf * tokens));
-            // 16 lanes share a row's 16-byte pieces, four heads at a time; the wavefront's sum in a fixed order
-            float acc = 0.0f;
-            const size_t row0 = (size_t)pos * heads * frames;
-            const uint32_t step = 4u * shares;
-            for (uint32_t c = lane & 15u; c < n16; c += 16) {
-                for (uint32_t h0 = (lane >> 4) + 4u * share; h0 < heads; h0 += 4u * step) {
-                    uint4 a[4], b[4];   // four heads' rows in flight (past the last head: the first of them again)
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; ++j) {
-                        const uint32_t h = h0 + j * step < heads ? h0 + j * step : h0;
-                        a[j] = reinterpret_cast<const uint4*>(qt + (row0 + (size_t)h * frames + (uint32_t)bf) * dim)[c];
-                        b[j] = reinterpret_cast<const uint4*>(kt + (row0 + (size_t)h * frames + f) * dim)[c];
-                    }
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; ++j) {
-                        const uint32_t qs[4] = {a[j].x, a[j].y, a[j].z, a[j].w}, ks[4] = {b[j].x, b[j].y, b[j].z, b[j].w};
-                        float with = acc;
+    // this workgroup's frames
+    const uint32_t per_part = split & 0x7FFu, shares = kParts ? (split >> 11) & 31u : 1u;
+    const uint32_t f0 = kParts ? min(part * per_part, frames) : 0u, f1 = kParts ? min(f0 + per_part, frames) : frames;
+    if (shares == 1u) {
+        for (uint32_t f = f0 + wave; f < f1; f += n_waves) {
+            float sc = __builtin_nanf("");
+            if (slot[f] >= 0) {   // (then the tile has a main anchor)
+                const uint32_t pos = (uint32_t)(row_of[bf] - (int32_t)((uint32_t)bf * tokens));
+                // 16 lanes share a row's 16-byte pieces, four heads at a time; the wavefront's sum in a fixed order
+                float acc = 0.0f;
+                const size_t base = (size_t)pos * heads * frames;
+                for (uint32_t c = lane & 15u; c < n16; c += 16) {
+#pragma unroll 4
+                    for (uint32_t h = lane >> 4; h < heads; h += 4) {
+                        const uint4 a = reinterpret_cast<const uint4*>(qt + (base + (size_t)h * frames + (uint32_t)bf) * dim)[c];
+                        const uint4 b = reinterpret_cast<const uint4*>(kt + (base + (size_t)h * frames + f) * dim)[c];
+                        const uint32_t qs[4] = {a.x, a.y, a.z, a.w}, ks[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            with = __builtin_fmaf(__uint_as_float(qs[i] << 16), __uint_as_float(ks[i] << 16), with);
-                            with = __builtin_fmaf(__uint_as_float(qs[i] & 0xFFFF0000u), __uint_as_float(ks[i] & 0xFFFF0000u), with);
+                            acc = __builtin_fmaf(__uint_as_float(qs[i] << 16), __uint_as_float(ks[i] << 16), acc);
+                            acc = __builtin_fmaf(__uint_as_float(qs[i] & 0xFFFF0000u), __uint_as_float(ks[i] & 0xFFFF0000u), acc);
                         }
-                        acc = h0 + j * step < heads ? with : acc;
+                    }
+                }
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+                sc = acc / (float)heads;
+                if (lane == 0)
+                    kept[(size_t)f * n_per_frame + slot[f]] = ((int32_t)f == bf || sc > prune_threshold) ? row_of[f] : -1;
+            }
+            if (lane == 0 && prune_scores) prune_scores[(size_t)f * tiles + tile] = sc;
+        }
+    } else {
+        // more wavefronts than frames: `shares` of them take a frame, every fourth of its heads in turn; addresses from scalar
+        // parts and no work past the last head (with 16 wavefronts on a compute unit instructions cost as much as a round of loads)
+        const uint32_t mine = (wave * (split >> 16)) >> 8, share = wave - mine * shares, f = f0 + mine;
+        const bool ok = f < f1, anchored = ok && slot[min(f, frames - 1u)] >= 0;   // (then the tile has a main anchor)
+        float sc = __builtin_nanf("");
+        if (anchored) {
+            const uint32_t pos = __builtin_amdgcn_readfirstlane((uint32_t)(row_of[bf] - (int32_t)((uint32_t)bf * tokens)));
+            const size_t row0 = (size_t)pos * heads * frames, head = (size_t)frames * n16;
+            const uint4* q0 = reinterpret_cast<const uint4*>(qt) + (row0 + (uint32_t)bf) * n16;
+            const uint4* k0 = reinterpret_cast<const uint4*>(kt) + (row0 + f) * n16;
+            const uint32_t own = lane >> 4, step = 4u * shares;
+            float acc = 0.0f;
+            for (uint32_t c = lane & 15u; c < n16; c += 16) {
+                for (uint32_t h0 = 4u * share; h0 < heads; h0 += 2u * step) {   // (wave-uniform)
+                    const bool two = h0 + step < heads;
+                    uint4 a[2] = {}, b[2] = {};   // two heads' rows in flight (zeros past the last head)
+                    if (h0 + own < heads) {
+                        a[0] = q0[(h0 + own) * head + c];
+                        b[0] = k0[(h0 + own) * head + c];
+                    }
+                    if (two && h0 + step + own < heads) {
+                        a[1] = q0[(h0 + step + own) * head + c];
+                        b[1] = k0[(h0 + step + own) * head + c];
+                    }
+#pragma unroll
+                    for (uint32_t j = 0; j < 2; ++j) {
+                        if (j && !two) break;
+                        const uint32_t qs[4] = {a[j].x, a[j].y, a[j].z, a[j].w}, ks[4] = {b[j].x, b[j].y, b[j].z, b[j].w};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            acc = __builtin_fmaf(__uint_as_float(qs[i] << 16), __uint_as_float(ks[i] << 16), acc);
+                            acc = __builtin_fmaf(__uint_as_float(qs[i] & 0xFFFF0000u), __uint_as_float(ks[i] & 0xFFFF0000u), acc);
+                        }
                     }
                 }
             }
@@ -998,14 +1036,10 @@ __global__ __launch_bounds__(kMainMaxThreads) void seda_main_anchor_kernel(
             for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
             sc = acc;
         }
-        if (shares > 1) {
-            if (lane == 0) share_sum[wave] = sc;
-            __syncthreads();
-            if (anchored && share == 0) {
-                for (uint32_t j = 1; j < shares; ++j) sc += share_sum[wave + j];
-            }
-        }
+        if (lane == 0) share_sum[wave] = sc;
+        __syncthreads();
         if (ok && lane == 0 && share == 0) {
+            for (uint32_t j = 1; j < shares; ++j) sc += share_sum[wave + j];
             sc /= (float)heads;   // (NaN without a candidate)
             if (anchored) kept[(size_t)f * n_per_frame + slot[f]] = ((int32_t)f == bf || sc > prune_threshold) ? row_of[f] : -1;
             if (prune_scores) prune_scores[(size_t)f * tiles + tile] = sc;

@@ -147,22 +147,23 @@ def test_seda_main_anchor_frames_heads_and_ties(F, frames, heads, dim):
                 assert kept.cpu().numpy()[f, tile] == (cand[f, tile] if keep else -1)
 
 
-# a tile's frames in 1 to 17 parts, wavefronts that share a frame's heads (up to six of them), a list that is overwritten
-@pytest.mark.parametrize("gh,gw,frames,heads,dim", [(4, 4, 17, 24, 72), (8, 24, 16, 5, 136), (20, 20, 5, 9, 8), (32, 32, 16, 24, 128), (37, 40, 3, 4, 64),
-                                                    (44, 44, 16, 3, 16), (45, 48, 16, 21, 24), (64, 64, 2, 1, 8)])
-def test_seda_main_anchor_in_parts(F, gh, gw, frames, heads, dim):
+# a tile's frames in 1 to 28 parts (some of them empty), one to six wavefronts per frame, a list that is overwritten
+@pytest.mark.parametrize("gh,gw,tile,frames,heads,dim", [(4, 4, 4, 17, 24, 72), (8, 16, 4, 6, 9, 120), (32, 32, 4, 30, 40, 32), (16, 16, 4, 16, 9, 128),
+                                                         (20, 20, 4, 40, 11, 96), (12, 12, 4, 70, 8, 128), (8, 8, 1, 80, 8, 128), (32, 32, 4, 16, 24, 128),
+                                                         (44, 44, 4, 16, 3, 16), (8, 24, 4, 16, 5, 136)])
+def test_seda_main_anchor_in_parts(F, gh, gw, tile, frames, heads, dim):
     tokens = gh * gw
     rng = np.random.default_rng(tokens + frames)
     ts = rng.random((tokens, heads, frames)).astype(np.float32)
-    cand = F.fb4_select_salient_tokens(torch.from_numpy(rng.random((frames, 1, tokens)).astype(np.float32)).cuda(), gh, gw).cpu().numpy()
+    cand = F.fb4_select_salient_tokens(torch.from_numpy(rng.random((frames, 1, tokens)).astype(np.float32)).cuda(), gh, gw, tile, tile).cpu().numpy()
     cand[rng.random(cand.shape) < 0.1] = -1
     qt, kt = synth.attention_qk(tokens * heads, frames, dim, seed=tokens, device="cuda")
     qt, kt = qt.view(tokens, heads, frames, dim), kt.view(tokens, heads, frames, dim)
-    main_r, kept_r, ps_r = O.seda_main_anchor(ts, synth.bf16_bits(qt), synth.bf16_bits(kt), cand, gh, gw, prune_threshold=1.0)
+    main_r, kept_r, ps_r = O.seda_main_anchor(ts, synth.bf16_bits(qt), synth.bf16_bits(kt), cand, gh, gw, tile, tile, prune_threshold=1.0)
     ts, cand = torch.from_numpy(ts).cuda(), torch.from_numpy(cand).cuda()
-    main, kept, ps = F.fb4_seda_main_anchor(ts, qt, kt, cand, gh, gw, prune_threshold=1.0, want_scores=True)
+    main, kept, ps = F.fb4_seda_main_anchor(ts, qt, kt, cand, gh, gw, tile, tile, prune_threshold=1.0, want_scores=True)
     over = cand.clone()
-    F.fb4_seda_main_anchor(ts, qt, kt, over, gh, gw, prune_threshold=1.0, kept=over)
+    F.fb4_seda_main_anchor(ts, qt, kt, over, gh, gw, tile, tile, prune_threshold=1.0, kept=over)
     torch.cuda.synchronize()
     assert np.array_equal(main.cpu().numpy(), main_r)
     got = ps.cpu().numpy()
