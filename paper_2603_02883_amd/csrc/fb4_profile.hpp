@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "fb4_tables.hpp"
 
 namespace fb4 {
@@ -73,7 +75,10 @@ __global__ __launch_bounds__(kProfileThreads) void profile_select_kernel(const u
 // kWords: metadata words per load, which divide the blocks of a row.
 // us, three launches / this (rows x blocks, groups, share of anchors): 16384 x 96, 64, 1/16 9.8 / 5.4, the same with all rows
 // anchors 13.6 / 7.9, with one dialect everywhere 14.1 / 7.8, with a tenth of the rows anchors of one group 26.8 / 15.3; 1000 x
-// 36, 64 8.7 / 4.9.  Every workgroup looks through all rows (65536 x 96, 512 groups 12.5 / 15.3), and one that gets all anchors
+// 36, 64 8.7 / 4.9.  Bound by its chain of dependent steps, most of it instructions of one workgroup: with the anchors found as bits
+// and the sums and maxima exchanged inside the vector ALU (a ballot, a place in the list and a branch per load, and ten LDS
+// round trips, before), launches in a graph, inputs changing: 16384 x 96, 64, 1/16 4.6 -> 3.6, all rows anchors 7.8 -> 6.5, 1000 x 36
+// 4.1 -> 3.4, 30000 x 96, 200, 1/16 6.5 -> 5.3.  Every workgroup looks through all rows (65536 x 96, 512 groups 12.5 / 15.3), and one that gets all anchors
 // takes 0.0041 a word and 0.0143 a load of the time that the atomics of three launches take for them (16384 x 97, a word a load,
 // 26.7 / 47.3; 65536 x 384, eight words, 86 / 202): profile_by_group keeps this below 1.
 inline bool profile_by_group(int64_t rows, int64_t blocks_per_row, int64_t n_groups, int words)
@@ -81,6 +86,19 @@ inline bool profile_by_group(int64_t rows, int64_t blocks_per_row, int64_t n_gro
     return n_groups <= 512 && rows <= 32768 && rows * n_groups <= (1 << 23) && blocks_per_row * (2 * words + 7) <= 400 * words;
 }
 constexpr int kProfileGroupThreads = 1024;
+// Lane 31 of each half-wavefront gets the half's values put together (exchanges inside the vector ALU: no LDS round trips).
+template <typename Op>
+__device__ __forceinline__ uint32_t half_wave(uint32_t v, Op op, uint32_t neutral)
+{
+    auto moved = [neutral](uint32_t x, auto ctrl) {
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)neutral, (int)x, decltype(ctrl)::value, 0xF, 0xF, false);
+    };
+    v = op(v, moved(v, std::integral_constant<int, 0xB1>{}));     // quad_perm [1,0,3,2]
+    v = op(v, moved(v, std::integral_constant<int, 0x4E>{}));     // quad_perm [2,3,0,1]
+    v = op(v, moved(v, std::integral_constant<int, 0x141>{}));    // row_half_mirror
+    v = op(v, moved(v, std::integral_constant<int, 0x140>{}));    // row_mirror
+    return op(v, moved(v, std::integral_constant<int, 0x142>{})); // row_bcast:15, the row before this one
+}
 constexpr uint32_t kProfileGroupRows = 16384;   // per look
 
 template <int kWords>
@@ -107,17 +125,31 @@ __global__ __launch_bounds__(kProfileGroupThreads) void profile_group_kernel(con
         for (uint32_t k = 0; k < kRead; ++k) group[k] = anchor_group[min(row0 + tid + k * kProfileGroupThreads, rows - 1u)];
         if (tid == 0) n_list = 0;
         __syncthreads();
+        // this thread's anchors as bits, then one place in the list for all of them
+        uint32_t mine = 0;
 #pragma unroll
-        for (uint32_t k = 0; k < kRead; ++k) {
-            const uint32_t off = tid + k * kProfileGroupThreads;
-            const bool mine = row0 + off < rows && (uint32_t)group[k] == g;   // (g < 2^31: a negative entry is none)
-            const unsigned long long m = __ballot(mine);
-            if (m) {   // (wave-uniform)
+        for (uint32_t k = 0; k < kRead; ++k) mine |= (uint32_t)group[k] == g ? 1u << k : 0u;   // (g < 2^31: a negative entry is none)
+        const uint32_t n = rows - row0;
+        mine &= n < kProfileGroupRows ? (1u << ((n + kProfileGroupThreads - 1u - min(tid, n)) / kProfileGroupThreads)) - 1u : 0xFFFFu;
+        if (__builtin_popcountll(__ballot(mine != 0u)) > 32 && __ballot(__builtin_popcount(mine) > 2)) {
+            // many anchors (wave-uniform): the list in the order of the rows, so that neighbours in it are neighbours in memory (16384 x
+            // 96, all rows anchors of one group, 117 us so and 120 by threads)
+#pragma unroll 1
+            for (uint32_t k = 0; k < kRead; ++k) {
+                const bool is = (mine >> k) & 1u;
+                const unsigned long long m = __ballot(is);
+                if (!m) continue;
                 uint32_t at = 0;
                 if (lane == 0) at = atomicAdd(&n_list, (uint32_t)__builtin_popcountll(m));
                 at = __builtin_amdgcn_readfirstlane(at);
-                if (mine) list[at + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = (uint16_t)off;
+                if (is) list[at + __builtin_popcountll(m & ((1ull << lane) - 1ull))] = (uint16_t)(tid + k * kProfileGroupThreads);
             }
+        } else if (mine) {
+            uint32_t at = atomicAdd(&n_list, (uint32_t)__builtin_popcount(mine));
+            do {
+                list[at++] = (uint16_t)(tid + (uint32_t)__builtin_ctz(mine) * kProfileGroupThreads);
+                mine &= mine - 1u;
+            } while (mine);
         }
         __syncthreads();
         const uint32_t per_row = nb / kWords, items = n_list * per_row;   // (the launcher bounds rows * nb)
@@ -138,9 +170,8 @@ __global__ __launch_bounds__(kProfileGroupThreads) void profile_group_kernel(con
     }
     {
         uint32_t c = hist[tid >> 5][d] + hist[tid >> 5][d + 32u];
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) c += (uint32_t)__shfl_xor((int)c, o);
-        if (d == 0) {
+        c = half_wave(c, [](uint32_t a, uint32_t b) { return a + b; }, 0u);
+        if (d == 31) {
             total[tid >> 5] = c;
             counts[(size_t)g * 32 + (tid >> 5)] = c;
         }
@@ -148,13 +179,9 @@ __global__ __launch_bounds__(kProfileGroupThreads) void profile_group_kernel(con
     __syncthreads();
     if (tid < 256) {   // 32 lanes per range bucket: the most frequent dialect, lowest DID on ties
         const bool in = (int)d < n_dialects && top == 8u + (tid >> 5);
-        unsigned long long key = in ? (((unsigned long long)total[d] + 1ull) << 5) | (31u - d) : 0ull;
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) {
-            const unsigned long long other = __shfl_xor(key, o);
-            key = other > key ? other : key;
-        }
-        if (d == 0) sub[(size_t)g * 8 + (tid >> 5)] = key ? (uint8_t)(31u - (uint32_t)(key & 31u)) : 255u;
+        uint32_t key = in ? ((total[d] + 1u) << 5) | (31u - d) : 0u;   // (fewer than 2^23 words: see profile_by_group)
+        key = half_wave(key, [](uint32_t a, uint32_t b) { return max(a, b); }, 0u);
+        if (d == 31) sub[(size_t)g * 8 + (tid >> 5)] = key ? (uint8_t)(31u - (key & 31u)) : 255u;
     }
 }
 
