@@ -119,15 +119,21 @@ static int row_stride(PyObject* t, const int64_t* d, int64_t* out)
     return rc;
 }
 
-// Sizes and address of a tensor of n dimensions.
-static int sized(PyObject* t, Py_ssize_t n, int64_t* d, void** out)
+// Sizes and address of a tensor of n dimensions that its type's reader takes.  (Copied at once, as everywhere here: the reader's
+// sizes are the tensor's own, which a later argument's methods, or another thread during the call, may change.)
+static int plain(PyObject* t, Py_ssize_t n, int64_t* d, void** out)
 {
     dl_tensor v;
-    if (look(t, &v) && v.ndim == n) {
-        for (Py_ssize_t i = 0; i < n; ++i) d[i] = v.shape[i];
-        *out = data_of(&v);
-        return 0;
-    }
+    if (!look(t, &v) || v.ndim != n) return -1;
+    for (Py_ssize_t i = 0; i < n; ++i) d[i] = v.shape[i];
+    *out = data_of(&v);
+    return 0;
+}
+
+// ... of any tensor of n dimensions.
+static int sized(PyObject* t, Py_ssize_t n, int64_t* d, void** out)
+{
+    if (plain(t, n, d, out) == 0) return 0;
     return shape(t, n, d) || tensor(t, out) ? -1 : 0;
 }
 
@@ -318,57 +324,52 @@ static PyObject* py_attention_scores(ARGS)
 // (scores, grid_h, grid_w, tile_h, tile_w, rows_out, stream)
 static PyObject* py_select_salient_tokens(ARGS)
 {
-    dl_tensor v;
-    void *out, *s;
-    int64_t gh, gw, th, tw;
-    if (n != 7 || !look(a[0], &v) || v.ndim != 3 || integer(a[1], &gh) || integer(a[2], &gw) || integer(a[3], &th) || integer(a[4], &tw) ||
-        tensor(a[5], &out) || address(a[6], &s) || v.shape[2] != gh * gw)
+    void *sc, *out, *s;
+    int64_t d[3], gh, gw, th, tw;
+    if (n != 7 || plain(a[0], 3, d, &sc) || integer(a[1], &gh) || integer(a[2], &gw) || integer(a[3], &th) || integer(a[4], &tw) ||
+        tensor(a[5], &out) || address(a[6], &s) || d[2] != gh * gw)
         return elsewhere(k_select_salient_tokens, a, n);
-    RETURN_CALL(fb4_select_salient_tokens(data_of(&v), v.shape[0], (int)v.shape[1], (int)gh, (int)gw, (int)th, (int)tw, out, s));
+    RETURN_CALL(fb4_select_salient_tokens(sc, d[0], (int)d[1], (int)gh, (int)gw, (int)th, (int)tw, out, s));
 }
 
 // (q, k, joint, frames, grid_h, grid_w, anchors, tile_h, tile_w, window, window_t, threshold, token_group, anchor_group, scores, stream)
 static PyObject* py_seda_assign(ARGS)
 {
-    dl_tensor v;
-    void *k, *anchors, *tg, *ag, *sc, *s;
-    int64_t frames, gh, gw, th, tw, w, wt, n_anchors;
-    if (n != 16 || !PyBool_Check(a[2]) || !PyFloat_Check(a[11]) || !look(a[0], &v) || v.ndim != (a[2] == Py_True ? 3 : 4) || tensor(a[1], &k) ||
+    void *q, *k, *anchors, *tg, *ag, *sc, *s;
+    int64_t d[4], frames, gh, gw, th, tw, w, wt, n_anchors;
+    if (n != 16 || !PyBool_Check(a[2]) || !PyFloat_Check(a[11]) || plain(a[0], a[2] == Py_True ? 3 : 4, d, &q) || tensor(a[1], &k) ||
         integer(a[3], &frames) || integer(a[4], &gh) || integer(a[5], &gw) || tensor(a[6], &anchors) || numel(a[6], &n_anchors) || integer(a[7], &th) ||
         integer(a[8], &tw) || integer(a[9], &w) || integer(a[10], &wt) || tensor(a[12], &tg) || tensor(a[13], &ag) || tensor(a[14], &sc) ||
         address(a[15], &s))
         return elsewhere(k_seda_assign, a, n);
     const int joint = a[2] == Py_True;
     const float threshold = (float)PyFloat_AS_DOUBLE(a[11]);
-    RETURN_CALL(fb4_seda_assign(data_of(&v), k, joint, frames, (int)v.shape[joint ? 0 : 1], (int)gh, (int)gw, v.shape[joint ? 2 : 3], anchors, n_anchors,
-                                (int)th, (int)tw, (int)w, (int)wt, threshold, tg, ag, sc, s));
+    RETURN_CALL(fb4_seda_assign(q, k, joint, frames, (int)d[joint ? 0 : 1], (int)gh, (int)gw, d[joint ? 2 : 3], anchors, n_anchors, (int)th, (int)tw,
+                                (int)w, (int)wt, threshold, tg, ag, sc, s));
 }
 
 // (temporal_scores, qt, kt, candidates, grid_h, grid_w, tile_h, tile_w, prune_threshold, main_anchor, kept, prune_scores, stream)
 static PyObject* py_seda_main_anchor(ARGS)
 {
-    dl_tensor q, c;
-    void *ts, *k, *main, *kept, *ps, *s;
-    int64_t gh, gw, th, tw;
-    if (n != 13 || !PyFloat_Check(a[8]) || tensor(a[0], &ts) || !look(a[1], &q) || q.ndim != 4 || tensor(a[2], &k) || !look(a[3], &c) || c.ndim != 2 ||
+    void *ts, *q, *k, *c, *main, *kept, *ps, *s;
+    int64_t d[4], dc[2], gh, gw, th, tw;
+    if (n != 13 || !PyFloat_Check(a[8]) || tensor(a[0], &ts) || plain(a[1], 4, d, &q) || tensor(a[2], &k) || plain(a[3], 2, dc, &c) ||
         integer(a[4], &gh) || integer(a[5], &gw) || integer(a[6], &th) || integer(a[7], &tw) || tensor(a[9], &main) || tensor(a[10], &kept) ||
-        tensor(a[11], &ps) || address(a[12], &s) || q.shape[0] != gh * gw || c.shape[0] != q.shape[2])
+        tensor(a[11], &ps) || address(a[12], &s) || d[0] != gh * gw || dc[0] != d[2])
         return elsewhere(k_seda_main_anchor, a, n);
     const float threshold = (float)PyFloat_AS_DOUBLE(a[8]);
-    RETURN_CALL(fb4_seda_main_anchor(ts, data_of(&q), k, q.shape[2], (int)q.shape[1], (int)gh, (int)gw, q.shape[3], data_of(&c), (int)c.shape[1], (int)th,
-                                     (int)tw, threshold, main, kept, ps, s));
+    RETURN_CALL(fb4_seda_main_anchor(ts, q, k, d[2], (int)d[1], (int)gh, (int)gw, d[3], c, (int)dc[1], (int)th, (int)tw, threshold, main, kept, ps, s));
 }
 
 // (luts, meta, anchor_group, n_groups, counts, sub_formatbooks, stream)
 static PyObject* py_seda_profile(ARGS)
 {
-    dl_tensor v;
-    void *h, *ag, *counts, *sub, *s;
-    int64_t g;
-    if (n != 7 || address(a[0], &h) || !look(a[1], &v) || v.ndim != 2 || tensor(a[2], &ag) || integer(a[3], &g) || tensor(a[4], &counts) ||
+    void *h, *m, *ag, *counts, *sub, *s;
+    int64_t d[2], g;
+    if (n != 7 || address(a[0], &h) || plain(a[1], 2, d, &m) || tensor(a[2], &ag) || integer(a[3], &g) || tensor(a[4], &counts) ||
         tensor(a[5], &sub) || address(a[6], &s))
         return elsewhere(k_seda_profile, a, n);
-    RETURN_CALL(fb4_seda_profile(h, data_of(&v), v.shape[0], v.shape[1], ag, (int)g, counts, sub, s));
+    RETURN_CALL(fb4_seda_profile(h, m, d[0], d[1], ag, (int)g, counts, sub, s));
 }
 
 // (fb4_opts, c_void_p, object with the same calls through ctypes)

@@ -327,3 +327,35 @@ def test_the_refresh_is_called_as_through_ctypes(recorder, kind):
     assert results(calls) == want
     assert not module.read_through(torch.Tensor, None)
     assert results(calls) == want
+
+
+@pytest.mark.parametrize("call", ["select_salient_tokens", "seda_assign", "seda_main_anchor", "seda_profile"])
+def test_sizes_are_those_at_the_start_of_a_call(recorder, call):
+    # (an argument's method that resizes an earlier argument: what another thread can do while the library runs)
+    module, notes = recorder
+    frames, heads, gh, gw, dim = 3, 5, 4, 6, 16
+
+    class Resizes:
+        def __init__(self, *tensors):
+            self.tensors = tensors
+
+        def data_ptr(self):
+            for t in self.tensors:
+                t.resize_([n // 2 for n in t.shape])
+            return 64
+
+    def result(which):
+        sc, out, meta = torch.zeros((frames, heads, gh * gw)), torch.zeros(72, dtype=torch.int32), torch.zeros((72, 9), dtype=torch.int16)
+        q, qt = torch.zeros((frames, heads, gh * gw, dim), dtype=torch.bfloat16), torch.zeros((gh * gw, heads, frames, dim), dtype=torch.bfloat16)
+        cand, h = torch.zeros((frames, 2), dtype=torch.int32), ctypes.c_void_p(64)
+        args = {"select_salient_tokens": (sc, gh, gw, 4, 4, Resizes(sc), 0),
+                "seda_assign": (q, Resizes(q), False, frames, gh, gw, cand, 4, 2, 5, 1, 1.5, out, out, None, 0),
+                "seda_main_anchor": (sc, qt, qt, cand, gh, gw, 4, 2, 1.5, out, out, Resizes(qt, cand), 0),
+                "seda_profile": (h, meta, out, 7, out, Resizes(meta), 0)}[call]
+        notes()
+        rc = getattr(which, call)(*args)
+        known = {a.data_ptr(): i for i, a in enumerate(args) if isinstance(a, torch.Tensor)}   # (addresses differ from call to call)
+        return rc, [known.get(v, v) for v in notes()]
+
+    assert module.read_through(torch.Tensor, torch.Tensor.__dlpack_c_exchange_api__)
+    assert result(module) == result(B.CtypesCall)
