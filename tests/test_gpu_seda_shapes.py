@@ -255,6 +255,24 @@ def test_seda_profile_by_group(F, rows, nb, groups, share):
     test_seda_profile_shapes(F, rows, nb, groups, share)
 
 
+# (one to sixteen rows per thread, a ragged last one, two looks; as many threads of a wavefront with anchors as get their places one by
+# one, one more, and all; one anchor of a thread or all of its rows)
+@pytest.mark.parametrize("rows", [64, 1023, 1024, 1025, 3071, 15361, 16384, 16447, 20000])
+def test_seda_profile_by_group_places_in_the_list(F, rows):
+    luts = F.fb4_build_luts(DEFAULT_FORMATBOOK)
+    reads, nb = min((rows + 1023) // 1024, 16), 5
+    meta = np.random.default_rng(rows).integers(0, 32, size=(rows, nb)).astype(np.uint16)
+    r = np.arange(rows)
+    for lanes in sorted({1, min(2 * reads, 64), min(2 * reads + 1, 64), 64}):
+        for every in (False, True):
+            group = np.where((r % 64 >= 64 - lanes) & (every | (r // 1024 % reads == r % 64 % reads)), 1, 7 * (r % 2) - 1).astype(np.int32)
+            counts, _ = F.fb4_seda_profile(luts, torch.from_numpy(meta.view(np.int16)).cuda(), torch.from_numpy(group).cuda(), 2)
+            torch.cuda.synchronize()
+            assert counts[0].sum().item() == 0
+            assert np.array_equal(counts[1].cpu().numpy(), np.bincount(meta[group == 1].ravel(), minlength=32)), (lanes, every)
+    luts.free()
+
+
 @pytest.mark.parametrize("offset", [0, 1, 2, 4])
 def test_seda_profile_alignment_and_concentration(F, offset):
     # metadata that start 0, 2, 4 and 8 bytes past a 16-byte boundary; every block the same dialect, every row the same group
