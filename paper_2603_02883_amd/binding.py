@@ -121,6 +121,10 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _get_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
+def _tiles(grid_h, grid_w, tile_h, tile_w):
+    return ((grid_h + tile_h - 1) // tile_h) * ((grid_w + tile_w - 1) // tile_w)
+
+
 class CtypesCall:
     """The calls of csrc/fb4_pycall.c through ctypes, with the same arguments: the C module hands over here whatever it does not
     read itself (other types than its own, other shapes, errors), and where there is no module every call comes here."""
@@ -181,6 +185,7 @@ class CtypesCall:
     def select_salient_tokens(scores, grid_h, grid_w, tile_h, tile_w, rows_out, s):
         frames, heads, tokens = scores.shape
         assert tokens == grid_h * grid_w
+        _tiles(grid_h, grid_w, tile_h, tile_w)   # (raises for tiles that are none)
         return _lib.fb4_select_salient_tokens(_dp(scores), frames, heads, grid_h, grid_w, tile_h, tile_w, _dp(rows_out), s)
 
     @staticmethod
@@ -196,6 +201,7 @@ class CtypesCall:
                          prune_scores, s):
         tokens, heads, frames, dim = qt.shape
         assert tokens == grid_h * grid_w and candidates.shape[0] == frames
+        _tiles(grid_h, grid_w, tile_h, tile_w)
         return _lib.fb4_seda_main_anchor(_dp(temporal_scores), _dp(qt), _dp(kt), frames, heads, grid_h, grid_w, dim,
                                          _dp(candidates), candidates.shape[1], tile_h, tile_w, float(prune_threshold),
                                          _dp(main_anchor), _dp(kept), _dp(prune_scores), s)
@@ -334,8 +340,7 @@ def fb4_select_salient_tokens(scores, grid_h, grid_w, tile_h=4, tile_w=4, rows_o
     if rows_out is None:
         frames, heads, tokens = scores.shape
         assert tokens == grid_h * grid_w
-        tiles = ((grid_h + tile_h - 1) // tile_h) * ((grid_w + tile_w - 1) // tile_w)
-        rows_out = torch.empty((frames, tiles), dtype=torch.int32, device=scores.device)
+        rows_out = torch.empty((frames, _tiles(grid_h, grid_w, tile_h, tile_w)), dtype=torch.int32, device=scores.device)
     _check(_call.select_salient_tokens(scores, grid_h, grid_w, tile_h, tile_w, rows_out, _stream(stream)), "fb4_select_salient_tokens")
     return rows_out
 
@@ -360,12 +365,13 @@ def fb4_seda_main_anchor(temporal_scores, qt, kt, candidates, grid_h, grid_w, ti
     candidates: int32 cuda [frames][n].  Returns (main_anchor int32 [tiles], kept int32 [frames][n]) and the compared
     scores float32 [frames][tiles] if asked."""
     main, ps = main_anchor, None
-    if main is None or want_scores:
-        tiles = ((grid_h + tile_h - 1) // tile_h) * ((grid_w + tile_w - 1) // tile_w)
+    if main is None or kept is None or want_scores:
+        tokens, heads, frames, dim = qt.shape
+        assert tokens == grid_h * grid_w and candidates.shape[0] == frames
+        tiles = _tiles(grid_h, grid_w, tile_h, tile_w)
         main = torch.empty(tiles, dtype=torch.int32, device=qt.device) if main is None else main
-        ps = torch.empty((qt.shape[2], tiles), dtype=torch.float32, device=qt.device) if want_scores else None
-    if kept is None:
-        kept = torch.empty_like(candidates)
+        kept = torch.empty_like(candidates) if kept is None else kept
+        ps = torch.empty((frames, tiles), dtype=torch.float32, device=qt.device) if want_scores else None
     _check(_call.seda_main_anchor(temporal_scores, qt, kt, candidates, grid_h, grid_w, tile_h, tile_w, prune_threshold, main, kept, ps,
                                   _stream(stream)), "fb4_seda_main_anchor")
     return (main, kept, ps) if want_scores else (main, kept)

@@ -327,7 +327,7 @@ static PyObject* py_select_salient_tokens(ARGS)
     void *sc, *out, *s;
     int64_t d[3], gh, gw, th, tw;
     if (n != 7 || plain(a[0], 3, d, &sc) || integer(a[1], &gh) || integer(a[2], &gw) || integer(a[3], &th) || integer(a[4], &tw) ||
-        tensor(a[5], &out) || address(a[6], &s) || d[2] != gh * gw)
+        tensor(a[5], &out) || address(a[6], &s) || d[2] != gh * gw || th == 0 || tw == 0)
         return elsewhere(k_select_salient_tokens, a, n);
     RETURN_CALL(fb4_select_salient_tokens(sc, d[0], (int)d[1], (int)gh, (int)gw, (int)th, (int)tw, out, s));
 }
@@ -355,7 +355,7 @@ static PyObject* py_seda_main_anchor(ARGS)
     int64_t d[4], dc[2], gh, gw, th, tw;
     if (n != 13 || !PyFloat_Check(a[8]) || tensor(a[0], &ts) || plain(a[1], 4, d, &q) || tensor(a[2], &k) || plain(a[3], 2, dc, &c) ||
         integer(a[4], &gh) || integer(a[5], &gw) || integer(a[6], &th) || integer(a[7], &tw) || tensor(a[9], &main) || tensor(a[10], &kept) ||
-        tensor(a[11], &ps) || address(a[12], &s) || d[0] != gh * gw || dc[0] != d[2])
+        tensor(a[11], &ps) || address(a[12], &s) || d[0] != gh * gw || dc[0] != d[2] || th == 0 || tw == 0)
         return elsewhere(k_seda_main_anchor, a, n);
     const float threshold = (float)PyFloat_AS_DOUBLE(a[8]);
     RETURN_CALL(fb4_seda_main_anchor(ts, q, k, d[2], (int)d[1], (int)gh, (int)gw, d[3], c, (int)dc[1], (int)th, (int)tw, threshold, main, kept, ps, s));

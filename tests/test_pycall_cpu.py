@@ -145,6 +145,34 @@ def test_calls_through_ctypes_answer_like_the_modules():
                     B._call = module
 
 
+class Stream:
+    cuda_stream = 0
+
+
+@pytest.mark.parametrize("through_ctypes", [False, True])
+def test_the_refresh_refuses_by_the_same_errors_with_outputs_given(monkeypatch, through_ctypes):
+    if through_ctypes:
+        monkeypatch.setattr(B, "_call", B.CtypesCall)
+    gh, gw, frames, heads, dim = 4, 6, 3, 5, 16
+    sc, ts = torch.zeros((frames, heads, gh * gw)), torch.zeros((gh * gw, heads, frames))
+    qt, cand = torch.zeros((gh * gw, heads, frames, dim), dtype=torch.bfloat16), torch.zeros((frames, 2), dtype=torch.int32)
+    main, s = torch.zeros(2, dtype=torch.int32), Stream()
+    for out in (None, cand):
+        for th, tw, error in ((0, 4, ZeroDivisionError), (4, 0, ZeroDivisionError), (None, 4, TypeError), (4, "4", TypeError)):
+            with pytest.raises(error):
+                B.fb4_select_salient_tokens(sc, gh, gw, th, tw, rows_out=out, stream=s)
+            for kw in (dict(main_anchor=None if out is None else main, kept=out), dict(main_anchor=main), dict(kept=cand)):
+                with pytest.raises(error):
+                    B.fb4_seda_main_anchor(ts, qt, qt, cand, gh, gw, th, tw, stream=s, **kw)
+        with pytest.raises(B.Fb4Error):
+            B.fb4_select_salient_tokens(sc, gh, gw, -1, 4, rows_out=cand, stream=s)
+        for kw in (dict(kept=out), dict(main_anchor=main, kept=out)):
+            with pytest.raises(AssertionError):
+                B.fb4_seda_main_anchor(ts, qt, qt, cand[1:], gh, gw, stream=s, **kw)
+            with pytest.raises(AttributeError):
+                B.fb4_seda_main_anchor(ts, qt, qt, None, gh, gw, stream=s, **kw)
+
+
 RECORDER = r"""
 #include <stdint.h>
 #include "fb4.h"
