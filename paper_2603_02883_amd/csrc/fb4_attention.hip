@@ -295,12 +295,14 @@ int fb4_seda_main_anchor(const float* temporal_scores, const void* qt, const voi
     const uintptr_t from = reinterpret_cast<uintptr_t>(candidates), to = reinterpret_cast<uintptr_t>(kept);
     const bool in_place = from < to + n_cand * sizeof(int32_t) && to < from + n_cand * sizeof(int32_t);
     const bool worth = heads * dim >= 1024 && (tiles % 8 == 0 || tiles <= 32) && !in_place;
-    const int64_t parts = worth ? std::max<int64_t>(std::min<int64_t>(256 / tiles, frames), 1) : 1;   // (256 compute units)
+    const int64_t most_parts = worth ? std::max<int64_t>(std::min<int64_t>(256 / tiles, frames), 1) : 1;   // (256 compute units)
+    const int64_t per_part = std::max<int64_t>((frames + most_parts - 1) / most_parts, 1);
+    const int64_t parts = std::max<int64_t>((frames + per_part - 1) / per_part, 1);   // (each has a frame)
     launch(parts > 1 ? seda_main_anchor_kernel<true> : seda_main_anchor_kernel<false>, dim3((unsigned)tiles, (unsigned)parts), dim3(threads), 0, s, temporal_scores,
                        static_cast<const uint16_t*>(qt), static_cast<const uint16_t*>(kt), (uint32_t)frames, (uint32_t)heads,
                        (uint32_t)grid_h, (uint32_t)grid_w, (uint32_t)dim, candidates, (uint32_t)n_per_frame, (uint32_t)tile_h,
                        (uint32_t)tile_w, prune_threshold, main_anchor, kept, prune_scores, threads / 64u, (uint32_t)tiles,
-                       main_anchor_split((uint32_t)frames, (uint32_t)parts, threads / 64u, (uint32_t)heads));
+                       main_anchor_split((uint32_t)per_part, (uint32_t)parts, threads / 64u, (uint32_t)heads));
     return hipGetLastError() == hipSuccess ? FB4_OK : FB4_ERR_HIP;
 }
 

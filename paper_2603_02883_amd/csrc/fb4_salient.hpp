@@ -883,9 +883,8 @@ constexpr int kMainMaxThreads = 1024;   // seda_main_anchor_kernel: 64 per frame
 constexpr uint32_t kMainMaxFrames = 1024;
 // How the pruning of a tile's frames is split: frames per part (of a tile: blockIdx.y), wavefronts per frame, and 256 / those, rounded
 // up, which divides a wavefront's number (a division would take as long as a load).
-inline uint32_t main_anchor_split(uint32_t frames, uint32_t parts, uint32_t n_waves, uint32_t heads)
+inline uint32_t main_anchor_split(uint32_t per_part, uint32_t parts, uint32_t n_waves, uint32_t heads)
 {
-    const uint32_t per_part = std::max((frames + parts - 1) / parts, 1u);
     const uint32_t shares = parts > 1 ? std::min(std::max(n_waves / per_part, 1u), (heads + 3) / 4) : 1u;
     return per_part | shares << 11 | ((256 + shares - 1) / shares) << 16;
 }

@@ -147,7 +147,51 @@ def test_seda_main_anchor_frames_heads_and_ties(F, frames, heads, dim):
                 assert kept.cpu().numpy()[f, tile] == (cand[f, tile] if keep else -1)
 
 
-# a tile's frames in 1 to 28 parts (some of them empty), one to six wavefronts per frame, a list that is overwritten
+def check_main_anchor(F, ts, qt, kt, cand, gh, gw, tile, threshold=1.0):
+    """Main anchors as the oracle's, scores to fp32 sums, and every entry of the list -- written anew or over the candidates -- as it follows
+    from the scores of the same call."""
+    tokens, heads, frames, dim = qt.shape
+    tiles_x = (gw + tile - 1) // tile
+    with np.errstate(invalid="ignore"):
+        main_r, kept_r, ps_r = O.seda_main_anchor(ts, synth.bf16_bits(qt), synth.bf16_bits(kt), cand, gh, gw, tile, tile, prune_threshold=threshold)
+    # A lane adds up 8 products per 16 bytes of a row, 16 lanes a row, every fourth head; then six exchanges, up to 16 shares and the division.
+    steps = 8 * ((dim + 127) // 128) * ((heads + 3) // 4) + 6 + 16 + 1
+    bound = np.full(ps_r.shape, np.nan)
+    at = np.flatnonzero(main_r >= 0)
+    bf, p = (torch.from_numpy(v).long().cuda() for v in np.divmod(main_r[at], tokens))
+    bound[:, at] = steps * 2.0 ** -24 / heads * (qt[p, :, bf].double().abs()[:, :, None] * kt[p].double().abs()).sum((1, 3)).t().cpu().numpy()
+    # an entry's tile, -1 for one of another frame and for a later one of a tile that the frame's list has named
+    tile_of = np.full(cand.shape, -1)
+    for f in range(frames):
+        seen = set()
+        for j, row in enumerate(cand[f].tolist()):
+            if f * tokens <= row < (f + 1) * tokens:
+                y, x = divmod(row - f * tokens, gw)
+                t = y // tile * tiles_x + x // tile
+                if t not in seen:
+                    tile_of[f, j] = t
+                seen.add(t)
+    main_frame = np.where(main_r >= 0, main_r // tokens, -1)
+    ts = torch.from_numpy(ts).cuda()
+    for in_place in (False, True):
+        given = torch.from_numpy(cand).cuda()
+        main, kept, ps = F.fb4_seda_main_anchor(ts, qt, kt, given, gh, gw, tile, tile, prune_threshold=threshold, want_scores=True,
+                                                kept=given if in_place else torch.full_like(given, 77777))
+        torch.cuda.synchronize()
+        assert np.array_equal(main.cpu().numpy(), main_r)
+        got, kept = ps.cpu().numpy(), kept.cpu().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(ps_r)) and np.array_equal(got[np.isinf(ps_r)], ps_r[np.isinf(ps_r)])
+        inside = np.isfinite(ps_r)
+        assert (np.abs(got[inside] - ps_r[inside]) <= bound[inside]).all()
+        score = np.take_along_axis(got, np.maximum(tile_of, 0), axis=1)
+        keep = (tile_of >= 0) & ((score > np.float32(threshold)) | (main_frame[np.maximum(tile_of, 0)] == np.arange(frames)[:, None]))
+        assert np.array_equal(kept, np.where(keep, cand, -1))
+        far = ~(np.abs(ps_r - threshold) <= bound)      # (where rounding cannot put the score on the other side of the threshold)
+        far = np.where(tile_of >= 0, np.take_along_axis(far, np.maximum(tile_of, 0), axis=1), True)
+        assert np.array_equal(kept[far], kept_r[far])
+
+
+# a tile's frames in 1 to 28 parts, one to six wavefronts per frame, a list that is overwritten
 @pytest.mark.parametrize("gh,gw,tile,frames,heads,dim", [(4, 4, 4, 17, 24, 72), (8, 16, 4, 6, 9, 120), (32, 32, 4, 30, 40, 32), (16, 16, 4, 16, 9, 128),
                                                          (20, 20, 4, 40, 11, 96), (12, 12, 4, 70, 8, 128), (8, 8, 1, 80, 8, 128), (32, 32, 4, 16, 24, 128),
                                                          (44, 44, 4, 16, 3, 16), (8, 24, 4, 16, 5, 136)])
@@ -158,22 +202,34 @@ def test_seda_main_anchor_in_parts(F, gh, gw, tile, frames, heads, dim):
     cand = F.fb4_select_salient_tokens(torch.from_numpy(rng.random((frames, 1, tokens)).astype(np.float32)).cuda(), gh, gw, tile, tile).cpu().numpy()
     cand[rng.random(cand.shape) < 0.1] = -1
     qt, kt = synth.attention_qk(tokens * heads, frames, dim, seed=tokens, device="cuda")
+    check_main_anchor(F, ts, qt.view(tokens, heads, frames, dim), kt.view(tokens, heads, frames, dim), cand, gh, gw, tile)
+
+
+# (ragged tiles at both edges, up to and from 32 tiles, more entries than a wavefront has lanes; the last: one part)
+@pytest.mark.parametrize("gh,gw,tile,frames,heads,dim", [(18, 19, 4, 20, 24, 72), (33, 30, 4, 7, 16, 64), (5, 3, 4, 33, 8, 128), (7, 62, 4, 3, 9, 256),
+                                                         (1, 9, 2, 2, 43, 24), (37, 35, 4, 6, 24, 72)])
+def test_seda_main_anchor_in_parts_of_lists_with_other_entries(F, gh, gw, tile, frames, heads, dim):
+    # several entries of a tile in a frame, entries of other frames, before the first row and beyond the last, tiles that no frame names;
+    # ties and NaN among the temporal scores, NaN and infinities in Q and K
+    tokens = gh * gw
+    rng = np.random.default_rng(tokens + frames)
+    n = 2 * ((gh + tile - 1) // tile) * ((gw + tile - 1) // tile) + 3
+    cand = (np.arange(frames)[:, None] * tokens + rng.integers(0, tokens, size=(frames, n))).astype(np.int64)
+    tile_of = cand % tokens // gw // tile * ((gw + tile - 1) // tile) + cand % tokens % gw // tile
+    cand = np.where(rng.random(cand.shape) < 0.15, rng.integers(-3, frames * tokens + 3, size=cand.shape), cand)
+    cand = np.where((tile_of == 1) & (cand >= 0), rng.choice([-1, frames * tokens, 0x7FFFFFFF, -0x80000000], size=cand.shape), cand).astype(np.int32)
+    ts = rng.integers(0, 3, size=(tokens, heads, frames)).astype(np.float32)
+    ts[rng.random(ts.shape) < 0.1 / heads] = np.nan
+    qt, kt = synth.attention_qk(tokens * heads, frames, dim, seed=tokens, device="cuda")
     qt, kt = qt.view(tokens, heads, frames, dim), kt.view(tokens, heads, frames, dim)
-    main_r, kept_r, ps_r = O.seda_main_anchor(ts, synth.bf16_bits(qt), synth.bf16_bits(kt), cand, gh, gw, tile, tile, prune_threshold=1.0)
-    ts, cand = torch.from_numpy(ts).cuda(), torch.from_numpy(cand).cuda()
-    main, kept, ps = F.fb4_seda_main_anchor(ts, qt, kt, cand, gh, gw, tile, tile, prune_threshold=1.0, want_scores=True)
-    over = cand.clone()
-    F.fb4_seda_main_anchor(ts, qt, kt, over, gh, gw, tile, tile, prune_threshold=1.0, kept=over)
-    torch.cuda.synchronize()
-    assert np.array_equal(main.cpu().numpy(), main_r)
-    got = ps.cpu().numpy()
-    inside = ~np.isnan(ps_r)
-    # fp32 sums of dim * heads products, against float64
-    bound = (dim * heads + 8) * 2.0 ** -23 * float(qt.float().norm(dim=-1).max() * kt.float().norm(dim=-1).max())
-    assert np.array_equal(np.isnan(got), ~inside) and np.abs(got[inside] - ps_r[inside]).max() <= bound
-    near = (np.abs(ps_r[inside] - 1.0) <= bound).sum()      # scores that rounding may put on either side of the threshold
-    assert (kept.cpu().numpy() != kept_r).sum() <= near
-    assert (over != kept).sum().item() <= near
+    for x, seed in ((qt, 1), (kt, 2)):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        at = torch.rand(x.shape, device="cuda", generator=g) * heads * dim
+        x[at < 0.03] = float("inf")
+        x[(at >= 0.03) & (at < 0.06)] = -float("inf")
+        x[(at >= 0.06) & (at < 0.09)] = float("nan")
+    check_main_anchor(F, ts, qt, kt, cand, gh, gw, tile)
 
 
 @pytest.mark.parametrize("gh,gw", [(16, 32), (19, 27), (2049, 2048)])
