@@ -291,11 +291,14 @@ int fb4_seda_main_anchor(const float* temporal_scores, const void* qt, const voi
     // second one: what a compute unit has of loads in flight is what the pruning takes.  us, one part / so (graph, inputs changing):
     // 64 tiles x 16 frames x 24 heads x 128 channels 7.85 / 7.05, 16 tiles 7.25 / 6.4, 64 x 32 x 16 x 64 10.4 / 8.5, 4 x 32 x 8 x 128 7.8 /
     // 6.6.  Not for short rows (64 x 16 x 8 x 72 5.4 / 5.7, 65 x 12 x 12 x 64 5.65 / 6.2) nor where many tiles' parts come to different
-    // XCDs (121 x 16 x 24 x 128 8.8 / 8.9), and not where `kept` overwrites the list that the other parts still read.
+    // XCDs (121 x 16 x 24 x 128 8.8 / 8.9), and not where `kept` overwrites the list that the other parts still read.  Two parts only
+    // from 12 frames on (46 shapes there 0.88 on average, 35 with fewer frames 0.99 and up to 1.045).  500 shapes of 1 to 200 frames in
+    // parts 0.83 of one part's time on average, at most 1.03; 500 in one part 1.00, at most 1.03.
     const uintptr_t from = reinterpret_cast<uintptr_t>(candidates), to = reinterpret_cast<uintptr_t>(kept);
     const bool in_place = from < to + n_cand * sizeof(int32_t) && to < from + n_cand * sizeof(int32_t);
     const bool worth = heads * dim >= 1024 && (tiles % 8 == 0 || tiles <= 32) && !in_place;
-    const int64_t most_parts = worth ? std::max<int64_t>(std::min<int64_t>(256 / tiles, frames), 1) : 1;   // (256 compute units)
+    int64_t most_parts = worth ? std::max<int64_t>(std::min<int64_t>(256 / tiles, frames), 1) : 1;   // (256 compute units)
+    if (most_parts == 2 && frames < 12) most_parts = 1;
     const int64_t per_part = std::max<int64_t>((frames + most_parts - 1) / most_parts, 1);
     const int64_t parts = std::max<int64_t>((frames + per_part - 1) / per_part, 1);   // (each has a frame)
     launch(parts > 1 ? seda_main_anchor_kernel<true> : seda_main_anchor_kernel<false>, dim3((unsigned)tiles, (unsigned)parts), dim3(threads), 0, s, temporal_scores,

@@ -205,9 +205,10 @@ def test_seda_main_anchor_in_parts(F, gh, gw, tile, frames, heads, dim):
     check_main_anchor(F, ts, qt.view(tokens, heads, frames, dim), kt.view(tokens, heads, frames, dim), cand, gh, gw, tile)
 
 
-# (ragged tiles at both edges, up to and from 32 tiles, more entries than a wavefront has lanes; the last: one part)
+# (ragged tiles at both edges, up to and from 32 tiles, more entries than a wavefront has lanes, both sides of the frames from which there
+# are two parts; the last: one part)
 @pytest.mark.parametrize("gh,gw,tile,frames,heads,dim", [(18, 19, 4, 20, 24, 72), (33, 30, 4, 7, 16, 64), (5, 3, 4, 33, 8, 128), (7, 62, 4, 3, 9, 256),
-                                                         (1, 9, 2, 2, 43, 24), (37, 35, 4, 6, 24, 72)])
+                                                         (1, 9, 2, 2, 43, 24), (29, 50, 4, 11, 8, 128), (29, 50, 4, 12, 8, 128), (37, 35, 4, 6, 24, 72)])
 def test_seda_main_anchor_in_parts_of_lists_with_other_entries(F, gh, gw, tile, frames, heads, dim):
     # several entries of a tile in a frame, entries of other frames, before the first row and beyond the last, tiles that no frame names;
     # ties and NaN among the temporal scores, NaN and infinities in Q and K
