@@ -176,42 +176,43 @@ def test_the_refresh_refuses_by_the_same_errors_with_outputs_given(monkeypatch, 
 RECORDER = r"""
 #include <stdint.h>
 #include "fb4.h"
-int64_t seen[16];
+int64_t seen[20];
 #define P(i, v) seen[i] = (int64_t)(uintptr_t)(v)
 #define N(i, v) seen[i] = (int64_t)(v)
+#define OPTIONS(o) N(18, (((o)->block * 100 + (o)->selector) * 100 + (o)->num_groups) * 100 + (o)->flags)
 int fb4_quantize(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, uint8_t* co, uint16_t* m, void* s)
-{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, co); P(5, m); return 0; }
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, co); P(5, m); P(16, s); P(17, l); OPTIONS(o); return 0; }
 int fb4_quantize_seda(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, const int32_t* tg, const uint8_t* sub, int g,
                       uint8_t* co, uint16_t* m, void* s)
-{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, tg); P(5, sub); N(6, g); P(7, co); P(8, m); return 0; }
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, tg); P(5, sub); N(6, g); P(7, co); P(8, m); P(16, s); P(17, l); OPTIONS(o); return 0; }
 int fb4_quantize_decompose(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, const int32_t* tg, const uint8_t* sub, int g,
                            const int32_t* sal, int64_t n, uint8_t* c1, uint16_t* m1, uint8_t* c2, uint16_t* m2, void* s)
-{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, tg); P(5, sub); N(6, g); P(7, sal); N(8, n); P(9, c1); P(10, m1); P(11, c2); P(12, m2); return 0; }
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, tg); P(5, sub); N(6, g); P(7, sal); N(8, n); P(9, c1); P(10, m1); P(11, c2); P(12, m2); P(16, s); P(17, l); OPTIONS(o); return 0; }
 int fb4_dequantize(const fb4_luts* l, const uint8_t* c1, const uint16_t* m1, int64_t r, int64_t c, int b, const uint8_t* c2, const uint16_t* m2,
                    const int32_t* sal, int64_t n, void* out, int dt, int64_t st, void* s)
-{ P(0, c1); P(1, m1); N(2, r); N(3, c); N(4, b); P(5, c2); P(6, m2); P(7, sal); N(8, n); P(9, out); N(10, dt); N(11, st); return 0; }
+{ P(0, c1); P(1, m1); N(2, r); N(3, c); N(4, b); P(5, c2); P(6, m2); P(7, sal); N(8, n); P(9, out); N(10, dt); N(11, st); P(16, s); P(17, l); return 0; }
 int fb4_repack_mxfp8(const fb4_luts* l, const uint8_t* co, const uint16_t* m, int64_t r, int64_t c, int b, uint8_t* e, int64_t st, uint8_t* sc, void* s)
-{ P(0, co); P(1, m); N(2, r); N(3, c); N(4, b); P(5, e); N(6, st); P(7, sc); return 0; }
+{ P(0, co); P(1, m); N(2, r); N(3, c); N(4, b); P(5, e); N(6, st); P(7, sc); P(16, s); P(17, l); return 0; }
 int fb4_layernorm_quantize(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, const float* ga, const float* be, float eps,
                            const int32_t* tg, const uint8_t* sub, int g, uint8_t* co, uint16_t* m, void* y, void* s)
-{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, ga); P(5, be); P(6, tg); P(7, sub); N(8, g); P(9, co); P(10, m); P(11, y); return 0; }
+{ P(0, x); N(1, r); N(2, c); N(3, st); P(4, ga); P(5, be); P(6, tg); P(7, sub); N(8, g); P(9, co); P(10, m); P(11, y); P(16, s); P(17, l); OPTIONS(o); N(19, eps * 1099511627776.0f); return 0; }
 int fb4_gelu_quantize(const fb4_luts* l, const fb4_opts* o, const void* x, int64_t r, int64_t c, int64_t st, int a, const int32_t* tg, const uint8_t* sub, int g,
                       uint8_t* co, uint16_t* m, void* s)
-{ P(0, x); N(1, r); N(2, c); N(3, st); N(4, a); P(5, tg); P(6, sub); N(7, g); P(8, co); P(9, m); return 0; }
+{ P(0, x); N(1, r); N(2, c); N(3, st); N(4, a); P(5, tg); P(6, sub); N(7, g); P(8, co); P(9, m); P(16, s); P(17, l); OPTIONS(o); return 0; }
 int fb4_attention_scores(const void* q, const void* k, int64_t g, int64_t t, int64_t d, int mode, float* out, void* s)
-{ P(0, q); P(1, k); N(2, g); N(3, t); N(4, d); N(5, mode); P(6, out); return 0; }
+{ P(0, q); P(1, k); N(2, g); N(3, t); N(4, d); N(5, mode); P(6, out); P(16, s); return 0; }
 int fb4_select_salient_tokens(const float* sc, int64_t f, int h, int gh, int gw, int th, int tw, int32_t* out, void* s)
-{ P(0, sc); N(1, f); N(2, h); N(3, gh); N(4, gw); N(5, th); N(6, tw); P(7, out); return 0; }
+{ P(0, sc); N(1, f); N(2, h); N(3, gh); N(4, gw); N(5, th); N(6, tw); P(7, out); P(16, s); return 0; }
 int fb4_seda_assign(const void* q, const void* k, int j, int64_t f, int h, int gh, int gw, int64_t d, const int32_t* an, int64_t n, int th, int tw, int w,
                     int wt, float t, int32_t* tg, int32_t* ag, float* sc, void* s)
 { P(0, q); P(1, k); N(2, j); N(3, f); N(4, h); N(5, gh * 1000 + gw); N(6, d); P(7, an); N(8, n); N(9, th * 1000 + tw); N(10, w * 1000 + wt);
-  N(11, t * 4096); P(12, tg); P(13, ag); P(14, sc); return 0; }
+  N(11, t * 4096); P(12, tg); P(13, ag); P(14, sc); P(16, s); return 0; }
 int fb4_seda_main_anchor(const float* ts, const void* q, const void* k, int64_t f, int h, int gh, int gw, int64_t d, const int32_t* c, int n, int th, int tw,
                          float t, int32_t* m, int32_t* kept, float* ps, void* s)
 { P(0, ts); P(1, q); P(2, k); N(3, f); N(4, h); N(5, gh); N(6, gw); N(7, d); P(8, c); N(9, n); N(10, th); N(11, tw); N(12, t * 4096); P(13, m);
-  P(14, kept); P(15, ps); return 0; }
+  P(14, kept); P(15, ps); P(16, s); return 0; }
 int fb4_seda_profile(const fb4_luts* l, const uint16_t* m, int64_t r, int64_t nb, const int32_t* ag, int g, uint32_t* c, uint8_t* sub, void* s)
-{ P(0, m); N(1, r); N(2, nb); P(3, ag); N(4, g); P(5, c); P(6, sub); return 0; }
+{ P(0, m); N(1, r); N(2, nb); P(3, ag); N(4, g); P(5, c); P(6, sub); P(16, s); P(17, l); return 0; }
 """
 
 
@@ -233,7 +234,7 @@ def recorder(tmp_path_factory, request):
     loader.exec_module(module)
     module.bind(B.fb4_opts, ctypes.c_void_p, B.CtypesCall)
     recording = ctypes.CDLL(str(lib))
-    seen = (ctypes.c_int64 * 16).in_dll(recording, "seen")
+    seen = (ctypes.c_int64 * 20).in_dll(recording, "seen")
     for call in B.EXPORTS:   # (what the module hands over to ctypes gets there too)
         if hasattr(recording, call):
             getattr(recording, call).argtypes = getattr(B.lib(), call).argtypes
@@ -387,3 +388,74 @@ def test_sizes_are_those_at_the_start_of_a_call(recorder, call):
 
     assert module.read_through(torch.Tensor, torch.Tensor.__dlpack_c_exchange_api__)
     assert result(module) == result(B.CtypesCall)
+
+
+def all_calls(module, x, stream, handle, o, eps):
+    """A call of every entry point with tensors and numbers of its own in every place."""
+    c, m, c2, m2 = (torch.zeros((4, 32), dtype=torch.uint8) for _ in range(4))
+    tg, sub, sal, ag = torch.zeros(4, dtype=torch.int32), torch.zeros((3, 8), dtype=torch.uint8), torch.zeros((2, 3), dtype=torch.int32), torch.zeros(4, dtype=torch.int32)
+    ga, be, y = torch.zeros(64), torch.zeros(64), torch.zeros((4, 64), dtype=torch.bfloat16)
+    frames, heads, gh, gw, dim = 3, 5, 4, 6, 16
+    sc, ts, ps = torch.zeros((frames, heads, gh * gw)), torch.zeros((gh * gw, heads, frames)), torch.zeros((frames, 4))
+    q, k = (torch.zeros((frames, heads, gh * gw, dim), dtype=torch.bfloat16) for _ in range(2))
+    qt, kt = (torch.zeros((gh * gw, heads, frames, dim), dtype=torch.bfloat16) for _ in range(2))
+    cand, kept, main = torch.zeros((frames, 2), dtype=torch.int32), torch.zeros((frames, 2), dtype=torch.int32), torch.zeros(4, dtype=torch.int32)
+    return {"quantize": lambda: module.quantize(handle, o, x, c, m, stream),
+            "quantize_seda": lambda: module.quantize_seda(handle, o, x, tg, sub, c, m, stream),
+            "quantize_decompose": lambda: module.quantize_decompose(handle, o, x, sal, tg, sub, c, m, c2, m2, stream),
+            "dequantize": lambda: module.dequantize(handle, c, m, 32, c2, m2, sal, y, 1, stream),
+            "repack_mxfp8": lambda: module.repack_mxfp8(handle, c, m, 32, c2, m2, stream),
+            "layernorm_quantize": lambda: module.layernorm_quantize(handle, o, x, ga, be, eps, tg, sub, c, m, y, stream),
+            "gelu_quantize": lambda: module.gelu_quantize(handle, o, x, 1, tg, sub, c, m, stream),
+            "attention_scores": lambda: module.attention_scores(q[0], k[0], 1, sc, stream),
+            "select_salient_tokens": lambda: module.select_salient_tokens(sc, gh, gw, 2, 3, main, stream),
+            "seda_assign": lambda: module.seda_assign(q, k, False, frames, gh, gw, cand, 2, 3, 5, 1, 1.5, tg, ag, ps, stream),
+            "seda_main_anchor": lambda: module.seda_main_anchor(ts, qt, kt, cand, gh, gw, 2, 3, 1.5, main, kept, ps, stream),
+            "seda_profile": lambda: module.seda_profile(handle, m, ag, 7, main, sub, stream)}
+
+
+@pytest.mark.parametrize("reader", [False, True])
+def test_streams_handles_options_and_eps_arrive(recorder, reader):
+    module, notes = recorder
+    module.read_through(torch.Tensor, torch.Tensor.__dlpack_c_exchange_api__ if reader else None)
+
+    class Asked:
+        which = None
+
+        def __getattr__(self, name):
+            return getattr(Asked.which, name)
+
+    untouched = -0x1111111111111112   # (what a place holds that a call does not write)
+    calls = all_calls(Asked(), X, 0x7001, ctypes.c_void_p(0x640), F.opts(16, F.SEL_SSE, 32, F.FLAG_TWO_STAGE), 0.25)
+    assert set(calls) == {n for n in dir(B.CtypesCall) if not n.startswith("_")}
+    options = ((16 * 100 + F.SEL_SSE) * 100 + 32) * 100 + F.FLAG_TWO_STAGE
+    for name, call in calls.items():
+        got = []
+        for Asked.which in (module, B.CtypesCall):
+            notes()
+            assert call() == 0
+            got.append(notes())
+        assert got[0] == got[1], name
+        with_handle = name not in ("attention_scores", "select_salient_tokens", "seda_assign", "seda_main_anchor")
+        with_options = "quantize" in name and name != "dequantize"
+        assert got[0][16:] == [0x7001, 0x640 if with_handle else untouched, options if with_options else untouched,
+                               1 << 38 if name == "layernorm_quantize" else untouched], name
+
+
+def test_a_copy_on_write_tensor_is_read_as_its_own(recorder):
+    # (a fresh lazy copy for every place, which the table's reader is the first to look at)
+    module, notes = recorder
+    assert module.read_through(torch.Tensor, torch.Tensor.__dlpack_c_exchange_api__)
+    c, o, h = torch.zeros((4, 32), dtype=torch.uint8), F.opts(), ctypes.c_void_p(64)
+    source = torch.zeros((2, 4, 64), dtype=torch.bfloat16)
+    for call in (lambda x: module.quantize(h, o, x[0], c, c, 0), lambda x: module.attention_scores(x, c, 0, c, 0), lambda x: module.seda_profile(h, x[0], c, 1, c, c, 0),
+                 lambda x: module.dequantize(h, x[0], c, 32, None, None, None, c, 0, 0), lambda x: module.repack_mxfp8(h, x[0], c, 32, c, c, 0),
+                 lambda x: module.select_salient_tokens(x, 8, 8, 4, 4, c, 0)):
+        x = torch._lazy_clone(source)
+        notes()
+        assert call(x) == 0
+        assert notes()[0] == x.data_ptr() != source.data_ptr()
+    x = torch._lazy_clone(source)
+    notes()
+    assert module.quantize(h, o, source[0], x, c, 0) == 0   # (an address alone)
+    assert notes()[4] == x.data_ptr() != source.data_ptr()
