@@ -84,6 +84,7 @@ struct FastArgs {
 };
 
 constexpr uint32_t kMaxFastGroups = 1023;   // SeDA groups whose exclusion rows fit the workgroup's LDS
+static_assert(kMaxFastGroups <= 0xFFFFu, "n_groups and n_dialects share an argument");
 
 // Division by nb for dividends below 2^31: (n * div_mul) >> div_shift with div_shift = 31 + ceil(log2 nb) and div_mul =
 // ceil(2^div_shift / nb).

@@ -81,9 +81,12 @@ __global__ __launch_bounds__(kProfileThreads) void profile_select_kernel(const u
 // 4.1 -> 3.4, 30000 x 96, 200, 1/16 6.5 -> 5.3.  Every workgroup looks through all rows (65536 x 96, 512 groups 12.5 / 15.3), and one that gets all anchors
 // takes 0.0041 a word and 0.0143 a load of the time that the atomics of three launches take for them (16384 x 97, a word a load,
 // 26.7 / 47.3; 65536 x 384, eight words, 86 / 202): profile_by_group keeps this below 1.
+constexpr int64_t kProfileGroupMaxRows = 32768;
+// (profile_group_kernel puts a count of words and a DID into 32 bits; the rule's rows have at most 400 * 8 / 23 words)
+static_assert(((kProfileGroupMaxRows * (400 * 8 / (2 * 8 + 7)) + 1) << 5 | 31) <= 0xFFFFFFFFll, "a group's words and a DID in 32 bits");
 inline bool profile_by_group(int64_t rows, int64_t blocks_per_row, int64_t n_groups, int words)
 {
-    return n_groups <= 512 && rows <= 32768 && rows * n_groups <= (1 << 23) && blocks_per_row * (2 * words + 7) <= 400 * words;
+    return n_groups <= 512 && rows <= kProfileGroupMaxRows && rows * n_groups <= (1 << 23) && blocks_per_row * (2 * words + 7) <= 400 * words;
 }
 constexpr int kProfileGroupThreads = 1024;
 // Lane 31 of each half-wavefront gets the half's values put together (exchanges inside the vector ALU: no LDS round trips).
@@ -190,7 +193,7 @@ __global__ __launch_bounds__(kProfileGroupThreads) void profile_group_kernel(con
     __syncthreads();
     if (tid < 256) {   // 32 lanes per range bucket: the most frequent dialect, lowest DID on ties
         const bool in = (int)d < n_dialects && top == 8u + (tid >> 5);
-        uint32_t key = in ? ((total[d] + 1u) << 5) | (31u - d) : 0u;   // (fewer than 2^23 words: see profile_by_group)
+        uint32_t key = in ? ((total[d] + 1u) << 5) | (31u - d) : 0u;   // (fits: see profile_by_group)
         key = half_wave(key, [](uint32_t a, uint32_t b) { return max(a, b); }, 0u);
         if (d == 31) sub[(size_t)g * 8 + (tid >> 5)] = key ? (uint8_t)(31u - (key & 31u)) : 255u;
     }
