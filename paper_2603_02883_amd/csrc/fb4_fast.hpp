@@ -903,8 +903,8 @@ __device__ __forceinline__ void compute_tile(const uint32_t (&w)[16], const uint
             uint32_t v = __builtin_amdgcn_perm(__builtin_amdgcn_perm(byte[3], byte[2], 0x0C0C0400u),
                                                __builtin_amdgcn_perm(byte[1], byte[0], 0x0C0C0400u), 0x05040100u);
             // sign bits: element 2m -> bit 8m+3, element 2m+1 -> bit 8m+7.  (selectors 8 to 11 of a byte permutation fill a byte with
-            // the sign of either half: no shift before the masks, 207 -> 199 vector instructions here; LayerNorm 16384 x 3072 30.0 -> 29.7
-            // us, exhaustive 12288 x 3072 25.55 -> 25.45, the kernels that memory or LDS bounds as before)
+            // the sign of either half: no shift before the masks, 207 -> 199 vector instructions here; us, in a graph, inputs changing:
+            // LayerNorm 16384 x 3072 31.0 -> 30.5, exhaustive 12288 x 3072 26.1 -> 25.8, the first stream of 16384 x 3072 22.6 either way)
             const uint32_t x01 = __builtin_amdgcn_perm(w[4 * c + 1], w[4 * c + 0], 0x0B090A08u);   // w0.lo w1.lo w0.hi w1.hi
             const uint32_t x23 = __builtin_amdgcn_perm(w[4 * c + 3], w[4 * c + 2], 0x0B090A08u);
             const uint32_t lo = __builtin_amdgcn_perm(x23, x01, 0x05040100u);   // the lower halves of w0..w3

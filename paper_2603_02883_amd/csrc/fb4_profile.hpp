@@ -73,14 +73,15 @@ __global__ __launch_bounds__(kProfileThreads) void profile_select_kernel(const u
 // dialects into 64 histograms, one per lane of a wavefront, so that neither many equal dialects nor many rows of one group
 // meet in one address, and picks the group's dialects.
 // kWords: metadata words per load, which divide the blocks of a row.
-// us, three launches / this (rows x blocks, groups, share of anchors): 16384 x 96, 64, 1/16 9.8 / 5.4, the same with all rows
-// anchors 13.6 / 7.9, with one dialect everywhere 14.1 / 7.8, with a tenth of the rows anchors of one group 26.8 / 15.3; 1000 x
-// 36, 64 8.7 / 4.9.  Bound by its chain of dependent steps, most of it instructions of one workgroup: with the anchors found as bits
-// and the sums and maxima exchanged inside the vector ALU (a ballot, a place in the list and a branch per load, and ten LDS
-// round trips, before), launches in a graph, inputs changing: 16384 x 96, 64, 1/16 4.6 -> 3.6, all rows anchors 7.8 -> 6.5, 1000 x 36
-// 4.1 -> 3.4, 30000 x 96, 200, 1/16 6.5 -> 5.3.  Every workgroup looks through all rows (65536 x 96, 512 groups 12.5 / 15.3), and one that gets all anchors
-// takes 0.0041 a word and 0.0143 a load of the time that the atomics of three launches take for them (16384 x 97, a word a load,
-// 26.7 / 47.3; 65536 x 384, eight words, 86 / 202): profile_by_group keeps this below 1.
+// us, three launches / this (rows x blocks, groups, share of anchors; graph, inputs changing): 16384 x 96, 64, 1/16 9.05 / 3.8, the
+// same with all rows anchors 12.8 / 5.8, with a tenth of the rows anchors of one group 26.7 / 14.4; 1000 x 36, 64, 1/16 7.9 / 3.55; 30000 x
+// 96, 200, 1/16 9.9 / 5.5.  Bound by its chain of dependent steps, most of it instructions of one workgroup: so a thread's anchors are
+// found as bits and the sums and maxima exchanged inside the vector ALU (against a ballot, a place in the list and a branch per load
+// and ten LDS round trips 0.82 of the time over 250 shapes of up to 512 groups, 0.855 over 400 with dense anchors).  Every workgroup
+// looks through all rows (65536 x 96, 512 groups, 1/16 11.9 / 11.9).  One that gets every row as an anchor takes 0.0025 a word and
+// 0.031 a load of the time that the atomics of three launches take for a row; the line below, 0.005 and 0.0175, was drawn where a tenth
+// of the rows are anchors.  It keeps that worst input below 1 with loads of eight words (32768 x 136, one group 379 / 324), and at the
+// longest rows that it takes with four, two and one up to 1.06, 1.27 and 1.47 (32768 x 43 378 / 557).
 constexpr int64_t kProfileGroupMaxRows = 32768;
 // (profile_group_kernel puts a count of words and a DID into 32 bits; the rule's rows have at most 400 * 8 / 23 words)
 static_assert(((kProfileGroupMaxRows * (400 * 8 / (2 * 8 + 7)) + 1) << 5 | 31) <= 0xFFFFFFFFll, "a group's words and a DID in 32 bits");
