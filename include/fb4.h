@@ -443,10 +443,15 @@ int fb4_seda_assign(const void* q, const void* k, int joint, int64_t frames, int
  *                    without candidates
  *   kept             device, int32 [frames][n_per_frame]: `candidates` with the
  *                    pruned and the invalid entries set to -1 -- the `anchors`
- *                    argument of fb4_seda_assign
+ *                    argument of fb4_seda_assign; may be `candidates` itself
  *   prune_scores     device, float [frames][tiles] or NULL: the scores that
  *                    were compared (NaN where a frame has no candidate)
  *   frames at most 1024 (FB4_ERR_UNSUPPORTED beyond)
+ * The order in which a pruning score's products are added in fp32 is not
+ * specified: it depends on the numbers of tiles, frames, heads and channels and
+ * on whether `kept` overlaps `candidates`, so a tile alone and among others, or in
+ * place and not, may differ in a score's last bits (and in a frame whose score
+ * lies that close to the threshold).  Calls of one form repeat exactly.
  */
 int fb4_seda_main_anchor(const float* temporal_scores, const void* qt, const void* kt, int64_t frames, int heads,
                          int grid_h, int grid_w, int64_t dim, const int32_t* candidates, int n_per_frame, int tile_h,
