@@ -25,8 +25,8 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 
 // Kernel launches.  The runtime keeps up to 112 bytes of kernel arguments with the launch itself and allocates for more, and the
 // launch syntax stores the configuration aside and fetches it back: an empty kernel, one launch behind the other from the host, takes
-// 3.42 us with 224 bytes in that syntax, 3.25 in one call, 2.64 with 16 to 112 bytes in one call (116 bytes: 3.25; 2.25 to 2.8 from box to
-// box and process to process).  So no kernel here
+// 3.42 us with 224 bytes in that syntax, 3.25 in one call, 2.64 with 16 to 112 bytes in one call (116 bytes: 3.25; 2.25 to 2.8 from machine
+// to machine and process to process).  So no kernel here
 // takes more, and a kernel that needs its grid's or workgroup's size, 256 bytes of implicit arguments, gets it passed.  fb4_quantize of
 // 300 x 1152, 40 calls in a row: 3.35 us of the host per call with 192 bytes and the syntax, 2.83 so (over thousands of calls the
 // kernels' own 3.4 us one behind the other are the longer part: 3.65 to 3.55).
